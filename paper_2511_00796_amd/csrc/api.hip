@@ -433,10 +433,20 @@ static int run_step(hx_engine *e, hx_kv *kv, int32_t batch, const int32_t *token
     float *ypart = (float *)(ws + e->map.ypart);
     const size_t attn_stride = (size_t)batch * e->q_dim;
 
-    HX_TIMED(HX_K_SETUP, hx_launch_step_setup(e, batch, positions, seq_lens, block_table, max_blocks, st));
     // prompt rows: consecutive rows of a sequence share one K/V stream (their schedule replaces the decode step's)
-    const bool chunked = !with_head && e->chunk_attention;
-    if (chunked) HX_TIMED(HX_K_SETUP, hx_launch_chunk_setup(e, batch, seq_lens, block_table, max_blocks, st));
+    const bool grouped = !with_head && e->chunk_attention;
+    // One or two rows (16 columns per KV head) over a very long cache only stream it: three of a workgroup's four wavefronts
+    // have nothing to multiply, and with few KV heads there are too few parts to fill the chip, so the kernel with one
+    // K/V stream per wavefront is the faster one (us per 3-layer call, bf16 | 8-bit cache, that kernel / the shared-stream
+    // one: 30 000 tokens, 2 KV heads 211 / 231 | 209 / 233, 4 KV heads 335 / 343 | 322 / 342, but 8 KV heads 400 / 355;
+    // 16 000 tokens, 4 KV heads 295 / 299 | 290 / 298; 8 000 tokens 287 / 275 | 284 / 275, and 288 / 264 with 7 rows).
+    const bool chunked = grouped && batch * e->G <= 16 && c->n_kv_heads <= 4 && max_blocks >= 1000, prompt = grouped && !chunked;
+    if (prompt) {
+        HX_TIMED(HX_K_SETUP, hx_launch_prompt_setup(e, batch, positions, seq_lens, block_table, max_blocks, st));
+    } else {
+        HX_TIMED(HX_K_SETUP, hx_launch_step_setup(e, batch, positions, seq_lens, block_table, max_blocks, st));
+        if (chunked) HX_TIMED(HX_K_SETUP, hx_launch_chunk_setup(e, batch, seq_lens, block_table, max_blocks, st));
+    }
     HX_TIMED(HX_K_NORM, hx_launch_embed_norm(e, batch, tokens, e->layers[0].g1, st));
     for (int l = 0; l < c->n_layers; ++l) {
         const hx_layer_map *lm = &e->layers[l];
@@ -445,7 +455,10 @@ static int run_step(hx_engine *e, hx_kv *kv, int32_t batch, const int32_t *token
                                                  positions, st));
         if (!with_head && l + 1 == c->n_layers) break;   // prompt rows: of the last layer only its K and V are needed
         float *capture = e->attn_capture ? e->attn_capture + l * attn_stride : nullptr;
-        if (chunked) {
+        if (prompt) {
+            HX_TIMED(HX_K_ATTENTION, hx_launch_prompt_attention(e, kv, l, batch, block_table, max_blocks, capture, st));
+            HX_TIMED(HX_K_COMBINE, hx_launch_prompt_combine(e, batch, capture, st));
+        } else if (chunked) {
             HX_TIMED(HX_K_ATTENTION, hx_launch_chunk_attention(e, kv, l, block_table, max_blocks, st));
             HX_TIMED(HX_K_COMBINE, hx_launch_chunk_combine(e, batch, capture, st));
         } else {
@@ -538,16 +551,17 @@ extern "C" int prefill_rows(hx_engine *e, hx_kv *kv, int32_t n_rows, const int32
     int rc;
     auto rows = [&](const int32_t *p, int b) { return p + (size_t)b * 256; };
     auto table = [&](int b) { return block_table + (size_t)b * 256 * max_blocks; };
-    const bool chunked = e->chunk_attention;
+    const bool grouped = e->chunk_attention;
 
-    // The schedules are per block (one small launch each); the row kernels and the grouped attention take all blocks in
-    // one launch (their block dimension strides through the workspaces), as do the products.
+    // The row kernels, the grouped attention and its schedule take all blocks in one launch (they stride through the
+    // workspaces), as do the products.
     const hx_engine *v0 = &view[0];
     const float *ypart0 = (const float *)(ws0 + m.ypart);
-    for (int b = 0; b < R; ++b) {
-        const hx_engine *vb = &view[b];
-        HX_TIMED(HX_K_SETUP, hx_launch_step_setup(vb, 256, rows(positions, b), rows(seq_lens, b), table(b), max_blocks, st));
-        if (chunked) HX_TIMED(HX_K_SETUP, hx_launch_chunk_setup(vb, 256, rows(seq_lens, b), table(b), max_blocks, st));
+    if (grouped) {
+        HX_TIMED(HX_K_SETUP, hx_launch_prompt_setup(v0, n_rows, positions, seq_lens, block_table, max_blocks, st, stride));
+    } else {
+        for (int b = 0; b < R; ++b)
+            HX_TIMED(HX_K_SETUP, hx_launch_step_setup(&view[b], 256, rows(positions, b), rows(seq_lens, b), table(b), max_blocks, st));
     }
     HX_TIMED(HX_K_NORM, hx_launch_embed_norm(v0, 256, tokens, e->layers[0].g1, st, R, stride));
     for (int l = 0; l < c->n_layers; ++l) {
@@ -560,9 +574,9 @@ extern "C" int prefill_rows(hx_engine *e, hx_kv *kv, int32_t n_rows, const int32
         HX_TIMED(HX_K_ROPE, hx_launch_rope_append(v0, kv, l, 256, ypart0, s_qkv, (size_t)256 * e->qkv_dim, positions, st, R, stride));
         if (l + 1 == c->n_layers) break;     // of the last layer only its K and V are needed
         float *capture = e->attn_capture ? e->attn_capture + l * attn_stride : nullptr;
-        if (chunked) {
-            // one launch over all blocks: each block has its own schedule; the wavefronts beyond a block's runs exit
-            HX_TIMED(HX_K_ATTENTION, hx_launch_chunk_attention(v0, kv, l, block_table, max_blocks, st, R, stride, 256));
+        if (grouped) {
+            HX_TIMED(HX_K_ATTENTION, hx_launch_prompt_attention(v0, kv, l, n_rows, block_table, max_blocks, capture, st, stride));
+            HX_TIMED(HX_K_COMBINE, hx_launch_prompt_combine(v0, n_rows, capture, st, stride));
         } else {
             for (int b = 0; b < R; ++b) {
                 const hx_engine *vb = &view[b];
@@ -571,7 +585,6 @@ extern "C" int prefill_rows(hx_engine *e, hx_kv *kv, int32_t n_rows, const int32
                 HX_TIMED(HX_K_COMBINE, hx_launch_combine(vb, 256, capture ? capture + (size_t)b * 256 * e->q_dim : nullptr, st));
             }
         }
-        if (chunked) HX_TIMED(HX_K_COMBINE, hx_launch_chunk_combine(v0, 256, capture, st, R, stride));
         HX_TIMED(HX_K_GEMM_O, hx_launch_gemm_wide(e, &lm->wo, R, ws0, stride, m.ap, HX_EPI_PARTIAL, m.ypart, 0, p_o, st));
         HX_TIMED(HX_K_NORM, hx_launch_reduce_norm(v0, 256, ypart0, s_o, (size_t)256 * c->hidden, lm->g2, st, R, stride));
         HX_TIMED(HX_K_GEMM_GATE_UP, hx_launch_gemm_wide(e, &lm->wgu, R, ws0, stride, m.xp, HX_EPI_SWIGLU, 0, m.mp, p_gu, st));

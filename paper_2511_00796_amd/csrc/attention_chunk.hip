@@ -1,4 +1,5 @@
-// Attention for prompt rows (prefill_chunk): consecutive rows of one sequence share one K/V stream.
+// Attention for one or two prompt rows over a long cache (prefill_chunk; other prompt calls: attention_prompt.hip):
+// consecutive rows of one sequence share one K/V stream per wavefront.
 //
 // A row of a prompt chunk is one token; row r of a sequence attends the keys [0, T_r), T_r = T_{r-1} + 1.  The decode
 // kernel would stream the whole prefix once per row.  Here up to min(HX_CHUNK_ROWS, 64 / G) consecutive rows of one
@@ -274,23 +275,11 @@ __global__ __launch_bounds__(64, 2) void attn_chunk_kernel(const char *__restric
                                                         const int32_t *__restrict__ sched,
                                                         const int32_t *__restrict__ ginfo, int n_kv, int G,
                                                         float scale_log2e, float *__restrict__ part_ml,
-                                                        float *__restrict__ part_o, size_t block_stride,
-                                                        size_t table_block_stride) {
+                                                        float *__restrict__ part_o) {
     // query operands of the 4 column blocks; every lane reads back only what it wrote itself
     __shared__ u32x4_t qs[HX_CHUNK_CB * (D / 32) * 64];
     const int w = blockIdx.x;
     const int lane = threadIdx.x;
-    if (blockIdx.y) {               // further row blocks of a wide prompt call: each with its own schedule, queries and
-        const size_t off = (size_t)blockIdx.y * block_stride;      // partial results, block_stride bytes apart
-        qp = (const uint16_t *)((const char *)qp + off);
-        pre = (const int32_t *)((const char *)pre + off);
-        lens = (const int32_t *)((const char *)lens + off);
-        sched = (const int32_t *)((const char *)sched + off);
-        ginfo = (const int32_t *)((const char *)ginfo + off);
-        part_ml = (float *)((char *)part_ml + off);
-        part_o = (float *)((char *)part_o + off);
-        table += (size_t)blockIdx.y * table_block_stride;
-    }
     const int S = sched[0], Nt = sched[1];
     int f = w * S;
     const int f1 = min(Nt, f + S);
@@ -393,20 +382,9 @@ __global__ __launch_bounds__(256) void attn_chunk_combine_kernel(int n_rows, int
                                                                  const float *__restrict__ part_ml,
                                                                  const float *__restrict__ part_o,
                                                                  uint16_t *__restrict__ ap, int m_groups,
-                                                                 float *__restrict__ attn_f32, size_t block_stride) {
+                                                                 float *__restrict__ attn_f32) {
     const int bh = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (bh >= n_rows * n_q) return;
-    if (blockIdx.y) {               // further row blocks of a wide prompt call: same layout, block_stride bytes apart
-        const size_t off = (size_t)blockIdx.y * block_stride;
-        pre = (const int32_t *)((const char *)pre + off);
-        lens = (const int32_t *)((const char *)lens + off);
-        sched = (const int32_t *)((const char *)sched + off);
-        rgrp = (const int32_t *)((const char *)rgrp + off);
-        part_ml = (const float *)((const char *)part_ml + off);
-        part_o = (const float *)((const char *)part_o + off);
-        ap = (uint16_t *)((char *)ap + off);
-        if (attn_f32) attn_f32 += (size_t)blockIdx.y * n_rows * n_q * D;
-    }
     const int lane = threadIdx.x & 63, d8 = lane & 15, ph = lane >> 4;
     const bool has_d = d8 < D / 8;
     const int b = bh / n_q, h = bh % n_q;
@@ -476,17 +454,16 @@ int hx_launch_chunk_setup(const hx_engine *e, int n_rows, const int32_t *seq_len
 }
 
 int hx_launch_chunk_attention(const hx_engine *e, const hx_kv *kv, int layer, const int32_t *table, int max_blocks,
-                              hipStream_t st, int blocks, size_t block_stride, int rows_per_block) {
+                              hipStream_t st) {
     const char *pool_layer = kv->pool + (size_t)layer * kv->layer_bytes;
     char *ws = e->ws;
     const float scale_log2e = (float)(1.4426950408889634 / sqrt((double)e->D));
-    dim3 grid(e->attn_waves, blocks), block(64);
+    dim3 grid(e->attn_waves), block(64);
 #define HX_CHUNK_ARGS                                                                                            \
     pool_layer, kv->block_bytes, (const uint16_t *)(ws + e->map.qp), table, max_blocks,                          \
         (const int32_t *)(ws + e->map.pre), (const int32_t *)(ws + e->map.lens),                                 \
         (const int32_t *)(ws + e->map.sched), (const int32_t *)(ws + e->map.chunk_ginfo), e->cfg.n_kv_heads,     \
-        e->G, scale_log2e, (float *)(ws + e->map.chunk_part_ml), (float *)(ws + e->map.chunk_part_o), block_stride,   \
-        (size_t)rows_per_block * max_blocks
+        e->G, scale_log2e, (float *)(ws + e->map.chunk_part_ml), (float *)(ws + e->map.chunk_part_o)
     if (kv->fp8) {
         if (e->D == 128) hipLaunchKernelGGL((attn_chunk_kernel<128, 2, true>), grid, block, 0, st, HX_CHUNK_ARGS);
         else             hipLaunchKernelGGL((attn_chunk_kernel<64, 3, true>), grid, block, 0, st, HX_CHUNK_ARGS);
@@ -499,16 +476,16 @@ int hx_launch_chunk_attention(const hx_engine *e, const hx_kv *kv, int layer, co
     return HX_OK;
 }
 
-int hx_launch_chunk_combine(const hx_engine *e, int n_rows, float *attn_f32_out, hipStream_t st, int blocks, size_t block_stride) {
+int hx_launch_chunk_combine(const hx_engine *e, int n_rows, float *attn_f32_out, hipStream_t st) {
     char *ws = e->ws;
     const int n_kv = e->cfg.n_kv_heads, n_q = e->cfg.n_q_heads;
     const int m_groups = hx_m_groups(n_rows);
-    dim3 cgrid((n_rows * n_q + 3) / 4, blocks), cblock(256);
+    dim3 cgrid((n_rows * n_q + 3) / 4), cblock(256);
 #define HX_CCOMB_ARGS                                                                                            \
     n_rows, n_q, n_kv, e->G, (const int32_t *)(ws + e->map.pre), (const int32_t *)(ws + e->map.lens),            \
         (const int32_t *)(ws + e->map.sched), (const int32_t *)(ws + e->map.chunk_rgrp),                         \
         (const float *)(ws + e->map.chunk_part_ml), (const float *)(ws + e->map.chunk_part_o),                   \
-        (uint16_t *)(ws + e->map.ap), m_groups, attn_f32_out, block_stride
+        (uint16_t *)(ws + e->map.ap), m_groups, attn_f32_out
     if (e->D == 128) hipLaunchKernelGGL((attn_chunk_combine_kernel<128>), cgrid, cblock, 0, st, HX_CCOMB_ARGS);
     else             hipLaunchKernelGGL((attn_chunk_combine_kernel<64>), cgrid, cblock, 0, st, HX_CCOMB_ARGS);
 #undef HX_CCOMB_ARGS

@@ -1,0 +1,552 @@
+// Attention for prompt rows (prefill_rows, and prefill_chunk beyond a handful of rows): one schedule over all rows of
+// the call, workgroups of four wavefronts that share a K/V stream through LDS.
+//
+// Consecutive rows of one sequence form a GROUP of up to 128 / G rows; its (row, query head of one KV head) pairs are
+// up to 128 columns, 32 per wavefront.  A step is the K and V of 32 tokens (two cache blocks, 16 KiB in bf16), copied
+// once per workgroup from the pool straight into LDS (three stages, requested two steps ahead):
+//     S^T[token, column] = K . q           D/16 x v_mfma_f32_32x32x16_bf16   (A = K from LDS, B = q in registers)
+//     O^T[d, column]    += V^T . P^T        D/32 x 2 blocks x (high, low part of P)
+// The accumulator layout of the first product (lane = column, 16 registers = 16 of the 32 tokens) is taken as the
+// B operand of the second by numbering the contraction index accordingly: the probabilities never cross lanes, and the
+// V operand is read from LDS in the matching order.  P enters as a high + low bf16 pair, as in the decode step.
+//
+// What bounds it: the matrix cores (24 products of 32 cycles per 32 x 32 scores at D = 128) and the softmax arithmetic
+// beside them, which the second workgroup of a compute unit overlaps.  Measured per layer, kernel + combine, against a
+// kernel that served 8 rows per K/V stream with one wavefront each and 16-row products of half the rate: 7B, one prompt
+// of 2048 tokens 89 + 13 us (214 + 69); 14B, 7 prompts of 5000 tokens, 8-bit cache 125 + 7 us (273 + 136); 1.5B, 200
+// rows behind 3000 cached tokens 18 + 10 us (41 + 9).
+//
+// Schedule: a pair (group, KV head) of more than S steps is cut into equal parts of at most S steps; S follows from the
+// work of the whole call (prompt_sched_kernel), so that a short call with a long cache fills the chip and a long one
+// writes few partial results.  An uncut pair writes its output itself; the parts of a cut one are merged by
+// prompt_combine_kernel.  Items run from the last group to the first: of one prompt the longest come first.
+//
+// Per-group arrays live where the 256-row workspaces keep their per-row ones: entry g in block g / 256 at g % 256.
+#include "hx_internal.h"
+
+#define HX_NEG_BIG (-1.0e30f)
+#define HX_PROMPT_COLS 128
+#define HX_PROMPT_MIN_STEPS 8
+
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+
+struct PromptArgs {
+    char *ws0;                          // workspace of the call's first 256 rows; the others follow at `stride` bytes
+    size_t stride;
+    size_t o_qp, o_pre, o_lens, o_ginfo, o_gslot, o_glist, o_sched, o_ap, o_ml, o_po;     // byte offsets in each
+    int n_rows, n_blocks, slots_per_block;
+    int n_kv, G, n_q, m_groups;
+    float *attn_f32;                    // [n_rows, n_q * D] or NULL
+};
+
+template <typename T>
+__device__ __forceinline__ T *group_entry(const PromptArgs &a, size_t off, int g) {
+    return (T *)(a.ws0 + (size_t)(g >> 8) * a.stride + off) + (g & 255);
+}
+
+// ---- per row: RoPE angles, the block of its position, and whether it continues the row before it -----------------------
+// grid = rows, 64 threads.  Row r continues row r - 1 if its length is one more and its table row repeats that of r - 1
+// over the blocks r - 1 uses.  Angles as in step_setup_kernel.
+__global__ __launch_bounds__(64) void prompt_rows_kernel(char *ws0, size_t stride, size_t o_cs, size_t o_blk, size_t o_cont,
+                                                         const int32_t *__restrict__ positions,
+                                                         const int32_t *__restrict__ seq_lens,
+                                                         const int32_t *__restrict__ table, int max_blocks, int half,
+                                                         double theta, int max_batch) {
+    const int r = blockIdx.x, lane = threadIdx.x;
+    char *ws = ws0 + (size_t)(r >> 8) * stride;
+    const int b = r & 255;
+    const int pos = positions[r];
+    bool ok = false;
+    if (r > 0) {
+        const int Tp = seq_lens[r - 1], T = seq_lens[r];
+        const int nb = (Tp + 15) >> 4;
+        ok = (T == Tp + 1) && nb <= max_blocks;
+        const int32_t *p = table + (size_t)(r - 1) * max_blocks, *q = table + (size_t)r * max_blocks;
+        for (int i = lane; i < nb && ok; i += 64) ok = p[i] == q[i];
+    }
+    const bool all = __all(ok);
+    if (lane == 0) {
+        ((int32_t *)(ws + o_cont))[b] = (r > 0 && all) ? 1 : 0;
+        ((int32_t *)(ws + o_blk))[b] = table[(size_t)r * max_blocks + (pos >> 4)];
+    }
+    float *cs = (float *)(ws + o_cs);
+    for (int i = lane; i < half; i += 64) {
+        const double ang = (double)pos * pow(theta, -(double)i / (double)half);
+        cs[(size_t)b * half + i] = (float)cos(ang);
+        cs[(size_t)max_batch * half + (size_t)b * half + i] = (float)sin(ang);
+    }
+}
+
+// ---- groups and their schedule ------------------------------------------------------------------------------------------
+// Inclusive scans over the 1024 threads of the one workgroup (wavefront shuffles, then the 16 wavefront totals).
+template <bool MAX>
+__device__ __forceinline__ int scan_1024(int v, int *red, int *total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(v, off);
+        if (lane >= off) v = MAX ? max(v, o) : v + o;
+    }
+    __syncthreads();                        // red may still be read from the scan before
+    if (lane == 63) red[wave] = v;
+    __syncthreads();
+    int before = MAX ? -1 : 0, all = MAX ? -1 : 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        if (w < wave) before = MAX ? max(before, red[w]) : before + red[w];
+        all = MAX ? max(all, red[w]) : all + red[w];
+    }
+    *total = all;
+    return MAX ? max(v, before) : v + before;
+}
+
+// pre[g] = items (group, KV head, part) of the groups before g, lens[g] = keys of the group's last row, ginfo[g] = first
+// row | rows << 16, gslot[g] = first partial slot of a cut group, glist = the cut groups; sched (block 0) = {S, items,
+// cut groups}.  n_rows <= 8192: up to 8 rows (later: groups) per thread.
+__global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const int32_t *__restrict__ seq_lens, size_t o_cont,
+                                                            int group_rows, int n_wgs) {
+    extern __shared__ int32_t sT[];                     // [n_rows] keys of each group's last row
+    __shared__ int red[16];
+    __shared__ long long redl[16];
+    const int tid = threadIdx.x, E = (a.n_rows + 1023) >> 10, r0 = tid * E, r1 = min(a.n_rows, r0 + E);
+    auto cont = [&](int r) { return *group_entry<int32_t>(a, o_cont, r); };
+    int run = -1;                                       // start of the last run of consecutive rows that begins here
+    for (int r = r0; r < r1; ++r) if (!cont(r)) run = r;
+    int total;
+    const int own = scan_1024<true>(run, red, &total);
+    int before = __shfl_up(own, 1);                     // the run that is open on entry: the scan up to the thread before
+    __syncthreads();
+    if ((tid & 63) == 63) red[tid >> 6] = own;
+    __syncthreads();
+    if ((tid & 63) == 0) before = tid ? red[(tid >> 6) - 1] : 0;
+    int n_start = 0, open = before;
+    for (int r = r0; r < r1; ++r) {
+        if (!cont(r)) open = r;
+        n_start += (r - open) % group_rows == 0;
+    }
+    int n_groups;
+    int gid = scan_1024<false>(n_start, red, &n_groups) - n_start - 1;
+    open = before;
+    for (int r = r0; r < r1; ++r) {
+        if (!cont(r)) open = r;
+        const int local = (r - open) % group_rows;
+        gid += local == 0;
+        const bool last = r + 1 == a.n_rows || !cont(r + 1) || local + 1 == group_rows;
+        if (last) {
+            const int T = seq_lens[r];
+            sT[gid] = T;
+            *group_entry<int32_t>(a, a.o_lens, gid) = T;
+            *group_entry<int32_t>(a, a.o_ginfo, gid) = (r - local) | ((local + 1) << 16);
+        }
+    }
+    __syncthreads();                                    // sT is complete; nobody reads cont any more (glist replaces it)
+    const int g0 = tid * E, g1 = min(n_groups, g0 + E);
+    long long units = 0;
+    for (int g = g0; g < g1; ++g) units += (sT[g] + 31) >> 5;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) units += __shfl_xor(units, off);
+    if ((tid & 63) == 0) redl[tid >> 6] = units;
+    __syncthreads();
+    units = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) units += redl[w];
+    units *= a.n_kv;
+    // The longest part: the share of one workgroup of the whole grid, at least HX_PROMPT_MIN_STEPS (a part costs its
+    // workgroup the queries and a partial result of 64 KiB), and long enough for the partial slots: a cut pair has at
+    // most 2 steps / S parts.
+    const long long cap = (long long)a.slots_per_block * a.n_blocks;
+    long long S = (units + n_wgs - 1) / n_wgs;
+    if (S < HX_PROMPT_MIN_STEPS) S = HX_PROMPT_MIN_STEPS;
+    if (S < (2 * units + cap - 1) / cap) S = (2 * units + cap - 1) / cap;
+    int items = 0, slots = 0, cut = 0;
+    for (int g = g0; g < g1; ++g) {
+        const int np = (int)((((sT[g] + 31) >> 5) + S - 1) / S);
+        items += np * a.n_kv;
+        if (np > 1) { slots += np * a.n_kv; ++cut; }
+    }
+    int n_items, n_slots, n_cut;
+    int at = scan_1024<false>(items, red, &n_items) - items;
+    int slot = scan_1024<false>(slots, red, &n_slots) - slots;
+    int ci = scan_1024<false>(cut, red, &n_cut) - cut;
+    for (int g = g0; g < g1; ++g) {
+        const int np = (int)((((sT[g] + 31) >> 5) + S - 1) / S);
+        *group_entry<int32_t>(a, a.o_pre, g) = at;
+        at += np * a.n_kv;
+        if (np > 1) {
+            *group_entry<int32_t>(a, a.o_gslot, g) = slot;
+            slot += np * a.n_kv;
+            *group_entry<int32_t>(a, a.o_glist, ci++) = g;
+        }
+    }
+    for (int g = n_groups + tid; g < a.n_blocks * 256; g += 1024) *group_entry<int32_t>(a, a.o_pre, g) = n_items;
+    if (tid == 0) {
+        int32_t *sched = (int32_t *)(a.ws0 + a.o_sched);
+        sched[0] = (int)S;
+        sched[1] = n_items;
+        sched[2] = n_cut;
+    }
+}
+
+// ---- the attention kernel -----------------------------------------------------------------------------------------------
+// The 32 columns of a wavefront, from its accumulators (register r of block i: d = 32 i + 8 (r / 4) + 4 (lane / 32) + r % 4)
+// for one 32-wide block i of d: bf16 into the packed operand of the output projection, unrounded if asked.
+template <int D>
+__device__ __forceinline__ void store_block(const PromptArgs &a, const f32x16_t &o, float inv, int row, int head, int i, int lane,
+                                            bool used) {
+    const int h = lane >> 5;
+    uint2 pk[4];
+    f32x4_t v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        v[q] = f32x4_t{o[4 * q] * inv, o[4 * q + 1] * inv, o[4 * q + 2] * inv, o[4 * q + 3] * inv};
+        pk[q].x = hx_cvt_pk_bf16(v[q][0], v[q][1]);
+        pk[q].y = hx_cvt_pk_bf16(v[q][2], v[q][3]);
+    }
+    uint16_t *ap = (uint16_t *)(a.ws0 + (size_t)(row >> 8) * a.stride + a.o_ap);
+#pragma unroll
+    for (int q = 0; q < 4; q += 2) {
+        // the two half-wavefronts hold 4 + 4 of every 8 consecutive d: exchange, so that each stores 8
+        const uint2 give = h ? pk[q] : pk[q + 1];
+        uint2 got;
+        got.x = __shfl_xor(give.x, 32);
+        got.y = __shfl_xor(give.y, 32);
+        const uint4 w = h ? make_uint4(got.x, got.y, pk[q + 1].x, pk[q + 1].y) : make_uint4(pk[q].x, pk[q].y, got.x, got.y);
+        if (used) *(uint4 *)(ap + hx_xp_index(row & 255, head * D + 32 * i + 8 * (q + h), a.m_groups)) = w;
+    }
+    if (a.attn_f32 && used) {
+        float *dst = a.attn_f32 + ((size_t)row * a.n_q + head) * D + 32 * i + 4 * h;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *(f32x4_t *)(dst + 8 * q) = v[q];
+    }
+}
+
+// group of item `it`: the last g with pre[g] <= it, by two ballots over the up to 32 x 256 entries
+__device__ __forceinline__ int find_group(const PromptArgs &a, int it, int lane) {
+    const int n = a.n_blocks * 256;
+    const int i1 = lane * 128;
+    const int v1 = i1 < n ? *group_entry<int32_t>(a, a.o_pre, i1) : 0x7fffffff;
+    const int seg = __popcll(__ballot(v1 <= it)) - 1;
+    const int i2 = seg * 128 + lane;
+    const int va = *group_entry<int32_t>(a, a.o_pre, i2), vb = *group_entry<int32_t>(a, a.o_pre, i2 + 64);
+    return __builtin_amdgcn_readfirstlane(seg * 128 + __popcll(__ballot(va <= it)) + __popcll(__ballot(vb <= it)) - 1);
+}
+
+template <int D, bool FP8>
+__global__ __launch_bounds__(256, 2) void attn_prompt_kernel(PromptArgs a, const char *__restrict__ pool_layer, size_t block_bytes,
+                                                             const int32_t *__restrict__ table, int max_blocks, float scale_log2e) {
+    constexpr int TILE = 16 * D * (FP8 ? 1 : 2);        // bytes of a K (or V) tile
+    constexpr int STAGE = 4 * TILE;                     // two blocks, K | V each
+    constexpr int NP = STAGE / 4096;                    // 1-KiB copies per wavefront and step
+    extern __shared__ char lds[];                       // [3][STAGE]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = lane >> 5, c32 = lane & 31;
+    const int32_t *sched = (const int32_t *)(a.ws0 + a.o_sched);
+    const int S = sched[0], n_items = sched[1];
+    const int G = a.G, n_kv = a.n_kv;
+    const int col = wave * 32 + c32, rl = col / G, gq = col - rl * G;
+    // this wavefront's part of a step: half a block (K or V) at most
+    constexpr int PER_TILE = TILE / 1024;               // copies per tile: 4, 2 or 1
+    for (int w = blockIdx.x; w < n_items; w += gridDim.x) {
+        const int it = n_items - 1 - w;
+        const int gi = find_group(a, it, lane);
+        const int info = *group_entry<int32_t>(a, a.o_ginfo, gi), T = *group_entry<int32_t>(a, a.o_lens, gi);
+        const int first = info & 0xffff, rows = info >> 16;
+        const int steps = (T + 31) >> 5, np = (steps + S - 1) / S, nblk = (T + 15) >> 4;
+        const int local = it - *group_entry<int32_t>(a, a.o_pre, gi);
+        const int kvh = local / np, part = local - kvh * np;
+        const int s0 = (int)((long long)part * steps / np), s1 = (int)((long long)(part + 1) * steps / np);
+        const size_t head_off = (size_t)kvh * 2 * TILE;
+        const int32_t *trow = table + (size_t)(first + rows - 1) * max_blocks;   // the group reads through its last row
+        const bool used = rl < rows;
+        const bool wave_used = wave * 32 < rows * G;    // wave-uniform
+        const int row = first + (used ? rl : 0);
+        const int tcol = used ? T - (rows - 1 - rl) : 0;
+        const int t_first = T - (rows - 1);
+
+        u32x4_t q[D / 16];
+        {
+            const uint4 *qp = (const uint4 *)(a.ws0 + (size_t)(row >> 8) * a.stride + a.o_qp) +
+                              ((size_t)(row & 255) * n_kv + kvh) * (D / 32) * 64;
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s) {
+                const uint4 v = qp[(s >> 1) * 64 + ((s & 1) * 2 + h) * 16 + (used ? gq : 0)];
+                q[s] = used ? u32x4_t{v.x, v.y, v.z, v.w} : u32x4_t{0u, 0u, 0u, 0u};
+            }
+        }
+        f32x16_t o[D / 32];
+#pragma unroll
+        for (int i = 0; i < D / 32; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[i][r] = 0.f;
+        float m = HX_NEG_BIG, l = 0.f;
+
+        int id0 = 2 * s0;                               // lane i holds the physical block of logical block id0 + i
+        int32_t ids = trow[min(id0 + lane, nblk - 1)];
+        auto request = [&](int s, int stage) {          // copies step s into a stage; blocks past the last repeat it
+            if (2 * s - id0 >= 64) { id0 += 64; ids = trow[min(id0 + lane, nblk - 1)]; }
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                const int piece = wave * NP + p, blk = piece / (2 * PER_TILE);
+                const int32_t id = __builtin_amdgcn_readlane(ids, 2 * s + blk - id0);
+                hx_copy_to_lds(pool_layer + (size_t)id * block_bytes + head_off + (size_t)(piece % (2 * PER_TILE)) * 1024,
+                               lane * 16, stage * STAGE + piece * 1024);
+            }
+        };
+        // everybody has left the stages of the item before
+        __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT(0));
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        request(s0, 0);
+        if (s0 + 1 < s1) request(s0 + 1, 1);
+        int stage = 0;
+        for (int s = s0; s < s1; ++s) {
+            if (s + 1 < s1) __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT(NP));
+            else __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT(0));
+            __builtin_amdgcn_s_barrier();               // step s is in its stage; the stage of step s - 1 is free
+            asm volatile("" ::: "memory");
+            if (s + 2 < s1) request(s + 2, stage >= 1 ? stage - 1 : 2);
+            if (wave_used) {
+                const char *st = lds + stage * STAGE;
+                const int t0 = s * 32;
+                // ---- scores of 32 tokens x 32 columns
+                f32x16_t sc;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+                const char *kb = st + (c32 >> 4) * 2 * TILE + (h * 16 + (c32 & 15)) * 16;
+                if (!FP8) {
+#pragma unroll
+                    for (int k = 0; k < D / 16; ++k) {
+                        const u32x4_t kop = *(const u32x4_t *)(kb + (k >> 1) * 1024 + (k & 1) * 512);
+                        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kop), __builtin_bit_cast(bf16x8_t, q[k]), sc, 0, 0, 0);
+                    }
+                } else {
+                    // 16 bytes hold the operand bytes of steps k and k + 2
+#pragma unroll
+                    for (int kp = 0; kp < D / 32; ++kp) {
+                        const int k = (kp >> 1) * 4 + (kp & 1);
+                        const u32x4_t raw = *(const u32x4_t *)(kb + (kp >> 1) * 1024 + (kp & 1) * 512);
+                        const uint2 a0 = hx_e4m3x4_to_bf16x4(raw.x), a1 = hx_e4m3x4_to_bf16x4(raw.y);
+                        const uint2 b0 = hx_e4m3x4_to_bf16x4(raw.z), b1 = hx_e4m3x4_to_bf16x4(raw.w);
+                        const u32x4_t ka = {a0.x, a0.y, a1.x, a1.y}, kc = {b0.x, b0.y, b1.x, b1.y};
+                        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ka), __builtin_bit_cast(bf16x8_t, q[k]), sc, 0, 0, 0);
+                        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kc), __builtin_bit_cast(bf16x8_t, q[k + 2]), sc, 0, 0, 0);
+                    }
+                }
+                // ---- softmax; register r is token t0 + 8 (r / 4) + 4 h + r % 4
+                float p[16];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) p[r] = sc[r];
+                if (t0 + 32 > t_first) {                // wave-uniform: some column ends inside these tokens
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (t0 + 8 * (r >> 2) + 4 * h + (r & 3) >= tcol) p[r] = -INFINITY;
+                }
+                float mx = p[0];
+#pragma unroll
+                for (int r = 1; r < 16; ++r) mx = fmaxf(mx, p[r]);
+                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                const float m_new = fmaxf(m, mx * scale_log2e);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(p[r], scale_log2e, -m_new));
+                float sum = 0.f;
+#pragma unroll
+                for (int r = 0; r < 16; r += 4) sum += (p[r] + p[r + 1]) + (p[r + 2] + p[r + 3]);
+                if (__builtin_amdgcn_ballot_w64(m_new != m) != 0ull) {     // rescale only when some maximum moved
+                    const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+                    l *= alpha;
+#pragma unroll
+                    for (int i = 0; i < D / 32; ++i) o[i] *= alpha;
+                    m = m_new;
+                }
+                l += sum;
+                uint32_t ph[8], pl[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    ph[j] = hx_cvt_pk_bf16(p[2 * j], p[2 * j + 1]);
+                    pl[j] = hx_cvt_pk_bf16(p[2 * j] - __uint_as_float(ph[j] << 16), p[2 * j + 1] - __uint_as_float(ph[j] & 0xffff0000u));
+                }
+                // ---- O^T += V^T P^T, one block of 16 tokens after the other: contraction slots 0..3 of a lane are tokens
+                // 4 h + 0..3 of the block, slots 4..7 tokens 8 + 4 h + 0..3
+                const bool ragged = t0 + 32 > T;        // wave-uniform: V of positions that do not exist may hold anything
+#pragma unroll
+                for (int blk = 0; blk < 2; ++blk) {
+                    const char *vb = st + (2 * blk + 1) * TILE;
+                    u32x4_t v[D / 32];
+                    if (!FP8) {
+                        const char *vl = vb + (h * 16 + (c32 & 15)) * 16 + (c32 >> 4) * 8;
+#pragma unroll
+                        for (int i = 0; i < D / 32; ++i) {
+                            const u32x2_t x = *(const u32x2_t *)(vl + i * 1024), y = *(const u32x2_t *)(vl + i * 1024 + 512);
+                            v[i] = u32x4_t{x.x, x.y, y.x, y.y};
+                        }
+                    } else {
+                        // 16 bytes: 4 tokens of d = c32 % 16 of four 16-wide d ranges
+                        const char *vl = vb + (h * 16 + (c32 & 15)) * 16;
+#pragma unroll
+                        for (int ip = 0; ip < D / 64; ++ip) {
+                            const u32x4_t x = *(const u32x4_t *)(vl + ip * 1024), y = *(const u32x4_t *)(vl + ip * 1024 + 512);
+                            const bool up = (c32 >> 4) != 0;
+                            const uint2 x0 = hx_e4m3x4_to_bf16x4(up ? x.y : x.x), y0 = hx_e4m3x4_to_bf16x4(up ? y.y : y.x);
+                            const uint2 x1 = hx_e4m3x4_to_bf16x4(up ? x.w : x.z), y1 = hx_e4m3x4_to_bf16x4(up ? y.w : y.z);
+                            v[2 * ip] = u32x4_t{x0.x, x0.y, y0.x, y0.y};
+                            v[2 * ip + 1] = u32x4_t{x1.x, x1.y, y1.x, y1.y};
+                        }
+                    }
+                    if (ragged) {
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            const int valid = T - (t0 + 16 * blk + 8 * e + 4 * h);
+                            const uint32_t m01 = valid >= 2 ? 0xffffffffu : (valid == 1 ? 0x0000ffffu : 0u);
+                            const uint32_t m23 = valid >= 4 ? 0xffffffffu : (valid == 3 ? 0x0000ffffu : 0u);
+#pragma unroll
+                            for (int i = 0; i < D / 32; ++i) { v[i][2 * e] &= m01; v[i][2 * e + 1] &= m23; }
+                        }
+                    }
+                    const u32x4_t hi = {ph[4 * blk], ph[4 * blk + 1], ph[4 * blk + 2], ph[4 * blk + 3]};
+                    const u32x4_t lo = {pl[4 * blk], pl[4 * blk + 1], pl[4 * blk + 2], pl[4 * blk + 3]};
+#pragma unroll
+                    for (int i = 0; i < D / 32; ++i)
+                        o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v[i]), __builtin_bit_cast(bf16x8_t, hi), o[i], 0, 0, 0);
+#pragma unroll
+                    for (int i = 0; i < D / 32; ++i)
+                        o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v[i]), __builtin_bit_cast(bf16x8_t, lo), o[i], 0, 0, 0);
+                }
+            }
+            stage = stage == 2 ? 0 : stage + 1;
+        }
+        if (!wave_used) continue;
+        l += __shfl_xor(l, 32);
+        if (np == 1) {
+            const float inv = 1.0f / l;
+#pragma unroll
+            for (int i = 0; i < D / 32; ++i) store_block<D>(a, o[i], inv, row, kvh * G + gq, i, lane, used);
+        } else {
+            // partial result in register order: [slot][wavefront][d block, 4 registers][lane], and [max 32 | sum 32]
+            const int slot = *group_entry<int32_t>(a, a.o_gslot, gi) + local;
+            char *sb = a.ws0 + (size_t)(slot / a.slots_per_block) * a.stride;
+            const size_t sub = (size_t)(slot % a.slots_per_block) * 4 + wave;
+            ((float *)(sb + a.o_ml))[sub * 64 + lane] = h ? l : m;
+            f32x4_t *po = (f32x4_t *)(sb + a.o_po) + sub * (D / 8) * 64 + lane;
+#pragma unroll
+            for (int i = 0; i < D / 32; ++i)
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4)
+                    po[(i * 4 + r4) * 64] = f32x4_t{o[i][4 * r4], o[i][4 * r4 + 1], o[i][4 * r4 + 2], o[i][4 * r4 + 3]};
+        }
+    }
+}
+
+// ---- combine: the parts of the cut pairs ------------------------------------------------------------------------------
+// Item = (cut group, KV head, 32 columns); one wavefront per 32-wide block of d.  Same lane layout as the partials;
+// parts are merged in order, four requested at a time.
+template <int D>
+__global__ __launch_bounds__(64 * (D / 32)) void prompt_combine_kernel(PromptArgs a) {
+    const int lane = threadIdx.x & 63, i = threadIdx.x >> 6, c32 = lane & 31;
+    const int32_t *sched = (const int32_t *)(a.ws0 + a.o_sched);
+    const int S = sched[0], n_items = sched[2] * a.n_kv * 4;
+    const int G = a.G;
+    for (int w = blockIdx.x; w < n_items; w += gridDim.x) {
+        const int cb = w & 3, kvh = (w >> 2) % a.n_kv;
+        const int gi = *group_entry<int32_t>(a, a.o_glist, (w >> 2) / a.n_kv);
+        const int info = *group_entry<int32_t>(a, a.o_ginfo, gi), T = *group_entry<int32_t>(a, a.o_lens, gi);
+        const int first = info & 0xffff, rows = info >> 16;
+        if (cb * 32 >= rows * G) continue;
+        const int np = (((T + 31) >> 5) + S - 1) / S;
+        const int slot0 = *group_entry<int32_t>(a, a.o_gslot, gi) + kvh * np;
+        const int col = cb * 32 + c32, rl = col / G, gq = col - rl * G;
+        const bool used = rl < rows;
+        auto base = [&](int p) { return a.ws0 + (size_t)((slot0 + p) / a.slots_per_block) * a.stride; };
+        auto sub = [&](int p) { return (size_t)((slot0 + p) % a.slots_per_block) * 4 + cb; };
+        float M = HX_NEG_BIG;
+        for (int p = 0; p < np; p += 4) {
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { const int pu = min(p + u, np - 1); v[u] = ((const float *)(base(pu) + a.o_ml))[sub(pu) * 64 + c32]; }
+            M = fmaxf(M, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+        }
+        f32x16_t acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        float den = 0.f;
+        for (int p = 0; p < np; p += 4) {
+            float pm[4], pl[4];
+            f32x4_t v[4][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int pu = min(p + u, np - 1);
+                const float *ml = (const float *)(base(pu) + a.o_ml) + sub(pu) * 64 + c32;
+                pm[u] = ml[0];
+                pl[u] = ml[32];
+                const f32x4_t *po = (const f32x4_t *)(base(pu) + a.o_po) + (sub(pu) * (D / 8) + i * 4) * 64 + lane;
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) v[u][r4] = po[r4 * 64];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float wu = p + u < np ? __builtin_amdgcn_exp2f(pm[u] - M) : 0.f;
+                den += wu * pl[u];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] += wu * v[u][r >> 2][r & 3];
+            }
+        }
+        store_block<D>(a, acc, 1.0f / den, first + (used ? rl : 0), kvh * G + gq, i, lane, used);
+    }
+}
+
+// ---- launchers ------------------------------------------------------------------------------------------------------------
+static PromptArgs prompt_args(const hx_engine *e, int n_rows, size_t stride, float *attn_f32) {
+    const hx_ws_map &m = e->map;
+    PromptArgs a;
+    a.ws0 = e->ws;
+    a.stride = stride;
+    a.o_qp = m.qp; a.o_pre = m.pre; a.o_lens = m.lens; a.o_ginfo = m.chunk_ginfo; a.o_gslot = m.chunk_rgrp; a.o_glist = m.chunk_cont;
+    a.o_sched = m.sched; a.o_ap = m.ap; a.o_ml = m.chunk_part_ml; a.o_po = m.chunk_part_o;
+    a.n_rows = n_rows;
+    a.n_blocks = (n_rows + 255) / 256;
+    a.slots_per_block = (e->attn_waves + e->cfg.max_batch * e->cfg.n_kv_heads) / 2;   // a slot here is two of that area's (64 columns)
+    a.n_kv = e->cfg.n_kv_heads; a.G = e->G; a.n_q = e->cfg.n_q_heads;
+    a.m_groups = hx_m_groups(n_rows < 256 ? n_rows : 256);
+    a.attn_f32 = attn_f32;
+    return a;
+}
+
+// e->ws: the workspace of the first 256 rows; `stride` bytes to the next (0 where n_rows <= 256)
+int hx_launch_prompt_setup(const hx_engine *e, int n_rows, const int32_t *positions, const int32_t *seq_lens, const int32_t *table,
+                           int max_blocks, hipStream_t st, size_t stride) {
+    if (n_rows < 1 || n_rows > HX_PREFILL_MAX_ROWS) return hx_fail(HX_E_RANGE, "%d prompt rows in one call", n_rows);
+    const PromptArgs a = prompt_args(e, n_rows, stride, nullptr);
+    hipLaunchKernelGGL(prompt_rows_kernel, dim3(n_rows), dim3(64), 0, st, e->ws, stride, e->map.cs, e->map.blk_new, e->map.chunk_cont,
+                       positions, seq_lens, table, max_blocks, e->D / 2, (double)e->cfg.rope_theta, e->cfg.max_batch);
+    HX_CHECK_LAUNCH("prompt_rows");
+    hipLaunchKernelGGL(prompt_sched_kernel, dim3(1), dim3(1024), (size_t)n_rows * 4, st, a, seq_lens, e->map.chunk_cont,
+                       HX_PROMPT_COLS / e->G, e->attn_waves / 4);
+    HX_CHECK_LAUNCH("prompt_sched");
+    return HX_OK;
+}
+
+int hx_launch_prompt_attention(const hx_engine *e, const hx_kv *kv, int layer, int n_rows, const int32_t *table, int max_blocks,
+                               float *attn_f32, hipStream_t st, size_t stride) {
+    const PromptArgs a = prompt_args(e, n_rows, stride, attn_f32);
+    const char *pool_layer = kv->pool + (size_t)layer * kv->layer_bytes;
+    const float scale_log2e = (float)(1.4426950408889634 / sqrt((double)e->D));
+    dim3 grid(e->attn_waves / 4), block(256);           // two workgroups of four wavefronts per compute unit
+    const size_t lds = 12 * kv->tile_bytes;             // three stages of two blocks
+#define HX_PROMPT_LAUNCH(DD, F8) \
+    hipLaunchKernelGGL((attn_prompt_kernel<DD, F8>), grid, block, lds, st, a, pool_layer, kv->block_bytes, table, max_blocks, scale_log2e)
+    if (e->D == 128) { if (kv->fp8) HX_PROMPT_LAUNCH(128, true); else HX_PROMPT_LAUNCH(128, false); }
+    else             { if (kv->fp8) HX_PROMPT_LAUNCH(64, true);  else HX_PROMPT_LAUNCH(64, false); }
+#undef HX_PROMPT_LAUNCH
+    HX_CHECK_LAUNCH("attn_prompt");
+    return HX_OK;
+}
+
+int hx_launch_prompt_combine(const hx_engine *e, int n_rows, float *attn_f32, hipStream_t st, size_t stride) {
+    const PromptArgs a = prompt_args(e, n_rows, stride, attn_f32);
+    const int items = n_rows * a.n_kv * 4;              // at most; the kernel strides over what there is
+    dim3 grid(items < 2048 ? items : 2048);
+    if (e->D == 128) hipLaunchKernelGGL((prompt_combine_kernel<128>), grid, dim3(256), 0, st, a);
+    else             hipLaunchKernelGGL((prompt_combine_kernel<64>), grid, dim3(128), 0, st, a);
+    HX_CHECK_LAUNCH("prompt_combine");
+    return HX_OK;
+}

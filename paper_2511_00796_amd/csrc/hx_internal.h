@@ -163,6 +163,17 @@ __host__ __device__ __forceinline__ int hx_vtile8_index(int t, int d) {
     return (d >> 6) * 1024 + ((((t >> 2) * 16) + (d & 15)) << 4) + (((d >> 5) & 1) << 3) + (((d >> 4) & 1) << 2) + (t & 3);
 }
 
+// 1 KiB from global memory straight into LDS (lane l's 16 bytes, at src + 16 l, to lds_off + 16 l).  Written as asm because
+// behind the builtin the compiler makes every LDS read wait for all copies in flight (it cannot tell the stages of a
+// ring apart).  m0 is set in the same statement and the compiler keeps nothing in it in these kernels (it is reserved: no
+// clobber can be declared).  The copy has no output register; the kernel waits for it by count (HX_COPY_WAIT) before the barrier that hands
+// a stage over, and for all of it before it ends.
+__device__ __forceinline__ void hx_copy_to_lds(const void *src, uint32_t lane_off, uint32_t lds_off) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_off), "s"(src), "s"(lds_off) : "memory");
+}
+// s_waitcnt immediate: at most n vector-memory operations outstanding, all LDS operations done
+#define HX_COPY_WAIT(n) (((n) & 15) | (((n) >> 4) << 14) | 0x0070)
+
 // ---- host-side descriptors ------------------------------------------------------------------------
 
 struct hx_matrix {          // one packed weight matrix
@@ -294,9 +305,15 @@ __device__ __forceinline__ void hx_philox4x32_10(uint32_t c0, uint32_t c1, uint3
 int hx_launch_chunk_setup(const hx_engine *e, int n_rows, const int32_t *seq_lens, const int32_t *table, int max_blocks,
                           hipStream_t st);
 int hx_launch_chunk_attention(const hx_engine *e, const hx_kv *kv, int layer, const int32_t *table, int max_blocks,
-                              hipStream_t st, int blocks = 1, size_t block_stride = 0, int rows_per_block = 0);
-int hx_launch_chunk_combine(const hx_engine *e, int n_rows, float *attn_f32_out, hipStream_t st, int blocks = 1,
-                            size_t block_stride = 0);
+                              hipStream_t st);
+int hx_launch_chunk_combine(const hx_engine *e, int n_rows, float *attn_f32_out, hipStream_t st);
+
+// attention_prompt.hip: block_stride = bytes between the workspaces of consecutive 256-row blocks
+int hx_launch_prompt_setup(const hx_engine *e, int n_rows, const int32_t *positions, const int32_t *seq_lens, const int32_t *table,
+                           int max_blocks, hipStream_t st, size_t block_stride = 0);
+int hx_launch_prompt_attention(const hx_engine *e, const hx_kv *kv, int layer, int n_rows, const int32_t *table, int max_blocks,
+                               float *attn_f32_out, hipStream_t st, size_t block_stride = 0);
+int hx_launch_prompt_combine(const hx_engine *e, int n_rows, float *attn_f32_out, hipStream_t st, size_t block_stride = 0);
 
 // attention_fp8.hip: the decode step's attention over an 8-bit cache
 int hx_launch_attention_fp8(const hx_engine *e, const hx_kv *kv, int layer, const int32_t *table, int max_blocks,
