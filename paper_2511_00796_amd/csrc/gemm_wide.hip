@@ -7,17 +7,16 @@
 // [k_step][8 m-groups][lane][8] in that block's workspace.  Both are already in matrix-core operand order, so
 // staging is a plain copy of 1-KiB pieces and every LDS read is 16 contiguous bytes per lane (conflict-free).
 //
-// Workgroup = 4 wavefronts in 2 x 2, each a 128 x 128 sub-tile = 4 x 4 accumulators of 32 x 32 (256 accumulator
-// registers: all a wavefront has beside its 256 ordinary ones, which is why there are no producer wavefronts).
-// A chunk is 2 k-steps: 16 pieces of X and 16 of W (32 KiB).  Every wavefront copies a quarter of each chunk,
-// global -> registers -> LDS: requested three chunks ahead (two register sets), written to LDS one chunk ahead, two
-// LDS stages, one barrier per chunk.  The barrier of chunk c + 1 is passed BEFORE the last k-step of chunk c is
-// multiplied, so that the first operand reads of the next chunk hide behind those products.  Measured on MI355X
-// (7B gate|up, 2048 rows): 45-48 % of the bf16 matrix peak.  The kernel with its copies alone (no arithmetic) takes as
-// long as the whole kernel: what bounds it is the rate at which the compute units can draw from the L2 (8-9 TB/s over
-// the chip, about 35 GB/s per compute unit when all are busy, however local the traffic: 80 % of the L2 requests of
-// this product hit), not the matrix cores (66 % with the copies removed) and not the LDS.  The direct global -> LDS
-// path (global_load_lds) was slower; a larger output tile, the only way to draw fewer bytes per flop, spills.
+// Workgroup = 8 wavefronts, two per SIMD: 2 x 4 sub-tiles of 128 x 64 (256 columns) or 4 x 2 of 64 x 96 (192 columns).
+// A chunk is 2 k-steps: 16 pieces of X and 2 WNT of W, each copied global -> LDS directly by one wavefront, requested two
+// chunks ahead into a ring of three stages; one barrier per chunk, passed BEFORE the chunk's last k-step is multiplied,
+// so that the first operand reads of the next chunk hide behind those products, as the reads of its second k-step hide
+// behind the first.  Reads, copies and products are laid out by hand in groups (sched_barrier).
+// What bounds it is the matrix cores' power: with random operands a loop of 32x32x16 products out of registers reaches
+// 1 550 TFLOP/s on this card (zeros: 2 410).  7B gate|up, 2048 rows, output stores left out: this kernel 1 253 TFLOP/s;
+// with its copies removed 1 442, with its products removed 1 965.  The four-wavefront kernel before it (128 x 128 per
+// wavefront, copies through registers) 1 195, and 951 against 1 086 with fp32 stores, which the second wavefront of a
+// SIMD overlaps.  Four or five stages, or chunks of 4 k-steps in two stages, were not faster (1 095, 1 088, 995).
 //
 // Workgroup numbering: consecutive workgroup ids go to different XCDs, so id -> (xcd, slot); the workgroups of one
 // XCD take all row blocks of a few column blocks and walk K in step: each XCD's L2 sees every weight once.
@@ -30,9 +29,9 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 namespace {
 
 constexpr int WIDE_KC = 2;        // k-steps per chunk
-constexpr int wide_lds_bytes(int wnt) { return 2 * WIDE_KC * (8 + wnt) * 1024; }
-
-#define HX_WIDE_LGKM0 0xC07F      /* s_waitcnt lgkmcnt(0) and nothing else */
+constexpr int WIDE_STAGES = 3;
+constexpr int WIDE_WAVES = 8;
+constexpr int wide_lds_bytes(int wnt) { return WIDE_STAGES * WIDE_KC * (8 + wnt) * 1024; }
 
 struct WideArgs {
     const uint4 *wp;              // packed weights of the matrix
@@ -46,11 +45,14 @@ struct WideArgs {
 };
 
 // WNT: 32-column tiles per workgroup: 8 (a 256 x 256 output tile) or 6 (256 x 192, for products that would otherwise
-// leave compute units idle)
-template <int WNT, int EPI, bool TAIL>
-__global__ __launch_bounds__(256) void gemm_wide_kernel(WideArgs a) {
-    constexpr int KC = WIDE_KC, TW = WNT / 2, PIECES = KC * (8 + WNT), LPW = PIECES / 4, STAGE_U4 = PIECES * 64;
-    extern __shared__ u32x4_t lds[];                    // [2 stages][PIECES][64 lanes]
+// leave compute units idle).  Splits hold whole chunks.
+template <int WNT, int EPI>
+__global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) {
+    constexpr int KC = WIDE_KC, NST = WIDE_STAGES, WCOL = WNT == 8 ? 4 : 2, WROW = WIDE_WAVES / WCOL, TM = 8 / WROW, TW = WNT / WCOL;
+    constexpr int PIECES = KC * (8 + WNT), STAGE_U4 = PIECES * 64;
+    constexpr int LPW = (PIECES + WIDE_WAVES - 1) / WIDE_WAVES, FULL = PIECES - (LPW - 1) * WIDE_WAVES;   // waves < FULL copy LPW pieces, the others one less
+    static_assert(KC == 2 && TM * TW == (WNT == 8 ? 8 : 6), "the operand registers alternate between two k-steps");
+    extern __shared__ u32x4_t lds[];                    // [NST][PIECES][64 lanes]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int w = blockIdx.x, xcd = w & 7, slot = w >> 3;
     const int b = slot % a.R, nbl = (slot / a.R) * 8 + xcd;
@@ -59,121 +61,109 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(WideArgs a) {
     const int nt0 = nbl * WNT;
     const int k_steps = a.k_steps;
     const int k0 = blockIdx.y * a.steps_per_split, k1 = min(k_steps, k0 + a.steps_per_split);
-    const int n_chunks = (k1 - k0 + KC - 1) / KC;
-    const uint4 *xp = (const uint4 *)(a.xp0 + (size_t)b * a.block_stride);
-    // this wavefront's share of the copies of a chunk: LPW streams, each a wave-uniform pointer that advances by a
-    // fixed step per chunk and stops at the matrix' last chunk (requests past the end re-read it: never used)
-    const uint4 *ptr[LPW];
-    int step[LPW], dsts[LPW];
+    const int n_chunks = (k1 - k0) / KC;
+    const u32x4_t *xp = (const u32x4_t *)(a.xp0 + (size_t)b * a.block_stride);
+    // this wavefront's share of the copies of a chunk: wave-uniform pointers that advance by a fixed step per chunk and
+    // stop at the split's last one (requests past the end repeat it: never used)
+    const bool full = wave < FULL;
+    const u32x4_t *ptr[LPW];
+    int step[LPW];
+    uint32_t dst[LPW];
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
-        const int p = wave * LPW + i;
+        const int p = min(i * WIDE_WAVES + wave, PIECES - 1);
         if (p < KC * 8) {
             const int kc = p >> 3, mg = p & 7;
-            ptr[i] = xp + ((size_t)(k0 + kc) * 8 + mg) * 64; step[i] = KC * 8 * 64; dsts[i] = kc * 8 + mg;
+            ptr[i] = xp + ((size_t)(k0 + kc) * 8 + mg) * 64; step[i] = KC * 8 * 64; dst[i] = (kc * 8 + mg) * 1024;
         } else {
             const int q = p - KC * 8, t = q / KC, kc = q % KC;
             const int nt = min(nt0 + t, a.n_tiles - 1);
-            ptr[i] = a.wp + ((size_t)nt * k_steps + k0 + kc) * 64; step[i] = KC * 64; dsts[i] = KC * 8 + kc * WNT + t;
+            ptr[i] = (const u32x4_t *)a.wp + ((size_t)nt * k_steps + k0 + kc) * 64; step[i] = KC * 64; dst[i] = (KC * 8 + kc * WNT + t) * 1024;
         }
     }
-    int next_c = 0;                                     // chunk the streams point at
-    auto fetch = [&](u32x4_t (&g)[LPW]) {               // global -> registers, then the streams move on
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) g[i] = *(const u32x4_t *)(ptr[i] + lane);
+    int next_c = 0;                                     // chunk the pointers stand at, and the stage it goes to
+    uint32_t next_stage = 0;
+    auto copy_one = [&](int i) {
+        if (i + 1 < LPW || full) hx_copy_to_lds(ptr[i], lane * 16, next_stage * (STAGE_U4 * 16) + dst[i]);
+    };
+    auto advance = [&]() {
         ++next_c;
-        const int adv = -(int)(k0 + next_c * KC < k_steps);     // all ones while the next chunk exists
+        const int go = -(int)(next_c < n_chunks);       // all ones while the next chunk exists
 #pragma unroll
-        for (int i = 0; i < LPW; ++i) ptr[i] += step[i] & adv;
+        for (int i = 0; i < LPW; ++i) ptr[i] += step[i] & go;
+        next_stage = next_stage + 1 == NST ? 0 : next_stage + 1;
     };
-    auto stash = [&](int c, const u32x4_t (&g)[LPW]) {  // registers -> the LDS stage of chunk c
-        u32x4_t *st = lds + (c & 1) * STAGE_U4;
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) st[dsts[i] * 64 + lane] = g[i];
+    // this wavefront's copies of the chunk before the last requested one have landed, its LDS reads are done; then everyone's
+    auto hand_over = [&]() {
+        if (full) __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT((NST - 2) * LPW));
+        else __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT((NST - 2) * (LPW - 1)));
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
     };
-    const int wm = wave >> 1, wn = wave & 1;
-    f32x16_t acc[4][TW];
+    const int wm = wave / WCOL, wn = wave % WCOL;
+    f32x16_t acc[TM][TW];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TW; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    u32x4_t a0[4], b0[TW], a1[4], b1[TW];
-    auto load_ops = [&](int c, int kc, u32x4_t (&x)[4], u32x4_t (&wt)[TW]) {
-        const u32x4_t *st = lds + (c & 1) * STAGE_U4;
+    u32x4_t x[2][TM], wt[2][TW];
+    const u32x4_t *base = lds + lane;
+    auto read_x = [&](uint32_t stage, int kc, int i) { x[kc & 1][i] = base[stage * STAGE_U4 + (kc * 8 + TM * wm + i) * 64]; };
+    auto read_w = [&](uint32_t stage, int kc, int j) { wt[kc & 1][j] = base[stage * STAGE_U4 + (KC * 8 + kc * WNT + wn * TW + j) * 64]; };
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = st[(kc * 8 + 4 * wm + i) * 64 + lane];
+    for (int s = 0; s < NST - 1; ++s) {
 #pragma unroll
-        for (int j = 0; j < TW; ++j) wt[j] = st[(KC * 8 + kc * WNT + wn * TW + j) * 64 + lane];
-    };
-    auto mfmas = [&](int ks, u32x4_t (&x)[4], u32x4_t (&wt)[TW]) {
-        if (TAIL && ks >= k1) {                         // the chunk that pads an odd count: multiply by zero
-#pragma unroll
-            for (int i = 0; i < 4; ++i) x[i] = u32x4_t{0u, 0u, 0u, 0u};
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < TW; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, wt[j]),
-                                                                    __builtin_bit_cast(bf16x8_t, x[i]), acc[i][j], 0, 0, 0);
-    };
-    // one chunk: g holds chunk c + 1 on entry and chunk c + 3 on exit
-    auto chunk = [&](int c, u32x4_t (&g)[LPW]) {
-        // k-step 0: its products; between them the operand reads of k-step 1, chunk c + 1 into its stage (which nobody
-        // reads any more: everyone has passed barrier c) and the requests for chunk c + 3
-        load_ops(c, 1, a1, b1);
-        stash(c + 1, g);
-        fetch(g);
-        mfmas(k0 + c * KC, a0, b0);
-#pragma unroll
-        for (int r = 0; r < 4 + TW; ++r) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // one matrix instruction,
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // one LDS read
-        }
-#pragma unroll
-        for (int r = 0; r < LPW; ++r) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);      // one LDS write,
-            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);      // one global load
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        // this wavefront has read all it needs of chunk c and has written its share of chunk c + 1.  A bare barrier:
-        // the LDS traffic it orders has been waited for explicitly, and no global store is outstanding in the loop.
-        __builtin_amdgcn_s_waitcnt(HX_WIDE_LGKM0);
-        __builtin_amdgcn_s_barrier();                  // barrier c + 1
-        asm volatile("" ::: "memory");
-        load_ops(c + 1, 0, a0, b0);
-        mfmas(k0 + c * KC + 1, a1, b1);
-#pragma unroll
-        for (int r = 0; r < 4 + TW; ++r) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 1);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    u32x4_t g0[LPW], g1[LPW];
-    fetch(g0);                                          // chunk 0
-    fetch(g1);                                          // chunk 1
-    stash(0, g0);
-    fetch(g0);                                          // chunk 2
-    __builtin_amdgcn_s_waitcnt(HX_WIDE_LGKM0);
-    __builtin_amdgcn_s_barrier();                      // barrier 0: chunk 0 is in its stage
-    asm volatile("" ::: "memory");
-    load_ops(0, 0, a0, b0);
-    for (int c = 0; c < n_chunks; c += 2) {             // an odd count runs one chunk more, with zero operands (TAIL)
-        chunk(c, g1);
-        chunk(c + 1, g0);
+        for (int i = 0; i < LPW; ++i) copy_one(i);
+        advance();
     }
+    hand_over();                                        // chunk 0 is in its stage
+#pragma unroll
+    for (int j = 0; j < TW; ++j) read_w(0, 0, j);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) read_x(0, 0, i);
+    uint32_t rd = 0;                                    // stage of chunk c
+    for (int c = 0; c < n_chunks; ++c) {
+        const uint32_t nrd = rd + 1 == NST ? 0 : rd + 1;
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc) {
+            // between the products of k-step kc: the operand reads of the next one (behind the barrier that hands over
+            // chunk c + 1, if it is that chunk's first), and, in k-step 0, the copies of chunk c + NST - 1 into the stage
+            // of chunk c - 1, which everybody has left
+            const bool last = kc + 1 == KC;
+            if (last) hand_over();
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                if (i == 0) {
+#pragma unroll
+                    for (int j = 0; j < TW; ++j) read_w(last ? nrd : rd, last ? 0 : kc + 1, j);
+                }
+                read_x(last ? nrd : rd, last ? 0 : kc + 1, i);
+                if (kc == 0) {
+#pragma unroll
+                    for (int q = 0; q < LPW; ++q) if (q * TM / LPW == i) copy_one(q);
+                }
+#pragma unroll
+                for (int j = 0; j < TW; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, wt[kc & 1][j]),
+                                                                        __builtin_bit_cast(bf16x8_t, x[kc & 1][i]), acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (kc == 0) advance();
+        }
+        rd = nrd;
+    }
+    __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT(0));        // no copy is in flight when the workgroup gives its LDS back
 
-    // accumulator register r of lane l: batch row m = 32*(4*wm + i) + l%32, column n = 32*nt + 8*(r/4) + 4*(l/32) + r%4
+    // accumulator register r of lane l: batch row m = 32*(TM*wm + i) + l%32, column n = 32*nt + 8*(r/4) + 4*(l/32) + r%4
     const int hl = lane >> 5, ml = lane & 31;
     if (EPI == HX_EPI_PARTIAL) {
         float *y = a.y0 + ((size_t)b * a.block_stride) / 4 + (size_t)blockIdx.y * 256 * a.N;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int m = 32 * (4 * wm + i) + ml;
+        for (int i = 0; i < TM; ++i) {
+            const int m = 32 * (TM * wm + i) + ml;
 #pragma unroll
             for (int j = 0; j < TW; ++j) {
                 const int nt = nt0 + wn * TW + j;
@@ -192,8 +182,8 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(WideArgs a) {
         // SiLU(gate) * up: rows 0..15 of a tile are gate columns 16*nt + p, rows 16..31 the matching up columns
         uint16_t *mp = a.mp0 + ((size_t)b * a.block_stride) / 2;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int m = 32 * (4 * wm + i) + ml;
+        for (int i = 0; i < TM; ++i) {
+            const int m = 32 * (TM * wm + i) + ml;
 #pragma unroll
             for (int j = 0; j < TW; ++j) {
                 const int nt = nt0 + wn * TW + j;
@@ -217,23 +207,23 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(WideArgs a) {
     }
 }
 
-template <int WNT, int EPI, bool TAIL>
+template <int WNT, int EPI>
 int launch_wide(dim3 grid, hipStream_t st, const WideArgs &a) {
     static std::once_flag once;
     static hipError_t configured = hipSuccess;
     std::call_once(once, [] {
-        configured = hipFuncSetAttribute((const void *)gemm_wide_kernel<WNT, EPI, TAIL>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        configured = hipFuncSetAttribute((const void *)gemm_wide_kernel<WNT, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                          wide_lds_bytes(WNT));
     });
     if (configured != hipSuccess) return hx_fail(HX_E_HIP, "hipFuncSetAttribute: %s", hipGetErrorString(configured));
-    hipLaunchKernelGGL((gemm_wide_kernel<WNT, EPI, TAIL>), grid, dim3(256), wide_lds_bytes(WNT), st, a);
+    hipLaunchKernelGGL((gemm_wide_kernel<WNT, EPI>), grid, dim3(64 * WIDE_WAVES), wide_lds_bytes(WNT), st, a);
     return HX_OK;
 }
 
 template <int WNT>
-int launch_wide_epi(int epilogue, bool tail, dim3 grid, hipStream_t st, const WideArgs &a) {
-    if (epilogue == HX_EPI_PARTIAL) return tail ? launch_wide<WNT, HX_EPI_PARTIAL, true>(grid, st, a) : launch_wide<WNT, HX_EPI_PARTIAL, false>(grid, st, a);
-    return tail ? launch_wide<WNT, HX_EPI_SWIGLU, true>(grid, st, a) : launch_wide<WNT, HX_EPI_SWIGLU, false>(grid, st, a);
+int launch_wide_epi(int epilogue, dim3 grid, hipStream_t st, const WideArgs &a) {
+    if (epilogue == HX_EPI_PARTIAL) return launch_wide<WNT, HX_EPI_PARTIAL>(grid, st, a);
+    return launch_wide<WNT, HX_EPI_SWIGLU>(grid, st, a);
 }
 
 }  // namespace
@@ -281,13 +271,9 @@ int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, 
     a.steps_per_split = ((m->k_steps + splits - 1) / splits + 1) & ~1;
     const int NB = (m->n_tiles + wnt - 1) / wnt;
     dim3 grid(((NB + 7) / 8) * 8 * row_blocks, splits);
-    bool tail = false;                                  // some split has an odd number of chunks
-    for (int s = 0; s < splits; ++s) {
-        const int k0 = s * a.steps_per_split, k1 = std::min(m->k_steps, k0 + a.steps_per_split);
-        if (k1 <= k0) return hx_fail(HX_E_RANGE, "%d splits leave split %d of %d k-steps empty", splits, s, m->k_steps);
-        if (((k1 - k0) / WIDE_KC) & 1) tail = true;
-    }
-    const int rc = wnt == 8 ? launch_wide_epi<8>(epilogue, tail, grid, st, a) : launch_wide_epi<6>(epilogue, tail, grid, st, a);
+    for (int sp = 0; sp < splits; ++sp)
+        if (sp * a.steps_per_split >= m->k_steps) return hx_fail(HX_E_RANGE, "%d splits leave split %d of %d k-steps empty", splits, sp, m->k_steps);
+    const int rc = wnt == 8 ? launch_wide_epi<8>(epilogue, grid, st, a) : launch_wide_epi<6>(epilogue, grid, st, a);
     if (rc) return rc;
     HX_CHECK_LAUNCH("gemm_wide");
     return HX_OK;
