@@ -7,7 +7,8 @@
 // [k_step][8 m-groups][lane][8] in that block's workspace.  Both are already in matrix-core operand order, so
 // staging is a plain copy of 1-KiB pieces and every LDS read is 16 contiguous bytes per lane (conflict-free).
 //
-// Workgroup = 8 wavefronts, two per SIMD: 2 x 4 sub-tiles of 128 x 64 (256 columns) or 4 x 2 of 64 x 96 (192 columns).
+// Workgroup = 8 wavefronts, two per SIMD: 2 x 4 sub-tiles of 128 x 64 (256 columns), 4 x 2 of 64 x 96 (192 columns), or 8
+// of 32 rows by all 224 or 160 columns.
 // A chunk is 2 k-steps: 16 pieces of X and 2 WNT of W, each copied global -> LDS directly by one wavefront, requested two
 // chunks ahead into a ring of three stages; one barrier per chunk, passed BEFORE the chunk's last k-step is multiplied,
 // so that the first operand reads of the next chunk hide behind those products, as the reads of its second k-step hide
@@ -18,8 +19,11 @@
 // wavefront, copies through registers) 1 195, and 951 against 1 086 with fp32 stores, which the second wavefront of a
 // SIMD overlaps.  Four or five stages, or chunks of 4 k-steps in two stages, were not faster (1 095, 1 088, 995).
 //
-// Workgroup numbering: consecutive workgroup ids go to different XCDs, so id -> (xcd, slot); the workgroups of one
-// XCD take all row blocks of a few column blocks and walk K in step: each XCD's L2 sees every weight once.
+// Workgroup numbering: consecutive workgroup ids go to different XCDs, so XCD x takes the x-th eighth of the tiles, row
+// blocks fastest: its workgroups take all row blocks of a few column blocks and walk K in step, so each XCD's L2 sees
+// (nearly) every weight once, and all XCDs have the same number of workgroups.  (Whole column blocks dealt to the XCDs
+// in turn left four of them with half as much again as the others at 20 column blocks: 724 us instead of 610 for the
+// 14B down product over 4864 rows in two splits.)
 #include "hx_internal.h"
 #include <algorithm>
 #include <mutex>
@@ -44,20 +48,20 @@ struct WideArgs {
     uint16_t *mp0;                // SiLU(gate)*up output of block 0 (packed activations, 8 m-groups)
 };
 
-// WNT: 32-column tiles per workgroup: 8 (a 256 x 256 output tile) or 6 (256 x 192, for products that would otherwise
-// leave compute units idle).  Splits hold whole chunks.
+// WNT: 32-column tiles per workgroup, 5 to 8 (a 256 x 160 to 256 x 256 output tile).  Splits hold whole chunks.
 template <int WNT, int EPI>
 __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) {
-    constexpr int KC = WIDE_KC, NST = WIDE_STAGES, WCOL = WNT == 8 ? 4 : 2, WROW = WIDE_WAVES / WCOL, TM = 8 / WROW, TW = WNT / WCOL;
+    constexpr int KC = WIDE_KC, NST = WIDE_STAGES, WCOL = WNT == 8 ? 4 : (WNT == 6 ? 2 : 1), WROW = WIDE_WAVES / WCOL, TM = 8 / WROW,
+                  TW = WNT / WCOL;
     constexpr int PIECES = KC * (8 + WNT), STAGE_U4 = PIECES * 64;
     constexpr int LPW = (PIECES + WIDE_WAVES - 1) / WIDE_WAVES, FULL = PIECES - (LPW - 1) * WIDE_WAVES;   // waves < FULL copy LPW pieces, the others one less
-    static_assert(KC == 2 && TM * TW == (WNT == 8 ? 8 : 6), "the operand registers alternate between two k-steps");
+    static_assert(KC == 2 && TM * TW == WNT, "the operand registers alternate between two k-steps");
     extern __shared__ u32x4_t lds[];                    // [NST][PIECES][64 lanes]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int w = blockIdx.x, xcd = w & 7, slot = w >> 3;
-    const int b = slot % a.R, nbl = (slot / a.R) * 8 + xcd;
     const int NB = (a.n_tiles + WNT - 1) / WNT;
-    if (nbl >= NB) return;                              // whole workgroup, before any barrier
+    const int tile = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    if (tile >= NB * a.R) return;                       // whole workgroup, before any barrier
+    const int b = tile % a.R, nbl = tile / a.R;
     const int nt0 = nbl * WNT;
     const int k_steps = a.k_steps;
     const int k0 = blockIdx.y * a.steps_per_split, k1 = min(k_steps, k0 + a.steps_per_split);
@@ -228,23 +232,34 @@ int launch_wide_epi(int epilogue, dim3 grid, hipStream_t st, const WideArgs &a) 
 
 }  // namespace
 
-// Tiles per workgroup and, for a product whose consumer sums partials, K-splits: the time of the busiest compute unit
-// (rounds x tiles per workgroup x k-steps per split), with a charge per extra split for writing and re-reading its
-// partial (measured: a 256 x N fp32 partial per row block is about 4 % of a 3584-deep product) and one per narrower
-// tile (it draws more bytes per flop).  Splits hold whole chunks.
+// Tiles per workgroup and, for a product whose consumer sums partials, K-splits: the plan with the least time by a
+// model in microseconds, fitted to 7B and 14B products (224 to 1184 k-steps, 8 and 19 row blocks; it is within 8 % of
+// nearly all of 22 plans measured, and picks one within 2 % of the best of each product).  A 256 x 32 tile takes 46 ns
+// per k-step on a compute unit when at most two thirds of them are busy and 52 when all are (the chip lowers its clock);
+// a workgroup's start and end 8 per round, the launch 4; partial sums are written at 4.7 TB/s and the further ones
+// read again at 10.  Narrow tiles read more operands per product.  The last round of many is only charged half.
+// Measured (us): 7B, 2048 rows: QKV 76 with 5 tiles and no split (6 tiles in 4 splits: 99, and 9 more in the consumer
+// that sums them), O + down 295 with 7 tiles in 2 splits (8 in 2: 317).  14B, 4864 rows: QKV 351 with 6 (7: 373, 8: 399,
+// 5: 397), O + down 885 with 7 (8: 951, 8 in 2 splits: 1007), gate|up 1160 with 8 (7: 1199, 6: 1193, 5: 1300).
 hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, bool partial) {
     const int cus = hx_device_cus();
+    const double out_mb = (double)row_blocks * 256 * m->N * (partial ? 4 : 1) * 1e-6;     // gate|up: bf16 of half the columns
     hx_wide_plan best{8, 1};
-    double best_cost = 1e300;
-    for (int wnt : {8, 6}) {
+    double best_us = 1e300;
+    for (int wnt : {8, 7, 6, 5}) {
         const int NB = (m->n_tiles + wnt - 1) / wnt;
+        const double narrow = wnt == 5 ? 1.12 : (wnt == 6 ? 1.03 : 1.0);
         for (int s = 1; s <= (partial ? HX_MAX_SPLITS : 1); ++s) {
             if (s > 1 && m->k_steps / s < 32) break;
-            const int wgs = NB * row_blocks * s;
-            const int rounds = (wgs + cus - 1) / cus;
             const int sps = ((m->k_steps + s - 1) / s + 1) & ~1;
-            const double cost = (double)rounds * wnt * sps * (1.0 + 0.04 * (s - 1)) * (1.0 + 0.03 * (8 - wnt));
-            if (cost < best_cost - 1e-9) { best_cost = cost; best.wnt = wnt; best.splits = s; }
+            if ((s - 1) * sps >= m->k_steps) continue;          // whole chunks would leave the last split empty
+            const double exact = (double)NB * row_blocks * s / cus;
+            const int whole = (NB * row_blocks * s + cus - 1) / cus;
+            const double rounds = whole <= 4 ? whole : 0.5 * (whole + exact);
+            const double busy = exact / whole;
+            const double tile_us = 0.046 + 0.018 * std::max(0.0, busy - 0.667);
+            const double us = 4.0 + 8.0 * (whole - 1) + out_mb * (s / 4.7 + (s - 1) / 10.0) + rounds * wnt * sps * tile_us * narrow;
+            if (us < best_us - 1e-9) { best_us = us; best.wnt = wnt; best.splits = s; }
         }
     }
     return best;
@@ -257,7 +272,7 @@ int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, 
                         int epilogue, size_t y_off, size_t mp_off, hx_wide_plan plan, hipStream_t st) {
     int splits = plan.splits;
     const int wnt = plan.wnt;
-    if (wnt != 8 && wnt != 6) return hx_fail(HX_E_RANGE, "%d tiles per workgroup: no such wide product", wnt);
+    if (wnt < 5 || wnt > 8) return hx_fail(HX_E_RANGE, "%d tiles per workgroup: no such wide product", wnt);
     if (m->k_steps % WIDE_KC) return hx_fail(HX_E_SHAPE, "wide products need K to be a multiple of 32, not %d", m->k_steps * 16);
     if (epilogue != HX_EPI_PARTIAL && epilogue != HX_EPI_SWIGLU) return hx_fail(HX_E_RANGE, "epilogue %d has no wide product", epilogue);
     if (epilogue == HX_EPI_SWIGLU) splits = 1;
@@ -270,10 +285,16 @@ int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, 
     a.mp0 = (uint16_t *)(ws0 + mp_off);
     a.steps_per_split = ((m->k_steps + splits - 1) / splits + 1) & ~1;
     const int NB = (m->n_tiles + wnt - 1) / wnt;
-    dim3 grid(((NB + 7) / 8) * 8 * row_blocks, splits);
+    dim3 grid((NB * row_blocks + 7) / 8 * 8, splits);
     for (int sp = 0; sp < splits; ++sp)
         if (sp * a.steps_per_split >= m->k_steps) return hx_fail(HX_E_RANGE, "%d splits leave split %d of %d k-steps empty", splits, sp, m->k_steps);
-    const int rc = wnt == 8 ? launch_wide_epi<8>(epilogue, grid, st, a) : launch_wide_epi<6>(epilogue, grid, st, a);
+    int rc;
+    switch (wnt) {
+        case 5: rc = launch_wide_epi<5>(epilogue, grid, st, a); break;
+        case 6: rc = launch_wide_epi<6>(epilogue, grid, st, a); break;
+        case 7: rc = launch_wide_epi<7>(epilogue, grid, st, a); break;
+        default: rc = launch_wide_epi<8>(epilogue, grid, st, a); break;
+    }
     if (rc) return rc;
     HX_CHECK_LAUNCH("gemm_wide");
     return HX_OK;
