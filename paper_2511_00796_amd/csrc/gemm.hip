@@ -15,39 +15,76 @@
 #include <mutex>
 
 // ---- weight packing ------------------------------------------------------------------------------------------
-// grid (n_tiles, ceil(k_steps / 4)), 256 threads: one wavefront per (n_tile, k_step).
-// col_phase 0: tile column c -> source column 32*nt + c.  col_phase 1 / 2 (gate / up): only lanes
-// c < 16 / c >= 16 are written, from source column 16*nt + c%16.
+// A workgroup turns 32 k x 512 columns of the row-major source (two k-steps) into operand order.  Thread = 8 k x 8
+// columns: eight 16-byte loads, a wavefront's each 1 KiB of one source row; transposed in registers to one 16-byte unit
+// (8 k of a column) per column, through LDS into output order, and stored 1 KiB per wavefront and instruction.
+// PHASE 0: tile column c = source column 32 * nt + c; PHASE 1 / 2 (gate / up): columns 0..15 / 16..31 of a tile, from
+// source column 16 * nt + c % 16 (runs of 256 bytes).  What bounds it is memory: see hx_launch_pack_matrix.
+#define HX_PACK_COLS 512
+template <int PHASE, bool ALIGNED>      // ALIGNED: 16-byte loads of the source are possible
 __global__ __launch_bounds__(256) void pack_matrix_kernel(const uint16_t *__restrict__ src, int64_t rows, int64_t cols,
-                                                          uint4 *__restrict__ dst, int k_steps, int col_phase) {
-    const int nt = blockIdx.x;
-    const int ks = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (ks >= k_steps) return;
-    const int lane = threadIdx.x & 63;
-    const int c = lane & 31, kh = lane >> 5;
-    int64_t col;
-    if (col_phase == 0) col = (int64_t)32 * nt + c;
-    else {
-        if ((col_phase == 1) != (c < 16)) return;
-        col = (int64_t)16 * nt + (c & 15);
+                                                          uint4 *__restrict__ dst, int k_steps, int n_tiles) {
+    __shared__ uint4 lds[2048];                         // unit of column c, k-step s, half kh: see unit() below
+    constexpr int TC = PHASE == 0 ? 32 : 16;            // source columns per tile
+    const int tid = threadIdx.x, cg = tid & 63, rg = tid >> 6;            // rg = 2 * k-step + half
+    const int64_t c0 = (int64_t)blockIdx.x * HX_PACK_COLS, col = c0 + 8 * cg, k0 = (int64_t)blockIdx.y * 32 + 8 * rg;
+    uint4 in[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        in[r] = make_uint4(0u, 0u, 0u, 0u);
+        if (k0 + r < rows) {
+            const uint16_t *p = src + (k0 + r) * cols + col;
+            if (ALIGNED) { if (col < cols) in[r] = *(const uint4 *)p; }
+            else {
+                uint16_t e[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) e[j] = col + j < cols ? p[j] : (uint16_t)0;
+                in[r] = make_uint4(e[0] | ((uint32_t)e[1] << 16), e[2] | ((uint32_t)e[3] << 16), e[4] | ((uint32_t)e[5] << 16),
+                                   e[6] | ((uint32_t)e[7] << 16));
+            }
+        }
     }
-    uint16_t v[8];
+    // units in output order: [tile][k-step][half][column of the tile]; the 8 of a thread are neighbours, so they are spread
+    // over the banks by the index of their group of 8
+    auto place = [](int u) { return (u & ~7) | ((u ^ (u >> 3)) & 7); };
+    const int first = (((8 * cg / TC) * 4 + rg) * TC) + (8 * cg) % TC;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        int64_t k = (int64_t)16 * ks + 8 * kh + j;
-        v[j] = (col < cols && k < rows) ? src[k * cols + col] : (uint16_t)0;
+        uint32_t w[4];
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const uint32_t a = ((const uint32_t *)&in[2 * h])[j >> 1], b = ((const uint32_t *)&in[2 * h + 1])[j >> 1];
+            w[h] = (j & 1) ? (a >> 16) | (b & 0xffff0000u) : (a & 0xffffu) | (b << 16);
+        }
+        lds[place(first + j)] = make_uint4(w[0], w[1], w[2], w[3]);
     }
-    uint4 o;
-    o.x = v[0] | ((uint32_t)v[1] << 16); o.y = v[2] | ((uint32_t)v[3] << 16);
-    o.z = v[4] | ((uint32_t)v[5] << 16); o.w = v[6] | ((uint32_t)v[7] << 16);
-    dst[((size_t)nt * k_steps + ks) * 64 + lane] = o;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int u = i * 256 + tid;
+        const int c = u % TC, kh = (u / TC) & 1, s = (u / (2 * TC)) & 1;
+        const int64_t nt = c0 / TC + u / (4 * TC);
+        const int ks = 2 * (int)blockIdx.y + s;
+        if (nt < n_tiles && ks < k_steps)
+            dst[((size_t)nt * k_steps + ks) * 64 + kh * 32 + (PHASE == 2 ? 16 : 0) + c] = lds[place(u)];
+    }
 }
 
+// us per matrix, 7B, source read and packed copy written (a thread per 8 k of one column, 64-byte pieces of the source rows,
+// before): gate 53 = 5.1 TB/s (104), QKV 14 (19), down 57 (65), LM head 411 = 5.3 TB/s (531); a device copy moves 4.8-5.3.
 int hx_launch_pack_matrix(const hx_engine *e, const hx_matrix *m, const void *src, int64_t rows, int64_t cols,
                           int col_phase, hipStream_t st) {
-    dim3 grid(m->n_tiles, (m->k_steps + 3) / 4), block(256);
-    hipLaunchKernelGGL(pack_matrix_kernel, grid, block, 0, st, (const uint16_t *)src, rows, cols,
-                       (uint4 *)(e->weights + m->offset), m->k_steps, col_phase);
+    const int64_t all = (int64_t)m->n_tiles * (col_phase ? 16 : 32);      // columns of the tiles, zeros beyond `cols` included
+    dim3 grid((unsigned)((all + HX_PACK_COLS - 1) / HX_PACK_COLS), (m->k_steps + 1) / 2), block(256);
+    const bool aligned = (uintptr_t)src % 16 == 0 && cols % 8 == 0;
+    uint4 *dst = (uint4 *)(e->weights + m->offset);
+#define HX_PACK(P, A) hipLaunchKernelGGL((pack_matrix_kernel<P, A>), grid, block, 0, st, (const uint16_t *)src, rows, cols, dst, m->k_steps, m->n_tiles)
+#define HX_PACK_P(P) do { if (aligned) HX_PACK(P, true); else HX_PACK(P, false); } while (0)
+    if (col_phase == 0) HX_PACK_P(0);
+    else if (col_phase == 1) HX_PACK_P(1);
+    else HX_PACK_P(2);
+#undef HX_PACK_P
+#undef HX_PACK
     HX_CHECK_LAUNCH("pack_matrix");
     return HX_OK;
 }
