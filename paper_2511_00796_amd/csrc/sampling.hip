@@ -14,6 +14,7 @@
 
 #define HX_NUC_THREADS 1024
 #define HX_NUC_BINS 2048
+#define HX_NUC_UNROLL 8
 #define HX_NUC_SCALE 1099511627776.0f   // 2^40
 
 // ascending key order = descending z; -0 and +0 share a key
@@ -22,13 +23,21 @@ __device__ __forceinline__ uint32_t nucleus_key(float z) {
     return ~(b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u));
 }
 
-__device__ __forceinline__ void load_group(const float *__restrict__ x, int V, int q, bool vec, float (&v)[4]) {
-    if (vec) {
-        const f32x4_t t = *(const f32x4_t *)(x + 4 * (size_t)q);
-        v[0] = t[0]; v[1] = t[1]; v[2] = t[2]; v[3] = t[3];
-    } else {
+// groups q0, q0 + HX_NUC_THREADS, ... of four entries, all requested before the first is used (one group at a time, the
+// passes waited for one load after the other: 38 round trips each over a 152 064-entry row); groups past the end repeat
+// the last one and are skipped by the caller
+__device__ __forceinline__ void load_groups(const float *__restrict__ x, int V, int q0, int n_groups, bool vec,
+                                            float (&v)[HX_NUC_UNROLL][4]) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = (4 * q + i < V) ? x[4 * (size_t)q + i] : 0.f;
+    for (int u = 0; u < HX_NUC_UNROLL; ++u) {
+        const size_t at = 4 * (size_t)min(q0 + u * HX_NUC_THREADS, n_groups - 1);
+        if (vec) {
+            const f32x4_t t = *(const f32x4_t *)(x + at);
+            v[u][0] = t[0]; v[u][1] = t[1]; v[u][2] = t[2]; v[u][3] = t[3];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[u][i] = x[at + i < (size_t)V ? at + i : (size_t)V - 1];
+        }
     }
 }
 
@@ -72,17 +81,20 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
         shift -= bits;
         for (int i = tid; i < HX_NUC_BINS; i += HX_NUC_THREADS) hist[i] = 0ull;
         __syncthreads();
-        for (int q = tid; q < n_groups; q += HX_NUC_THREADS) {
-            float v[4];
-            load_group(x, V, q, vec, v);
+        for (int q0 = tid; q0 < n_groups; q0 += HX_NUC_THREADS * HX_NUC_UNROLL) {
+            float v[HX_NUC_UNROLL][4];
+            load_groups(x, V, q0, n_groups, vec, v);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (4 * q + i >= V) continue;
-                const float z = v[i] * inv_t;
-                const uint32_t key = nucleus_key(z);
-                if (pass == 0 || (key >> hi_shift) == prefix) {
-                    const unsigned long long w = (unsigned long long)(expf(z - zmax) * HX_NUC_SCALE);
-                    if (w) atomicAdd(&hist[(key >> shift) & ((1u << bits) - 1u)], w);
+            for (int u = 0; u < HX_NUC_UNROLL; ++u) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (4 * (q0 + u * HX_NUC_THREADS) + i >= V) continue;
+                    const float z = v[u][i] * inv_t;
+                    const uint32_t key = nucleus_key(z);
+                    if (pass == 0 || (key >> hi_shift) == prefix) {
+                        const unsigned long long w = (unsigned long long)(expf(z - zmax) * HX_NUC_SCALE);
+                        if (w) atomicAdd(&hist[(key >> shift) & ((1u << bits) - 1u)], w);
+                    }
                 }
             }
         }
@@ -126,27 +138,31 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
     const uint32_t pos = (uint32_t)positions[m];
     float best = -INFINITY, best_z = 0.f;
     int32_t best_i = 0x7fffffff, count = 0;
-    for (int q = tid; q < n_groups; q += HX_NUC_THREADS) {
-        float v[4];
-        load_group(x, V, q, vec, v);
-        bool any = false;
-        bool keep[4];
+    for (int q0 = tid; q0 < n_groups; q0 += HX_NUC_THREADS * HX_NUC_UNROLL) {
+        float v[HX_NUC_UNROLL][4];
+        load_groups(x, V, q0, n_groups, vec, v);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            keep[i] = (4 * q + i < V) && nucleus_key(v[i] * inv_t) <= key_tau;
-            any |= keep[i];
-        }
-        if (!any) continue;
-        uint32_t w[4];
-        hx_philox4x32_10((uint32_t)q, row, pos, 0x53414D50u, key0, key1, w);
+        for (int u4 = 0; u4 < HX_NUC_UNROLL; ++u4) {
+            const int q = q0 + u4 * HX_NUC_THREADS;
+            bool any = false;
+            bool keep[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (!keep[i]) continue;
-            ++count;
-            const float z = v[i] * inv_t;
-            const float u = ((float)(w[i] >> 9) + 0.5f) * (1.0f / 8388608.0f);
-            const float y = z - logf(-logf(u));
-            if (y > best) { best = y; best_i = 4 * q + i; best_z = z; }   // a thread's indices ascend
+            for (int i = 0; i < 4; ++i) {
+                keep[i] = (4 * q + i < V) && nucleus_key(v[u4][i] * inv_t) <= key_tau;
+                any |= keep[i];
+            }
+            if (!any) continue;
+            uint32_t w[4];
+            hx_philox4x32_10((uint32_t)q, row, pos, 0x53414D50u, key0, key1, w);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (!keep[i]) continue;
+                ++count;
+                const float z = v[u4][i] * inv_t;
+                const float u = ((float)(w[i] >> 9) + 0.5f) * (1.0f / 8388608.0f);
+                const float y = z - logf(-logf(u));
+                if (y > best) { best = y; best_i = 4 * q + i; best_z = z; }   // a thread's indices ascend
+            }
         }
     }
 #pragma unroll
