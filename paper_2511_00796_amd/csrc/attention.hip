@@ -303,13 +303,16 @@ __global__ __launch_bounds__(64) void attn_splitk_kernel(const char *__restrict_
 // ---- combine ---------------------------------------------------------------------------------------------
 // o = sum_c 2^(m_c - M) o_c / sum_c 2^(m_c - M) l_c over the partial results of the pair (sequence, KV head):
 // the runs w0..w1 that cover its tiles, found from the schedule, in slots w + pair.
-// One wavefront per (sequence, query head).  Maximum and denominator: lane i takes partials i, i+64, ..., reduced by
-// a fixed shuffle tree.  Numerator: lane = (phase 0..3, d8 0..15); phase p takes partials p, p+4, ... in order, then
-// the four phases are summed by a fixed shuffle tree (deterministic).  Lanes of phase 0
+// WPP wavefronts per (sequence, query head).  Maximum and denominator: lane i takes partials i, i+64, ..., reduced by
+// a fixed shuffle tree (every wavefront for itself).  Numerator: lane = (phase 0..3, d8 0..15); phase p of wavefront w
+// takes partials 16 w + p + 4 u (u < 4), then those 16 WPP further, in order, then the phases are summed by a fixed shuffle tree and the
+// wavefronts in order (deterministic).  Lanes of phase 0
 // write the bf16-rounded result into the packed activation buffer of the output projection and, if asked,
 // the unrounded fp32 values.  D = 64 uses lanes d8 < 8 only.
-template <int D>
-__global__ __launch_bounds__(256) void attn_combine_kernel(int batch, int n_q, int n_kv, int G,
+// WPP = 1, four pairs per workgroup: batches with a few partials per pair.  WPP = 8: short batches of long sequences,
+// where a pair has a hundred partials and more (its one wavefront went through them in a dozen dependent steps).
+template <int D, int WPP>
+__global__ __launch_bounds__(WPP == 1 ? 256 : 64 * WPP) void attn_combine_kernel(int batch, int n_q, int n_kv, int G,
                                                            const int32_t *__restrict__ pre,
                                                            const int32_t *__restrict__ lens,
                                                            const int32_t *__restrict__ sched,
@@ -317,8 +320,10 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(int batch, int n_q, i
                                                            const float *__restrict__ part_o,
                                                            uint16_t *__restrict__ ap, int m_groups,
                                                            float *__restrict__ attn_f32) {
-    const int bh = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (bh >= batch * n_q) return;
+    __shared__ float part[WPP == 1 ? 1 : WPP][WPP == 1 ? 1 : D];
+    const int wave = threadIdx.x >> 6, pw = WPP == 1 ? 0 : wave;         // wavefront of the workgroup / of the pair
+    const int bh = WPP == 1 ? blockIdx.x * 4 + wave : blockIdx.x;
+    if (bh >= batch * n_q) return;                       // whole wavefronts; for WPP > 1 the grid is exact
     const int lane = threadIdx.x & 63, d8 = lane & 15, ph = lane >> 4;
     const bool has_d = d8 < D / 8;
     const int b = bh / n_q, h = bh % n_q;
@@ -336,7 +341,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(int batch, int n_q, i
     float acc[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-    if (n <= 8) {                   // the usual case (a few partials per pair): each 16-lane group takes every fourth
+    if (WPP == 1 && n <= 8) {       // the usual case (a few partials per pair): each 16-lane group takes every fourth
         for (int it = s0 + ph; it <= s1; it += 4) M = fmaxf(M, part_ml[(size_t)it * 32 + g]);
         M = fmaxf(M, __shfl_xor(M, 16));
         M = fmaxf(M, __shfl_xor(M, 32));
@@ -362,7 +367,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(int batch, int n_q, i
         }
 #pragma unroll
         for (int sh = 1; sh < 64; sh <<= 1) den += __shfl_xor(den, sh);
-        for (int it = s0 + ph; it <= s1; it += 16) {
+        for (int it = s0 + 16 * pw + ph; it <= s1; it += 16 * WPP) {
             float w[4];
             f32x4_t a[4], c[4];
 #pragma unroll
@@ -388,6 +393,18 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(int batch, int n_q, i
     for (int j = 0; j < 8; ++j) {
         acc[j] += __shfl_xor(acc[j], 16);
         acc[j] += __shfl_xor(acc[j], 32);
+    }
+    if (WPP > 1) {
+        if (ph == 0 && has_d)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) part[pw][d8 * 8 + j] = acc[j];
+        __syncthreads();
+        if (pw != 0) return;
+#pragma unroll
+        for (int w = 1; w < WPP; ++w)
+            if (has_d)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc[j] += part[w][d8 * 8 + j];
     }
     if (ph != 0 || !has_d) return;
     const float inv = 1.0f / den;
@@ -424,17 +441,26 @@ int hx_launch_attention(const hx_engine *e, const hx_kv *kv, int layer, int batc
     return HX_OK;
 }
 
-int hx_launch_combine(const hx_engine *e, int batch, float *attn_f32_out, hipStream_t st, const hx_attn_bufs *bufs) {
+int hx_launch_combine(const hx_engine *e, int batch, int max_blocks, float *attn_f32_out, hipStream_t st, const hx_attn_bufs *bufs) {
     const hx_attn_bufs own = hx_attn_bufs_of(e);
     const hx_attn_bufs &a = bufs ? *bufs : own;
     const int n_kv = e->cfg.n_kv_heads, n_q = e->cfg.n_q_heads;
     const int m_groups = hx_m_groups(batch);
-    dim3 cgrid((batch * n_q + 3) / 4), cblock(256);
+    // A pair has about attn_waves / (batch * n_kv) partials and at most one per block: with more than 32 its eight wavefronts
+    // pay (170 partials, 3 rows of 7B: 13.0 -> 8.0 us; 1 row of 1.5B, 200 blocks: 11.5 -> 7.6).
+    const bool many = max_blocks > 32 && e->attn_waves > 32 * batch * n_kv;
+    dim3 cgrid(many ? batch * n_q : (batch * n_q + 3) / 4), cblock(many ? 512 : 256);
 #define HX_COMB_ARGS                                                                                             \
     batch, n_q, n_kv, e->G, (const int32_t *)a.pre, (const int32_t *)a.lens, (const int32_t *)a.sched,            \
         (const float *)a.part_ml, (const float *)a.part_o, a.ap, m_groups, attn_f32_out
-    if (e->D == 128) hipLaunchKernelGGL((attn_combine_kernel<128>), cgrid, cblock, 0, st, HX_COMB_ARGS);
-    else             hipLaunchKernelGGL((attn_combine_kernel<64>), cgrid, cblock, 0, st, HX_COMB_ARGS);
+#define HX_COMB_LAUNCH(DD)                                                                                         \
+    do {                                                                                                         \
+        if (many) hipLaunchKernelGGL((attn_combine_kernel<DD, 8>), cgrid, cblock, 0, st, HX_COMB_ARGS);          \
+        else      hipLaunchKernelGGL((attn_combine_kernel<DD, 1>), cgrid, cblock, 0, st, HX_COMB_ARGS);          \
+    } while (0)
+    if (e->D == 128) HX_COMB_LAUNCH(128);
+    else             HX_COMB_LAUNCH(64);
+#undef HX_COMB_LAUNCH
 #undef HX_COMB_ARGS
     HX_CHECK_LAUNCH("attn_combine");
     return HX_OK;
