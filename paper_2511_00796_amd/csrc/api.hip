@@ -566,8 +566,8 @@ extern "C" int prefill_rows(hx_engine *e, hx_kv *kv, int32_t n_rows, const int32
     HX_TIMED(HX_K_NORM, hx_launch_embed_norm(v0, 256, tokens, e->layers[0].g1, st, R, stride));
     for (int l = 0; l < c->n_layers; ++l) {
         const hx_layer_map *lm = &e->layers[l];
-        const hx_wide_plan p_qkv = hx_plan_wide(&lm->wqkv, R, true), p_o = hx_plan_wide(&lm->wo, R, true),
-                           p_gu = hx_plan_wide(&lm->wgu, R, false), p_d = hx_plan_wide(&lm->wd, R, true);
+        const hx_wide_plan p_qkv = hx_plan_wide(&lm->wqkv, R, HX_EPI_PARTIAL), p_o = hx_plan_wide(&lm->wo, R, HX_EPI_PARTIAL),
+                           p_gu = hx_plan_wide(&lm->wgu, R, HX_EPI_SWIGLU), p_d = hx_plan_wide(&lm->wd, R, HX_EPI_PARTIAL);
         const int s_qkv = p_qkv.splits, s_o = p_o.splits, s_d = p_d.splits;
         HX_TIMED(HX_K_GEMM_QKV, hx_launch_gemm_wide(e, &lm->wqkv, R, ws0, stride, m.xp, HX_EPI_PARTIAL, m.ypart, 0, p_qkv, st));
         // K and V of every row of the call enter the cache before any row attends
@@ -869,7 +869,7 @@ extern "C" int hx_stage_linear_rows(hx_engine *e, int kind, int layer, int32_t n
         default: return hx_fail(HX_E_SHAPE, "tensor kind %d has no wide product", kind);
     }
     const bool swiglu = kind == HX_T_WG;
-    const hx_wide_plan plan = hx_plan_wide(w, R, !swiglu);
+    const hx_wide_plan plan = hx_plan_wide(w, R, swiglu ? HX_EPI_SWIGLU : HX_EPI_PARTIAL);
     hx_engine view = *e;
     int rc;
     for (int b = 0; b < R; ++b) {

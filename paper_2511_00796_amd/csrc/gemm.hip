@@ -11,6 +11,7 @@
 // Epilogues: plain fp32 partials; SiLU(gate) * up -> bf16 packed activations of the down
 // projection; logits + per-tile argmax candidates; logits + per-tile sampling candidates and log-sum-exp pieces.
 #include "hx_internal.h"
+#include "lm_epilogue.h"
 #include <algorithm>
 #include <mutex>
 
@@ -408,85 +409,17 @@ __global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK>::NP)) void gemm_st
                 }
             }
         }
-    } else if (EPI == HX_EPI_LOGITS) {
-        // logits and the best (value, index) of this lane's 16 columns, ascending column order
-#pragma unroll
-        for (int g = 0; g < MG; ++g) {
-            const int m = 32 * g + ml;
-            float best = -INFINITY;
-            int best_n = 0x7fffffff;
-#pragma unroll
-            for (int j4 = 0; j4 < 4; ++j4) {
-                const int n = 32 * nt + 8 * j4 + 4 * hl;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float v = acc[g][4 * j4 + i];
-                    if (n + i < a_N && v > best) { best = v; best_n = n + i; }
-                }
-                if (a_y != nullptr && m < a_M && n < a_N)
-                    *(f32x4_t *)(a_y + (size_t)m * a_N + n) =
-                        f32x4_t{acc[g][4 * j4], acc[g][4 * j4 + 1], acc[g][4 * j4 + 2], acc[g][4 * j4 + 3]};
-            }
-            const float ov = __shfl_xor(best, 32);
-            const int on = __shfl_xor(best_n, 32);
-            if (ov > best || (ov == best && on < best_n)) { best = ov; best_n = on; }
-            if (hl == 0 && m < a_M) {
-                a_amax_val[(size_t)m * a_n_tiles + nt] = best;
-                a_amax_idx[(size_t)m * a_n_tiles + nt] = best_n;
-            }
-        }
     } else {
-        // Temperature sample by Gumbel-max, and the pieces of the log-sum-exp: per (row, tile) the best perturbed
-        // score y = z + g with its column and its z, the tile's max of z and its sum of exp(z - max).
-        // z = logit * (1/T); g = -log(-log(u)); u from one generator block per 4 consecutive columns.
+        const hx_lm_args lm{a_y, a_M, a_N, a_n_tiles, a_amax_val, a_amax_idx, a_positions, a_row_ids, a_inv_t, a_key0, a_key1,
+                            a_samp_z, a_samp_m, a_samp_s};
+        // one copy of the tile's code, the accumulators moved up behind it (unrolled it spills and leaves the instruction
+        // cache); m-groups that only pad the batch are left out
+#pragma unroll 1
+        for (int g = 0; 32 * g < a_M; ++g) {
+            if (EPI == HX_EPI_LOGITS) hx_lm_greedy_tile(lm, acc[0], 32 * g + ml, nt, lane);
+            else                      hx_lm_sample_tile(lm, acc[0], 32 * g + ml, nt, lane);
 #pragma unroll
-        for (int g = 0; g < MG; ++g) {
-            const int m = 32 * g + ml;
-            const bool row_ok = m < a_M;
-            const uint32_t row = row_ok ? (a_row_ids ? (uint32_t)a_row_ids[m] : (uint32_t)m) : 0u;
-            const uint32_t pos = row_ok ? (uint32_t)a_positions[m] : 0u;
-            float best = -INFINITY, best_z = 0.f, zmax = -INFINITY;
-            int best_n = 0x7fffffff;
-            float z[16];
-#pragma unroll
-            for (int j4 = 0; j4 < 4; ++j4) {
-                const int n = 32 * nt + 8 * j4 + 4 * hl;
-                uint32_t w[4];
-                hx_philox4x32_10((uint32_t)(n >> 2), row, pos, 0x53414D50u, a_key0, a_key1, w);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float zi = acc[g][4 * j4 + i] * a_inv_t;
-                    z[4 * j4 + i] = (n + i < a_N) ? zi : -INFINITY;
-                    const float u = ((float)(w[i] >> 9) + 0.5f) * (1.0f / 8388608.0f);
-                    const float y = zi - logf(-logf(u));
-                    if (n + i < a_N) {
-                        if (y > best) { best = y; best_n = n + i; best_z = zi; }
-                        zmax = fmaxf(zmax, zi);
-                    }
-                }
-                if (a_y != nullptr && row_ok && n < a_N)
-                    *(f32x4_t *)(a_y + (size_t)m * a_N + n) =
-                        f32x4_t{acc[g][4 * j4], acc[g][4 * j4 + 1], acc[g][4 * j4 + 2], acc[g][4 * j4 + 3]};
-            }
-            // the two half-wavefronts hold the two halves of the tile's 32 columns
-            const float tmax = fmaxf(zmax, __shfl_xor(zmax, 32));
-            float sum = 0.f;
-            if (tmax > -INFINITY) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) sum += expf(z[i] - tmax);     // exp(-inf) = 0 for columns past N
-            }
-            sum += __shfl_xor(sum, 32);
-            const float oy = __shfl_xor(best, 32), oz = __shfl_xor(best_z, 32);
-            const int on = __shfl_xor(best_n, 32);
-            if (oy > best || (oy == best && on < best_n)) { best = oy; best_n = on; best_z = oz; }
-            if (hl == 0 && row_ok) {
-                const size_t o = (size_t)m * a_n_tiles + nt;
-                a_amax_val[o] = best;
-                a_amax_idx[o] = best_n;
-                a_samp_z[o] = best_z;
-                a_samp_m[o] = tmax;
-                a_samp_s[o] = sum;
-            }
+            for (int k = 0; k + 1 < MG; ++k) acc[k] = acc[k + 1];
         }
     }
 }
@@ -516,8 +449,11 @@ template <int MG, int WN, int WK>
 static int launch_epi(int epilogue, dim3 grid, hipStream_t st, const GemmArgs &a) {
     if (epilogue == HX_EPI_PARTIAL) return launch_one<MG, WN, WK, HX_EPI_PARTIAL>(grid, st, a);
     if (epilogue == HX_EPI_SWIGLU) return launch_one<MG, WN, WK, HX_EPI_SWIGLU>(grid, st, a);
-    if (epilogue == HX_EPI_SAMPLE) return launch_one<MG, WN, WK, HX_EPI_SAMPLE>(grid, st, a);
-    return launch_one<MG, WN, WK, HX_EPI_LOGITS>(grid, st, a);
+    if constexpr (MG <= 4) {                             // more rows: the workgroup-tiled product
+        if (epilogue == HX_EPI_SAMPLE) return launch_one<MG, WN, WK, HX_EPI_SAMPLE>(grid, st, a);
+        if (epilogue == HX_EPI_LOGITS) return launch_one<MG, WN, WK, HX_EPI_LOGITS>(grid, st, a);
+    }
+    return hx_fail(HX_E_RANGE, "epilogue %d for %d m-groups", epilogue, MG);
 }
 
 template <int MG>
@@ -610,6 +546,15 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
     if (epilogue == HX_EPI_SAMPLE && !sample) return hx_fail(HX_E_NULL, "sampling parameters missing");
     const int mg = hx_m_groups(batch);
     const bool partial = epilogue == HX_EPI_PARTIAL;
+    if ((epilogue == HX_EPI_LOGITS || epilogue == HX_EPI_SAMPLE) && batch > 128) {
+        // Beyond 128 rows the streaming kernel has one wavefront per SIMD with all rows' accumulators, and nothing beside its
+        // multiplications or its epilogue; the workgroup-tiled product has two.  1.5B, 256 rows, sampled: 327 -> 204 us.
+        const hx_lm_args lm{y, batch, m->N, m->n_tiles, (float *)(e->ws + e->map.amax_val), (int32_t *)(e->ws + e->map.amax_idx),
+                            sample ? sample->positions : nullptr, sample ? sample->row_ids : nullptr,
+                            sample ? sample->inv_temperature : 1.0f, sample ? sample->key0 : 0u, sample ? sample->key1 : 0u,
+                            (float *)(e->ws + e->map.samp_z), (float *)(e->ws + e->map.samp_m), (float *)(e->ws + e->map.samp_s)};
+        return hx_launch_gemm_wide(e, m, 1, (char *)xp, 0, 0, epilogue, 0, 0, hx_plan_wide(m, 1, epilogue), st, &lm);
+    }
     gemm_launch plan[2];
     const int n_launch = plan_product(m->n_tiles, m->k_steps, mg, partial, plan);
     for (int li = 0; li < n_launch; ++li) {

@@ -25,6 +25,7 @@
 // in turn left four of them with half as much again as the others at 20 column blocks: 724 us instead of 610 for the
 // 14B down product over 4864 rows in two splits.)
 #include "hx_internal.h"
+#include "lm_epilogue.h"
 #include <algorithm>
 #include <mutex>
 
@@ -46,6 +47,7 @@ struct WideArgs {
     float *y0;                    // fp32 output of block 0 ([splits][256][N]), same stride between blocks
     int steps_per_split;
     uint16_t *mp0;                // SiLU(gate)*up output of block 0 (packed activations, 8 m-groups)
+    hx_lm_args lm;                // LM head (one block)
 };
 
 // WNT: 32-column tiles per workgroup, 5 to 8 (a 256 x 160 to 256 x 256 output tile).  Splits hold whole chunks.
@@ -182,7 +184,7 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
                 }
             }
         }
-    } else {
+    } else if (EPI == HX_EPI_SWIGLU) {
         // SiLU(gate) * up: rows 0..15 of a tile are gate columns 16*nt + p, rows 16..31 the matching up columns
         uint16_t *mp = a.mp0 + ((size_t)b * a.block_stride) / 2;
 #pragma unroll
@@ -208,6 +210,22 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
                 }
             }
         }
+    } else {
+        // one copy of the tile's code, the accumulators moved up behind it
+#pragma unroll 1
+        for (int i = 0; i < TM; ++i) {
+            const int m0 = 32 * (TM * wm + i);
+#pragma unroll 1
+            for (int j = 0; j < TW; ++j) {
+                const int nt = nt0 + wn * TW + j;
+                if (nt < a.n_tiles && m0 < a.lm.M) {
+                    if (EPI == HX_EPI_LOGITS) hx_lm_greedy_tile(a.lm, acc[0][0], m0 + ml, nt, lane);
+                    else                      hx_lm_sample_tile(a.lm, acc[0][0], m0 + ml, nt, lane);
+                }
+#pragma unroll
+                for (int k = 0; k + 1 < TM * TW; ++k) acc[k / TW][k % TW] = acc[(k + 1) / TW][(k + 1) % TW];
+            }
+        }
     }
 }
 
@@ -227,6 +245,8 @@ int launch_wide(dim3 grid, hipStream_t st, const WideArgs &a) {
 template <int WNT>
 int launch_wide_epi(int epilogue, dim3 grid, hipStream_t st, const WideArgs &a) {
     if (epilogue == HX_EPI_PARTIAL) return launch_wide<WNT, HX_EPI_PARTIAL>(grid, st, a);
+    if (epilogue == HX_EPI_LOGITS) return launch_wide<WNT, HX_EPI_LOGITS>(grid, st, a);
+    if (epilogue == HX_EPI_SAMPLE) return launch_wide<WNT, HX_EPI_SAMPLE>(grid, st, a);
     return launch_wide<WNT, HX_EPI_SWIGLU>(grid, st, a);
 }
 
@@ -241,9 +261,10 @@ int launch_wide_epi(int epilogue, dim3 grid, hipStream_t st, const WideArgs &a) 
 // Measured (us): 7B, 2048 rows: QKV 76 with 5 tiles and no split (6 tiles in 4 splits: 99, and 9 more in the consumer
 // that sums them), O + down 295 with 7 tiles in 2 splits (8 in 2: 317).  14B, 4864 rows: QKV 351 with 6 (7: 373, 8: 399,
 // 5: 397), O + down 885 with 7 (8: 951, 8 in 2 splits: 1007), gate|up 1160 with 8 (7: 1199, 6: 1193, 5: 1300).
-hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, bool partial) {
+hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, int epilogue) {
     const int cus = hx_device_cus();
-    const double out_mb = (double)row_blocks * 256 * m->N * (partial ? 4 : 1) * 1e-6;     // gate|up: bf16 of half the columns
+    const bool partial = epilogue == HX_EPI_PARTIAL;
+    const double out_mb = (double)row_blocks * 256 * m->N * (epilogue == HX_EPI_SWIGLU ? 1 : 4) * 1e-6;   // gate|up: bf16 of half the columns
     hx_wide_plan best{8, 1};
     double best_us = 1e300;
     for (int wnt : {8, 7, 6, 5}) {
@@ -269,13 +290,14 @@ hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, bool partial) {
 // the fp32 output ([splits][256][N]) and the SiLU*mul output inside each block's workspace; ws0 = block 0's
 // workspace, block_stride bytes between blocks.
 int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, char *ws0, size_t block_stride, size_t xp_off,
-                        int epilogue, size_t y_off, size_t mp_off, hx_wide_plan plan, hipStream_t st) {
+                        int epilogue, size_t y_off, size_t mp_off, hx_wide_plan plan, hipStream_t st, const hx_lm_args *lm) {
     int splits = plan.splits;
     const int wnt = plan.wnt;
     if (wnt < 5 || wnt > 8) return hx_fail(HX_E_RANGE, "%d tiles per workgroup: no such wide product", wnt);
     if (m->k_steps % WIDE_KC) return hx_fail(HX_E_SHAPE, "wide products need K to be a multiple of 32, not %d", m->k_steps * 16);
-    if (epilogue != HX_EPI_PARTIAL && epilogue != HX_EPI_SWIGLU) return hx_fail(HX_E_RANGE, "epilogue %d has no wide product", epilogue);
-    if (epilogue == HX_EPI_SWIGLU) splits = 1;
+    const bool head = epilogue == HX_EPI_LOGITS || epilogue == HX_EPI_SAMPLE;
+    if (head && (!lm || row_blocks != 1)) return hx_fail(HX_E_RANGE, "the LM head takes one block of rows");
+    if (epilogue != HX_EPI_PARTIAL) splits = 1;
     if (block_stride % 16) return hx_fail(HX_E_RANGE, "block stride %zu is not a multiple of 16", block_stride);
     WideArgs a;
     a.wp = (const uint4 *)(e->weights + m->offset);
@@ -283,6 +305,7 @@ int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, 
     a.xp0 = ws0 + xp_off; a.block_stride = block_stride; a.R = row_blocks;
     a.y0 = (float *)(ws0 + y_off);
     a.mp0 = (uint16_t *)(ws0 + mp_off);
+    a.lm = head ? *lm : hx_lm_args{};
     a.steps_per_split = ((m->k_steps + splits - 1) / splits + 1) & ~1;
     const int NB = (m->n_tiles + wnt - 1) / wnt;
     dim3 grid((NB * row_blocks + 7) / 8 * 8, splits);

@@ -293,9 +293,8 @@ __device__ __forceinline__ void hx_philox4x32_10(uint32_t c0, uint32_t c1, uint3
                                                  uint32_t k1, uint32_t (&out)[4]) {
 #pragma unroll
     for (int round = 0; round < 10; ++round) {
-        const uint32_t hi0 = __umulhi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
-        const uint32_t hi1 = __umulhi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
-        c0 = hi1 ^ c1 ^ k0; c1 = lo1; c2 = hi0 ^ c3 ^ k1; c3 = lo0;
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
+        c0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0; c1 = (uint32_t)p1; c2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1; c3 = (uint32_t)p0;
         k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
     }
     out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
@@ -327,9 +326,10 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
                    const hx_sample_params *sample = nullptr);
 // gemm_wide.hip: products over several 256-row blocks at once (prompt rows)
 struct hx_wide_plan { int wnt, splits; };        // 32-column tiles per workgroup, K-splits
-hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, bool partial);
+struct hx_lm_args;
+hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, int epilogue);
 int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, char *ws0, size_t block_stride, size_t xp_off,
-                        int epilogue, size_t y_off, size_t mp_off, hx_wide_plan plan, hipStream_t st);
+                        int epilogue, size_t y_off, size_t mp_off, hx_wide_plan plan, hipStream_t st, const hx_lm_args *lm = nullptr);
 
 int hx_launch_sample_final(const hx_engine *e, int batch, int32_t *tokens_out, float *logprobs_out, hipStream_t st);
 int hx_gemm_splits(const hx_matrix *m, int batch);   // K-splits the planner uses for a product with split partials
