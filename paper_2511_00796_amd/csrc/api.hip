@@ -451,7 +451,7 @@ static int run_step(hx_engine *e, hx_kv *kv, int32_t batch, const int32_t *token
     for (int l = 0; l < c->n_layers; ++l) {
         const hx_layer_map *lm = &e->layers[l];
         HX_TIMED(HX_K_GEMM_QKV, hx_launch_gemm(e, &lm->wqkv, batch, ws + e->map.xp, HX_EPI_PARTIAL, ypart, nullptr, st));
-        HX_TIMED(HX_K_ROPE, hx_launch_rope_append(e, kv, l, batch, ypart, hx_gemm_splits(&lm->wqkv, batch), (size_t)batch * e->qkv_dim,
+        HX_TIMED(HX_K_ROPE, hx_launch_rope_append(e, kv, l, batch, ypart, hx_gemm_splits(e, &lm->wqkv, batch), hx_gemm_split_stride(e, &lm->wqkv, batch),
                                                  positions, st));
         if (!with_head && l + 1 == c->n_layers) break;   // prompt rows: of the last layer only its K and V are needed
         float *capture = e->attn_capture ? e->attn_capture + l * attn_stride : nullptr;
@@ -467,11 +467,11 @@ static int run_step(hx_engine *e, hx_kv *kv, int32_t batch, const int32_t *token
             HX_TIMED(HX_K_COMBINE, hx_launch_combine(e, batch, max_blocks, capture, st));
         }
         HX_TIMED(HX_K_GEMM_O, hx_launch_gemm(e, &lm->wo, batch, ws + e->map.ap, HX_EPI_PARTIAL, ypart, nullptr, st));
-        HX_TIMED(HX_K_NORM, hx_launch_reduce_norm(e, batch, ypart, hx_gemm_splits(&lm->wo, batch), (size_t)batch * c->hidden, lm->g2, st));
+        HX_TIMED(HX_K_NORM, hx_launch_reduce_norm(e, batch, ypart, hx_gemm_splits(e, &lm->wo, batch), hx_gemm_split_stride(e, &lm->wo, batch), lm->g2, st));
         HX_TIMED(HX_K_GEMM_GATE_UP, hx_launch_gemm(e, &lm->wgu, batch, ws + e->map.xp, HX_EPI_SWIGLU, nullptr, ws + e->map.mp, st));
         HX_TIMED(HX_K_GEMM_DOWN, hx_launch_gemm(e, &lm->wd, batch, ws + e->map.mp, HX_EPI_PARTIAL, ypart, nullptr, st));
         const size_t next_gain = (l + 1 < c->n_layers) ? e->layers[l + 1].g1 : e->gf;
-        HX_TIMED(HX_K_NORM, hx_launch_reduce_norm(e, batch, ypart, hx_gemm_splits(&lm->wd, batch), (size_t)batch * c->hidden, next_gain, st));
+        HX_TIMED(HX_K_NORM, hx_launch_reduce_norm(e, batch, ypart, hx_gemm_splits(e, &lm->wd, batch), hx_gemm_split_stride(e, &lm->wd, batch), next_gain, st));
     }
     if (!with_head) return HX_OK;
     if (sample && sample->top_p < 1.0f) {
@@ -903,11 +903,11 @@ extern "C" int hx_stage_linear(hx_engine *e, int kind, int layer, int32_t batch,
         case HX_T_WQKV:
             if ((rc = hx_launch_pack_x(e, batch, x_dev, c->hidden, ws + e->map.xp, st))) return rc;
             if ((rc = hx_launch_gemm(e, &lm->wqkv, batch, ws + e->map.xp, HX_EPI_PARTIAL, ypart, nullptr, st))) return rc;
-            return hx_launch_sum_partials(e, batch, ypart, hx_gemm_splits(&lm->wqkv, batch), (size_t)batch * e->qkv_dim, e->qkv_dim, y_dev, st);
+            return hx_launch_sum_partials(e, batch, ypart, hx_gemm_splits(e, &lm->wqkv, batch), hx_gemm_split_stride(e, &lm->wqkv, batch), e->qkv_dim, y_dev, st);
         case HX_T_WO:
             if ((rc = hx_launch_pack_x(e, batch, x_dev, e->q_dim, ws + e->map.ap, st))) return rc;
             if ((rc = hx_launch_gemm(e, &lm->wo, batch, ws + e->map.ap, HX_EPI_PARTIAL, ypart, nullptr, st))) return rc;
-            return hx_launch_sum_partials(e, batch, ypart, hx_gemm_splits(&lm->wo, batch), (size_t)batch * c->hidden, c->hidden, y_dev, st);
+            return hx_launch_sum_partials(e, batch, ypart, hx_gemm_splits(e, &lm->wo, batch), hx_gemm_split_stride(e, &lm->wo, batch), c->hidden, y_dev, st);
         case HX_T_WG:
             if ((rc = hx_launch_pack_x(e, batch, x_dev, c->hidden, ws + e->map.xp, st))) return rc;
             if ((rc = hx_launch_gemm(e, &lm->wgu, batch, ws + e->map.xp, HX_EPI_SWIGLU, nullptr, ws + e->map.mp, st))) return rc;
@@ -915,7 +915,7 @@ extern "C" int hx_stage_linear(hx_engine *e, int kind, int layer, int32_t batch,
         case HX_T_WD:
             if ((rc = hx_launch_pack_x(e, batch, x_dev, c->intermediate, ws + e->map.mp, st))) return rc;
             if ((rc = hx_launch_gemm(e, &lm->wd, batch, ws + e->map.mp, HX_EPI_PARTIAL, ypart, nullptr, st))) return rc;
-            return hx_launch_sum_partials(e, batch, ypart, hx_gemm_splits(&lm->wd, batch), (size_t)batch * c->hidden, c->hidden, y_dev, st);
+            return hx_launch_sum_partials(e, batch, ypart, hx_gemm_splits(e, &lm->wd, batch), hx_gemm_split_stride(e, &lm->wd, batch), c->hidden, y_dev, st);
         case HX_T_WLM:
             if ((rc = hx_launch_pack_x(e, batch, x_dev, c->hidden, ws + e->map.xp, st))) return rc;
             if ((rc = hx_launch_gemm(e, &e->wlm, batch, ws + e->map.xp, HX_EPI_LOGITS, y_dev, nullptr, st))) return rc;

@@ -1,4 +1,5 @@
-// Small-M weight-streaming matrix products  Y[M, N] = X[M, K] W[K, N]  (M = batch <= 256).
+// Small-M weight-streaming matrix products  Y[M, N] = X[M, K] W[K, N]  (M = batch <= 128;
+// more rows: gemm_wide.hip).
 //
 // The weights dominate the bytes, so the kernel is organised around streaming each packed weight
 // tile exactly once, straight from HBM into the A operand of v_mfma_f32_32x32x16_bf16 (32 output
@@ -96,8 +97,7 @@ int hx_launch_pack_matrix(const hx_engine *e, const hx_matrix *m, const void *sr
 // the end.  Every consumer keeps RING weight loads (1 KiB each, non-temporal) in flight in a register ring
 // and issues no other vector-memory load, so the in-order load counter never makes it wait for anything but
 // the tile it is about to use.  Producers stage the activations of the coming chunks (KC k-steps of every
-// k-slice, 32 KiB per stage, four stages; two stages of 64 KiB for 8 m-groups) in LDS: through their own
-// registers where two chunks fit them, else with the direct L2 -> LDS load; one workgroup barrier per chunk
+// k-slice, 32 KiB per stage, four stages) in LDS through their own registers; one workgroup barrier per chunk
 // hands a stage over.
 #ifndef HX_GEMM_RING
 #define HX_GEMM_RING 16
@@ -125,14 +125,9 @@ __device__ __forceinline__ u32x4_t hx_stream_load(const uint4 *p) {   // read-on
     return __builtin_nontemporal_load((const u32x4_t *)p);
 }
 
-// s_waitcnt immediate: wait until at most n vector-memory operations are outstanding, nothing else
-#define HX_VMCNT(n) (((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
-
 template <int MG, int WK> struct GemmGeom {
-    // stages: 4 x 32 KiB; with 8 m-groups 2 x 64 KiB, so that a stage still holds 8 k-steps (one barrier per 8)
-    static constexpr int NBUF = MG >= 8 ? 2 : 4;
-    static constexpr int STAGE_KB = MG >= 8 ? 64 : 32;
-    static constexpr int KC0 = STAGE_KB / (WK * MG);
+    static constexpr int NBUF = 4;                                  // stages of at most 32 KiB
+    static constexpr int KC0 = 32 / (WK * MG);
     static constexpr int KC = KC0 > 8 ? 8 : (KC0 < 1 ? 1 : KC0);   // k-steps per LDS chunk
     static constexpr int SLICE_U4 = KC * MG * 64;                   // uint4 per k-slice per stage
     static constexpr int PVT = WK * KC * MG;                        // 1-KiB copies per stage
@@ -154,17 +149,13 @@ __global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK>::NP)) void gemm_st
     const int32_t *__restrict__ a_positions, const int32_t *__restrict__ a_row_ids, float a_inv_t, uint32_t a_key0,
     uint32_t a_key1, float *__restrict__ a_samp_z, float *__restrict__ a_samp_m, float *__restrict__ a_samp_s) {
     using GG = GemmGeom<MG, WK>;
-    // 8 m-groups: a step takes twice as long (matrix-core time), so half the ring covers the same latency and the
-    // revolution that fills it is half as long
-    constexpr int RING = MG >= 8 ? HX_GEMM_RING / 2 : HX_GEMM_RING;
-    constexpr int NBUF = GG::NBUF, LOOK = NBUF - 1;
+    constexpr int RING = HX_GEMM_RING;
+    constexpr int NBUF = GG::NBUF;
     constexpr int KC = GG::KC, CPR = RING / KC, SLICE_U4 = GG::SLICE_U4, NC = WN * WK;
     // with at most 8 wavefronts per workgroup each may use 256 registers: enough to read B operands ahead
-    constexpr bool PREFETCH_B = (NC + GG::NP <= 8) && MG <= 4;
-    // activations staged through producer registers (two sets of PVP x 16 bytes per lane) where those fit
-    constexpr bool COPY_VIA_REGISTERS = GG::PVP <= 16;
+    constexpr bool PREFETCH_B = NC + GG::NP <= 8;
     static_assert(RING % KC == 0, "ring must hold whole chunks");
-    static_assert(LOOK * GG::PVP <= 63, "the stages in flight must fit the load counter");
+    static_assert((RING / KC) % 2 == 0, "the producers' register sets alternate in pairs of chunks");
     extern __shared__ u32x4_t xs[];                      // [NBUF][WK][SLICE_U4]
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -188,26 +179,9 @@ __global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK>::NP)) void gemm_st
         const u32x4_t *xp4 = (const u32x4_t *)a_xp;
         const int last_u4 = a_k_steps * MG * 64 - 1;
         const int pid = wave - NC;
-        auto copy_chunk = [&](int v) {                       // direct L2 -> LDS copy of virtual chunk v
-            const int buf = v % NBUF;
-            const int c = max(v - CPR, 0);
-#pragma unroll
-            for (int f = 0; f < GG::PVP; ++f) {
-                const int ff = pid * GG::PVP + f;        // copy index in the stage: (k-slice, 1-KiB piece)
-                const int w = ff / (KC * MG), i = ff % (KC * MG);
-                const int kb = min(split1, split0 + w * a_steps_per_wave);
-                const int src = min((kb + c * KC) * MG * 64 + i * 64 + lane, last_u4);
-                __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)(xp4 + src),
-                                                 (void __attribute__((address_space(3))) *)&xs[(buf * WK + w) * SLICE_U4 + i * 64],
-                                                 16, 0, 0);
-            }
-        };
-        const int n_virtual = n_chunks + CPR;
-        if constexpr (COPY_VIA_REGISTERS) {
         // The copy goes through registers (global load, then LDS store): measured faster than the direct L2 -> LDS
         // path, which slows the weight stream of the same compute unit down when both run (timing lab: weights alone
         // 27 us, direct copy alone 18 us, both 49 us for 60 workgroups).
-        static_assert(!COPY_VIA_REGISTERS || (RING / KC) % 2 == 0, "register sets alternate in pairs of chunks");
         u32x4_t ra[GG::PVP], rb[GG::PVP];
         auto load_chunk = [&](int c, u32x4_t (&r)[GG::PVP]) {
 #pragma unroll
@@ -251,19 +225,6 @@ __global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK>::NP)) void gemm_st
         __syncthreads();
         __syncthreads();
         __syncthreads();
-        } else {
-#pragma unroll
-        for (int q = 0; q < LOOK; ++q) copy_chunk(q);
-        for (int v = 0; v < n_virtual; ++v) {                    // barrier v ends the consumers' virtual chunk v
-            if (v + LOOK < n_virtual) {
-                copy_chunk(v + LOOK);                            // into the stage the consumers left at the last barrier
-                __builtin_amdgcn_s_waitcnt(HX_VMCNT((LOOK - 1) * GG::PVP)); // stage v + 1 has landed
-            } else {
-                __builtin_amdgcn_s_waitcnt(HX_VMCNT(0));      // nothing is in flight once the loop ends
-            }
-            __syncthreads();
-        }
-        }
         if (WK > 1) __syncthreads();
         return;
     }
@@ -449,11 +410,8 @@ template <int MG, int WN, int WK>
 static int launch_epi(int epilogue, dim3 grid, hipStream_t st, const GemmArgs &a) {
     if (epilogue == HX_EPI_PARTIAL) return launch_one<MG, WN, WK, HX_EPI_PARTIAL>(grid, st, a);
     if (epilogue == HX_EPI_SWIGLU) return launch_one<MG, WN, WK, HX_EPI_SWIGLU>(grid, st, a);
-    if constexpr (MG <= 4) {                             // more rows: the workgroup-tiled product
-        if (epilogue == HX_EPI_SAMPLE) return launch_one<MG, WN, WK, HX_EPI_SAMPLE>(grid, st, a);
-        if (epilogue == HX_EPI_LOGITS) return launch_one<MG, WN, WK, HX_EPI_LOGITS>(grid, st, a);
-    }
-    return hx_fail(HX_E_RANGE, "epilogue %d for %d m-groups", epilogue, MG);
+    if (epilogue == HX_EPI_SAMPLE) return launch_one<MG, WN, WK, HX_EPI_SAMPLE>(grid, st, a);
+    return launch_one<MG, WN, WK, HX_EPI_LOGITS>(grid, st, a);
 }
 
 template <int MG>
@@ -464,13 +422,11 @@ static int launch_shape(int wn, int wk, int epilogue, dim3 grid, hipStream_t st,
         if (wn == 6) return launch_epi<MG, 6, 1>(epilogue, grid, st, a);
     }
     if (wn == 4 && wk == 2) return launch_epi<MG, 4, 2>(epilogue, grid, st, a);
-    if constexpr (MG <= 4) {
-        // ten n-tiles per workgroup (twelve wavefronts): only for products that run in several rounds (the LM head)
-        if (wn == 10 && wk == 1 && epilogue != HX_EPI_PARTIAL) {
-            if (epilogue == HX_EPI_SWIGLU) return launch_one<MG, 10, 1, HX_EPI_SWIGLU>(grid, st, a);
-            if (epilogue == HX_EPI_SAMPLE) return launch_one<MG, 10, 1, HX_EPI_SAMPLE>(grid, st, a);
-            return launch_one<MG, 10, 1, HX_EPI_LOGITS>(grid, st, a);
-        }
+    // ten n-tiles per workgroup (twelve wavefronts): only for products that run in several rounds (the LM head)
+    if (wn == 10 && wk == 1 && epilogue != HX_EPI_PARTIAL) {
+        if (epilogue == HX_EPI_SWIGLU) return launch_one<MG, 10, 1, HX_EPI_SWIGLU>(grid, st, a);
+        if (epilogue == HX_EPI_SAMPLE) return launch_one<MG, 10, 1, HX_EPI_SAMPLE>(grid, st, a);
+        return launch_one<MG, 10, 1, HX_EPI_LOGITS>(grid, st, a);
     }
     return hx_fail(HX_E_RANGE, "unsupported product shape wn=%d wk=%d for %d m-groups", wn, wk, MG);
 }
@@ -535,10 +491,21 @@ extern "C" int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, 
     return HX_OK;
 }
 
-int hx_gemm_splits(const hx_matrix *m, int batch) {
+// Beyond 128 rows the workgroup-tiled product of gemm_wide.hip takes over: one block of 256 rows, those past the batch
+// computed and never read.  Its partials are 256 rows apart, so fewer splits fit the buffer of an engine for fewer rows.
+static bool wide_rows(int batch) { return batch > 128; }
+static hx_wide_plan plan_wide_batch(const hx_engine *e, const hx_matrix *m, int epilogue) {
+    return hx_plan_wide(m, 1, epilogue, HX_MAX_SPLITS * e->cfg.max_batch / 256);
+}
+int hx_gemm_splits(const hx_engine *e, const hx_matrix *m, int batch) {
+    if (wide_rows(batch)) return plan_wide_batch(e, m, HX_EPI_PARTIAL).splits;
     gemm_launch plan[2];
     plan_product(m->n_tiles, m->k_steps, hx_m_groups(batch), true, plan);
     return plan[0].splits;
+}
+size_t hx_gemm_split_stride(const hx_engine *e, const hx_matrix *m, int batch) {
+    (void)e;
+    return (size_t)(wide_rows(batch) ? 256 : batch) * m->N;
 }
 
 int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void *xp, int epilogue, float *y,
@@ -546,14 +513,16 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
     if (epilogue == HX_EPI_SAMPLE && !sample) return hx_fail(HX_E_NULL, "sampling parameters missing");
     const int mg = hx_m_groups(batch);
     const bool partial = epilogue == HX_EPI_PARTIAL;
-    if ((epilogue == HX_EPI_LOGITS || epilogue == HX_EPI_SAMPLE) && batch > 128) {
-        // Beyond 128 rows the streaming kernel has one wavefront per SIMD with all rows' accumulators, and nothing beside its
-        // multiplications or its epilogue; the workgroup-tiled product has two.  1.5B, 256 rows, sampled: 327 -> 204 us.
+    if (wide_rows(batch)) {
+        // The streaming kernel has one wavefront per SIMD with all rows' accumulators, and nothing beside its multiplications
+        // or its epilogue; the workgroup-tiled product has two.  LM head, 1.5B, 256 rows, sampled: 327 -> 204 us; the other
+        // products: see hx_plan_wide.
         const hx_lm_args lm{y, batch, m->N, m->n_tiles, (float *)(e->ws + e->map.amax_val), (int32_t *)(e->ws + e->map.amax_idx),
                             sample ? sample->positions : nullptr, sample ? sample->row_ids : nullptr,
                             sample ? sample->inv_temperature : 1.0f, sample ? sample->key0 : 0u, sample ? sample->key1 : 0u,
                             (float *)(e->ws + e->map.samp_z), (float *)(e->ws + e->map.samp_m), (float *)(e->ws + e->map.samp_s)};
-        return hx_launch_gemm_wide(e, m, 1, (char *)xp, 0, 0, epilogue, 0, 0, hx_plan_wide(m, 1, epilogue), st, &lm);
+        return hx_launch_gemm_wide(e, m, 1, e->ws, 0, (const char *)xp - e->ws, epilogue, partial ? (char *)y - e->ws : 0,
+                                   mp_out ? (char *)mp_out - e->ws : 0, plan_wide_batch(e, m, epilogue), st, &lm);
     }
     gemm_launch plan[2];
     const int n_launch = plan_product(m->n_tiles, m->k_steps, mg, partial, plan);
@@ -589,8 +558,7 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
             case 1: rc = launch_shape<1>(pl.wn, pl.wk, epilogue, grid, st, a); break;
             case 2: rc = launch_shape<2>(pl.wn, pl.wk, epilogue, grid, st, a); break;
             case 4: rc = launch_shape<4>(pl.wn, pl.wk, epilogue, grid, st, a); break;
-            case 8: rc = launch_shape<8>(pl.wn, pl.wk, epilogue, grid, st, a); break;
-            default: return hx_fail(HX_E_RANGE, "batch %d exceeds 256", batch);
+            default: return hx_fail(HX_E_RANGE, "%d rows for the streaming product", batch);
         }
         if (rc) return rc;
         HX_CHECK_LAUNCH("gemm_stream");

@@ -7,8 +7,8 @@
 // [k_step][8 m-groups][lane][8] in that block's workspace.  Both are already in matrix-core operand order, so
 // staging is a plain copy of 1-KiB pieces and every LDS read is 16 contiguous bytes per lane (conflict-free).
 //
-// Workgroup = 8 wavefronts, two per SIMD: 2 x 4 sub-tiles of 128 x 64 (256 columns), 4 x 2 of 64 x 96 (192 columns), or 8
-// of 32 rows by all 224 or 160 columns.
+// Workgroup = 8 wavefronts, two per SIMD: 2 x 4 sub-tiles of 128 x 64 (256 columns), 4 x 2 of 64 x 96 or 64 x 64
+// (192, 128 columns), or 8 of 32 rows by all 224 or 160 columns.
 // A chunk is 2 k-steps: 16 pieces of X and 2 WNT of W, each copied global -> LDS directly by one wavefront, requested two
 // chunks ahead into a ring of three stages; one barrier per chunk, passed BEFORE the chunk's last k-step is multiplied,
 // so that the first operand reads of the next chunk hide behind those products, as the reads of its second k-step hide
@@ -19,8 +19,8 @@
 // wavefront, copies through registers) 1 195, and 951 against 1 086 with fp32 stores, which the second wavefront of a
 // SIMD overlaps.  Four or five stages, or chunks of 4 k-steps in two stages, were not faster (1 095, 1 088, 995).
 //
-// Workgroup numbering: consecutive workgroup ids go to different XCDs, so XCD x takes the x-th eighth of the tiles, row
-// blocks fastest: its workgroups take all row blocks of a few column blocks and walk K in step, so each XCD's L2 sees
+// Workgroup numbering: consecutive workgroup ids go to different XCDs, so XCD x takes the x-th eighth of the work, row
+// blocks fastest, splits slowest: its workgroups take all row blocks of a few column blocks and walk K in step, so each XCD's L2 sees
 // (nearly) every weight once, and all XCDs have the same number of workgroups.  (Whole column blocks dealt to the XCDs
 // in turn left four of them with half as much again as the others at 20 column blocks: 724 us instead of 610 for the
 // 14B down product over 4864 rows in two splits.)
@@ -45,15 +45,16 @@ struct WideArgs {
     size_t block_stride;
     int R;                        // 256-row blocks
     float *y0;                    // fp32 output of block 0 ([splits][256][N]), same stride between blocks
-    int steps_per_split;
+    int steps_per_split, splits;
     uint16_t *mp0;                // SiLU(gate)*up output of block 0 (packed activations, 8 m-groups)
     hx_lm_args lm;                // LM head (one block)
 };
 
-// WNT: 32-column tiles per workgroup, 5 to 8 (a 256 x 160 to 256 x 256 output tile).  Splits hold whole chunks.
-template <int WNT, int EPI>
+// WNT: 32-column tiles per workgroup, 4 to 8 (a 256 x 128 to 256 x 256 output tile).  Splits hold whole chunks; ODD:
+// but for the last, whose second k-step is missing.  (As a run-time condition in the loop this cost the narrow tiles 11 %.)
+template <int WNT, int EPI, bool ODD>
 __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) {
-    constexpr int KC = WIDE_KC, NST = WIDE_STAGES, WCOL = WNT == 8 ? 4 : (WNT == 6 ? 2 : 1), WROW = WIDE_WAVES / WCOL, TM = 8 / WROW,
+    constexpr int KC = WIDE_KC, NST = WIDE_STAGES, WCOL = WNT == 8 ? 4 : (WNT % 2 ? 1 : 2), WROW = WIDE_WAVES / WCOL, TM = 8 / WROW,
                   TW = WNT / WCOL;
     constexpr int PIECES = KC * (8 + WNT), STAGE_U4 = PIECES * 64;
     constexpr int LPW = (PIECES + WIDE_WAVES - 1) / WIDE_WAVES, FULL = PIECES - (LPW - 1) * WIDE_WAVES;   // waves < FULL copy LPW pieces, the others one less
@@ -61,17 +62,18 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
     extern __shared__ u32x4_t lds[];                    // [NST][PIECES][64 lanes]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int NB = (a.n_tiles + WNT - 1) / WNT;
-    const int tile = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-    if (tile >= NB * a.R) return;                       // whole workgroup, before any barrier
+    const int item = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    const int split = item / (NB * a.R), tile = item - split * (NB * a.R);
+    if (split >= a.splits) return;                      // whole workgroup, before any barrier
     const int b = tile % a.R, nbl = tile / a.R;
     const int nt0 = nbl * WNT;
     const int k_steps = a.k_steps;
-    const int k0 = blockIdx.y * a.steps_per_split, k1 = min(k_steps, k0 + a.steps_per_split);
-    const int n_chunks = (k1 - k0) / KC;
+    const int k0 = split * a.steps_per_split, k1 = min(k_steps, k0 + a.steps_per_split);
+    const int n_chunks = (k1 - k0 + 1) / KC;            // an odd last k-step (a down product): its partner counts as zero
     const u32x4_t *xp = (const u32x4_t *)(a.xp0 + (size_t)b * a.block_stride);
     // this wavefront's share of the copies of a chunk: wave-uniform pointers that advance by a fixed step per chunk and
     // stop at the split's last one (requests past the end repeat it: never used)
-    const bool full = wave < FULL;
+    const bool full = FULL == WIDE_WAVES || wave < FULL;
     const u32x4_t *ptr[LPW];
     int step[LPW];
     uint32_t dst[LPW];
@@ -139,7 +141,15 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
             // chunk c + 1, if it is that chunk's first), and, in k-step 0, the copies of chunk c + NST - 1 into the stage
             // of chunk c - 1, which everybody has left
             const bool last = kc + 1 == KC;
-            if (last) hand_over();
+            if (last) {
+                hand_over();
+                if (ODD && 2 * c + 1 >= k1 - k0) {          // both, as what lies behind either may hold anything; the copies stay
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) x[kc & 1][i] = u32x4_t{0u, 0u, 0u, 0u};   // inside the buffers: a down
+#pragma unroll
+                    for (int j = 0; j < TW; ++j) wt[kc & 1][j] = u32x4_t{0u, 0u, 0u, 0u};  // matrix and its input are followed by others
+                }
+            }
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
                 if (i == 0) {
@@ -166,7 +176,7 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
     // accumulator register r of lane l: batch row m = 32*(TM*wm + i) + l%32, column n = 32*nt + 8*(r/4) + 4*(l/32) + r%4
     const int hl = lane >> 5, ml = lane & 31;
     if (EPI == HX_EPI_PARTIAL) {
-        float *y = a.y0 + ((size_t)b * a.block_stride) / 4 + (size_t)blockIdx.y * 256 * a.N;
+        float *y = a.y0 + ((size_t)b * a.block_stride) / 4 + (size_t)split * 256 * a.N;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int m = 32 * (TM * wm + i) + ml;
@@ -229,25 +239,28 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
     }
 }
 
-template <int WNT, int EPI>
+template <int WNT, int EPI, bool ODD>
 int launch_wide(dim3 grid, hipStream_t st, const WideArgs &a) {
     static std::once_flag once;
     static hipError_t configured = hipSuccess;
     std::call_once(once, [] {
-        configured = hipFuncSetAttribute((const void *)gemm_wide_kernel<WNT, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        configured = hipFuncSetAttribute((const void *)gemm_wide_kernel<WNT, EPI, ODD>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                          wide_lds_bytes(WNT));
     });
     if (configured != hipSuccess) return hx_fail(HX_E_HIP, "hipFuncSetAttribute: %s", hipGetErrorString(configured));
-    hipLaunchKernelGGL((gemm_wide_kernel<WNT, EPI>), grid, dim3(64 * WIDE_WAVES), wide_lds_bytes(WNT), st, a);
+    hipLaunchKernelGGL((gemm_wide_kernel<WNT, EPI, ODD>), grid, dim3(64 * WIDE_WAVES), wide_lds_bytes(WNT), st, a);
     return HX_OK;
 }
 
 template <int WNT>
 int launch_wide_epi(int epilogue, dim3 grid, hipStream_t st, const WideArgs &a) {
-    if (epilogue == HX_EPI_PARTIAL) return launch_wide<WNT, HX_EPI_PARTIAL>(grid, st, a);
-    if (epilogue == HX_EPI_LOGITS) return launch_wide<WNT, HX_EPI_LOGITS>(grid, st, a);
-    if (epilogue == HX_EPI_SAMPLE) return launch_wide<WNT, HX_EPI_SAMPLE>(grid, st, a);
-    return launch_wide<WNT, HX_EPI_SWIGLU>(grid, st, a);
+    if (epilogue == HX_EPI_PARTIAL) {
+        if (a.k_steps & 1) return launch_wide<WNT, HX_EPI_PARTIAL, true>(grid, st, a);
+        return launch_wide<WNT, HX_EPI_PARTIAL, false>(grid, st, a);
+    }
+    if (epilogue == HX_EPI_LOGITS) return launch_wide<WNT, HX_EPI_LOGITS, false>(grid, st, a);
+    if (epilogue == HX_EPI_SAMPLE) return launch_wide<WNT, HX_EPI_SAMPLE, false>(grid, st, a);
+    return launch_wide<WNT, HX_EPI_SWIGLU, false>(grid, st, a);
 }
 
 }  // namespace
@@ -261,16 +274,19 @@ int launch_wide_epi(int epilogue, dim3 grid, hipStream_t st, const WideArgs &a) 
 // Measured (us): 7B, 2048 rows: QKV 76 with 5 tiles and no split (6 tiles in 4 splits: 99, and 9 more in the consumer
 // that sums them), O + down 295 with 7 tiles in 2 splits (8 in 2: 317).  14B, 4864 rows: QKV 351 with 6 (7: 373, 8: 399,
 // 5: 397), O + down 885 with 7 (8: 951, 8 in 2 splits: 1007), gate|up 1160 with 8 (7: 1199, 6: 1193, 5: 1300).
-hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, int epilogue) {
+// One block of 256 rows (us; in brackets the streaming kernel of gemm.hip, which it replaces beyond 128 rows): 1.5B QKV 14.8
+// (17.4), O 14.8 (16.1), gate|up 27.6 (32.2), down 21.1 (25.3); 7B 20.4 (21.1), 18.4 (19.5), 78.4 (88.6), 46.7 (50.2);
+// 14B 31.2 (32.9), 25.7 (27.3), 90.9 (89.7), 46.6 (51.5).
+hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, int epilogue, int max_splits) {
     const int cus = hx_device_cus();
     const bool partial = epilogue == HX_EPI_PARTIAL;
     const double out_mb = (double)row_blocks * 256 * m->N * (epilogue == HX_EPI_SWIGLU ? 1 : 4) * 1e-6;   // gate|up: bf16 of half the columns
     hx_wide_plan best{8, 1};
     double best_us = 1e300;
-    for (int wnt : {8, 7, 6, 5}) {
+    for (int wnt : {8, 7, 6, 5, 4}) {
         const int NB = (m->n_tiles + wnt - 1) / wnt;
-        const double narrow = wnt == 5 ? 1.12 : (wnt == 6 ? 1.03 : 1.0);
-        for (int s = 1; s <= (partial ? HX_MAX_SPLITS : 1); ++s) {
+        const double narrow = wnt == 4 ? 1.2 : (wnt == 5 ? 1.12 : (wnt == 6 ? 1.03 : 1.0));
+        for (int s = 1; s <= (partial ? max_splits : 1); ++s) {
             if (s > 1 && m->k_steps / s < 32) break;
             const int sps = ((m->k_steps + s - 1) / s + 1) & ~1;
             if ((s - 1) * sps >= m->k_steps) continue;          // whole chunks would leave the last split empty
@@ -293,8 +309,9 @@ int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, 
                         int epilogue, size_t y_off, size_t mp_off, hx_wide_plan plan, hipStream_t st, const hx_lm_args *lm) {
     int splits = plan.splits;
     const int wnt = plan.wnt;
-    if (wnt < 5 || wnt > 8) return hx_fail(HX_E_RANGE, "%d tiles per workgroup: no such wide product", wnt);
-    if (m->k_steps % WIDE_KC) return hx_fail(HX_E_SHAPE, "wide products need K to be a multiple of 32, not %d", m->k_steps * 16);
+    if (wnt < 4 || wnt > 8) return hx_fail(HX_E_RANGE, "%d tiles per workgroup: no such wide product", wnt);
+    if (m->k_steps % 2 && epilogue != HX_EPI_PARTIAL)   // hidden sizes are multiples of 32: only a down product's K can be odd
+        return hx_fail(HX_E_SHAPE, "epilogue %d over %d k-steps has no wide product", epilogue, m->k_steps);
     const bool head = epilogue == HX_EPI_LOGITS || epilogue == HX_EPI_SAMPLE;
     if (head && (!lm || row_blocks != 1)) return hx_fail(HX_E_RANGE, "the LM head takes one block of rows");
     if (epilogue != HX_EPI_PARTIAL) splits = 1;
@@ -308,11 +325,13 @@ int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, 
     a.lm = head ? *lm : hx_lm_args{};
     a.steps_per_split = ((m->k_steps + splits - 1) / splits + 1) & ~1;
     const int NB = (m->n_tiles + wnt - 1) / wnt;
-    dim3 grid((NB * row_blocks + 7) / 8 * 8, splits);
+    a.splits = splits;
+    dim3 grid((NB * row_blocks * splits + 7) / 8 * 8);
     for (int sp = 0; sp < splits; ++sp)
         if (sp * a.steps_per_split >= m->k_steps) return hx_fail(HX_E_RANGE, "%d splits leave split %d of %d k-steps empty", splits, sp, m->k_steps);
     int rc;
     switch (wnt) {
+        case 4: rc = launch_wide_epi<4>(epilogue, grid, st, a); break;
         case 5: rc = launch_wide_epi<5>(epilogue, grid, st, a); break;
         case 6: rc = launch_wide_epi<6>(epilogue, grid, st, a); break;
         case 7: rc = launch_wide_epi<7>(epilogue, grid, st, a); break;

@@ -327,12 +327,14 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
 // gemm_wide.hip: products over several 256-row blocks at once (prompt rows)
 struct hx_wide_plan { int wnt, splits; };        // 32-column tiles per workgroup, K-splits
 struct hx_lm_args;
-hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, int epilogue);
+hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, int epilogue, int max_splits = HX_MAX_SPLITS);
 int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, char *ws0, size_t block_stride, size_t xp_off,
                         int epilogue, size_t y_off, size_t mp_off, hx_wide_plan plan, hipStream_t st, const hx_lm_args *lm = nullptr);
 
 int hx_launch_sample_final(const hx_engine *e, int batch, int32_t *tokens_out, float *logprobs_out, hipStream_t st);
-int hx_gemm_splits(const hx_matrix *m, int batch);   // K-splits the planner uses for a product with split partials
+// a product with split partials: the K-splits hx_launch_gemm uses, and the elements between their outputs
+int hx_gemm_splits(const hx_engine *e, const hx_matrix *m, int batch);
+size_t hx_gemm_split_stride(const hx_engine *e, const hx_matrix *m, int batch);
 int hx_launch_argmax_final(const hx_engine *e, int batch, int32_t *tokens_out, hipStream_t st);
 
 // elementwise.hip

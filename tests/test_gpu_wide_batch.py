@@ -1,0 +1,51 @@
+"""Products of more than 128 rows outside prefill_rows: batches at the edges of the workgroup-tiled kernel, an odd number of
+k-steps, engines for fewer than 256 rows (whose partial buffer caps the K-splits), column blocks that end inside a
+workgroup's tile, and the sampled head.  Reference: the product in float64."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_00796_amd import synth
+from test_gpu_prefill import build
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hx():
+    from paper_2511_00796_amd import binding
+    binding.load()
+    return binding
+
+
+# intermediate 688 = 43 k-steps, 16 = one; 2080 = 130; vocab 1000: the last head tile holds 8 columns
+SHAPES = {"odd": synth.ModelShape("wb-odd", 1, 256, 4, 2, 64, 688, 1000), "one": synth.ModelShape("wb-one", 1, 64, 1, 1, 64, 16, 64),
+          "splits": synth.ModelShape("wb-splits", 1, 1536, 12, 2, 128, 2080, 2048)}
+
+
+@pytest.mark.parametrize("batch,max_batch", [(129, 129), (130, 200), (255, 256), (256, 256)])
+@pytest.mark.parametrize("name", sorted(SHAPES))
+def test_products_beyond_128_rows(hx, name, batch, max_batch):
+    s = SHAPES[name]
+    eng = build(hx, s, 5, max_batch, 64)
+    w = {k: v.double().cuda() for k, v in synth.layer_weights(s, 0, 5).items()}
+    g = torch.Generator(device="cuda").manual_seed(7)
+    head = synth.global_weights(s, 5)["wlm"].double().cuda()
+    for kind, mat in ((hx.HX_T_WQKV, w["wqkv"]), (hx.HX_T_WO, w["wo"]), (hx.HX_T_WD, w["wd"]), (hx.HX_T_WG, None), (hx.HX_T_WLM, head)):
+        K = s.hidden if mat is None else mat.shape[0]
+        N = s.intermediate if mat is None else mat.shape[1]
+        x = torch.randn(batch, K, generator=g, device="cuda").bfloat16().float()
+        y = eng.stage_linear(kind, 0, x)
+        y = y[0] if isinstance(y, tuple) else y
+        torch.cuda.synchronize()
+        assert y.shape == (batch, N)
+        xd = x.double()
+        if mat is None:
+            gate = xd @ w["wg"]
+            ref = gate * torch.sigmoid(gate) * (xd @ w["wu"])
+            # one bf16 rounding of the result (2^-8 at most with ties and the fp32 sums' own error)
+            assert ((y.double() - ref).abs() <= ref.abs() * 2.0 ** -7 + 1e-5).all(), (name, kind)
+        else:
+            # fp32 sums of exact products: a few units of 2^-24 of the sum of magnitudes
+            bound = xd.abs() @ mat.abs()
+            assert ((y.double() - (xd @ mat)).abs() <= 1e-5 * bound).all(), (name, kind)
