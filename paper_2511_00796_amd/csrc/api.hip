@@ -475,9 +475,9 @@ static int run_step(hx_engine *e, hx_kv *kv, int32_t batch, const int32_t *token
     }
     if (!with_head) return HX_OK;
     if (sample && sample->top_p < 1.0f) {
-        // the kept set needs every logit of the row again: the head writes them (with its per-tile maxima), then
+        // the kept set needs every logit of the row again: the head writes them (with its per-tile maxima and winners), then
         // one workgroup per row selects and draws
-        HX_TIMED(HX_K_GEMM_LM, hx_launch_gemm(e, &e->wlm, batch, ws + e->map.xp, HX_EPI_LOGITS, logits_out, nullptr, st));
+        HX_TIMED(HX_K_GEMM_LM, hx_launch_gemm(e, &e->wlm, batch, ws + e->map.xp, HX_EPI_SAMPLE, logits_out, nullptr, st, sample));
         HX_TIMED(HX_K_SETUP, hx_launch_nucleus(e, batch, logits_out, sample, next_tokens_out, logprobs_out, st));
     } else if (sample) {
         HX_TIMED(HX_K_GEMM_LM, hx_launch_gemm(e, &e->wlm, batch, ws + e->map.xp, HX_EPI_SAMPLE, logits_out, nullptr, st, sample));
@@ -832,7 +832,7 @@ extern "C" int hx_stage_lm_head_top_p(hx_engine *e, int32_t batch, const float *
     sp.top_p = top_p;
     sp.nucleus_sizes = nucleus_sizes_out;
     if ((rc = hx_launch_pack_x(e, batch, x_dev, e->cfg.hidden, e->ws + e->map.xp, st))) return rc;
-    if ((rc = hx_launch_gemm(e, &e->wlm, batch, e->ws + e->map.xp, HX_EPI_LOGITS, logits_out, nullptr, st))) return rc;
+    if ((rc = hx_launch_gemm(e, &e->wlm, batch, e->ws + e->map.xp, HX_EPI_SAMPLE, logits_out, nullptr, st, &sp))) return rc;
     return hx_launch_nucleus(e, batch, logits_out, &sp, tokens_out, logprobs_out, st);
 }
 

@@ -8,8 +8,9 @@
 // entries that match the digits chosen so far, and walks it from the largest z down to the digit where the
 // running mass reaches the target.  Mass is 40-bit fixed point, w_i = floor(exp(z_i - max z) * 2^40), added with
 // integer LDS atomics: the sums are exact, so the kept set does not depend on the order of the additions and the
-// kernel is deterministic.  A last pass draws among the kept entries.  Four reads of the row (from the memory-side
-// cache: the LM head has just written it).
+// kernel is deterministic.  The draw takes the tile winners that the LM head's sampling epilogue has left, on the whole
+// chip (here, one workgroup per row, drawing again for every kept entry was 90 of 144 us at 64 rows of 152 064 logits).
+// Three reads of the row (from the memory-side cache: the LM head has just written it).
 #include "hx_internal.h"
 
 #define HX_NUC_THREADS 1024
@@ -42,7 +43,8 @@ __device__ __forceinline__ void load_groups(const float *__restrict__ x, int V, 
 }
 
 __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
-    const float *__restrict__ logits, int V, const float *__restrict__ tile_max, int n_tiles,
+    const float *__restrict__ logits, int V, const float *__restrict__ cand_y, const int32_t *__restrict__ cand_i,
+    const float *__restrict__ cand_z, const float *__restrict__ tile_zmax, int n_tiles,
     const int32_t *__restrict__ positions, const int32_t *__restrict__ row_ids, float inv_t, float top_p, uint32_t key0,
     uint32_t key1, int32_t *__restrict__ tok_out, float *__restrict__ lp_out, int32_t *__restrict__ size_out) {
     __shared__ unsigned long long hist[HX_NUC_BINS];
@@ -58,9 +60,9 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
     const bool vec = (V & 3) == 0;                // rows then start on 16-byte boundaries
     const int n_groups = (V + 3) >> 2;
 
-    // max z from the LM head's per-tile maxima of the raw logits (scaling by 1/T > 0 is monotone)
+    // max z from the LM head's per-tile maxima
     float mx = -INFINITY;
-    for (int t = tid; t < n_tiles; t += HX_NUC_THREADS) mx = fmaxf(mx, tile_max[(size_t)m * n_tiles + t]);
+    for (int t = tid; t < n_tiles; t += HX_NUC_THREADS) mx = fmaxf(mx, tile_zmax[(size_t)m * n_tiles + t]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
     if (lane == 0) redf[wave] = mx;
@@ -68,7 +70,7 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
     mx = redf[0];
 #pragma unroll
     for (int w = 1; w < HX_NUC_THREADS / 64; ++w) mx = fmaxf(mx, redf[w]);
-    const float zmax = mx * inv_t;
+    const float zmax = mx;
     __syncthreads();
 
     uint32_t prefix = 0;                          // digits chosen so far (the high bits of tau's key)
@@ -133,36 +135,65 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
     const uint32_t key_tau = prefix;
     const unsigned long long mass = sh_mass;      // of all entries with key <= key_tau, i.e. z >= tau
 
-    // the draw: largest z_i - log(-log(u_i)) among the kept entries, smaller index on ties
+    // The draw: largest z_i - log(-log(u_i)) among the kept entries, smaller index on ties.  The LM head has left the best
+    // perturbed score of every 32-column tile: where that entry is kept it is the tile's best kept one, too.  Only the
+    // other tiles (about 1 - top_p of them) are gone through again, by eight lanes each.
     const uint32_t row = row_ids ? (uint32_t)row_ids[m] : (uint32_t)m;
     const uint32_t pos = (uint32_t)positions[m];
     float best = -INFINITY, best_z = 0.f;
     int32_t best_i = 0x7fffffff, count = 0;
-    for (int q0 = tid; q0 < n_groups; q0 += HX_NUC_THREADS * HX_NUC_UNROLL) {
-        float v[HX_NUC_UNROLL][4];
-        load_groups(x, V, q0, n_groups, vec, v);
+    auto consider = [&](float y, int32_t i, float z) { if (y > best || (y == best && i < best_i)) { best = y; best_i = i; best_z = z; } };
+    for (int t0 = tid - lane; t0 < n_tiles; t0 += HX_NUC_THREADS) {      // whole wavefronts
+        const int t = t0 + lane;
+        bool again = false;
+        if (t < n_tiles) {
+            const size_t o = (size_t)m * n_tiles + t;
+            const float z = cand_z[o];
+            if (nucleus_key(z) <= key_tau) consider(cand_y[o], cand_i[o], z);
+            else again = true;
+        }
+        unsigned long long todo = __ballot(again);
+        while (todo) {
+            int mine = -1;                         // lane's tile: the (lane / 8)-th of the next eight
 #pragma unroll
-        for (int u4 = 0; u4 < HX_NUC_UNROLL; ++u4) {
-            const int q = q0 + u4 * HX_NUC_THREADS;
-            bool any = false;
-            bool keep[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                keep[i] = (4 * q + i < V) && nucleus_key(v[u4][i] * inv_t) <= key_tau;
-                any |= keep[i];
+            for (int k = 0; k < 8; ++k) {
+                if (todo) {
+                    const int b = __ffsll((long long)todo) - 1;
+                    if ((lane >> 3) == k) mine = t0 + b;
+                    todo &= todo - 1;
+                }
             }
-            if (!any) continue;
-            uint32_t w[4];
-            hx_philox4x32_10((uint32_t)q, row, pos, 0x53414D50u, key0, key1, w);
+            const int q = mine * 8 + (lane & 7);
+            if (mine >= 0 && q < n_groups) {
+                float v[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (!keep[i]) continue;
-                ++count;
-                const float z = v[u4][i] * inv_t;
-                const float u = ((float)(w[i] >> 9) + 0.5f) * (1.0f / 8388608.0f);
-                const float y = z - logf(-logf(u));
-                if (y > best) { best = y; best_i = 4 * q + i; best_z = z; }   // a thread's indices ascend
+                for (int i = 0; i < 4; ++i) v[i] = 4 * q + i < V ? x[4 * (size_t)q + i] : -INFINITY;
+                bool keep[4], any = false;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { keep[i] = 4 * q + i < V && nucleus_key(v[i] * inv_t) <= key_tau; any |= keep[i]; }
+                if (any) {
+                    uint32_t w[4];
+                    hx_philox4x32_10((uint32_t)q, row, pos, 0x53414D50u, key0, key1, w);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (!keep[i]) continue;
+                        const float z = v[i] * inv_t;
+                        const float u = ((float)(w[i] >> 9) + 0.5f) * (1.0f / 8388608.0f);
+                        consider(z - logf(-logf(u)), 4 * q + i, z);
+                    }
+                }
             }
+        }
+    }
+    if (size_out) {                               // the number of kept entries, where it is asked for
+        for (int q0 = tid; q0 < n_groups; q0 += HX_NUC_THREADS * HX_NUC_UNROLL) {
+            float v[HX_NUC_UNROLL][4];
+            load_groups(x, V, q0, n_groups, vec, v);
+#pragma unroll
+            for (int u = 0; u < HX_NUC_UNROLL; ++u)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    count += 4 * (q0 + u * HX_NUC_THREADS) + i < V && nucleus_key(v[u][i] * inv_t) <= key_tau;
         }
     }
 #pragma unroll
@@ -189,7 +220,8 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
 int hx_launch_nucleus(const hx_engine *e, int batch, const float *logits, const hx_sample_params *sample,
                       int32_t *tokens_out, float *logprobs_out, hipStream_t st) {
     hipLaunchKernelGGL(nucleus_kernel, dim3(batch), dim3(HX_NUC_THREADS), 0, st, logits, e->cfg.vocab,
-                       (const float *)(e->ws + e->map.amax_val), e->wlm.n_tiles, sample->positions, sample->row_ids,
+                       (const float *)(e->ws + e->map.amax_val), (const int32_t *)(e->ws + e->map.amax_idx),
+                       (const float *)(e->ws + e->map.samp_z), (const float *)(e->ws + e->map.samp_m), e->wlm.n_tiles, sample->positions, sample->row_ids,
                        sample->inv_temperature, sample->top_p, sample->key0, sample->key1, tokens_out, logprobs_out,
                        sample->nucleus_sizes);
     HX_CHECK_LAUNCH("nucleus");
