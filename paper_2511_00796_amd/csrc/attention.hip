@@ -152,21 +152,22 @@ __device__ __forceinline__ void stream_tiles(AttnState<D> &st, const bf16x8_t (&
             }
             float s4[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) s4[r] = (tok0 + r >= t0 && tok0 + r < t1) ? sc[r] * scale_log2e : -INFINITY;
+            for (int r = 0; r < 4; ++r) s4[r] = sc[r] * scale_log2e;
             // V of positions that do not exist must not reach the product as NaN/Inf
             u32x4_t vv[D / 32];
 #pragma unroll
             for (int q = 0; q < D / 32; ++q) vv[q] = ring[s][D / 32 + q];
             if (i < 0 || t0 + (i + 1) * 16 > t1) {             // wave-uniform: a tile with missing tokens
                 const int valid = (i < 0) ? 0 : (t1 - tok0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s4[r] = r < valid ? s4[r] : -INFINITY;
                 const uint32_t m01 = valid >= 2 ? 0xffffffffu : (valid == 1 ? 0x0000ffffu : 0u);
                 const uint32_t m23 = valid >= 4 ? 0xffffffffu : (valid == 3 ? 0x0000ffffu : 0u);
 #pragma unroll
                 for (int q = 0; q < D / 32; ++q) { vv[q].x &= m01; vv[q].y &= m23; vv[q].z &= m01; vv[q].w &= m23; }
             }
             float mx = fmaxf(fmaxf(s4[0], s4[1]), fmaxf(s4[2], s4[3]));
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            mx = hx_max_of_16_lane_groups(mx);
             const float m_new = fmaxf(st.m, mx);
             const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
             float p[4];

@@ -61,7 +61,7 @@ __device__ __forceinline__ void stream_tiles8(AttnState8<D> &st, const bf16x8_t 
             hx_hold_operands(kop, sc);                         // converted operands outlive the products that read them
             float s4[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) s4[r] = (tok0 + r >= t0 && tok0 + r < t1) ? sc[r] * scale_log2e : -INFINITY;
+            for (int r = 0; r < 4; ++r) s4[r] = sc[r] * scale_log2e;
             // V: operand step q = dwords 2 (q % 2) (rows d < 16 of the step) and 2 (q % 2) + 1 (rows d >= 16) of load
             // D/64 + q / 2; a dword holds this lane's 4 tokens, one byte each.  Bytes of positions that do not
             // exist may hold anything (also NaN codes): they are cleared before the conversion.
@@ -74,22 +74,26 @@ __device__ __forceinline__ void stream_tiles8(AttnState8<D> &st, const bf16x8_t 
             }
             if (i < 0 || t0 + (i + 1) * 16 > t1) {             // wave-uniform: a tile with missing tokens
                 const int valid = (i < 0) ? 0 : (t1 - tok0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s4[r] = r < valid ? s4[r] : -INFINITY;
                 const uint32_t keep = valid >= 4 ? 0xffffffffu : (valid <= 0 ? 0u : ((1u << (8 * valid)) - 1u));
 #pragma unroll
                 for (int q = 0; q < D / 32; ++q) { vlo[q] &= keep; vhi[q] &= keep; }
             }
             float mx = fmaxf(fmaxf(s4[0], s4[1]), fmaxf(s4[2], s4[3]));
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            mx = hx_max_of_16_lane_groups(mx);
             const float m_new = fmaxf(st.m, mx);
             const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
             float p[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(s4[r] - m_new);
             st.l = st.l * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
-            st.m = m_new;
+            // the accumulators are rescaled only when some maximum moved (else alpha is exactly 1 in every lane)
+            if (__builtin_amdgcn_ballot_w64(m_new != st.m) != 0ull) {
 #pragma unroll
-            for (int nn = 0; nn < D / 16; ++nn) st.o[nn] *= alpha;
+                for (int nn = 0; nn < D / 16; ++nn) st.o[nn] *= alpha;
+            }
+            st.m = m_new;
             // probabilities as a high + low bf16 pair, as in the bf16 kernel
             uint2 ph, pl;
             ph.x = hx_cvt_pk_bf16(p[0], p[1]);

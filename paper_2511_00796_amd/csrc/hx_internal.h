@@ -132,6 +132,16 @@ __device__ __forceinline__ uint32_t hx_cvt_pk_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
+// largest of the four values that lanes l, l ^ 16, l ^ 32, l ^ 48 hold, in all of them: two row swaps between registers
+// (a shuffle through the LDS unit takes about a hundred cycles, twice per tile in the attention kernels)
+__device__ __forceinline__ float hx_max_of_16_lane_groups(float x) {
+    const unsigned int v = __float_as_uint(x);
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    const unsigned int m = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
+    const auto b = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
 // m-groups (of 32 rows) of the packed activation buffers for a batch: rounded up to 1, 2, 4 or 8 so that
 // producers and the matrix products agree on one layout per batch size
 __host__ __device__ __forceinline__ int hx_m_groups(int batch) {
