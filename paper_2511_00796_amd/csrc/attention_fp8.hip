@@ -6,7 +6,7 @@
 // operand is converted to bf16 in registers right before its product -- exactly, every E4M3 value is a bf16 value --
 // and from there on the arithmetic is the bf16 kernel's.  The ring holds the raw bytes (4 tiles of 4 KiB in flight at
 // head size 128: with the converted operands held in registers past their products, a deeper ring costs more in
-// register pressure than it gains; measured 194 us per launch at depth 4, 207 at depth 6, 214 at depth 7).
+// register pressure than it gains; measured 187 us per launch at depth 4, 188 at depth 5, 189 at 6, 207 at 8).
 #include "hx_internal.h"
 
 #define HX_NEG_BIG (-1.0e30f)

@@ -24,7 +24,9 @@ __device__ __forceinline__ float block_sum(float v, float *red) {
 // MODE 1: x += sum_s ypart[s]       (after the output / down projection)
 // MODE 2: x read only               (norm of a caller-supplied row; nothing stored back to x)
 // then u = bf16( x * rsqrt(mean(x^2) + eps) * g ) into the packed buffer xp, or as fp32 into y_f32.
-template <int MODE>
+// MAXS: split partials that are requested (those past `splits` repeat the last one, so a row of one or two partials must not
+// pay for nine: 14B, 4864 rows, two partials 114 -> 102 us = 4.4 TB/s)
+template <int MODE, int MAXS>
 __global__ __launch_bounds__(HX_NORM_THREADS) void norm_kernel(float *__restrict__ x, const float *__restrict__ x_in,
                                                               const int32_t *__restrict__ tokens,
                                                               const uint16_t *__restrict__ embed,
@@ -60,9 +62,9 @@ __global__ __launch_bounds__(HX_NORM_THREADS) void norm_kernel(float *__restrict
                 if (MODE == 1) {
                     // all split partials are requested before the first is used (one memory round trip instead
                     // of one per split); they are added in split order
-                    f32x4_t ya[HX_MAX_SPLITS], yc[HX_MAX_SPLITS];
+                    f32x4_t ya[MAXS], yc[MAXS];
 #pragma unroll
-                    for (int s = 0; s < HX_MAX_SPLITS; ++s) {
+                    for (int s = 0; s < MAXS; ++s) {
                         const float *yp = ypart + min(s, splits - 1) * split_stride + (size_t)b * H + i0;
                         ya[s] = *(const f32x4_t *)yp;
                         yc[s] = *(const f32x4_t *)(yp + 4);
@@ -71,7 +73,7 @@ __global__ __launch_bounds__(HX_NORM_THREADS) void norm_kernel(float *__restrict
 #pragma unroll
                     for (int j = 0; j < 8; ++j) add[j] = 0.f;
 #pragma unroll
-                    for (int s = 0; s < HX_MAX_SPLITS; ++s) {
+                    for (int s = 0; s < MAXS; ++s) {
                         if (s < splits) {
 #pragma unroll
                             for (int j = 0; j < 4; ++j) { add[j] += ya[s][j]; add[4 + j] += yc[s][j]; }
@@ -123,7 +125,7 @@ __global__ __launch_bounds__(HX_NORM_THREADS) void norm_kernel(float *__restrict
 
 int hx_launch_embed_norm(const hx_engine *e, int batch, const int32_t *tokens, size_t gain_off, hipStream_t st, int blocks,
                          size_t block_stride) {
-    hipLaunchKernelGGL((norm_kernel<0>), dim3(batch, blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x),
+    hipLaunchKernelGGL((norm_kernel<0, 1>), dim3(batch, blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x),
                        (const float *)nullptr, tokens, (const uint16_t *)(e->weights + e->embed),
                        (const float *)nullptr, 0, (size_t)0, (const uint16_t *)(e->weights + gain_off), e->cfg.hidden,
                        e->cfg.rms_eps, (uint16_t *)(e->ws + e->map.xp), hx_m_groups(batch), (float *)nullptr, block_stride);
@@ -133,16 +135,22 @@ int hx_launch_embed_norm(const hx_engine *e, int batch, const int32_t *tokens, s
 
 int hx_launch_reduce_norm(const hx_engine *e, int batch, const float *ypart, int splits, size_t split_stride,
                           size_t gain_off, hipStream_t st, int blocks, size_t block_stride) {
-    hipLaunchKernelGGL((norm_kernel<1>), dim3(batch, blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x),
-                       (const float *)nullptr, (const int32_t *)nullptr, (const uint16_t *)nullptr, ypart, splits,
-                       split_stride, (const uint16_t *)(e->weights + gain_off), e->cfg.hidden, e->cfg.rms_eps,
-                       (uint16_t *)(e->ws + e->map.xp), hx_m_groups(batch), (float *)nullptr, block_stride);
+#define HX_REDUCE_NORM(MAXS)                                                                                      \
+    hipLaunchKernelGGL((norm_kernel<1, MAXS>), dim3(batch, blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x), \
+                       (const float *)nullptr, (const int32_t *)nullptr, (const uint16_t *)nullptr, ypart, splits, \
+                       split_stride, (const uint16_t *)(e->weights + gain_off), e->cfg.hidden, e->cfg.rms_eps,    \
+                       (uint16_t *)(e->ws + e->map.xp), hx_m_groups(batch), (float *)nullptr, block_stride)
+    if (splits == 1) HX_REDUCE_NORM(1);
+    else if (splits == 2) HX_REDUCE_NORM(2);
+    else if (splits <= 4) HX_REDUCE_NORM(4);
+    else HX_REDUCE_NORM(HX_MAX_SPLITS);
+#undef HX_REDUCE_NORM
     HX_CHECK_LAUNCH("reduce_norm");
     return HX_OK;
 }
 
 int hx_launch_norm_only(const hx_engine *e, int batch, const float *x, size_t gain_off, float *y, hipStream_t st) {
-    hipLaunchKernelGGL((norm_kernel<2>), dim3(batch), dim3(HX_NORM_THREADS), 0, st, (float *)nullptr, x,
+    hipLaunchKernelGGL((norm_kernel<2, 1>), dim3(batch), dim3(HX_NORM_THREADS), 0, st, (float *)nullptr, x,
                        (const int32_t *)nullptr, (const uint16_t *)nullptr, (const float *)nullptr, 0, (size_t)0,
                        (const uint16_t *)(e->weights + gain_off), e->cfg.hidden, e->cfg.rms_eps, (uint16_t *)nullptr,
                        hx_m_groups(batch), y, (size_t)0);

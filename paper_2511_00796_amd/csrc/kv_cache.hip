@@ -110,11 +110,15 @@ int hx_launch_kv_scatter(const hx_kv *kv, int layer, const void *k, const void *
 // q is written as the packed bf16 B operand of the attention kernel, k and v are rounded to bf16 (or, for an 8-bit
 // cache, from fp32 straight to E4M3) and stored
 // at (block_table[b][pos/16], pos%16); the block id comes from the per-step table written by step_setup_kernel.
-// One thread per work item of 16 values: for q and k heads, 8 consecutive d of the lower half and the 8
-// matching d of the upper half (both ends of the rotation, two 16-byte stores); for v, 16 consecutive d.
-// grid (batch, ceil(items / 128)), 128 threads.  Query rows g >= G of the packed operand are never written:
-// they only feed accumulator columns that nobody reads.
-template <int D, bool FP8>
+// One thread per work item of 8 values, two groups of four: for q and k heads, 4 consecutive d of the lower half and the 4
+// matching d of the upper half (both ends of the rotation); for v, 8 consecutive d.  MAXS: split partials that are
+// requested, all before the first is used, and added in split order; those past `splits` repeat the last one, so a row
+// of one or two partials must not pay for nine.  grid (batch, ceil(items / 128)), 128 threads.  Query rows g >= G of the
+// packed operand are never written: they only feed accumulator columns that nobody reads.
+// What bounds it is the latency of its loads on a decode step (hence all of them at once: 16 values per thread took two
+// rounds) and their number on a prompt call.  us: 1.5B, 64 sequences 6.9 -> 4.9, 7B, 128 sequences 7.1 -> 6.3; one partial,
+// 7B, 2048 rows 25 -> 18, 14B, 4864 rows, 8-bit cache 88 -> 58.
+template <int D, bool FP8, int MAXS>
 __global__ __launch_bounds__(128) void rope_append_kernel(const float *__restrict__ ypart, int splits,
                                                           size_t split_stride, const uint16_t *__restrict__ bias,
                                                           int has_bias, const float *__restrict__ cs,
@@ -124,7 +128,7 @@ __global__ __launch_bounds__(128) void rope_append_kernel(const float *__restric
                                                           uint16_t *__restrict__ qp, int n_q, int n_kv, int G,
                                                           int max_batch, size_t block_stride) {
     constexpr int HALF = D / 2;
-    constexpr int RPH = HALF / 8;                         // rotation items per head
+    constexpr int RPH = HALF / 4;                         // rotation items per head
     const int b = blockIdx.x;
     if (blockIdx.z) {               // further row blocks of a wide prompt call: same layout, block_stride bytes apart
         const size_t off = (size_t)blockIdx.z * block_stride;
@@ -136,92 +140,88 @@ __global__ __launch_bounds__(128) void rope_append_kernel(const float *__restric
     }
     const int item = blockIdx.y * blockDim.x + threadIdx.x;
     const int rot_items = (n_q + n_kv) * RPH;
-    const int v_items = n_kv * (D / 16);
+    const int v_items = n_kv * (D / 8);
     if (item >= rot_items + v_items) return;
     const int qkv_dim = (n_q + 2 * n_kv) * D;
+    const bool rot = item < rot_items;
+    // first of the four columns of each group; the two are HALF apart (rotation) or neighbours (v)
+    const int head = rot ? item / RPH : 0, i0 = rot ? (item % RPH) * 4 : 0;
+    const int vi = item - rot_items;
+    const int col = rot ? head * D + i0 : (n_q + n_kv) * D + vi * 8, gap = rot ? HALF : 4;
+
+    f32x4_t ya[MAXS], yc[MAXS];
+    const float *src = ypart + (size_t)b * qkv_dim + col;
+#pragma unroll
+    for (int sp = 0; sp < MAXS; ++sp) {
+        const float *p = src + min(sp, splits - 1) * split_stride;
+        ya[sp] = *(const f32x4_t *)p;
+        yc[sp] = *(const f32x4_t *)(p + gap);
+    }
+    const f32x4_t cosv = *(const f32x4_t *)(cs + (size_t)b * HALF + i0);
+    const f32x4_t sinv = *(const f32x4_t *)(cs + (size_t)max_batch * HALF + (size_t)b * HALF + i0);
+    uint2 ba = make_uint2(0u, 0u), bc = ba;
+    if (has_bias) { ba = *(const uint2 *)(bias + col); bc = *(const uint2 *)(bias + col + gap); }
     const int pos = positions[b];
     const int32_t blk = blk_new[b];                     // block of position pos, looked up once per step
     const int slot = pos & 15;
 
-    auto gather8 = [&](int col, float *out) {            // sum of the split partials + bias, 8 consecutive columns
-        // every partial is requested before the first is used; they are added in split order
-        f32x4_t ya[HX_MAX_SPLITS], yc[HX_MAX_SPLITS];
+    float lo[4], hi[4];                                  // sum of the split partials + bias
 #pragma unroll
-        for (int sp = 0; sp < HX_MAX_SPLITS; ++sp) {
-            const float *src = ypart + min(sp, splits - 1) * split_stride + (size_t)b * qkv_dim + col;
-            ya[sp] = *(const f32x4_t *)src;
-            yc[sp] = *(const f32x4_t *)(src + 4);
+    for (int j = 0; j < 4; ++j) { lo[j] = 0.f; hi[j] = 0.f; }
+#pragma unroll
+    for (int sp = 0; sp < MAXS; ++sp) {
+        if (sp < splits) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { lo[j] += ya[sp][j]; hi[j] += yc[sp][j]; }
         }
+    }
+    if (has_bias) {
+        const uint16_t *a16 = (const uint16_t *)&ba, *c16 = (const uint16_t *)&bc;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) out[j] = 0.f;
-#pragma unroll
-        for (int sp = 0; sp < HX_MAX_SPLITS; ++sp) {
-            if (sp < splits) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) { out[j] += ya[sp][j]; out[4 + j] += yc[sp][j]; }
-            }
-        }
-        if (has_bias) {
-            const uint4 raw = *(const uint4 *)(bias + col);
-            const uint16_t *b16 = (const uint16_t *)&raw;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) out[j] += hx_bf16_to_f32(b16[j]);
-        }
-    };
-    auto pack8 = [](const float *v) {
-        uint4 pk;
-        pk.x = hx_cvt_pk_bf16(v[0], v[1]); pk.y = hx_cvt_pk_bf16(v[2], v[3]);
-        pk.z = hx_cvt_pk_bf16(v[4], v[5]); pk.w = hx_cvt_pk_bf16(v[6], v[7]);
-        return pk;
-    };
+        for (int j = 0; j < 4; ++j) { lo[j] += hx_bf16_to_f32(a16[j]); hi[j] += hx_bf16_to_f32(c16[j]); }
+    }
+    auto pack4 = [](const float *v) { return make_uint2(hx_cvt_pk_bf16(v[0], v[1]), hx_cvt_pk_bf16(v[2], v[3])); };
 
-    if (item < rot_items) {
-        const int head = item / RPH, i0 = (item % RPH) * 8;
-        float lo[8], hi[8], r0[8], r1[8];
-        gather8(head * D + i0, lo);
-        gather8(head * D + HALF + i0, hi);
-        const float *cosv = cs + (size_t)b * HALF + i0;
-        const float *sinv = cs + (size_t)max_batch * HALF + (size_t)b * HALF + i0;
+    if (rot) {
+        float r[8];                                      // rotated: lower four, upper four
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < 4; ++j) {
             const float c = cosv[j], sn = sinv[j];
-            r0[j] = lo[j] * c - hi[j] * sn;
-            r1[j] = hi[j] * c + lo[j] * sn;
+            r[j] = lo[j] * c - hi[j] * sn;
+            r[4 + j] = hi[j] * c + lo[j] * sn;
         }
+        const int d0 = i0, d1 = i0 + HALF;
         if (head < n_q) {
             const int kvh = head / G, g = head % G;
             uint16_t *dst = qp + ((size_t)b * n_kv + kvh) * (D / 32) * 512;
-            const int d0 = i0, d1 = i0 + HALF;
-            *(uint4 *)(dst + (d0 >> 5) * 512 + ((((d0 >> 3) & 3) * 16 + g) << 3)) = pack8(r0);
-            *(uint4 *)(dst + (d1 >> 5) * 512 + ((((d1 >> 3) & 3) * 16 + g) << 3)) = pack8(r1);
+            *(uint2 *)(dst + (d0 >> 5) * 512 + ((((d0 >> 3) & 3) * 16 + g) << 3) + (d0 & 7)) = pack4(r);
+            *(uint2 *)(dst + (d1 >> 5) * 512 + ((((d1 >> 3) & 3) * 16 + g) << 3) + (d1 & 7)) = pack4(r + 4);
         } else {
             const int kvh = head - n_q;
             char *ktile = pool_layer + (size_t)blk * block_bytes + (size_t)kvh * 2 * tile_bytes;
             if (FP8) {                                     // 8-bit cache: fp32 -> E4M3 directly
-                *(uint2 *)(ktile + hx_ktile8_index(slot, i0)) = hx_pack8_e4m3(r0);
-                *(uint2 *)(ktile + hx_ktile8_index(slot, i0 + HALF)) = hx_pack8_e4m3(r1);
+                const uint2 k8 = hx_pack8_e4m3(r);
+                *(uint32_t *)(ktile + hx_ktile8_index(slot, d0)) = k8.x;
+                *(uint32_t *)(ktile + hx_ktile8_index(slot, d1)) = k8.y;
             } else {
-                *(uint4 *)((uint16_t *)ktile + hx_ktile_index(slot, i0)) = pack8(r0);
-                *(uint4 *)((uint16_t *)ktile + hx_ktile_index(slot, i0 + HALF)) = pack8(r1);
+                *(uint2 *)((uint16_t *)ktile + hx_ktile_index(slot, d0)) = pack4(r);
+                *(uint2 *)((uint16_t *)ktile + hx_ktile_index(slot, d1)) = pack4(r + 4);
             }
         }
     } else {
-        const int vi = item - rot_items;
-        const int kvh = vi / (D / 16), d0 = (vi % (D / 16)) * 16;
+        const int kvh = vi / (D / 8), d0 = (vi % (D / 8)) * 8;
         uint16_t *vtile = (uint16_t *)(pool_layer + (size_t)blk * block_bytes + (size_t)kvh * 2 * tile_bytes + tile_bytes);
         float v[8];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            gather8((n_q + n_kv) * D + kvh * D + d0 + 8 * h, v);
-            if (FP8) {
-                const uint2 vp = hx_pack8_e4m3(v);
-                const uint8_t *vb = (const uint8_t *)&vp;
+        for (int j = 0; j < 4; ++j) { v[j] = lo[j]; v[4 + j] = hi[j]; }
+        if (FP8) {
+            const uint2 vp = hx_pack8_e4m3(v);
+            const uint8_t *vb = (const uint8_t *)&vp;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) ((uint8_t *)vtile)[hx_vtile8_index(slot, d0 + 8 * h + j)] = vb[j];
-            } else {
+            for (int j = 0; j < 8; ++j) ((uint8_t *)vtile)[hx_vtile8_index(slot, d0 + j)] = vb[j];
+        } else {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) vtile[hx_vtile_index(slot, d0 + 8 * h + j)] = hx_f32_to_bf16(v[j]);
-            }
+            for (int j = 0; j < 8; ++j) vtile[hx_vtile_index(slot, d0 + j)] = hx_f32_to_bf16(v[j]);
         }
     }
 }
@@ -234,14 +234,22 @@ int hx_launch_rope_append(const hx_engine *e, const hx_kv *kv, int layer, int ba
     const uint16_t *bias = (const uint16_t *)(e->weights + lm.bqkv);
     const float *cs = (const float *)(e->ws + e->map.cs);
     uint16_t *qp = (uint16_t *)(e->ws + e->map.qp);
-    const int items = (e->cfg.n_q_heads + e->cfg.n_kv_heads) * (e->D / 16) + e->cfg.n_kv_heads * (e->D / 16);
+    const int items = (e->cfg.n_q_heads + e->cfg.n_kv_heads) * (e->D / 8) + e->cfg.n_kv_heads * (e->D / 8);
     dim3 grid(batch, (items + 127) / 128, blocks), block(128);
-#define HX_ROPE_LAUNCH(DD, F8)                                                                                  \
-    hipLaunchKernelGGL((rope_append_kernel<DD, F8>), grid, block, 0, st, ypart, splits, split_stride, bias,    \
+#define HX_ROPE_LAUNCH(DD, F8, MAXS)                                                                            \
+    hipLaunchKernelGGL((rope_append_kernel<DD, F8, MAXS>), grid, block, 0, st, ypart, splits, split_stride, bias, \
                        e->cfg.qkv_bias, cs, positions, (const int32_t *)(e->ws + e->map.blk_new), pool_layer, kv->block_bytes, \
                        kv->tile_bytes, qp, e->cfg.n_q_heads, e->cfg.n_kv_heads, e->G, e->cfg.max_batch, block_stride)
-    if (e->D == 128) { if (kv->fp8) HX_ROPE_LAUNCH(128, true); else HX_ROPE_LAUNCH(128, false); }
-    else             { if (kv->fp8) HX_ROPE_LAUNCH(64, true);  else HX_ROPE_LAUNCH(64, false); }
+#define HX_ROPE_LAUNCH_S(DD, F8)                                                                                \
+    do {                                                                                                        \
+        if (splits == 1) HX_ROPE_LAUNCH(DD, F8, 1);                                                             \
+        else if (splits == 2) HX_ROPE_LAUNCH(DD, F8, 2);                                                        \
+        else if (splits <= 4) HX_ROPE_LAUNCH(DD, F8, 4);                                                        \
+        else HX_ROPE_LAUNCH(DD, F8, HX_MAX_SPLITS);                                                             \
+    } while (0)
+    if (e->D == 128) { if (kv->fp8) HX_ROPE_LAUNCH_S(128, true); else HX_ROPE_LAUNCH_S(128, false); }
+    else             { if (kv->fp8) HX_ROPE_LAUNCH_S(64, true);  else HX_ROPE_LAUNCH_S(64, false); }
+#undef HX_ROPE_LAUNCH_S
 #undef HX_ROPE_LAUNCH
     HX_CHECK_LAUNCH("rope_append");
     return HX_OK;
