@@ -443,11 +443,11 @@ static int run_step(hx_engine *e, hx_kv *kv, int32_t batch, const int32_t *token
     const bool chunked = grouped && batch * e->G <= 16 && c->n_kv_heads <= 4 && max_blocks >= 1000, prompt = grouped && !chunked;
     if (prompt) {
         HX_TIMED(HX_K_SETUP, hx_launch_prompt_setup(e, batch, positions, seq_lens, block_table, max_blocks, st));
+        HX_TIMED(HX_K_NORM, hx_launch_embed_norm(e, batch, tokens, e->layers[0].g1, st));
     } else {
-        HX_TIMED(HX_K_SETUP, hx_launch_step_setup(e, batch, positions, seq_lens, block_table, max_blocks, st));
+        HX_TIMED(HX_K_NORM, hx_launch_step_begin(e, batch, tokens, positions, seq_lens, block_table, max_blocks, e->layers[0].g1, st));
         if (chunked) HX_TIMED(HX_K_SETUP, hx_launch_chunk_setup(e, batch, seq_lens, block_table, max_blocks, st));
     }
-    HX_TIMED(HX_K_NORM, hx_launch_embed_norm(e, batch, tokens, e->layers[0].g1, st));
     for (int l = 0; l < c->n_layers; ++l) {
         const hx_layer_map *lm = &e->layers[l];
         HX_TIMED(HX_K_GEMM_QKV, hx_launch_gemm(e, &lm->wqkv, batch, ws + e->map.xp, HX_EPI_PARTIAL, ypart, nullptr, st));

@@ -20,53 +20,17 @@
 // tile, and the running sum is reduced once at the end.  K/V tiles are stored in operand order
 // in the pool, so they go from HBM to registers with contiguous 1-KiB loads and need no LDS.
 #include "hx_internal.h"
+#include "step_setup.h"
 
 #define HX_NEG_BIG (-1.0e30f)
 
-// ---- per-step setup: schedule + RoPE angles ----------------------------------------------------------------
-// block 0: sched[0] = S (tiles per wavefront), sched[1] = Nt (tiles in all), pre[b] = blocks of the sequences
-// before b (pre[b] = total for b >= batch, HX_PREFIX_LEN entries), lens[b] = seq_lens[b] (0 for b >= batch).
-// blocks 1..batch: cos/sin of pos * theta^(-2i/D), evaluated in double, stored fp32; and the physical block that
-// holds the new position (one look-up per step instead of one per layer in the append kernel).
-__global__ __launch_bounds__(256) void step_setup_kernel(int batch, int n_kv, int n_waves,
-                                                         const int32_t *__restrict__ positions,
-                                                         const int32_t *__restrict__ seq_lens,
-                                                         const int32_t *__restrict__ table, int max_blocks,
-                                                         int32_t *__restrict__ pre, int32_t *__restrict__ lens,
-                                                         int32_t *__restrict__ sched, int32_t *__restrict__ blk_new,
-                                                         float *__restrict__ cs, int half, double theta, int max_batch) {
+// ---- per-step setup: schedule + RoPE angles (step_setup.h) ------------------------------------------------------
+// block 0: the schedule; blocks 1..batch: the rows
+__global__ __launch_bounds__(256) void step_setup_kernel(hx_setup_args a) {
     if (blockIdx.x == 0) {
-        if (seq_lens == nullptr) return;
-        __shared__ int32_t scan[256];
-        const int b = threadIdx.x;
-        const int T = b < batch ? seq_lens[b] : 0;
-        const int cnt = (T + 15) >> 4;
-        scan[b] = cnt;
-        __syncthreads();
-        for (int off = 1; off < 256; off <<= 1) {       // inclusive Hillis-Steele scan
-            int v = (b >= off) ? scan[b - off] : 0;
-            __syncthreads();
-            scan[b] += v;
-            __syncthreads();
-        }
-        const int total = scan[255];
-        pre[b] = scan[b] - cnt;                          // b >= batch: cnt = 0, so pre[b] = total
-        lens[b] = T;
-        for (int i = 256 + b; i < HX_PREFIX_LEN; i += 256) pre[i] = total;
-        if (b == 0) {
-            const long long nt = (long long)total * n_kv;
-            sched[0] = (int)((nt + n_waves - 1) / n_waves);
-            sched[1] = (int)nt;
-        }
-    } else if (positions != nullptr) {
-        int b = blockIdx.x - 1;
-        if (threadIdx.x == 0 && table != nullptr) blk_new[b] = table[(size_t)b * max_blocks + (positions[b] >> 4)];
-        double pos = (double)positions[b];
-        for (int i = threadIdx.x; i < half; i += blockDim.x) {
-            double ang = pos * pow(theta, -(double)i / (double)half);
-            cs[(size_t)b * half + i] = (float)cos(ang);
-            cs[(size_t)max_batch * half + (size_t)b * half + i] = (float)sin(ang);
-        }
+        if (a.seq_lens != nullptr) hx_setup_schedule(a);
+    } else if (a.positions != nullptr) {
+        hx_setup_row(a, blockIdx.x - 1);
     }
 }
 
@@ -77,16 +41,19 @@ hx_attn_bufs hx_attn_bufs_of(const hx_engine *e) {
                         (uint16_t *)(ws + e->map.ap)};
 }
 
+hx_setup_args hx_setup_args_of(const hx_engine *e, int batch, const int32_t *positions, const int32_t *seq_lens, const int32_t *table,
+                               int max_blocks, const hx_attn_bufs &bufs) {
+    return hx_setup_args{batch, e->cfg.n_kv_heads, e->attn_waves, positions, seq_lens, table, max_blocks, bufs.pre, bufs.lens, bufs.sched,
+                         (int32_t *)(e->ws + e->map.blk_new), (float *)(e->ws + e->map.cs), e->D / 2, (double)e->cfg.rope_theta,
+                         e->cfg.max_batch};
+}
+
 int hx_launch_step_setup(const hx_engine *e, int batch, const int32_t *positions, const int32_t *seq_lens,
                          const int32_t *table, int max_blocks, hipStream_t st, const hx_attn_bufs *bufs) {
-    char *ws = e->ws;
-    const hx_attn_bufs own = hx_attn_bufs_of(e);
     if (bufs && positions) return hx_fail(HX_E_RANGE, "the schedule-only set-up takes no positions");
-    const hx_attn_bufs &a = bufs ? *bufs : own;
     // without positions only block 0 runs: the per-row blocks would write the engine's RoPE tables
-    hipLaunchKernelGGL(step_setup_kernel, dim3(positions ? batch + 1 : 1), dim3(256), 0, st, batch, e->cfg.n_kv_heads, e->attn_waves,
-                       positions, seq_lens, table, max_blocks, a.pre, a.lens, a.sched, (int32_t *)(ws + e->map.blk_new),
-                       (float *)(ws + e->map.cs), e->D / 2, (double)e->cfg.rope_theta, e->cfg.max_batch);
+    hipLaunchKernelGGL(step_setup_kernel, dim3(positions ? batch + 1 : 1), dim3(256), 0, st,
+                       hx_setup_args_of(e, batch, positions, seq_lens, table, max_blocks, bufs ? *bufs : hx_attn_bufs_of(e)));
     HX_CHECK_LAUNCH("step_setup");
     return HX_OK;
 }

@@ -2,6 +2,7 @@
 // (which also rounds to bf16 and writes the packed B operand of the next product), and the small
 // pack / unpack helpers used by the single-stage hooks.
 #include "hx_internal.h"
+#include "step_setup.h"
 
 // 512 threads x 8 elements cover a row of up to 4096 in one iteration, i.e. one memory round trip for the residual
 // and all split partials (measured against 256 threads at hidden 3584: 8.3 instead of 8.8 us per launch, timed with events)
@@ -27,22 +28,12 @@ __device__ __forceinline__ float block_sum(float v, float *red) {
 // MAXS: split partials that are requested (those past `splits` repeat the last one, so a row of one or two partials must not
 // pay for nine: 14B, 4864 rows, two partials 114 -> 102 us = 4.4 TB/s)
 template <int MODE, int MAXS>
-__global__ __launch_bounds__(HX_NORM_THREADS) void norm_kernel(float *__restrict__ x, const float *__restrict__ x_in,
-                                                              const int32_t *__restrict__ tokens,
-                                                              const uint16_t *__restrict__ embed,
-                                                              const float *__restrict__ ypart, int splits,
-                                                              size_t split_stride, const uint16_t *__restrict__ gain,
-                                                              int H, float eps, uint16_t *__restrict__ xp, int m_groups,
-                                                              float *__restrict__ y_f32, size_t block_stride) {
+__device__ __forceinline__ void norm_row(int b, float *__restrict__ x, const float *__restrict__ x_in,
+                                         const int32_t *__restrict__ tokens, const uint16_t *__restrict__ embed,
+                                         const float *__restrict__ ypart, int splits, size_t split_stride,
+                                         const uint16_t *__restrict__ gain, int H, float eps, uint16_t *__restrict__ xp, int m_groups,
+                                         float *__restrict__ y_f32) {
     __shared__ float red[8];
-    const int b = blockIdx.x;
-    if (blockIdx.y) {               // further row blocks of a wide prompt call: same layout, block_stride bytes apart
-        const size_t off = (size_t)blockIdx.y * block_stride;
-        x = (float *)((char *)x + off);
-        if (ypart) ypart = (const float *)((const char *)ypart + off);
-        xp = (uint16_t *)((char *)xp + off);
-        if (tokens) tokens += (size_t)blockIdx.y * gridDim.x;
-    }
     float v[HX_NORM_MAX_IT][8];
     float ss = 0.f;
 #pragma unroll
@@ -121,6 +112,48 @@ __global__ __launch_bounds__(HX_NORM_THREADS) void norm_kernel(float *__restrict
             }
         }
     }
+}
+
+template <int MODE, int MAXS>
+__global__ __launch_bounds__(HX_NORM_THREADS) void norm_kernel(float *__restrict__ x, const float *__restrict__ x_in,
+                                                              const int32_t *__restrict__ tokens,
+                                                              const uint16_t *__restrict__ embed,
+                                                              const float *__restrict__ ypart, int splits,
+                                                              size_t split_stride, const uint16_t *__restrict__ gain,
+                                                              int H, float eps, uint16_t *__restrict__ xp, int m_groups,
+                                                              float *__restrict__ y_f32, size_t block_stride) {
+    if (blockIdx.y) {               // further row blocks of a wide prompt call: same layout, block_stride bytes apart
+        const size_t off = (size_t)blockIdx.y * block_stride;
+        x = (float *)((char *)x + off);
+        if (ypart) ypart = (const float *)((const char *)ypart + off);
+        xp = (uint16_t *)((char *)xp + off);
+        if (tokens) tokens += (size_t)blockIdx.y * gridDim.x;
+    }
+    norm_row<MODE, MAXS>(blockIdx.x, x, x_in, tokens, embed, ypart, splits, split_stride, gain, H, eps, xp, m_groups, y_f32);
+}
+
+// The start of a decode step in one launch: the embedding and first norm of the rows (blocks 0..batch-1), their angles and
+// blocks (batch..2 batch-1) and the attention schedule (the last).  Two launches cost a short step 3 us more (tiny model,
+// 4 rows: 86.6 -> 83.6 us a step).
+__global__ __launch_bounds__(HX_NORM_THREADS) void step_begin_kernel(hx_setup_args a, float *__restrict__ x,
+                                                                     const int32_t *__restrict__ tokens,
+                                                                     const uint16_t *__restrict__ embed,
+                                                                     const uint16_t *__restrict__ gain, int H, float eps,
+                                                                     uint16_t *__restrict__ xp, int m_groups) {
+    const int blk = blockIdx.x;
+    if (blk < a.batch) norm_row<0, 1>(blk, x, nullptr, tokens, embed, nullptr, 0, 0, gain, H, eps, xp, m_groups, nullptr);
+    else if (blk < 2 * a.batch) hx_setup_row(a, blk - a.batch);
+    else hx_setup_schedule(a);
+}
+
+int hx_launch_step_begin(const hx_engine *e, int batch, const int32_t *tokens, const int32_t *positions, const int32_t *seq_lens,
+                         const int32_t *table, int max_blocks, size_t gain_off, hipStream_t st) {
+    hipLaunchKernelGGL(step_begin_kernel, dim3(2 * batch + 1), dim3(HX_NORM_THREADS), 0, st,
+                       hx_setup_args_of(e, batch, positions, seq_lens, table, max_blocks, hx_attn_bufs_of(e)), (float *)(e->ws + e->map.x),
+                       tokens, (const uint16_t *)(e->weights + e->embed), (const uint16_t *)(e->weights + gain_off), e->cfg.hidden,
+                       e->cfg.rms_eps, (uint16_t *)(e->ws + e->map.xp), hx_m_groups(batch));
+    HX_CHECK_LAUNCH("step_begin");
+    return HX_OK;
 }
 
 int hx_launch_embed_norm(const hx_engine *e, int batch, const int32_t *tokens, size_t gain_off, hipStream_t st, int blocks,

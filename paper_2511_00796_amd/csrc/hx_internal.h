@@ -351,6 +351,8 @@ int hx_launch_argmax_final(const hx_engine *e, int batch, int32_t *tokens_out, h
 // blocks > 1 (wide prompt calls): the same launch over further 256-row blocks whose workspaces follow at block_stride bytes
 int hx_launch_embed_norm(const hx_engine *e, int batch, const int32_t *tokens, size_t gain_off, hipStream_t st, int blocks = 1,
                          size_t block_stride = 0);
+int hx_launch_step_begin(const hx_engine *e, int batch, const int32_t *tokens, const int32_t *positions, const int32_t *seq_lens,
+                         const int32_t *table, int max_blocks, size_t gain_off, hipStream_t st);   // step_setup + embed_norm
 int hx_launch_reduce_norm(const hx_engine *e, int batch, const float *ypart, int splits, size_t split_stride,
                           size_t gain_off, hipStream_t st, int blocks = 1, size_t block_stride = 0);
 int hx_launch_pack_x(const hx_engine *e, int batch, const float *x, int K, void *xp, hipStream_t st);
