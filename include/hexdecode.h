@@ -278,8 +278,8 @@ int hx_attention_waves(const hx_engine *engine); /* wavefronts of the attention 
      HX_CHUNK_ATTENTION=0   prefill_chunk attends every row on its own (the decode step's kernel) instead of in groups
                             of consecutive rows, read at hx_engine_create; for comparison                            */
 
-/* How a matrix product of n_tiles 32-column tiles and k_steps 16-row steps is launched for `batch` rows (host logic
-   only, no GPU work): tiles per workgroup, k-slices per workgroup, and K-splits whose fp32 partial results the consumer
+/* How the streaming product of n_tiles 32-column tiles and k_steps 16-row steps is launched for `batch` rows (host logic
+   only, no GPU work; it runs batches of up to 128 rows, larger ones go through the workgroup-tiled product of prefill_rows): tiles per workgroup, k-slices per workgroup, and K-splits whose fp32 partial results the consumer
    kernel adds (only if `partial` != 0; products with a fused epilogue are never split).  HX_E_RANGE for sizes < 1 or
    batch > 256, HX_E_NULL for NULL outputs. */
 int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, int32_t partial, int32_t *tiles_per_workgroup_out,

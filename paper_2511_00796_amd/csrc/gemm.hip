@@ -439,12 +439,13 @@ static int launch_shape(int wn, int wk, int epilogue, dim3 grid, hipStream_t st,
 // K-splits (at most HX_MAX_SPLITS, at least 16 k-steps each) -- that minimises the time of the busiest compute
 // unit: rounds x (wn tiles + 3 tile-times for the round's own copy of the activations, which every workgroup
 // draws from the L2 whatever its width) x whole ring revolutions; split products, which run in one round and
-// read only a K-slice of the activations, and 256-row products keep a small charge per extra tile instead (five
+// read only a K-slice of the activations, keep a small charge per extra tile instead (five
 // consumers on four SIMDs); ties go to the smaller wn and fewer splits.
 // Examples: the 1184 tiles of the 7B gate|up matrix make 296 workgroups of 4 (two rounds on 256 compute
 // units) but 237 workgroups of 5 (one round); the 4752 tiles of the LM head make five rounds of 4, four of 5 or
 // two of 10, measured 253 / 244 / 230 us.  Ten tiles per workgroup are twelve wavefronts (three per SIMD): only
-// for products without split partials and up to 128 rows.  HX_GEMM_SHAPE="wn,wk,splits" overrides (tuning).
+// for products without split partials and up to 128 rows (beyond them hx_plan_wide plans, and what hx_plan_product answers
+// for such batches is not used).  HX_GEMM_SHAPE="wn,wk,splits" overrides (tuning).
 
 struct gemm_launch { int wn, wk, splits, tile0, tiles; };
 
