@@ -16,6 +16,7 @@
 #define HX_NUC_THREADS 1024
 #define HX_NUC_BINS 2048
 #define HX_NUC_UNROLL 8
+#define HX_NUC_TILES 4
 #define HX_NUC_SCALE 1099511627776.0f   // 2^40
 
 // ascending key order = descending z; -0 and +0 share a key
@@ -24,22 +25,24 @@ __device__ __forceinline__ uint32_t nucleus_key(float z) {
     return ~(b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u));
 }
 
-// groups q0, q0 + HX_NUC_THREADS, ... of four entries, all requested before the first is used (one group at a time, the
+// group q: entries 4 q .. 4 q + 3 of the row
+__device__ __forceinline__ void load_group(const float *__restrict__ x, int V, int q, bool vec, float (&v)[4]) {
+    const size_t at = 4 * (size_t)q;
+    if (vec) {
+        const f32x4_t t = *(const f32x4_t *)(x + at);
+        v[0] = t[0]; v[1] = t[1]; v[2] = t[2]; v[3] = t[3];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = x[at + i < (size_t)V ? at + i : (size_t)V - 1];
+    }
+}
+// groups q0, q0 + HX_NUC_THREADS, ..., all requested before the first is used (one group at a time, the
 // passes waited for one load after the other: 38 round trips each over a 152 064-entry row); groups past the end repeat
 // the last one and are skipped by the caller
 __device__ __forceinline__ void load_groups(const float *__restrict__ x, int V, int q0, int n_groups, bool vec,
                                             float (&v)[HX_NUC_UNROLL][4]) {
 #pragma unroll
-    for (int u = 0; u < HX_NUC_UNROLL; ++u) {
-        const size_t at = 4 * (size_t)min(q0 + u * HX_NUC_THREADS, n_groups - 1);
-        if (vec) {
-            const f32x4_t t = *(const f32x4_t *)(x + at);
-            v[u][0] = t[0]; v[u][1] = t[1]; v[u][2] = t[2]; v[u][3] = t[3];
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[u][i] = x[at + i < (size_t)V ? at + i : (size_t)V - 1];
-        }
-    }
+    for (int u = 0; u < HX_NUC_UNROLL; ++u) load_group(x, V, min(q0 + u * HX_NUC_THREADS, n_groups - 1), vec, v[u]);
 }
 
 __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
@@ -136,8 +139,11 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
     const unsigned long long mass = sh_mass;      // of all entries with key <= key_tau, i.e. z >= tau
 
     // The draw: largest z_i - log(-log(u_i)) among the kept entries, smaller index on ties.  The LM head has left the best
-    // perturbed score of every 32-column tile: where that entry is kept it is the tile's best kept one, too.  Only the
-    // other tiles (about 1 - top_p of them) are gone through again, by eight lanes each.
+    // perturbed score of every 32-column tile: where that entry is kept it is the tile's best kept one, too.  Of the other
+    // tiles those whose largest z is not kept hold nothing kept; only the rest are gone through again, by eight lanes each,
+    // 32 tiles requested at a time.  Head + draw, us, 151 936 logits (drawing again for every kept entry | all other tiles gone
+    // through, eight at a time | this): one kept entry 163 | 203 | 166 at 1 row, 210 | 230 | 197 at 64; top_p 0.3 of flat
+    // logits 226 | 241 | 226 and 269 | 269 | 259; 0.95: 226 | 199 | 194 and 269 | 224 | 224.
     const uint32_t row = row_ids ? (uint32_t)row_ids[m] : (uint32_t)m;
     const uint32_t pos = (uint32_t)positions[m];
     float best = -INFINITY, best_z = 0.f;
@@ -148,38 +154,42 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
         bool again = false;
         if (t < n_tiles) {
             const size_t o = (size_t)m * n_tiles + t;
-            const float z = cand_z[o];
-            if (nucleus_key(z) <= key_tau) consider(cand_y[o], cand_i[o], z);
-            else again = true;
+            const float z = cand_z[o], y = cand_y[o], zm = tile_zmax[o];
+            const int32_t i = cand_i[o];
+            if (nucleus_key(z) <= key_tau) consider(y, i, z);
+            else again = nucleus_key(zm) <= key_tau;
         }
-        unsigned long long todo = __ballot(again);
-        while (todo) {
-            int mine = -1;                         // lane's tile: the (lane / 8)-th of the next eight
+        const unsigned long long todo = __ballot(again);
+        const int n = __popcll(todo);
+        if (n == 0) continue;
+        // lanes 0..n-1 get the tiles to go through, in order; the other lanes what is left
+        const int rank = __popcll(todo & ((1ull << lane) - 1ull));
+        const int packed = __builtin_amdgcn_ds_permute(4 * (again ? rank : n + lane - rank), t);
+        for (int k0 = 0; k0 < n; k0 += 8 * HX_NUC_TILES) {
+            float v[HX_NUC_TILES][4];
+            int q[HX_NUC_TILES];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                if (todo) {
-                    const int b = __ffsll((long long)todo) - 1;
-                    if ((lane >> 3) == k) mine = t0 + b;
-                    todo &= todo - 1;
-                }
+            for (int u = 0; u < HX_NUC_TILES; ++u) {
+                const int k = k0 + 8 * u + (lane >> 3);
+                const int g = __shfl(packed, min(k, n - 1)) * 8 + (lane & 7);        // a group of four entries
+                q[u] = k < n && g < n_groups ? g : -1;
+                load_group(x, V, min(g, n_groups - 1), vec, v[u]);
             }
-            const int q = mine * 8 + (lane & 7);
-            if (mine >= 0 && q < n_groups) {
-                float v[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = 4 * q + i < V ? x[4 * (size_t)q + i] : -INFINITY;
+            for (int u = 0; u < HX_NUC_TILES; ++u) {
+                if (q[u] < 0) continue;
                 bool keep[4], any = false;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) { keep[i] = 4 * q + i < V && nucleus_key(v[i] * inv_t) <= key_tau; any |= keep[i]; }
+                for (int i = 0; i < 4; ++i) { keep[i] = 4 * q[u] + i < V && nucleus_key(v[u][i] * inv_t) <= key_tau; any |= keep[i]; }
                 if (any) {
                     uint32_t w[4];
-                    hx_philox4x32_10((uint32_t)q, row, pos, 0x53414D50u, key0, key1, w);
+                    hx_philox4x32_10((uint32_t)q[u], row, pos, 0x53414D50u, key0, key1, w);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         if (!keep[i]) continue;
-                        const float z = v[i] * inv_t;
-                        const float u = ((float)(w[i] >> 9) + 0.5f) * (1.0f / 8388608.0f);
-                        consider(z - logf(-logf(u)), 4 * q + i, z);
+                        const float z = v[u][i] * inv_t;
+                        const float un = ((float)(w[i] >> 9) + 0.5f) * (1.0f / 8388608.0f);
+                        consider(z - logf(-logf(un)), 4 * q[u] + i, z);
                     }
                 }
             }

@@ -1,0 +1,33 @@
+"""The draw where its kernels change: kept sets from one entry to nearly all of them (which tiles the nucleus draw goes
+through again), a vocabulary that ends inside a tile.  Reference: the oracle's samplers on the step's own logits."""
+import numpy as np
+import pytest
+import torch
+
+import test_gpu_top_p
+from paper_2511_00796_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hx():
+    from paper_2511_00796_amd import binding
+    binding.load()
+    return binding
+
+
+# 1000 = 31 tiles and 8 columns, 33324 = 1041 and 12: more tiles than the 1024 threads that look at them at once.
+# (temperature, top_p): one kept entry, a few, some in every tile, all but the least likely
+@pytest.mark.parametrize("temperature,top_p", [(0.002, 0.9), (0.02, 0.5), (0.1, 0.3), (1.0, 0.05), (1.0, 0.5), (1.0, 0.9999)])
+@pytest.mark.parametrize("vocab,batch", [(1000, 5), (33324, 64), (70000, 3)])
+def test_kept_sets_of_every_size(hx, vocab, batch, temperature, top_p):
+    s = synth.ModelShape("kept", 1, 256, 4, 2, 64, 688, vocab)
+    eng = hx.Engine(s, batch, 64)
+    g = torch.Generator(device="cuda").manual_seed(13)
+    eng.weights_pack(hx.HX_T_WLM, 0, torch.empty(256, vocab, dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02, generator=g))
+    x = torch.randn(batch, 256, generator=g, device="cuda")
+    pos = torch.arange(100, 100 + batch, dtype=torch.int32, device="cuda")
+    y, tok, lp, n = (t.cpu().numpy() for t in eng.stage_lm_head_top_p(x, pos, temperature, top_p, 31))
+    print("kept %d..%d of %d" % (n.min(), n.max(), vocab))
+    test_gpu_top_p.check_against_oracle(tok, lp, n, y, temperature, top_p, 31, np.arange(batch), pos.cpu().numpy(), "kept")
