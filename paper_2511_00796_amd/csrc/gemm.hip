@@ -23,10 +23,12 @@
 // PHASE 0: tile column c = source column 32 * nt + c; PHASE 1 / 2 (gate / up): columns 0..15 / 16..31 of a tile, from
 // source column 16 * nt + c % 16 (runs of 256 bytes).  What bounds it is memory: see hx_launch_pack_matrix.
 #define HX_PACK_COLS 512
-template <int PHASE, bool ALIGNED>      // ALIGNED: 16-byte loads of the source are possible
+// The source may lie at any element: the 16-byte loads are written as copies from a 2-byte-aligned address (one load
+// instruction, which the hardware takes at any alignment), and only a group of columns that ends past the row goes by elements.
+template <int PHASE>
 __global__ __launch_bounds__(256) void pack_matrix_kernel(const uint16_t *__restrict__ src, int64_t rows, int64_t cols,
                                                           uint4 *__restrict__ dst, int k_steps, int n_tiles) {
-    __shared__ uint4 lds[2048];                         // unit of column c, k-step s, half kh: see unit() below
+    __shared__ uint4 lds[2048];                         // unit of column c, k-step s, half kh: see place() below
     constexpr int TC = PHASE == 0 ? 32 : 16;            // source columns per tile
     const int tid = threadIdx.x, cg = tid & 63, rg = tid >> 6;            // rg = 2 * k-step + half
     const int64_t c0 = (int64_t)blockIdx.x * HX_PACK_COLS, col = c0 + 8 * cg, k0 = (int64_t)blockIdx.y * 32 + 8 * rg;
@@ -34,16 +36,18 @@ __global__ __launch_bounds__(256) void pack_matrix_kernel(const uint16_t *__rest
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
         in[r] = make_uint4(0u, 0u, 0u, 0u);
-        if (k0 + r < rows) {
-            const uint16_t *p = src + (k0 + r) * cols + col;
-            if (ALIGNED) { if (col < cols) in[r] = *(const uint4 *)p; }
-            else {
-                uint16_t e[8];
+        const uint16_t *p = src + (k0 + r) * cols + col;
+        if (k0 + r < rows && col + 8 <= cols) __builtin_memcpy(&in[r], p, 16);
+    }
+    if (col < cols && col + 8 > cols) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) e[j] = col + j < cols ? p[j] : (uint16_t)0;
-                in[r] = make_uint4(e[0] | ((uint32_t)e[1] << 16), e[2] | ((uint32_t)e[3] << 16), e[4] | ((uint32_t)e[5] << 16),
-                                   e[6] | ((uint32_t)e[7] << 16));
-            }
+        for (int r = 0; r < 8; ++r) {
+            const uint16_t *p = src + (k0 + r) * cols + col;
+            uint16_t e[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) e[j] = k0 + r < rows && col + j < cols ? p[j] : (uint16_t)0;
+            in[r] = make_uint4(e[0] | ((uint32_t)e[1] << 16), e[2] | ((uint32_t)e[3] << 16), e[4] | ((uint32_t)e[5] << 16),
+                               e[6] | ((uint32_t)e[7] << 16));
         }
     }
     // units in output order: [tile][k-step][half][column of the tile]; the 8 of a thread are neighbours, so they are spread
@@ -74,18 +78,17 @@ __global__ __launch_bounds__(256) void pack_matrix_kernel(const uint16_t *__rest
 
 // us per matrix, 7B, source read and packed copy written (a thread per 8 k of one column, 64-byte pieces of the source rows,
 // before): gate 53 = 5.1 TB/s (104), QKV 14 (19), down 57 (65), LM head 411 = 5.3 TB/s (531); a device copy moves 4.8-5.3.
+// From a source one element off a 16-byte boundary, same matrix again and again: O 9.7 (16.2; element loads in this kernel
+// 20.7), gate 49 (138; 82), LM head 403 (700; 619), and with 152 068 columns 423 (578; 628).
 int hx_launch_pack_matrix(const hx_engine *e, const hx_matrix *m, const void *src, int64_t rows, int64_t cols,
                           int col_phase, hipStream_t st) {
     const int64_t all = (int64_t)m->n_tiles * (col_phase ? 16 : 32);      // columns of the tiles, zeros beyond `cols` included
     dim3 grid((unsigned)((all + HX_PACK_COLS - 1) / HX_PACK_COLS), (m->k_steps + 1) / 2), block(256);
-    const bool aligned = (uintptr_t)src % 16 == 0 && cols % 8 == 0;
     uint4 *dst = (uint4 *)(e->weights + m->offset);
-#define HX_PACK(P, A) hipLaunchKernelGGL((pack_matrix_kernel<P, A>), grid, block, 0, st, (const uint16_t *)src, rows, cols, dst, m->k_steps, m->n_tiles)
-#define HX_PACK_P(P) do { if (aligned) HX_PACK(P, true); else HX_PACK(P, false); } while (0)
-    if (col_phase == 0) HX_PACK_P(0);
-    else if (col_phase == 1) HX_PACK_P(1);
-    else HX_PACK_P(2);
-#undef HX_PACK_P
+#define HX_PACK(P) hipLaunchKernelGGL((pack_matrix_kernel<P>), grid, block, 0, st, (const uint16_t *)src, rows, cols, dst, m->k_steps, m->n_tiles)
+    if (col_phase == 0) HX_PACK(0);
+    else if (col_phase == 1) HX_PACK(1);
+    else HX_PACK(2);
 #undef HX_PACK
     HX_CHECK_LAUNCH("pack_matrix");
     return HX_OK;

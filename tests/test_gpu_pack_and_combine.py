@@ -1,5 +1,5 @@
-"""Weight packing where its loads change (sources that cannot be read 16 bytes at a time, an odd number of k-steps, column
-counts inside a workgroup's 512), and the attention combine at the number of partials where it changes kernels."""
+"""Weight packing where its loads change (sources off a 16-byte boundary, rows that end inside a group of 8 columns, an odd
+number of k-steps, column counts inside a workgroup's 512), and the attention combine at the number of partials where it changes kernels."""
 import numpy as np
 import pytest
 import torch
