@@ -23,6 +23,7 @@
 //
 // Per-group arrays live where the 256-row workspaces keep their per-row ones: entry g in block g / 256 at g % 256.
 #include "hx_internal.h"
+#include <type_traits>
 
 #define HX_NEG_BIG (-1.0e30f)
 #define HX_PROMPT_COLS 128
@@ -189,36 +190,40 @@ __global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const 
 }
 
 // ---- the attention kernel -----------------------------------------------------------------------------------------------
-// The 32 columns of a wavefront, from its accumulators (register r of block i: d = 32 i + 8 (r / 4) + 4 (lane / 32) + r % 4)
-// for one 32-wide block i of d: bf16 into the packed operand of the output projection, unrounded if asked.
+// The 32 columns of a wavefront, 16 of the 32 d of block i: the values d = 32 i + 8 (q + {0, 1}) + 4 (lane / 32) + 0..3 for one
+// q of 0 and 2, bf16 into the packed operand of the output projection, unrounded if asked.
+template <int D>
+__device__ __forceinline__ void store_pair(const PromptArgs &a, f32x4_t v0, f32x4_t v1, float inv, int row, int head, int i, int q, int lane,
+                                           bool used) {
+    const int h = lane >> 5;
+    v0 *= inv;
+    v1 *= inv;
+    const uint2 p0 = make_uint2(hx_cvt_pk_bf16(v0[0], v0[1]), hx_cvt_pk_bf16(v0[2], v0[3]));
+    const uint2 p1 = make_uint2(hx_cvt_pk_bf16(v1[0], v1[1]), hx_cvt_pk_bf16(v1[2], v1[3]));
+    // the two half-wavefronts hold 4 + 4 of every 8 consecutive d: exchange, so that each stores 8
+    const uint2 give = h ? p0 : p1;
+    uint2 got;
+    got.x = __shfl_xor(give.x, 32);
+    got.y = __shfl_xor(give.y, 32);
+    const uint4 w = h ? make_uint4(got.x, got.y, p1.x, p1.y) : make_uint4(p0.x, p0.y, got.x, got.y);
+    uint16_t *ap = (uint16_t *)(a.ws0 + (size_t)(row >> 8) * a.stride + a.o_ap);
+    if (!used) return;
+    *(uint4 *)(ap + hx_xp_index(row & 255, head * D + 32 * i + 8 * (q + h), a.m_groups)) = w;
+    if (a.attn_f32) {
+        float *dst = a.attn_f32 + ((size_t)row * a.n_q + head) * D + 32 * i + 4 * h + 8 * q;
+        *(f32x4_t *)dst = v0;
+        *(f32x4_t *)(dst + 8) = v1;
+    }
+}
+
+// all of block i from an accumulator (register r: d = 32 i + 8 (r / 4) + 4 (lane / 32) + r % 4)
 template <int D>
 __device__ __forceinline__ void store_block(const PromptArgs &a, const f32x16_t &o, float inv, int row, int head, int i, int lane,
                                             bool used) {
-    const int h = lane >> 5;
-    uint2 pk[4];
-    f32x4_t v[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        v[q] = f32x4_t{o[4 * q] * inv, o[4 * q + 1] * inv, o[4 * q + 2] * inv, o[4 * q + 3] * inv};
-        pk[q].x = hx_cvt_pk_bf16(v[q][0], v[q][1]);
-        pk[q].y = hx_cvt_pk_bf16(v[q][2], v[q][3]);
-    }
-    uint16_t *ap = (uint16_t *)(a.ws0 + (size_t)(row >> 8) * a.stride + a.o_ap);
-#pragma unroll
-    for (int q = 0; q < 4; q += 2) {
-        // the two half-wavefronts hold 4 + 4 of every 8 consecutive d: exchange, so that each stores 8
-        const uint2 give = h ? pk[q] : pk[q + 1];
-        uint2 got;
-        got.x = __shfl_xor(give.x, 32);
-        got.y = __shfl_xor(give.y, 32);
-        const uint4 w = h ? make_uint4(got.x, got.y, pk[q + 1].x, pk[q + 1].y) : make_uint4(pk[q].x, pk[q].y, got.x, got.y);
-        if (used) *(uint4 *)(ap + hx_xp_index(row & 255, head * D + 32 * i + 8 * (q + h), a.m_groups)) = w;
-    }
-    if (a.attn_f32 && used) {
-        float *dst = a.attn_f32 + ((size_t)row * a.n_q + head) * D + 32 * i + 4 * h;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) *(f32x4_t *)(dst + 8 * q) = v[q];
-    }
+    for (int q = 0; q < 4; q += 2)
+        store_pair<D>(a, f32x4_t{o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]},
+                      f32x4_t{o[4 * q + 4], o[4 * q + 5], o[4 * q + 6], o[4 * q + 7]}, inv, row, head, i, q, lane, used);
 }
 
 // group of item `it`: the last g with pre[g] <= it, by two ballots over the up to 32 x 256 entries
@@ -438,11 +443,13 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_kernel(PromptArgs a, const
 }
 
 // ---- combine: the parts of the cut pairs ------------------------------------------------------------------------------
-// Item = (cut group, KV head, 32 columns); one wavefront per 32-wide block of d.  Same lane layout as the partials;
-// parts are merged in order, four requested at a time.
+// Item = (cut group, KV head, 32 columns); two wavefronts per 32-wide block of d, 16 d each.  Same lane layout as the partials;
+// parts are merged in order, four or eight requested at a time, in one pass: what bounds it is the latency of those requests.
+// us per launch (two passes, four parts at a time, 32 d per wavefront, two divisions per part to find its slot): 2 pairs of 117
+// parts (one row over 30 000 tokens, 1.5B) 46 -> 26, 12 pairs of 32 parts 15.1 -> 9.6, 1.5B, 201 rows behind 3000 tokens 9.4 -> 7.2.
 template <int D>
-__global__ __launch_bounds__(64 * (D / 32)) void prompt_combine_kernel(PromptArgs a) {
-    const int lane = threadIdx.x & 63, i = threadIdx.x >> 6, c32 = lane & 31;
+__global__ __launch_bounds__(64 * (D / 16)) void prompt_combine_kernel(PromptArgs a) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = wave >> 1, q = 2 * (wave & 1), c32 = lane & 31;
     const int32_t *sched = (const int32_t *)(a.ws0 + a.o_sched);
     const int S = sched[0], n_items = sched[2] * a.n_kv * 4;
     const int G = a.G;
@@ -452,45 +459,49 @@ __global__ __launch_bounds__(64 * (D / 32)) void prompt_combine_kernel(PromptArg
         const int info = *group_entry<int32_t>(a, a.o_ginfo, gi), T = *group_entry<int32_t>(a, a.o_lens, gi);
         const int first = info & 0xffff, rows = info >> 16;
         if (cb * 32 >= rows * G) continue;
-        const int np = (((T + 31) >> 5) + S - 1) / S;
-        const int slot0 = *group_entry<int32_t>(a, a.o_gslot, gi) + kvh * np;
+        const int np = __builtin_amdgcn_readfirstlane((((T + 31) >> 5) + S - 1) / S);
+        const int slot0 = __builtin_amdgcn_readfirstlane(*group_entry<int32_t>(a, a.o_gslot, gi) + kvh * np);
+        const int blk0 = slot0 / a.slots_per_block, rem0 = slot0 - blk0 * a.slots_per_block;
         const int col = cb * 32 + c32, rl = col / G, gq = col - rl * G;
         const bool used = rl < rows;
-        auto base = [&](int p) { return a.ws0 + (size_t)((slot0 + p) / a.slots_per_block) * a.stride; };
-        auto sub = [&](int p) { return (size_t)((slot0 + p) % a.slots_per_block) * 4 + cb; };
-        float M = HX_NEG_BIG;
-        for (int p = 0; p < np; p += 4) {
-            float v[4];
+        float m = HX_NEG_BIG, den = 0.f;
+        f32x4_t acc[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+        auto merge = [&](int p, auto n) {                // parts p .. p + n - 1; past the last it again, with weight 0
+            constexpr int U = decltype(n)::value;
+            float pm[U], pl[U];
+            f32x4_t v[U][2];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { const int pu = min(p + u, np - 1); v[u] = ((const float *)(base(pu) + a.o_ml))[sub(pu) * 64 + c32]; }
-            M = fmaxf(M, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
-        }
-        f32x16_t acc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-        float den = 0.f;
-        for (int p = 0; p < np; p += 4) {
-            float pm[4], pl[4];
-            f32x4_t v[4][4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int pu = min(p + u, np - 1);
-                const float *ml = (const float *)(base(pu) + a.o_ml) + sub(pu) * 64 + c32;
+            for (int u = 0; u < U; ++u) {
+                int rem = rem0 + min(p + u, np - 1), blk = blk0;
+                if (rem >= a.slots_per_block) { blk += rem / a.slots_per_block; rem %= a.slots_per_block; }      // wave-uniform, rare
+                const char *sb = a.ws0 + (size_t)blk * a.stride;
+                const size_t sub = (size_t)rem * 4 + cb;
+                const float *ml = (const float *)(sb + a.o_ml) + sub * 64 + c32;
                 pm[u] = ml[0];
                 pl[u] = ml[32];
-                const f32x4_t *po = (const f32x4_t *)(base(pu) + a.o_po) + (sub(pu) * (D / 8) + i * 4) * 64 + lane;
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) v[u][r4] = po[r4 * 64];
+                const f32x4_t *po = (const f32x4_t *)(sb + a.o_po) + (sub * (D / 8) + i * 4 + q) * 64 + lane;
+                v[u][0] = po[0];
+                v[u][1] = po[64];
             }
+            float m_new = m;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float wu = p + u < np ? __builtin_amdgcn_exp2f(pm[u] - M) : 0.f;
+            for (int u = 0; u < U; ++u) m_new = fmaxf(m_new, pm[u]);
+            const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+            m = m_new;
+            den *= alpha;
+            acc[0] *= alpha;
+            acc[1] *= alpha;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float wu = p + u < np ? __builtin_amdgcn_exp2f(pm[u] - m) : 0.f;
                 den += wu * pl[u];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[r] += wu * v[u][r >> 2][r & 3];
+                acc[0] += wu * v[u][0];
+                acc[1] += wu * v[u][1];
             }
-        }
-        store_block<D>(a, acc, 1.0f / den, first + (used ? rl : 0), kvh * G + gq, i, lane, used);
+        };
+        if (np <= 4) merge(0, std::integral_constant<int, 4>{});
+        else for (int p = 0; p < np; p += 8) merge(p, std::integral_constant<int, 8>{});
+        store_pair<D>(a, acc[0], acc[1], 1.0f / den, first + (used ? rl : 0), kvh * G + gq, i, q, lane, used);
     }
 }
 
@@ -545,8 +556,8 @@ int hx_launch_prompt_combine(const hx_engine *e, int n_rows, float *attn_f32, hi
     const PromptArgs a = prompt_args(e, n_rows, stride, attn_f32);
     const int items = n_rows * a.n_kv * 4;              // at most; the kernel strides over what there is
     dim3 grid(items < 2048 ? items : 2048);
-    if (e->D == 128) hipLaunchKernelGGL((prompt_combine_kernel<128>), grid, dim3(256), 0, st, a);
-    else             hipLaunchKernelGGL((prompt_combine_kernel<64>), grid, dim3(128), 0, st, a);
+    if (e->D == 128) hipLaunchKernelGGL((prompt_combine_kernel<128>), grid, dim3(512), 0, st, a);
+    else             hipLaunchKernelGGL((prompt_combine_kernel<64>), grid, dim3(256), 0, st, a);
     HX_CHECK_LAUNCH("prompt_combine");
     return HX_OK;
 }
