@@ -237,34 +237,49 @@ __device__ __forceinline__ int find_group(const PromptArgs &a, int it, int lane)
     return __builtin_amdgcn_readfirstlane(seg * 128 + __popcll(__ballot(va <= it)) + __popcll(__ballot(vb <= it)) - 1);
 }
 
+// A group of at most 32 columns (one row of many sequences, the last row or two of a prompt) gives one wavefront something to
+// multiply, and alone that takes it longer over a step of 4 or 8 KiB (1 us) than the memory takes to deliver one.  Where a step
+// is that small (an 8-bit cache, or head size 64) the wavefronts of such a group each take every fourth step, in two LDS stages
+// of their own and without a barrier, and are merged at the end; parts of one or two steps are not worth the merge.  us per
+// 3-layer call, 8-bit cache, 64 rows of 64 sequences behind 8000 tokens (one K/V stream per wavefront with 16-row products, before
+// this kernel | sharing every step | this): 14B 684 | 813 | 679, 7B 475 | 549 | 484, 1.5B 271 | 287 | 254; 256 rows of 256 sequences,
+// 2000 tokens: 886 | 1080 | 935, 656 | 717 | 654, 375 | 371 | 338.  With steps of 16 KiB the sharing of one step is 1-2 % faster.
+template <int D, bool FP8> constexpr int prompt_step_bytes() { return 4 * 16 * D * (FP8 ? 1 : 2); }
+template <int D, bool FP8> constexpr bool prompt_split_steps() { return prompt_step_bytes<D, FP8>() <= 8192; }
+template <int D, bool FP8> constexpr int prompt_lds_bytes() { return (prompt_split_steps<D, FP8>() ? 8 : 3) * prompt_step_bytes<D, FP8>(); }
+
 template <int D, bool FP8>
 __global__ __launch_bounds__(256, 2) void attn_prompt_kernel(PromptArgs a, const char *__restrict__ pool_layer, size_t block_bytes,
                                                              const int32_t *__restrict__ table, int max_blocks, float scale_log2e) {
     constexpr int TILE = 16 * D * (FP8 ? 1 : 2);        // bytes of a K (or V) tile
-    constexpr int STAGE = 4 * TILE;                     // two blocks, K | V each
+    constexpr int STAGE = prompt_step_bytes<D, FP8>();  // two blocks, K | V each
     constexpr int NP = STAGE / 4096;                    // 1-KiB copies per wavefront and step
-    extern __shared__ char lds[];                       // [3][STAGE]
+    extern __shared__ char lds[];                       // [3][STAGE]; where the wavefronts take steps of their own [2][4][STAGE]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = lane >> 5, c32 = lane & 31;
     const int32_t *sched = (const int32_t *)(a.ws0 + a.o_sched);
-    const int S = sched[0], n_items = sched[1];
+    const int S = __builtin_amdgcn_readfirstlane(sched[0]), n_items = __builtin_amdgcn_readfirstlane(sched[1]);
     const int G = a.G, n_kv = a.n_kv;
-    const int col = wave * 32 + c32, rl = col / G, gq = col - rl * G;
+    // (row of the group, query head) of this lane's column: among its wavefront's 32, or among the 32 all of them share
+    const int rl_w = (wave * 32 + c32) / G, gq_w = wave * 32 + c32 - rl_w * G, rl_n = c32 / G, gq_n = c32 - rl_n * G;
     // this wavefront's part of a step: half a block (K or V) at most
     constexpr int PER_TILE = TILE / 1024;               // copies per tile: 4, 2 or 1
     for (int w = blockIdx.x; w < n_items; w += gridDim.x) {
         const int it = n_items - 1 - w;
         const int gi = find_group(a, it, lane);
-        const int info = *group_entry<int32_t>(a, a.o_ginfo, gi), T = *group_entry<int32_t>(a, a.o_lens, gi);
+        const int info = __builtin_amdgcn_readfirstlane(*group_entry<int32_t>(a, a.o_ginfo, gi));
+        const int T = __builtin_amdgcn_readfirstlane(*group_entry<int32_t>(a, a.o_lens, gi));
         const int first = info & 0xffff, rows = info >> 16;
         const int steps = (T + 31) >> 5, np = (steps + S - 1) / S, nblk = (T + 15) >> 4;
-        const int local = it - *group_entry<int32_t>(a, a.o_pre, gi);
+        const int local = it - __builtin_amdgcn_readfirstlane(*group_entry<int32_t>(a, a.o_pre, gi));
         const int kvh = local / np, part = local - kvh * np;
-        const int s0 = (int)((long long)part * steps / np), s1 = (int)((long long)(part + 1) * steps / np);
+        const int s0 = part * steps / np, s1 = (part + 1) * steps / np;          // steps <= 2^15: no overflow
         const size_t head_off = (size_t)kvh * 2 * TILE;
         const int32_t *trow = table + (size_t)(first + rows - 1) * max_blocks;   // the group reads through its last row
+        const bool narrow = prompt_split_steps<D, FP8>() && rows * G <= 32 && steps > 2 * np;   // the same for the whole workgroup
+        const int rl = narrow ? rl_n : rl_w, gq = narrow ? gq_n : gq_w;
         const bool used = rl < rows;
-        const bool wave_used = wave * 32 < rows * G;    // wave-uniform
+        const bool wave_used = narrow || wave * 32 < rows * G;  // wave-uniform
         // A group of at most 32 columns only streams: with a second step in flight it is 1-2 % slower (64 rows of 64 sequences,
         // 8000 tokens, 7B, us per 3-layer call: 649 | 660).
         const bool two_ahead = rows * G > 32;
@@ -294,163 +309,226 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_kernel(PromptArgs a, const
         // Waited for here and at the reload: at a use behind copies the wait for it would be one for all of them, every step (so it
         // was: 1.5B, 201 rows behind 3000 tokens 243 us per 3-layer call instead of 229).
         asm volatile("" : "+v"(ids));
-        auto request = [&](int s, int stage) {          // copies step s into a stage; blocks past the last repeat it
-            if (2 * s - id0 >= 64) {
+        auto request = [&](int s, int stage, int p0) {  // copies NP pieces of step s, from p0 on, into a stage; blocks past the
+            if (2 * s - id0 >= 64) {                    // last repeat it
                 id0 += 64;
                 ids = trow[min(id0 + lane, nblk - 1)];
                 asm volatile("" : "+v"(ids));
             }
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
-                const int piece = wave * NP + p, blk = piece / (2 * PER_TILE);
+                const int piece = p0 + p, blk = piece / (2 * PER_TILE);
                 const int32_t id = __builtin_amdgcn_readlane(ids, 2 * s + blk - id0);
-                hx_copy_to_lds(pool_layer + (size_t)id * block_bytes + head_off + (size_t)(piece % (2 * PER_TILE)) * 1024,
-                               lane * 16, stage * STAGE + piece * 1024);
+                const uint64_t src = (uint64_t)(pool_layer + (size_t)id * block_bytes + head_off + (size_t)(piece % (2 * PER_TILE)) * 1024);
+                const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)src), hi = __builtin_amdgcn_readfirstlane((uint32_t)(src >> 32));
+                hx_copy_to_lds((const void *)(((uint64_t)hi << 32) | lo), lane * 16, stage * STAGE + piece * 1024);
             }
+        };
+        auto request_all = [&](int s, int stage) {      // a step of this wavefront's own
+#pragma unroll 1
+            for (int q = 0; q < 4; ++q) request(s, stage, q * NP);
         };
         // everybody has left the stages of the item before
         __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT(0));
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        request(s0, 0);
-        if (s0 + 1 < s1) request(s0 + 1, 1);
-        int stage = 0;
-        for (int s = s0; s < s1; ++s) {
-            if (s + 1 < s1 && two_ahead) __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT(NP));
-            else __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT(0));
-            __builtin_amdgcn_s_barrier();               // step s is in its stage; the stage of step s - 1 is free
-            asm volatile("" ::: "memory");
-            if (s + 2 < s1) request(s + 2, stage >= 1 ? stage - 1 : 2);
-            if (wave_used) {
-                const char *st = lds + stage * STAGE;
-                const int t0 = s * 32;
-                // ---- scores of 32 tokens x 32 columns
-                f32x16_t sc;
+        auto attend = [&](int s, const char *st) {      // multiplies step s, which lies at st
+            const int t0 = s * 32;
+            // ---- scores of 32 tokens x 32 columns
+            f32x16_t sc;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) sc[r] = 0.f;
-                const char *kb = st + (c32 >> 4) * 2 * TILE + (h * 16 + (c32 & 15)) * 16;
-                constexpr int NK = FP8 ? D / 32 : D / 16;   // 16-byte reads of K, all requested before the first product
-                u32x4_t kr[NK];
+            for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+            const char *kb = st + (c32 >> 4) * 2 * TILE + (h * 16 + (c32 & 15)) * 16;
+            constexpr int NK = FP8 ? D / 32 : D / 16;   // 16-byte reads of K, all requested before the first product
+            u32x4_t kr[NK];
 #pragma unroll
-                for (int k = 0; k < NK; ++k) kr[k] = *(const u32x4_t *)(kb + (k >> 1) * 1024 + (k & 1) * 512);
-                __builtin_amdgcn_sched_barrier(0);
-                if (!FP8) {
+            for (int k = 0; k < NK; ++k) kr[k] = *(const u32x4_t *)(kb + (k >> 1) * 1024 + (k & 1) * 512);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!FP8) {
 #pragma unroll
-                    for (int k = 0; k < D / 16; ++k)
-                        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kr[k]), __builtin_bit_cast(bf16x8_t, q[k]), sc, 0, 0, 0);
-                } else {
-                    // 16 bytes hold the operand bytes of steps k and k + 2
+                for (int k = 0; k < D / 16; ++k)
+                    sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kr[k]), __builtin_bit_cast(bf16x8_t, q[k]), sc, 0, 0, 0);
+            } else {
+                // 16 bytes hold the operand bytes of steps k and k + 2
 #pragma unroll
-                    for (int kp = 0; kp < D / 32; ++kp) {
-                        const int k = (kp >> 1) * 4 + (kp & 1);
-                        const u32x4_t raw = kr[kp];
-                        const uint2 a0 = hx_e4m3x4_to_bf16x4(raw.x), a1 = hx_e4m3x4_to_bf16x4(raw.y);
-                        const uint2 b0 = hx_e4m3x4_to_bf16x4(raw.z), b1 = hx_e4m3x4_to_bf16x4(raw.w);
-                        const u32x4_t ka = {a0.x, a0.y, a1.x, a1.y}, kc = {b0.x, b0.y, b1.x, b1.y};
-                        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ka), __builtin_bit_cast(bf16x8_t, q[k]), sc, 0, 0, 0);
-                        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kc), __builtin_bit_cast(bf16x8_t, q[k + 2]), sc, 0, 0, 0);
-                    }
-                }
-                // ---- softmax; register r is token t0 + 8 (r / 4) + 4 h + r % 4
-                float p[16];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) p[r] = sc[r];
-                if (t0 + 32 > t_first) {                // wave-uniform: some column ends inside these tokens
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        if (t0 + 8 * (r >> 2) + 4 * h + (r & 3) >= tcol) p[r] = -INFINITY;
-                }
-                float mx = p[0];
-#pragma unroll
-                for (int r = 1; r < 16; ++r) mx = fmaxf(mx, p[r]);
-                mx = fmaxf(mx, __shfl_xor(mx, 32));
-                const float m_new = fmaxf(m, mx * scale_log2e);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(p[r], scale_log2e, -m_new));
-                float sum = 0.f;
-#pragma unroll
-                for (int r = 0; r < 16; r += 4) sum += (p[r] + p[r + 1]) + (p[r + 2] + p[r + 3]);
-                if (__builtin_amdgcn_ballot_w64(m_new != m) != 0ull) {     // rescale only when some maximum moved
-                    const float alpha = __builtin_amdgcn_exp2f(m - m_new);
-                    l *= alpha;
-#pragma unroll
-                    for (int i = 0; i < D / 32; ++i) o[i] *= alpha;
-                    m = m_new;
-                }
-                l += sum;
-                uint32_t ph[8], pl[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    ph[j] = hx_cvt_pk_bf16(p[2 * j], p[2 * j + 1]);
-                    pl[j] = hx_cvt_pk_bf16(p[2 * j] - __uint_as_float(ph[j] << 16), p[2 * j + 1] - __uint_as_float(ph[j] & 0xffff0000u));
-                }
-                // ---- O^T += V^T P^T, one block of 16 tokens after the other: contraction slots 0..3 of a lane are tokens
-                // 4 h + 0..3 of the block, slots 4..7 tokens 8 + 4 h + 0..3
-                const bool ragged = t0 + 32 > T;        // wave-uniform: V of positions that do not exist may hold anything
-#pragma unroll
-                for (int blk = 0; blk < 2; ++blk) {
-                    const char *vb = st + (2 * blk + 1) * TILE;
-                    u32x4_t v[D / 32];
-                    if (!FP8) {
-                        const char *vl = vb + (h * 16 + (c32 & 15)) * 16 + (c32 >> 4) * 8;
-#pragma unroll
-                        for (int i = 0; i < D / 32; ++i) {
-                            const u32x2_t x = *(const u32x2_t *)(vl + i * 1024), y = *(const u32x2_t *)(vl + i * 1024 + 512);
-                            v[i] = u32x4_t{x.x, x.y, y.x, y.y};
-                        }
-                    } else {
-                        // 16 bytes: 4 tokens of d = c32 % 16 of four 16-wide d ranges
-                        const char *vl = vb + (h * 16 + (c32 & 15)) * 16;
-#pragma unroll
-                        for (int ip = 0; ip < D / 64; ++ip) {
-                            const u32x4_t x = *(const u32x4_t *)(vl + ip * 1024), y = *(const u32x4_t *)(vl + ip * 1024 + 512);
-                            const bool up = (c32 >> 4) != 0;
-                            const uint2 x0 = hx_e4m3x4_to_bf16x4(up ? x.y : x.x), y0 = hx_e4m3x4_to_bf16x4(up ? y.y : y.x);
-                            const uint2 x1 = hx_e4m3x4_to_bf16x4(up ? x.w : x.z), y1 = hx_e4m3x4_to_bf16x4(up ? y.w : y.z);
-                            v[2 * ip] = u32x4_t{x0.x, x0.y, y0.x, y0.y};
-                            v[2 * ip + 1] = u32x4_t{x1.x, x1.y, y1.x, y1.y};
-                        }
-                    }
-                    if (ragged) {
-#pragma unroll
-                        for (int e = 0; e < 2; ++e) {
-                            const int valid = T - (t0 + 16 * blk + 8 * e + 4 * h);
-                            const uint32_t m01 = valid >= 2 ? 0xffffffffu : (valid == 1 ? 0x0000ffffu : 0u);
-                            const uint32_t m23 = valid >= 4 ? 0xffffffffu : (valid == 3 ? 0x0000ffffu : 0u);
-#pragma unroll
-                            for (int i = 0; i < D / 32; ++i) { v[i][2 * e] &= m01; v[i][2 * e + 1] &= m23; }
-                        }
-                    }
-                    const u32x4_t hi = {ph[4 * blk], ph[4 * blk + 1], ph[4 * blk + 2], ph[4 * blk + 3]};
-                    const u32x4_t lo = {pl[4 * blk], pl[4 * blk + 1], pl[4 * blk + 2], pl[4 * blk + 3]};
-#pragma unroll
-                    for (int i = 0; i < D / 32; ++i)
-                        o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v[i]), __builtin_bit_cast(bf16x8_t, hi), o[i], 0, 0, 0);
-#pragma unroll
-                    for (int i = 0; i < D / 32; ++i)
-                        o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v[i]), __builtin_bit_cast(bf16x8_t, lo), o[i], 0, 0, 0);
+                for (int kp = 0; kp < D / 32; ++kp) {
+                    const int k = (kp >> 1) * 4 + (kp & 1);
+                    const u32x4_t raw = kr[kp];
+                    const uint2 a0 = hx_e4m3x4_to_bf16x4(raw.x), a1 = hx_e4m3x4_to_bf16x4(raw.y);
+                    const uint2 b0 = hx_e4m3x4_to_bf16x4(raw.z), b1 = hx_e4m3x4_to_bf16x4(raw.w);
+                    const u32x4_t ka = {a0.x, a0.y, a1.x, a1.y}, kc = {b0.x, b0.y, b1.x, b1.y};
+                    sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ka), __builtin_bit_cast(bf16x8_t, q[k]), sc, 0, 0, 0);
+                    sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kc), __builtin_bit_cast(bf16x8_t, q[k + 2]), sc, 0, 0, 0);
                 }
             }
-            stage = stage == 2 ? 0 : stage + 1;
+            // ---- softmax; register r is token t0 + 8 (r / 4) + 4 h + r % 4
+            float p[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) p[r] = sc[r];
+            if (t0 + 32 > t_first) {                // wave-uniform: some column ends inside these tokens
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (t0 + 8 * (r >> 2) + 4 * h + (r & 3) >= tcol) p[r] = -INFINITY;
+            }
+            float mx = p[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, p[r]);
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m, mx * scale_log2e);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(p[r], scale_log2e, -m_new));
+            float sum = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; r += 4) sum += (p[r] + p[r + 1]) + (p[r + 2] + p[r + 3]);
+            if (__builtin_amdgcn_ballot_w64(m_new != m) != 0ull) {     // rescale only when some maximum moved
+                const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+                l *= alpha;
+#pragma unroll
+                for (int i = 0; i < D / 32; ++i) o[i] *= alpha;
+                m = m_new;
+            }
+            l += sum;
+            uint32_t ph[8], pl[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                ph[j] = hx_cvt_pk_bf16(p[2 * j], p[2 * j + 1]);
+                pl[j] = hx_cvt_pk_bf16(p[2 * j] - __uint_as_float(ph[j] << 16), p[2 * j + 1] - __uint_as_float(ph[j] & 0xffff0000u));
+            }
+            // ---- O^T += V^T P^T, one block of 16 tokens after the other: contraction slots 0..3 of a lane are tokens
+            // 4 h + 0..3 of the block, slots 4..7 tokens 8 + 4 h + 0..3
+            const bool ragged = t0 + 32 > T;        // wave-uniform: V of positions that do not exist may hold anything
+#pragma unroll
+            for (int blk = 0; blk < 2; ++blk) {
+                const char *vb = st + (2 * blk + 1) * TILE;
+                u32x4_t v[D / 32];
+                if (!FP8) {
+                    const char *vl = vb + (h * 16 + (c32 & 15)) * 16 + (c32 >> 4) * 8;
+#pragma unroll
+                    for (int i = 0; i < D / 32; ++i) {
+                        const u32x2_t x = *(const u32x2_t *)(vl + i * 1024), y = *(const u32x2_t *)(vl + i * 1024 + 512);
+                        v[i] = u32x4_t{x.x, x.y, y.x, y.y};
+                    }
+                } else {
+                    // 16 bytes: 4 tokens of d = c32 % 16 of four 16-wide d ranges
+                    const char *vl = vb + (h * 16 + (c32 & 15)) * 16;
+#pragma unroll
+                    for (int ip = 0; ip < D / 64; ++ip) {
+                        const u32x4_t x = *(const u32x4_t *)(vl + ip * 1024), y = *(const u32x4_t *)(vl + ip * 1024 + 512);
+                        const bool up = (c32 >> 4) != 0;
+                        const uint2 x0 = hx_e4m3x4_to_bf16x4(up ? x.y : x.x), y0 = hx_e4m3x4_to_bf16x4(up ? y.y : y.x);
+                        const uint2 x1 = hx_e4m3x4_to_bf16x4(up ? x.w : x.z), y1 = hx_e4m3x4_to_bf16x4(up ? y.w : y.z);
+                        v[2 * ip] = u32x4_t{x0.x, x0.y, y0.x, y0.y};
+                        v[2 * ip + 1] = u32x4_t{x1.x, x1.y, y1.x, y1.y};
+                    }
+                }
+                if (ragged) {
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const int valid = T - (t0 + 16 * blk + 8 * e + 4 * h);
+                        const uint32_t m01 = valid >= 2 ? 0xffffffffu : (valid == 1 ? 0x0000ffffu : 0u);
+                        const uint32_t m23 = valid >= 4 ? 0xffffffffu : (valid == 3 ? 0x0000ffffu : 0u);
+#pragma unroll
+                        for (int i = 0; i < D / 32; ++i) { v[i][2 * e] &= m01; v[i][2 * e + 1] &= m23; }
+                    }
+                }
+                const u32x4_t hi = {ph[4 * blk], ph[4 * blk + 1], ph[4 * blk + 2], ph[4 * blk + 3]};
+                const u32x4_t lo = {pl[4 * blk], pl[4 * blk + 1], pl[4 * blk + 2], pl[4 * blk + 3]};
+#pragma unroll
+                for (int i = 0; i < D / 32; ++i)
+                    o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v[i]), __builtin_bit_cast(bf16x8_t, hi), o[i], 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < D / 32; ++i)
+                    o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v[i]), __builtin_bit_cast(bf16x8_t, lo), o[i], 0, 0, 0);
+            }
+        };
+        if (narrow) {                                   // every wavefront for itself, in stages of its own: no barrier
+            if (s0 + wave < s1) {
+                int stage = wave;
+                request_all(s0 + wave, stage);
+                for (int s = s0 + wave; s < s1; s += 4) {
+                    const int next = stage ^ 4;
+                    __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT(0));
+                    asm volatile("" ::: "memory");
+                    if (s + 4 < s1) request_all(s + 4, next);
+                    attend(s, lds + stage * STAGE);
+                    stage = next;
+                }
+            }
+        } else {
+            request(s0, 0, wave * NP);
+            if (s0 + 1 < s1) request(s0 + 1, 1, wave * NP);
+            int stage = 0;
+            for (int s = s0; s < s1; ++s) {
+                if (s + 1 < s1 && two_ahead) __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT(NP));
+                else __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT(0));
+                __builtin_amdgcn_s_barrier();           // step s is in its stage; the stage of step s - 1 is free
+                asm volatile("" ::: "memory");
+                if (s + 2 < s1) request(s + 2, stage >= 1 ? stage - 1 : 2, wave * NP);
+                if (wave_used) attend(s, lds + stage * STAGE);
+                stage = stage == 2 ? 0 : stage + 1;
+            }
         }
         if (!wave_used) continue;
         l += __shfl_xor(l, 32);
-        if (np == 1) {
-            const float inv = 1.0f / l;
+        if (narrow) {
+            // merge the wavefronts' results in their order; wavefront i ends up with block i of d
+            float *red = (float *)lds;
+            __builtin_amdgcn_s_barrier();               // nobody reads a stage any more
+            asm volatile("" ::: "memory");
+            red[wave * 64 + lane] = h ? l : m;
+            __syncthreads();
+            float mw[4], lw[4];
 #pragma unroll
-            for (int i = 0; i < D / 32; ++i) store_block<D>(a, o[i], inv, row, kvh * G + gq, i, lane, used);
-        } else {
-            // partial result in register order: [slot][wavefront][d block, 4 registers][lane], and [max 32 | sum 32]
-            const int slot = *group_entry<int32_t>(a, a.o_gslot, gi) + local;
-            char *sb = a.ws0 + (size_t)(slot / a.slots_per_block) * a.stride;
-            const size_t sub = (size_t)(slot % a.slots_per_block) * 4 + wave;
-            ((float *)(sb + a.o_ml))[sub * 64 + lane] = h ? l : m;
-            f32x4_t *po = (f32x4_t *)(sb + a.o_po) + sub * (D / 8) * 64 + lane;
+            for (int j = 0; j < 4; ++j) { mw[j] = red[j * 64 + c32]; lw[j] = red[j * 64 + 32 + c32]; }
+            __syncthreads();
+            f32x4_t *ro = (f32x4_t *)lds + lane;
 #pragma unroll
             for (int i = 0; i < D / 32; ++i)
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4)
+                    ro[((wave * (D / 32) + i) * 4 + r4) * 64] = f32x4_t{o[i][4 * r4], o[i][4 * r4 + 1], o[i][4 * r4 + 2], o[i][4 * r4 + 3]};
+            __syncthreads();
+            m = mw[0];
+#pragma unroll
+            for (int j = 1; j < 4; ++j) m = fmaxf(m, mw[j]);
+            l = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[0][r] = 0.f;
+            if (wave >= D / 32) continue;               // the barrier before the next item's copies holds the others back
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float wj = __builtin_amdgcn_exp2f(mw[j] - m);
+                l += wj * lw[j];
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const f32x4_t x = ro[((j * (D / 32) + wave) * 4 + r4) * 64];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) o[0][4 * r4 + r] += wj * x[r];
+                }
+            }
+        }
+        if (np == 1) {
+            const float inv = 1.0f / l;
+            if (narrow) store_block<D>(a, o[0], inv, row, kvh * G + gq, wave, lane, used);
+            else {
+#pragma unroll
+                for (int i = 0; i < D / 32; ++i) store_block<D>(a, o[i], inv, row, kvh * G + gq, i, lane, used);
+            }
+        } else {
+            // partial result in register order: [slot][32 columns][d block, 4 registers][lane], and [max 32 | sum 32]
+            const int slot = *group_entry<int32_t>(a, a.o_gslot, gi) + local;
+            char *sb = a.ws0 + (size_t)(slot / a.slots_per_block) * a.stride;
+            const size_t sub = (size_t)(slot % a.slots_per_block) * 4 + (narrow ? 0 : wave);
+            if (!narrow || wave == 0) ((float *)(sb + a.o_ml))[sub * 64 + lane] = h ? l : m;
+            f32x4_t *po = (f32x4_t *)(sb + a.o_po) + sub * (D / 8) * 64 + lane;
+            if (narrow) po += wave * 4 * 64;
+#pragma unroll
+            for (int i = 0; i < D / 32; ++i) {
+                if (narrow && i > 0) break;
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4)
                     po[(i * 4 + r4) * 64] = f32x4_t{o[i][4 * r4], o[i][4 * r4 + 1], o[i][4 * r4 + 2], o[i][4 * r4 + 3]};
+            }
         }
     }
 }
@@ -555,9 +633,8 @@ int hx_launch_prompt_attention(const hx_engine *e, const hx_kv *kv, int layer, i
     const char *pool_layer = kv->pool + (size_t)layer * kv->layer_bytes;
     const float scale_log2e = (float)(1.4426950408889634 / sqrt((double)e->D));
     dim3 grid(e->attn_waves / 4), block(256);           // two workgroups of four wavefronts per compute unit
-    const size_t lds = 12 * kv->tile_bytes;             // three stages of two blocks
 #define HX_PROMPT_LAUNCH(DD, F8) \
-    hipLaunchKernelGGL((attn_prompt_kernel<DD, F8>), grid, block, lds, st, a, pool_layer, kv->block_bytes, table, max_blocks, scale_log2e)
+    hipLaunchKernelGGL((attn_prompt_kernel<DD, F8>), grid, block, (prompt_lds_bytes<DD, F8>()), st, a, pool_layer, kv->block_bytes, table, max_blocks, scale_log2e)
     if (e->D == 128) { if (kv->fp8) HX_PROMPT_LAUNCH(128, true); else HX_PROMPT_LAUNCH(128, false); }
     else             { if (kv->fp8) HX_PROMPT_LAUNCH(64, true);  else HX_PROMPT_LAUNCH(64, false); }
 #undef HX_PROMPT_LAUNCH

@@ -58,7 +58,7 @@ def layer0_attention(hx, s, plan, kv_dtype, waves, monkeypatch, seed=31):
 
 # (heads, KV heads, head size, plan of (keys cached, rows)).  Up to 16 columns over 1000 blocks or more take the kernel
 # with a stream per wavefront; 128 / G rows are one group, 32 columns a wavefront; 32 tokens are a step, 8 steps the
-# shortest part.
+# shortest part.  In groups of at most 32 columns the wavefronts may take steps of their own.
 CASES = {
     "16-columns-1000-blocks": (16, 2, 128, [(15990, 2)]),
     "16-columns-999-blocks": (16, 2, 128, [(15982, 2)]),
@@ -69,6 +69,9 @@ CASES = {
     "one-step": (8, 2, 64, [(0, 32)]),
     "one-token-beyond": (8, 2, 64, [(0, 33)]),
     "cut-at-the-last-token": (4, 2, 128, [(3040, 33), (15, 31)]),
+    "narrow-3-to-9-steps": (8, 1, 128, [(70, 1), (97, 1), (128, 2), (160, 1), (290, 4), (290, 5), (0, 2)]),
+    "narrow-32-and-33-columns": (11, 1, 64, [(300, 3), (301, 2), (95, 2), (64, 3)]),
+    "narrow-long-and-cut": (16, 2, 128, [(9000, 1), (777, 2), (8191, 2), (40, 1)]),
     "all-single": (4, 4, 64, [(40 * i + i % 17, 1) for i in range(40)]),
     "across-workspaces": (6, 2, 128, [(0, 250), (1500, 13), (3, 500), (33, 5)]),
     "across-workspaces-64": (16, 1, 64, [(900, 255), (0, 2), (64, 511)]),
