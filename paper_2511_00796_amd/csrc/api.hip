@@ -142,11 +142,11 @@ static size_t map_workspace(hx_engine *e) {
     const size_t slots = (size_t)e->attn_waves + B * c->n_kv_heads;
     m->part_ml = take(slots * 32 * 4);
     m->part_o = take(slots * e->G * e->D * 4);
-    m->chunk_cont = take(256 * 4);
-    m->chunk_ginfo = take(256 * 4);
-    m->chunk_rgrp = take(256 * 4);
-    m->chunk_part_ml = take(slots * 4 * 32 * 4);
-    m->chunk_part_o = take(slots * 4 * 16 * e->D * 4);
+    m->prompt_cont = take(256 * 4);
+    m->prompt_ginfo = take(256 * 4);
+    m->prompt_gslot = take(256 * 4);
+    m->prompt_part_ml = take(slots * 4 * 32 * 4);
+    m->prompt_part_o = take(slots * 4 * 16 * e->D * 4);
     m->amax_val = take(B * e->wlm.n_tiles * 4);
     m->amax_idx = take(B * e->wlm.n_tiles * 4);
     m->samp_z = take(B * e->wlm.n_tiles * 4);
@@ -172,7 +172,6 @@ static int init_engine_shape(hx_engine *e, const hx_model_config *cfg) {
     // HX_CHUNK_ATTENTION=0: prompt rows go through the decode step's attention, one K/V stream per row (comparison)
     const char *ca = getenv("HX_CHUNK_ATTENTION");
     e->chunk_attention = !(ca && atoi(ca) == 0);
-    e->chunk_rows = 64 / e->G < HX_CHUNK_ROWS ? 64 / e->G : HX_CHUNK_ROWS;     // G <= 16: at least 4 rows
     return HX_OK;
 }
 
@@ -434,19 +433,12 @@ static int run_step(hx_engine *e, hx_kv *kv, int32_t batch, const int32_t *token
     const size_t attn_stride = (size_t)batch * e->q_dim;
 
     // prompt rows: consecutive rows of a sequence share one K/V stream (their schedule replaces the decode step's)
-    const bool grouped = !with_head && e->chunk_attention;
-    // One or two rows (16 columns per KV head) over a very long cache only stream it: three of a workgroup's four wavefronts
-    // have nothing to multiply, and with few KV heads there are too few parts to fill the chip, so the kernel with one
-    // K/V stream per wavefront is the faster one (us per 3-layer call, bf16 | 8-bit cache, that kernel / the shared-stream
-    // one: 30 000 tokens, 2 KV heads 211 / 231 | 209 / 233, 4 KV heads 335 / 343 | 322 / 342, but 8 KV heads 400 / 355;
-    // 16 000 tokens, 4 KV heads 295 / 299 | 290 / 298; 8 000 tokens 287 / 275 | 284 / 275, and 288 / 264 with 7 rows).
-    const bool chunked = grouped && batch * e->G <= 16 && c->n_kv_heads <= 4 && max_blocks >= 1000, prompt = grouped && !chunked;
+    const bool prompt = !with_head && e->chunk_attention;
     if (prompt) {
         HX_TIMED(HX_K_SETUP, hx_launch_prompt_setup(e, batch, positions, seq_lens, block_table, max_blocks, st));
         HX_TIMED(HX_K_NORM, hx_launch_embed_norm(e, batch, tokens, e->layers[0].g1, st));
     } else {
         HX_TIMED(HX_K_NORM, hx_launch_step_begin(e, batch, tokens, positions, seq_lens, block_table, max_blocks, e->layers[0].g1, st));
-        if (chunked) HX_TIMED(HX_K_SETUP, hx_launch_chunk_setup(e, batch, seq_lens, block_table, max_blocks, st));
     }
     for (int l = 0; l < c->n_layers; ++l) {
         const hx_layer_map *lm = &e->layers[l];
@@ -458,9 +450,6 @@ static int run_step(hx_engine *e, hx_kv *kv, int32_t batch, const int32_t *token
         if (prompt) {
             HX_TIMED(HX_K_ATTENTION, hx_launch_prompt_attention(e, kv, l, batch, block_table, max_blocks, capture, st));
             HX_TIMED(HX_K_COMBINE, hx_launch_prompt_combine(e, batch, capture, st));
-        } else if (chunked) {
-            HX_TIMED(HX_K_ATTENTION, hx_launch_chunk_attention(e, kv, l, block_table, max_blocks, st));
-            HX_TIMED(HX_K_COMBINE, hx_launch_chunk_combine(e, batch, capture, st));
         } else {
             if (kv->fp8) HX_TIMED(HX_K_ATTENTION, hx_launch_attention_fp8(e, kv, l, block_table, max_blocks, st));
             else HX_TIMED(HX_K_ATTENTION, hx_launch_attention(e, kv, l, batch, seq_lens, block_table, max_blocks, st));

@@ -1,4 +1,4 @@
-// Attention for prompt rows (prefill_rows, and prefill_chunk beyond a handful of rows): one schedule over all rows of
+// Attention for prompt rows (prefill_rows, prefill_chunk): one schedule over all rows of
 // the call, workgroups of four wavefronts that share a K/V stream through LDS.
 //
 // Consecutive rows of one sequence form a GROUP of up to 128 / G rows; its (row, query head of one KV head) pairs are
@@ -602,8 +602,8 @@ static PromptArgs prompt_args(const hx_engine *e, int n_rows, size_t stride, flo
     PromptArgs a;
     a.ws0 = e->ws;
     a.stride = stride;
-    a.o_qp = m.qp; a.o_pre = m.pre; a.o_lens = m.lens; a.o_ginfo = m.chunk_ginfo; a.o_gslot = m.chunk_rgrp; a.o_glist = m.chunk_cont;
-    a.o_sched = m.sched; a.o_ap = m.ap; a.o_ml = m.chunk_part_ml; a.o_po = m.chunk_part_o;
+    a.o_qp = m.qp; a.o_pre = m.pre; a.o_lens = m.lens; a.o_ginfo = m.prompt_ginfo; a.o_gslot = m.prompt_gslot; a.o_glist = m.prompt_cont;
+    a.o_sched = m.sched; a.o_ap = m.ap; a.o_ml = m.prompt_part_ml; a.o_po = m.prompt_part_o;
     a.n_rows = n_rows;
     a.n_blocks = (n_rows + 255) / 256;
     a.slots_per_block = (e->attn_waves + e->cfg.max_batch * e->cfg.n_kv_heads) / 2;   // a slot here is two of that area's (64 columns)
@@ -618,10 +618,10 @@ int hx_launch_prompt_setup(const hx_engine *e, int n_rows, const int32_t *positi
                            int max_blocks, hipStream_t st, size_t stride) {
     if (n_rows < 1 || n_rows > HX_PREFILL_MAX_ROWS) return hx_fail(HX_E_RANGE, "%d prompt rows in one call", n_rows);
     const PromptArgs a = prompt_args(e, n_rows, stride, nullptr);
-    hipLaunchKernelGGL(prompt_rows_kernel, dim3(n_rows), dim3(64), 0, st, e->ws, stride, e->map.cs, e->map.blk_new, e->map.chunk_cont,
+    hipLaunchKernelGGL(prompt_rows_kernel, dim3(n_rows), dim3(64), 0, st, e->ws, stride, e->map.cs, e->map.blk_new, e->map.prompt_cont,
                        positions, seq_lens, table, max_blocks, e->D / 2, (double)e->cfg.rope_theta, e->cfg.max_batch);
     HX_CHECK_LAUNCH("prompt_rows");
-    hipLaunchKernelGGL(prompt_sched_kernel, dim3(1), dim3(1024), (size_t)n_rows * 4, st, a, seq_lens, e->map.chunk_cont,
+    hipLaunchKernelGGL(prompt_sched_kernel, dim3(1), dim3(1024), (size_t)n_rows * 4, st, a, seq_lens, e->map.prompt_cont,
                        HX_PROMPT_COLS / e->G, e->attn_waves / 4);
     HX_CHECK_LAUNCH("prompt_sched");
     return HX_OK;

@@ -1,6 +1,5 @@
-"""The attention of prompt calls where its schedule can go wrong: the edges of the kernel for one or two rows over a long
-cache, groups that end at a workspace of 256 rows, and pairs cut into few or many parts (HX_ATTN_WAVES sets
-the number of workgroups the work is cut for).  Reference: the same call with HX_CHUNK_ATTENTION=0, which sends every
+"""The attention of prompt calls where its schedule can go wrong: one or two rows over a long cache, groups that end at a
+workspace of 256 rows, and pairs cut into few or many parts (HX_ATTN_WAVES sets the number of workgroups the work is cut for).  Reference: the same call with HX_CHUNK_ATTENTION=0, which sends every
 row through the decode step's attention (held to the oracle by its own tests); same products, other order of sums."""
 import numpy as np
 import pytest
@@ -56,8 +55,7 @@ def layer0_attention(hx, s, plan, kv_dtype, waves, monkeypatch, seed=31):
     return out
 
 
-# (heads, KV heads, head size, plan of (keys cached, rows)).  Up to 16 columns over 1000 blocks or more take the kernel
-# with a stream per wavefront; 128 / G rows are one group, 32 columns a wavefront; 32 tokens are a step, 8 steps the
+# (heads, KV heads, head size, plan of (keys cached, rows)).  128 / G rows are one group, 32 columns a wavefront; 32 tokens are a step, 8 steps the
 # shortest part.  In groups of at most 32 columns the wavefronts may take steps of their own.
 CASES = {
     "16-columns-1000-blocks": (16, 2, 128, [(15990, 2)]),
