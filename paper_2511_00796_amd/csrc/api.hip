@@ -453,7 +453,7 @@ static int run_step(hx_engine *e, hx_kv *kv, int32_t batch, const int32_t *token
         } else {
             if (kv->fp8) HX_TIMED(HX_K_ATTENTION, hx_launch_attention_fp8(e, kv, l, block_table, max_blocks, st));
             else HX_TIMED(HX_K_ATTENTION, hx_launch_attention(e, kv, l, batch, seq_lens, block_table, max_blocks, st));
-            HX_TIMED(HX_K_COMBINE, hx_launch_combine(e, batch, max_blocks, capture, st));
+            HX_TIMED(HX_K_COMBINE, hx_launch_combine(e, batch, capture, st));
         }
         HX_TIMED(HX_K_GEMM_O, hx_launch_gemm(e, &lm->wo, batch, ws + e->map.ap, HX_EPI_PARTIAL, ypart, nullptr, st));
         HX_TIMED(HX_K_NORM, hx_launch_reduce_norm(e, batch, ypart, hx_gemm_splits(e, &lm->wo, batch), hx_gemm_split_stride(e, &lm->wo, batch), lm->g2, st));
@@ -571,7 +571,7 @@ extern "C" int prefill_rows(hx_engine *e, hx_kv *kv, int32_t n_rows, const int32
                 const hx_engine *vb = &view[b];
                 if (kv->fp8) HX_TIMED(HX_K_ATTENTION, hx_launch_attention_fp8(vb, kv, l, table(b), max_blocks, st));
                 else HX_TIMED(HX_K_ATTENTION, hx_launch_attention(vb, kv, l, 256, rows(seq_lens, b), table(b), max_blocks, st));
-                HX_TIMED(HX_K_COMBINE, hx_launch_combine(vb, 256, max_blocks, capture ? capture + (size_t)b * 256 * e->q_dim : nullptr, st));
+                HX_TIMED(HX_K_COMBINE, hx_launch_combine(vb, 256, capture ? capture + (size_t)b * 256 * e->q_dim : nullptr, st));
             }
         }
         HX_TIMED(HX_K_GEMM_O, hx_launch_gemm_wide(e, &lm->wo, R, ws0, stride, m.ap, HX_EPI_PARTIAL, m.ypart, 0, p_o, st));
@@ -721,7 +721,7 @@ extern "C" int hx_stage_attention(hx_engine *e, hx_kv *kv, int layer, int32_t ba
     if (kv->fp8) rc = hx_launch_attention_fp8(e, kv, layer, block_table, max_blocks, st);
     else rc = hx_launch_attention(e, kv, layer, batch, seq_lens, block_table, max_blocks, st);
     if (rc) return rc;
-    return hx_launch_combine(e, batch, max_blocks, out_dev, st);
+    return hx_launch_combine(e, batch, out_dev, st);
 }
 
 // ---- the attention stage without a workspace ---------------------------------------------------------------------
@@ -782,7 +782,7 @@ extern "C" int hx_stage_attention_static(hx_engine *e, hx_kv *kv, int layer, int
     if (kv->fp8) rc = hx_launch_attention_fp8(e, kv, layer, block_table, max_blocks, st, &bufs);
     else rc = hx_launch_attention(e, kv, layer, batch, seq_lens, block_table, max_blocks, st, &bufs);
     if (rc) return rc;
-    return hx_launch_combine(e, batch, max_blocks, out_dev, st, &bufs);
+    return hx_launch_combine(e, batch, out_dev, st, &bufs);
 }
 
 extern "C" int hx_stage_rmsnorm(hx_engine *e, int gain_kind, int layer, int32_t batch, const float *x_dev, float *y_dev,

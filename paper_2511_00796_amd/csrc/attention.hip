@@ -277,8 +277,10 @@ __global__ __launch_bounds__(64) void attn_splitk_kernel(const char *__restrict_
 // wavefronts in order (deterministic).  Lanes of phase 0
 // write the bf16-rounded result into the packed activation buffer of the output projection and, if asked,
 // the unrounded fp32 values.  D = 64 uses lanes d8 < 8 only.
-// WPP = 1, four pairs per workgroup: batches with a few partials per pair.  WPP = 8: short batches of long sequences,
-// where a pair has a hundred partials and more (its one wavefront went through them in a dozen dependent steps).
+// WPP = 1, four pairs per workgroup: batches whose pairs have a few partials.  WPP = 8: batches whose pairs may have a hundred and
+// more (its one wavefront went through them in a dozen dependent steps); a pair that has at most HX_COMBINE_FEW all the same is
+// done by its first wavefront as with WPP = 1, bit for bit.
+#define HX_COMBINE_FEW 32
 template <int D, int WPP>
 __global__ __launch_bounds__(WPP == 1 ? 256 : 64 * WPP) void attn_combine_kernel(int batch, int n_q, int n_kv, int G,
                                                            const int32_t *__restrict__ pre,
@@ -305,11 +307,13 @@ __global__ __launch_bounds__(WPP == 1 ? 256 : 64 * WPP) void attn_combine_kernel
     // partial per lane, 64 at a time; the weighted sum of the o vectors four partials per 16-lane group and iteration,
     // all requested before the first is used.
     const int n = s1 - s0 + 1;
+    const int waves = WPP > 1 && n > HX_COMBINE_FEW ? WPP : 1;      // that share the pair: the same for the whole workgroup
+    if (pw >= waves) return;
     float M = HX_NEG_BIG, den = 0.f;
     float acc[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-    if (WPP == 1 && n <= 8) {       // the usual case (a few partials per pair): each 16-lane group takes every fourth
+    if (n <= 8) {       // the usual case (a few partials per pair): each 16-lane group takes every fourth
         for (int it = s0 + ph; it <= s1; it += 4) M = fmaxf(M, part_ml[(size_t)it * 32 + g]);
         M = fmaxf(M, __shfl_xor(M, 16));
         M = fmaxf(M, __shfl_xor(M, 32));
@@ -335,7 +339,7 @@ __global__ __launch_bounds__(WPP == 1 ? 256 : 64 * WPP) void attn_combine_kernel
         }
 #pragma unroll
         for (int sh = 1; sh < 64; sh <<= 1) den += __shfl_xor(den, sh);
-        for (int it = s0 + 16 * pw + ph; it <= s1; it += 16 * WPP) {
+        for (int it = s0 + 16 * pw + ph; it <= s1; it += 16 * waves) {
             float w[4];
             f32x4_t a[4], c[4];
 #pragma unroll
@@ -362,7 +366,7 @@ __global__ __launch_bounds__(WPP == 1 ? 256 : 64 * WPP) void attn_combine_kernel
         acc[j] += __shfl_xor(acc[j], 16);
         acc[j] += __shfl_xor(acc[j], 32);
     }
-    if (WPP > 1) {
+    if (WPP > 1 && waves > 1) {
         if (ph == 0 && has_d)
 #pragma unroll
             for (int j = 0; j < 8; ++j) part[pw][d8 * 8 + j] = acc[j];
@@ -409,14 +413,16 @@ int hx_launch_attention(const hx_engine *e, const hx_kv *kv, int layer, int batc
     return HX_OK;
 }
 
-int hx_launch_combine(const hx_engine *e, int batch, int max_blocks, float *attn_f32_out, hipStream_t st, const hx_attn_bufs *bufs) {
+int hx_launch_combine(const hx_engine *e, int batch, float *attn_f32_out, hipStream_t st, const hx_attn_bufs *bufs) {
     const hx_attn_bufs own = hx_attn_bufs_of(e);
     const hx_attn_bufs &a = bufs ? *bufs : own;
     const int n_kv = e->cfg.n_kv_heads, n_q = e->cfg.n_q_heads;
     const int m_groups = hx_m_groups(batch);
-    // A pair has about attn_waves / (batch * n_kv) partials and at most one per block: with more than 32 its eight wavefronts
-    // pay (170 partials, 3 rows of 7B: 13.0 -> 8.0 us; 1 row of 1.5B, 200 blocks: 11.5 -> 7.6).
-    const bool many = max_blocks > 32 && e->attn_waves > 32 * batch * n_kv;
+    // A pair has about attn_waves / (batch * n_kv) partials, if its sequence has as many blocks (which only the device knows): with
+    // more than 32 its eight wavefronts pay (170 partials, 3 rows of 7B: 13.0 -> 8.0 us; 1 row of 1.5B, 200 blocks: 11.5 -> 7.6), and
+    // for shorter sequences the seven that leave at once cost nothing (1 to 8 rows, 20 to 400 tokens: 17.3-18.3 us with the
+    // attention kernel either way).
+    const bool many = e->attn_waves > HX_COMBINE_FEW * batch * n_kv;
     dim3 cgrid(many ? batch * n_q : (batch * n_q + 3) / 4), cblock(many ? 512 : 256);
 #define HX_COMB_ARGS                                                                                             \
     batch, n_q, n_kv, e->G, (const int32_t *)a.pre, (const int32_t *)a.lens, (const int32_t *)a.sched,            \

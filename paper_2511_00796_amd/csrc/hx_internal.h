@@ -279,7 +279,7 @@ int hx_launch_step_setup(const hx_engine *e, int batch, const int32_t *positions
                          const hx_attn_bufs *bufs = nullptr);                    // (bufs: positions must be NULL)
 int hx_launch_attention(const hx_engine *e, const hx_kv *kv, int layer, int batch, const int32_t *seq_lens,
                         const int32_t *table, int max_blocks, hipStream_t st, const hx_attn_bufs *bufs = nullptr);
-int hx_launch_combine(const hx_engine *e, int batch, int max_blocks, float *attn_f32_out, hipStream_t st, const hx_attn_bufs *bufs = nullptr);
+int hx_launch_combine(const hx_engine *e, int batch, float *attn_f32_out, hipStream_t st, const hx_attn_bufs *bufs = nullptr);
 
 // gemm.hip
 int hx_launch_pack_matrix(const hx_engine *e, const hx_matrix *m, const void *src, int64_t rows, int64_t cols,

@@ -47,3 +47,21 @@ def test_prompt_chunk(hx, plan, cache):
         out.append(cap[0].clone())
     torch.cuda.synchronize()
     assert float(out[0].abs().max()) > 0 and torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("cache", ["bf16", "fp8"])
+@pytest.mark.parametrize("d,lens", [(128, [500]), (128, [512, 17, 300]), (64, [100, 512]), (128, [8000, 30, 3000])])
+def test_decode_attention(hx, d, lens, cache):
+    s = synth.ModelShape("width", 1, 256, 6, 2, d, 688, 1000)
+    eng = build(hx, s, 3, len(lens), 8192, hx.HX_KV_FP8_E4M3 if cache == "fp8" else hx.HX_KV_BF16)
+    both, nb = tables(lens, 5)
+    start = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    q = torch.randn(len(lens), s.q_dim, generator=torch.Generator(device="cuda").manual_seed(2), device="cuda")
+    out = []
+    for table in both:
+        kv = hx.KVCache(eng, nb)
+        k, v = synth.kv_fill(s, 0, int(np.sum(lens)), 3, device="cuda")
+        kv.prefill_fill(0, k, v, dev(start), dev(table))
+        out.append(eng.stage_attention(kv, 0, q, dev(np.array(lens, dtype=np.int32)), dev(table)))
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1])
