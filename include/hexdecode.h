@@ -273,15 +273,18 @@ int hx_attention_waves(const hx_engine *engine); /* wavefronts of the attention 
    same tolerances, only summation order changes):
      HX_ATTN_WAVES=n        wavefronts of the attention kernel, read at hx_engine_create (default 8 per compute unit
                             of the device: 2048 on an MI355X)
-     HX_GEMM_SHAPE=wn,wk,s  force tiles per workgroup (4..6, or 4 with wk = 2), k-slices per workgroup and K-splits
-     HX_GEMM_MAX_SPLITS=s   upper bound of the planner's K-splits (1..9)
+     HX_GEMM_SHAPE=wn,wk,s  force tiles per workgroup, k-slices per workgroup and K-splits of the products of a batch: wn 4..6
+                            with wk = 1 or 4 with wk = 2 for up to 128 rows, wn 4..8 with wk = 1 beyond; a shape that does
+                            not exist for a product is ignored for it.  prefill_rows plans its own
+     HX_GEMM_MAX_SPLITS=s   upper bound of the planner's K-splits for a batch (1..9)
      HX_CHUNK_ATTENTION=0   prefill_chunk attends every row on its own (the decode step's kernel) instead of in groups
                             of consecutive rows, read at hx_engine_create; for comparison                            */
 
-/* How the streaming product of n_tiles 32-column tiles and k_steps 16-row steps is launched for `batch` rows (host logic
-   only, no GPU work; it runs batches of up to 128 rows, larger ones go through the workgroup-tiled product of prefill_rows): tiles per workgroup, k-slices per workgroup, and K-splits whose fp32 partial results the consumer
-   kernel adds (only if `partial` != 0; products with a fused epilogue are never split).  HX_E_RANGE for sizes < 1 or
-   batch > 256, HX_E_NULL for NULL outputs. */
+/* How the matrix product of n_tiles 32-column tiles and k_steps 16-row steps is launched for `batch` rows (host logic only,
+   no GPU work): tiles per workgroup, k-slices per workgroup, and K-splits whose fp32 partial results the consumer kernel
+   adds (only if `partial` != 0; products with a fused epilogue are never split).  Up to 128 rows that is the streaming
+   product, beyond them the workgroup-tiled one of prefill_rows over one block of 256 rows, as an engine with max_batch 256
+   runs it (one for fewer rows may split less).  HX_E_RANGE for sizes < 1 or batch > 256, HX_E_NULL for NULL outputs. */
 int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, int32_t partial, int32_t *tiles_per_workgroup_out,
                     int32_t *k_slices_out, int32_t *splits_out);
 

@@ -447,20 +447,29 @@ static int launch_shape(int wn, int wk, int epilogue, dim3 grid, hipStream_t st,
 // Examples: the 1184 tiles of the 7B gate|up matrix make 296 workgroups of 4 (two rounds on 256 compute
 // units) but 237 workgroups of 5 (one round); the 4752 tiles of the LM head make five rounds of 4, four of 5 or
 // two of 10, measured 253 / 244 / 230 us.  Ten tiles per workgroup are twelve wavefronts (three per SIMD): only
-// for products without split partials and up to 128 rows (beyond them hx_plan_wide plans, and what hx_plan_product answers
-// for such batches is not used).  HX_GEMM_SHAPE="wn,wk,splits" overrides (tuning).
+// for products without split partials.  HX_GEMM_SHAPE="wn,wk,splits" overrides (tuning).  Batches of more than 128 rows:
+// hx_plan_wide, under the same two knobs.
 
 struct gemm_launch { int wn, wk, splits, tile0, tiles; };
 
-static int plan_product(int n_tiles, int k_steps, int mg, bool partial, gemm_launch *out) {
+// HX_GEMM_MAX_SPLITS, and HX_GEMM_SHAPE="wn,wk,splits"
+static int splits_allowed(int most) {
+    const char *cap = getenv("HX_GEMM_MAX_SPLITS");
+    return cap ? std::max(1, std::min(most, atoi(cap))) : most;
+}
+static bool forced_shape(int *wn, int *wk, int *splits) {
+    const char *ov = getenv("HX_GEMM_SHAPE");
+    return ov && sscanf(ov, "%d,%d,%d", wn, wk, splits) == 3 && *splits >= 1;
+}
+
+static int plan_product(int n_tiles, int k_steps, bool partial, gemm_launch *out) {
     const int cus = hx_device_cus();
     gemm_launch best{4, 1, 1, 0, n_tiles};
     double best_cost = 1e300;
-    int max_s = partial ? HX_MAX_SPLITS : 1;
-    if (const char *cap = getenv("HX_GEMM_MAX_SPLITS")) max_s = partial ? std::max(1, std::min(HX_MAX_SPLITS, atoi(cap))) : 1;
+    const int max_s = partial ? splits_allowed(HX_MAX_SPLITS) : 1;
     static const int widths[] = {4, 5, 6, 10};
     for (int wn : widths) {
-        if (wn == 10 && (partial || mg > 4)) continue;
+        if (wn == 10 && partial) continue;
         for (int s = 1; s <= max_s; ++s) {
             if (s > 1 && k_steps / s < 16) break;
             const int wgs = ((n_tiles + wn - 1) / wn) * s;
@@ -469,42 +478,55 @@ static int plan_product(int n_tiles, int k_steps, int mg, bool partial, gemm_lau
             // busiest compute unit: rounds x (wn tiles + the activations) x whole ring revolutions (one more to fill
             // the ring), plus a small charge per split for writing and re-reading its partial tile
             const int revolutions = (sps + HX_GEMM_RING - 1) / HX_GEMM_RING + 1;
-            const double width = (partial || mg > 4) ? wn + 0.35 * (wn - 4) : wn + 3.0;   // as measured on each kind
+            const double width = partial ? wn + 0.35 * (wn - 4) : wn + 3.0;   // as measured on each kind
             const double cost = (double)rounds * width * revolutions * (1.0 + 0.02 * (s - 1));
             if (cost < best_cost - 1e-9) { best_cost = cost; best.wn = wn; best.splits = s; }
         }
     }
     int a, b, c;
-    const char *ov = getenv("HX_GEMM_SHAPE");
-    if (ov && sscanf(ov, "%d,%d,%d", &a, &b, &c) == 3 && c >= 1 && c <= max_s && k_steps / (b * c) >= 1 &&
-        ((b == 1 && a >= 4 && a <= 6) || (a == 4 && b == 2))) {
+    if (forced_shape(&a, &b, &c) && c <= max_s && ((b == 1 && a >= 4 && a <= 6) || (a == 4 && b == 2)) && k_steps / (b * c) >= 1) {
         best.wn = a; best.wk = b; best.splits = c;
     }
     out[0] = best;
     return 1;
 }
 
-// The plan of one product, for inspection: tiles per workgroup, k-slices per workgroup, K-splits.
+// Beyond 128 rows the workgroup-tiled product of gemm_wide.hip takes over: one block of 256 rows, those past the batch
+// computed and never read.  Its partials are 256 rows apart, so fewer splits fit the buffer of an engine for fewer rows.
+static bool wide_rows(int batch) { return batch > 128; }
+static hx_wide_plan plan_wide_batch(const hx_matrix *m, int epilogue, int max_batch) {
+    const int max_s = epilogue == HX_EPI_PARTIAL ? splits_allowed(HX_MAX_SPLITS * max_batch / 256) : 1;
+    hx_wide_plan plan = hx_plan_wide(m, 1, epilogue, max_s);
+    int wn, wk, sp;                                      // forced: 4 to 8 tiles, no k-slices, no split without k-steps
+    if (forced_shape(&wn, &wk, &sp) && wk == 1 && wn >= 4 && wn <= 8 && sp <= max_s && (sp - 1) * hx_wide_split_steps(m, sp) < m->k_steps) {
+        plan.wnt = wn;
+        plan.splits = sp;
+    }
+    return plan;
+}
+
+// The plan of one product, for inspection: tiles per workgroup, k-slices per workgroup, K-splits.  Beyond 128 rows as an
+// engine for 256 rows runs it.
 extern "C" int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, int32_t partial, int32_t *wn_out,
                                int32_t *wk_out, int32_t *splits_out) {
     if (!wn_out || !wk_out || !splits_out) return hx_fail(HX_E_NULL, "an output pointer is NULL");
     if (n_tiles < 1 || k_steps < 1 || batch < 1 || batch > 256) return hx_fail(HX_E_RANGE, "product %d x %d for batch %d", n_tiles, k_steps, batch);
+    if (wide_rows(batch)) {
+        const hx_matrix m{0, 16 * k_steps, 32 * n_tiles, k_steps, n_tiles};
+        const hx_wide_plan plan = plan_wide_batch(&m, partial ? HX_EPI_PARTIAL : HX_EPI_SWIGLU, 256);
+        *wn_out = plan.wnt; *wk_out = 1; *splits_out = plan.splits;
+        return HX_OK;
+    }
     gemm_launch plan[2];
-    plan_product(n_tiles, k_steps, hx_m_groups(batch), partial != 0, plan);
+    plan_product(n_tiles, k_steps, partial != 0, plan);
     *wn_out = plan[0].wn; *wk_out = plan[0].wk; *splits_out = plan[0].splits;
     return HX_OK;
 }
 
-// Beyond 128 rows the workgroup-tiled product of gemm_wide.hip takes over: one block of 256 rows, those past the batch
-// computed and never read.  Its partials are 256 rows apart, so fewer splits fit the buffer of an engine for fewer rows.
-static bool wide_rows(int batch) { return batch > 128; }
-static hx_wide_plan plan_wide_batch(const hx_engine *e, const hx_matrix *m, int epilogue) {
-    return hx_plan_wide(m, 1, epilogue, HX_MAX_SPLITS * e->cfg.max_batch / 256);
-}
 int hx_gemm_splits(const hx_engine *e, const hx_matrix *m, int batch) {
-    if (wide_rows(batch)) return plan_wide_batch(e, m, HX_EPI_PARTIAL).splits;
+    if (wide_rows(batch)) return plan_wide_batch(m, HX_EPI_PARTIAL, e->cfg.max_batch).splits;
     gemm_launch plan[2];
-    plan_product(m->n_tiles, m->k_steps, hx_m_groups(batch), true, plan);
+    plan_product(m->n_tiles, m->k_steps, true, plan);
     return plan[0].splits;
 }
 size_t hx_gemm_split_stride(const hx_engine *e, const hx_matrix *m, int batch) {
@@ -526,10 +548,10 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
                             sample ? sample->inv_temperature : 1.0f, sample ? sample->key0 : 0u, sample ? sample->key1 : 0u,
                             (float *)(e->ws + e->map.samp_z), (float *)(e->ws + e->map.samp_m), (float *)(e->ws + e->map.samp_s)};
         return hx_launch_gemm_wide(e, m, 1, e->ws, 0, (const char *)xp - e->ws, epilogue, partial ? (char *)y - e->ws : 0,
-                                   mp_out ? (char *)mp_out - e->ws : 0, plan_wide_batch(e, m, epilogue), st, &lm);
+                                   mp_out ? (char *)mp_out - e->ws : 0, plan_wide_batch(m, epilogue, e->cfg.max_batch), st, &lm);
     }
     gemm_launch plan[2];
-    const int n_launch = plan_product(m->n_tiles, m->k_steps, mg, partial, plan);
+    const int n_launch = plan_product(m->n_tiles, m->k_steps, partial, plan);
     for (int li = 0; li < n_launch; ++li) {
         const gemm_launch &pl = plan[li];
         GemmArgs a;

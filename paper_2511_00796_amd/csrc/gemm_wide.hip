@@ -277,6 +277,8 @@ int launch_wide_epi(int epilogue, dim3 grid, hipStream_t st, const WideArgs &a) 
 // One block of 256 rows (us; in brackets the streaming kernel of gemm.hip, which it replaces beyond 128 rows): 1.5B QKV 14.8
 // (17.4), O 14.8 (16.1), gate|up 27.6 (32.2), down 21.1 (25.3); 7B 20.4 (21.1), 18.4 (19.5), 78.4 (88.6), 46.7 (50.2);
 // 14B 31.2 (32.9), 25.7 (27.3), 90.9 (89.7), 46.6 (51.5).
+int hx_wide_split_steps(const hx_matrix *m, int splits) { return ((m->k_steps + splits - 1) / splits + 1) & ~1; }
+
 hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, int epilogue, int max_splits) {
     const int cus = hx_device_cus();
     const bool partial = epilogue == HX_EPI_PARTIAL;
@@ -288,7 +290,7 @@ hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, int epilogue, int 
         const double narrow = wnt == 4 ? 1.2 : (wnt == 5 ? 1.12 : (wnt == 6 ? 1.03 : 1.0));
         for (int s = 1; s <= (partial ? max_splits : 1); ++s) {
             if (s > 1 && m->k_steps / s < 32) break;
-            const int sps = ((m->k_steps + s - 1) / s + 1) & ~1;
+            const int sps = hx_wide_split_steps(m, s);
             if ((s - 1) * sps >= m->k_steps) continue;          // whole chunks would leave the last split empty
             const double exact = (double)NB * row_blocks * s / cus;
             const int whole = (NB * row_blocks * s + cus - 1) / cus;
@@ -323,7 +325,7 @@ int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, 
     a.y0 = (float *)(ws0 + y_off);
     a.mp0 = (uint16_t *)(ws0 + mp_off);
     a.lm = head ? *lm : hx_lm_args{};
-    a.steps_per_split = ((m->k_steps + splits - 1) / splits + 1) & ~1;
+    a.steps_per_split = hx_wide_split_steps(m, splits);
     const int NB = (m->n_tiles + wnt - 1) / wnt;
     a.splits = splits;
     dim3 grid((NB * row_blocks * splits + 7) / 8 * 8);

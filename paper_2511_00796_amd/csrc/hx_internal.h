@@ -329,6 +329,7 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
 // gemm_wide.hip: products over several 256-row blocks at once (prompt rows)
 struct hx_wide_plan { int wnt, splits; };        // 32-column tiles per workgroup, K-splits
 struct hx_lm_args;
+int hx_wide_split_steps(const hx_matrix *m, int splits);      // k-steps of each split but the last: whole chunks of two
 hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, int epilogue, int max_splits = HX_MAX_SPLITS);
 int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, char *ws0, size_t block_stride, size_t xp_off,
                         int epilogue, size_t y_off, size_t mp_off, hx_wide_plan plan, hipStream_t st, const hx_lm_args *lm = nullptr);

@@ -97,7 +97,8 @@ int main() {
                 for (int batch : {1, 33, 64, 128, 256}) {
                     int32_t wn = 0, wk = 0, sp = 0;
                     EXPECT(hx_plan_product((p[1] + 31) / 32, p[0] / 16, batch, p[2], &wn, &wk, &sp) == HX_OK);
-                    EXPECT(((wn >= 4 && wn <= 6) || (wn == 10 && !p[2] && batch <= 128)) && wk >= 1 && sp >= 1 && sp <= 9 && (p[2] || sp == 1));
+                    EXPECT(batch <= 128 ? (wn >= 4 && wn <= 6) || (wn == 10 && !p[2]) : wn >= 4 && wn <= 8 && wk == 1);
+                    EXPECT(wk >= 1 && sp >= 1 && sp <= 9 && (p[2] || sp == 1));
                 }
         }
     }

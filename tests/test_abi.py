@@ -106,9 +106,9 @@ def test_engine_create_validates_buffers_on_the_host():
     assert lib.hx_engine_destroy(None) == binding.HX_E_NULL
 
 
-def test_product_plans_fill_the_chip_and_respect_their_limits():
+def test_product_plans_fill_the_chip_and_respect_their_limits(monkeypatch):
     """Host-side launch planner: every plan keeps at least 16 k-steps per split, never splits a product whose epilogue
-    needs the whole sum, stays within 9 splits and 4..6 tiles per workgroup (10 only for unsplit products of up to 128 rows),
+    needs the whole sum, stays within 9 splits and 4..6 tiles per workgroup (10 only for unsplit products; 4..8 beyond 128 rows),
     and for the 7B shapes picks the plans the design rests on (gate|up: 237 workgroups of 5 = one round on 256 compute
     units; O and QKV: 7 splits of exactly two ring revolutions; down: 9 splits; LM head: two rounds of 10 tiles)."""
     lib = binding.load()
@@ -123,7 +123,10 @@ def test_product_plans_fill_the_chip_and_respect_their_limits():
                               (s.intermediate, s.hidden, True), (s.hidden, s.vocab, False)):
             for batch in (1, 4, 64, 128, 256):
                 wn, wk, sp = plan((N + 31) // 32, K // 16, batch, partial)
-                assert (4 <= wn <= 6 or (wn == 10 and not partial and batch <= 128)) and wk == 1 and 1 <= sp <= 9
+                if batch <= 128:
+                    assert (4 <= wn <= 6 or (wn == 10 and not partial)) and wk == 1 and 1 <= sp <= 9
+                else:                                   # the workgroup-tiled product
+                    assert 4 <= wn <= 8 and wk == 1 and 1 <= sp <= 9
                 assert sp == 1 or (K // 16) // sp >= 16
                 assert partial or sp == 1
     s = synth.QWEN_7B
@@ -132,7 +135,18 @@ def test_product_plans_fill_the_chip_and_respect_their_limits():
     assert plan(s.qkv_dim // 32, s.hidden // 16, 128, True) == (4, 1, 7)
     assert plan(s.hidden // 32, s.intermediate // 16, 128, True) == (4, 1, 9)
     assert plan(s.vocab // 32, s.hidden // 16, 128, False) == (10, 1, 1)
-    assert plan(s.vocab // 32, s.hidden // 16, 256, False) == (4, 1, 1)
+    # beyond 128 rows the answer is the plan of the product that runs there, under the same knobs
+    assert plan(s.vocab // 32, s.hidden // 16, 256, False) == (7, 1, 1)
+    down = (s.hidden // 32, s.intermediate // 16)
+    assert plan(*down, 256, True)[2] > 2
+    monkeypatch.setenv("HX_GEMM_MAX_SPLITS", "2")
+    assert plan(*down, 256, True)[2] <= 2 and plan(*down, 128, True)[2] <= 2
+    monkeypatch.delenv("HX_GEMM_MAX_SPLITS")
+    monkeypatch.setenv("HX_GEMM_SHAPE", "7,1,3")
+    assert plan(*down, 256, True) == (7, 1, 3) and plan(*down, 128, True) == (4, 1, 9)       # 7 tiles: only beyond 128 rows
+    monkeypatch.setenv("HX_GEMM_SHAPE", "4,2,2")
+    assert plan(*down, 128, True) == (4, 2, 2) and plan(*down, 256, True)[1] == 1            # k-slices: only up to 128
+    monkeypatch.delenv("HX_GEMM_SHAPE")
     none = C.c_int32()
     assert lib.hx_plan_product(0, 10, 4, 1, C.byref(none), C.byref(none), C.byref(none)) == binding.HX_E_RANGE
     assert lib.hx_plan_product(10, 10, 300, 1, C.byref(none), C.byref(none), C.byref(none)) == binding.HX_E_RANGE

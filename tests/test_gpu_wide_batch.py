@@ -49,3 +49,18 @@ def test_products_beyond_128_rows(hx, name, batch, max_batch):
             # fp32 sums of exact products: a few units of 2^-24 of the sum of magnitudes
             bound = xd.abs() @ mat.abs()
             assert ((y.double() - (xd @ mat)).abs() <= 1e-5 * bound).all(), (name, kind)
+
+
+@pytest.mark.parametrize("knob,value", [("HX_GEMM_MAX_SPLITS", "1"), ("HX_GEMM_SHAPE", "5,1,2"), ("HX_GEMM_SHAPE", "8,1,3"), ("HX_GEMM_SHAPE", "4,2,1")])
+@pytest.mark.parametrize("batch,max_batch", [(130, 130), (256, 256)])
+def test_forced_plans_beyond_128_rows(hx, batch, max_batch, knob, value, monkeypatch):
+    """The knobs that force plans hold beyond 128 rows, too; a shape that does not exist there, or needs more partial results
+    than the engine's buffer holds, is ignored."""
+    s = SHAPES["splits"]
+    eng = build(hx, s, 5, max_batch, 64)
+    wd = synth.layer_weights(s, 0, 5)["wd"].double().cuda()
+    x = torch.randn(batch, s.intermediate, generator=torch.Generator(device="cuda").manual_seed(7), device="cuda").bfloat16().float()
+    monkeypatch.setenv(knob, value)
+    y = eng.stage_linear(hx.HX_T_WD, 0, x)
+    torch.cuda.synchronize()
+    assert ((y.double() - x.double() @ wd).abs() <= 1e-5 * (x.double().abs() @ wd.abs())).all()
