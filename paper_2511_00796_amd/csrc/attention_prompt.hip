@@ -344,23 +344,25 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_kernel(PromptArgs a, const
 #pragma unroll
             for (int k = 0; k < NK; ++k) kr[k] = *(const u32x4_t *)(kb + (k >> 1) * 1024 + (k & 1) * 512);
             __builtin_amdgcn_sched_barrier(0);
+            u32x4_t ko[D / 16];                         // the operand of every step of k
             if (!FP8) {
 #pragma unroll
-                for (int k = 0; k < D / 16; ++k)
-                    sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kr[k]), __builtin_bit_cast(bf16x8_t, q[k]), sc, 0, 0, 0);
+                for (int k = 0; k < D / 16; ++k) ko[k] = kr[k];
             } else {
                 // 16 bytes hold the operand bytes of steps k and k + 2
 #pragma unroll
                 for (int kp = 0; kp < D / 32; ++kp) {
                     const int k = (kp >> 1) * 4 + (kp & 1);
-                    const u32x4_t raw = kr[kp];
-                    const uint2 a0 = hx_e4m3x4_to_bf16x4(raw.x), a1 = hx_e4m3x4_to_bf16x4(raw.y);
-                    const uint2 b0 = hx_e4m3x4_to_bf16x4(raw.z), b1 = hx_e4m3x4_to_bf16x4(raw.w);
-                    const u32x4_t ka = {a0.x, a0.y, a1.x, a1.y}, kc = {b0.x, b0.y, b1.x, b1.y};
-                    sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ka), __builtin_bit_cast(bf16x8_t, q[k]), sc, 0, 0, 0);
-                    sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kc), __builtin_bit_cast(bf16x8_t, q[k + 2]), sc, 0, 0, 0);
+                    const uint2 a0 = hx_e4m3x4_to_bf16x4(kr[kp].x), a1 = hx_e4m3x4_to_bf16x4(kr[kp].y);
+                    const uint2 b0 = hx_e4m3x4_to_bf16x4(kr[kp].z), b1 = hx_e4m3x4_to_bf16x4(kr[kp].w);
+                    ko[k] = u32x4_t{a0.x, a0.y, a1.x, a1.y};
+                    ko[k + 2] = u32x4_t{b0.x, b0.y, b1.x, b1.y};
                 }
             }
+#pragma unroll
+            for (int k = 0; k < D / 16; ++k)
+                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ko[k]), __builtin_bit_cast(bf16x8_t, q[k]), sc, 0, 0, 0);
+            hx_hold_operands(ko, sc);
             // ---- softmax; register r is token t0 + 8 (r / 4) + 4 h + r % 4
             float p[16];
 #pragma unroll
@@ -431,14 +433,14 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_kernel(PromptArgs a, const
                         for (int i = 0; i < D / 32; ++i) { v[i][2 * e] &= m01; v[i][2 * e + 1] &= m23; }
                     }
                 }
-                const u32x4_t hi = {ph[4 * blk], ph[4 * blk + 1], ph[4 * blk + 2], ph[4 * blk + 3]};
-                const u32x4_t lo = {pl[4 * blk], pl[4 * blk + 1], pl[4 * blk + 2], pl[4 * blk + 3]};
+                const u32x4_t pp[2] = {{ph[4 * blk], ph[4 * blk + 1], ph[4 * blk + 2], ph[4 * blk + 3]},
+                                       {pl[4 * blk], pl[4 * blk + 1], pl[4 * blk + 2], pl[4 * blk + 3]}};
 #pragma unroll
-                for (int i = 0; i < D / 32; ++i)
-                    o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v[i]), __builtin_bit_cast(bf16x8_t, hi), o[i], 0, 0, 0);
+                for (int part = 0; part < 2; ++part)
 #pragma unroll
-                for (int i = 0; i < D / 32; ++i)
-                    o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v[i]), __builtin_bit_cast(bf16x8_t, lo), o[i], 0, 0, 0);
+                    for (int i = 0; i < D / 32; ++i)
+                        o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v[i]), __builtin_bit_cast(bf16x8_t, pp[part]), o[i], 0, 0, 0);
+                hx_hold_operands(v, pp, o);
             }
         };
         if (narrow) {                                   // every wavefront for itself, in stages of its own: no barrier

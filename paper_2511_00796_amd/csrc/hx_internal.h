@@ -85,10 +85,10 @@ __device__ __forceinline__ uint2 hx_e4m3x4_to_bf16x4(uint32_t w) {
 // scores on ragged tiles (gone with every wait forced; gone with the operands held two or more wait states, not with
 // one).  Operands that stay live -- the bf16 kernels multiply straight out of their load registers, and what follows
 // their products closely are accumulator-register reads, which are harmless -- are not exposed.  These statements keep
-// short-lived operands live for four wait states.  The form with `acc` is the one for 16x16x32 products: it also
-// takes the products' accumulator as an in-out operand, which orders it behind the last product of the chain (an
-// asm statement that only names the operands may be scheduled in front of a product that is still to read them --
-// seen in builds with other ring depths, where the add then followed the product directly).
+// short-lived operands live for four wait states (an assembly scan in the tests checks the distance).  The form with
+// `acc` is the one for 16x16x32 products: it also takes the products' accumulator as an in-out operand, which orders it
+// behind the last product of the chain (an asm statement that only names the operands may be scheduled in front of a product
+// that is still to read them -- seen in builds with other ring depths, where the add then followed the product directly).
 template <int N>
 __device__ __forceinline__ void hx_hold_operands(const unsigned int __attribute__((ext_vector_type(4))) (&op)[N]) {
     if constexpr (N == 4) asm volatile("s_nop 3" : : "v"(op[0]), "v"(op[1]), "v"(op[2]), "v"(op[3]));
@@ -102,15 +102,24 @@ __device__ __forceinline__ void hx_hold_operands(const unsigned int __attribute_
     else if constexpr (N == 2) asm volatile("s_nop 3" : "+v"(acc) : "v"(op[0]), "v"(op[1]));
     else static_assert(N == 2 || N == 4, "operand steps of head sizes 64 and 128");
 }
+// The same for 32x32x16 products (attention_prompt.hip), which have never been seen to suffer (in builds without these statements
+// the kernel had a hundred such writes 2 to 6 slots behind them, and its results were right): free of cost, and one rule for
+// all attention kernels.  Behind a chain over D / 16 operand steps, and behind the products of the
+// D / 32 blocks of V with the high and the low part of the probabilities (all their accumulators: each orders its own).
+typedef unsigned int hx_u32x4_t __attribute__((ext_vector_type(4)));
 template <int N>
-__device__ __forceinline__ void hx_hold_operands(const unsigned int __attribute__((ext_vector_type(4))) (&op)[N],
-                                                 const unsigned int __attribute__((ext_vector_type(4))) (&op2)[N],
-                                                 f32x4_t &acc) {
+__device__ __forceinline__ void hx_hold_operands(const hx_u32x4_t (&op)[N], f32x16_t &acc) {
+    if constexpr (N == 8)
+        asm volatile("s_nop 3" : "+v"(acc) : "v"(op[0]), "v"(op[1]), "v"(op[2]), "v"(op[3]), "v"(op[4]), "v"(op[5]), "v"(op[6]), "v"(op[7]));
+    else if constexpr (N == 4) asm volatile("s_nop 3" : "+v"(acc) : "v"(op[0]), "v"(op[1]), "v"(op[2]), "v"(op[3]));
+    else static_assert(N == 4 || N == 8, "operand steps of head sizes 64 and 128");
+}
+template <int N>
+__device__ __forceinline__ void hx_hold_operands(const hx_u32x4_t (&v)[N], const hx_u32x4_t (&p)[2], f32x16_t (&acc)[N]) {
     if constexpr (N == 4)
-        asm volatile("s_nop 3" : "+v"(acc) : "v"(op[0]), "v"(op[1]), "v"(op[2]), "v"(op[3]), "v"(op2[0]), "v"(op2[1]),
-                     "v"(op2[2]), "v"(op2[3]));
-    else if constexpr (N == 2) asm volatile("s_nop 3" : "+v"(acc) : "v"(op[0]), "v"(op[1]), "v"(op2[0]), "v"(op2[1]));
-    else static_assert(N == 2 || N == 4, "operand steps of head sizes 64 and 128");
+        asm volatile("s_nop 3" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]) : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(p[0]), "v"(p[1]));
+    else if constexpr (N == 2) asm volatile("s_nop 3" : "+v"(acc[0]), "+v"(acc[1]) : "v"(v[0]), "v"(v[1]), "v"(p[0]), "v"(p[1]));
+    else static_assert(N == 2 || N == 4, "d blocks of head sizes 64 and 128");
 }
 
 // round-to-nearest-even on the upper half of the fp32 pattern (finite inputs)
