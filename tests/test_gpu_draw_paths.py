@@ -1,11 +1,14 @@
-"""The draw where its kernels change: kept sets from one entry to nearly all of them (which tiles the nucleus draw goes
-through again), a vocabulary that ends inside a tile.  Reference: the oracle's samplers on the step's own logits."""
+"""The draw where its kernels change: batches beyond 128 rows (the workgroup-tiled LM head leaves the candidates), a
+vocabulary that ends inside a tile, and kept sets from one entry to nearly all of them (which tiles the nucleus draw
+goes through again).  Reference: the oracle's samplers on the step's own logits."""
 import numpy as np
 import pytest
 import torch
 
+import oracle
+import test_gpu_sampling
 import test_gpu_top_p
-from paper_2511_00796_amd import synth
+from paper_2511_00796_amd import synth, workload
 
 pytestmark = pytest.mark.gpu
 
@@ -17,7 +20,35 @@ def hx():
     return binding
 
 
-# 1000 = 31 tiles and 8 columns, 33324 = 1041 and 12: more tiles than the 1024 threads that look at them at once.
+# 1000 = 31 tiles and 8 columns, 33324 = 1041 and 12: more tiles than the 1024 threads that first look at them
+@pytest.mark.parametrize("batch,max_batch", [(129, 129), (130, 200), (200, 200), (256, 256)])
+@pytest.mark.parametrize("vocab", [1000, 33324])
+def test_draws_beyond_128_rows(hx, vocab, batch, max_batch):
+    s = synth.ModelShape("draw", 1, 256, 4, 2, 64, 688, vocab)
+    dw = workload.build(synth.Workload("draw", s, max_batch, "uniform", 1, 40, 77))
+    args = (dw.tokens[:batch].contiguous(), dw.positions[:batch].contiguous(), dw.seq_lens_d[:batch].contiguous(),
+            dw.table_d[:batch].contiguous())
+    pos = args[1].cpu().numpy()
+    logits = torch.empty(batch, vocab, device="cuda")
+    tok = torch.empty(batch, dtype=torch.int32, device="cuda")
+    lp = torch.empty(batch, device="cuda")
+    n = torch.empty(batch, dtype=torch.int32, device="cuda")
+    dw.engine.decode_step(dw.kv, *args, logits, tok)
+    greedy = logits.clone()
+    assert torch.equal(tok.long(), greedy.argmax(1))
+    ids = torch.from_numpy(np.random.default_rng(2).permutation(5000)[:batch].astype(np.int32)).cuda()
+    for row_ids, rows in ((None, np.arange(batch)), (ids, ids.cpu().numpy())):
+        logits.fill_(float("nan"))
+        dw.engine.decode_step_sample(dw.kv, *args, 0.7, 9, logits, tok, lp, row_ids)
+        assert torch.equal(logits, greedy)
+        test_gpu_sampling.check_against_oracle(tok.cpu().numpy(), lp.cpu().numpy(), greedy.cpu().numpy(), 0.7, 9, rows, pos, "sample")
+        logits.fill_(float("nan"))
+        dw.engine.decode_step_top_p(dw.kv, *args, 0.3, 0.8, 9, logits, tok, lp, row_ids, n)
+        assert torch.equal(logits, greedy)
+        test_gpu_top_p.check_against_oracle(tok.cpu().numpy(), lp.cpu().numpy(), n.cpu().numpy(), greedy.cpu().numpy(), 0.3, 0.8, 9,
+                                            rows, pos, "top-p")
+
+
 # (temperature, top_p): one kept entry, a few, some in every tile, all but the least likely
 @pytest.mark.parametrize("temperature,top_p", [(0.002, 0.9), (0.02, 0.5), (0.1, 0.3), (1.0, 0.05), (1.0, 0.5), (1.0, 0.9999)])
 @pytest.mark.parametrize("vocab,batch", [(1000, 5), (33324, 64), (70000, 3)])

@@ -1,6 +1,6 @@
 """Products of more than 128 rows outside prefill_rows: batches at the edges of the workgroup-tiled kernel, an odd number of
 k-steps, engines for fewer than 256 rows (whose partial buffer caps the K-splits), column blocks that end inside a
-workgroup's tile, and the sampled head.  Reference: the product in float64."""
+workgroup's tile; the sampled heads: test_gpu_draw_paths.py.  Reference: the product in float64."""
 import numpy as np
 import pytest
 import torch
