@@ -181,11 +181,13 @@ __host__ __device__ __forceinline__ int hx_vtile8_index(int t, int d) {
     return (d >> 6) * 1024 + ((((t >> 2) * 16) + (d & 15)) << 4) + (((d >> 5) & 1) << 3) + (((d >> 4) & 1) << 2) + (t & 3);
 }
 
-// 1 KiB from global memory straight into LDS (lane l's 16 bytes, at src + 16 l, to lds_off + 16 l).  Written as asm because
-// behind the builtin the compiler makes every LDS read wait for all copies in flight (it cannot tell the stages of a
-// ring apart).  m0 is set in the same statement and the compiler keeps nothing in it in these kernels (it is reserved: no
-// clobber can be declared).  The copy has no output register; the kernel waits for it by count (HX_COPY_WAIT) before the barrier that hands
-// a stage over, and for all of it before it ends.
+// 1 KiB from global memory straight into LDS (lane l's 16 bytes, at src + 16 l, to LDS address lds_off + 16 l).  lds_off counts from
+// the start of the workgroup's LDS: the kernels that use this have one, dynamic, __shared__ array, which begins there, and no
+// static one (a test on the generated code holds them to that; the array's address taken in the kernel instead made the
+// widest product 1 % slower).  Written as asm because behind the builtin the compiler makes every LDS read wait for all
+// copies in flight (it cannot tell the stages of a ring apart).  m0 is set in the same statement and the compiler keeps nothing
+// in it in these kernels (it is reserved: no clobber can be declared).  The copy has no output register; the kernel waits for
+// it by count (HX_COPY_WAIT) before the barrier that hands a stage over, and for all of it before it ends.
 __device__ __forceinline__ void hx_copy_to_lds(const void *src, uint32_t lane_off, uint32_t lds_off) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_off), "s"(src), "s"(lds_off) : "memory");
 }

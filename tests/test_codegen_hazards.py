@@ -118,14 +118,29 @@ _Z4demov:
     assert len(exposures(through, 6)) == 1 and exposures(through, 6)[0][1] == 3
 
 
-@pytest.mark.parametrize("source,window,shape", GUARDED)
-def test_no_vector_write_close_behind_a_product_that_reads_the_register(source, window, shape, tmp_path):
+def assembly(source, tmp_path):
     out = tmp_path / (source + ".s")
     cmd = [hxbuild.HIPCC, *[f for f in hxbuild.FLAGS if f != "-fPIC"], "--cuda-device-only", "-S",
            os.path.join(hxbuild.CSRC, source), "-o", str(out)]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
-    text = out.read_text()
+    return out.read_text()
+
+
+@pytest.mark.parametrize("source,window,shape", GUARDED)
+def test_no_vector_write_close_behind_a_product_that_reads_the_register(source, window, shape, tmp_path):
+    text = assembly(source, tmp_path)
     assert "v_mfma_f32_%s_bf16" % shape in text
     found = exposures(text, window, shape)
     assert not found, "\n".join("%s: %d slots: %s <- %s" % (k[:60], d, a, b) for k, d, a, b in found[:10])
+
+
+@pytest.mark.parametrize("source", ["attention_prompt.hip", "gemm_wide.hip"])
+def test_kernels_that_copy_straight_into_lds_have_only_the_dynamic_array(source, tmp_path):
+    """The copies count their LDS addresses from 0, where the dynamic __shared__ array begins as long as there is no static one."""
+    text = assembly(source, tmp_path)
+    copying = {k for k, t in instructions(text) if t.startswith("global_load_lds")}
+    static = {n: int(b) for b, n in re.findall(r"\.group_segment_fixed_size: (\d+).*?\.name: +(\S+)", text, re.S)}
+    assert len(copying) >= 4
+    for kernel in copying:
+        assert static[kernel] == 0, (kernel, static[kernel])
