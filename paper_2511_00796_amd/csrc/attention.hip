@@ -16,7 +16,7 @@
 //     O^T[d, g]    += V_tile^T[d, token] . P^T[token, g] v_mfma_f32_16x16x16_bf16 (A = V tile, B = P)
 // The accumulator layout of the first product (lane = query head g, 4 registers = 4 tokens) is
 // exactly the B-operand layout of the second, so the probabilities never cross lanes; only the
-// running maximum is exchanged between the four 16-lane groups with two wavefront shuffles per
+// running maximum is exchanged between the four 16-lane groups, with two register swaps per
 // tile, and the running sum is reduced once at the end.  K/V tiles are stored in operand order
 // in the pool, so they go from HBM to registers with contiguous 1-KiB loads and need no LDS.
 #include "hx_internal.h"

@@ -133,8 +133,8 @@ __global__ __launch_bounds__(HX_NORM_THREADS) void norm_kernel(float *__restrict
 }
 
 // The start of a decode step in one launch: the embedding and first norm of the rows (blocks 0..batch-1), their angles and
-// blocks (batch..2 batch-1) and the attention schedule (the last).  Two launches cost a short step 3 us more (tiny model,
-// 4 rows: 86.6 -> 83.6 us a step).
+// blocks (batch..2 batch-1) and the attention schedule (the last): one boundary between dependent launches, 2 to 3 us, less per
+// step (a whole step of the tiny model moves by no more than its spread, 84 to 92 us).
 __global__ __launch_bounds__(HX_NORM_THREADS) void step_begin_kernel(hx_setup_args a, float *__restrict__ x,
                                                                      const int32_t *__restrict__ tokens,
                                                                      const uint16_t *__restrict__ embed,

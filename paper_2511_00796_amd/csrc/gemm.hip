@@ -183,8 +183,8 @@ __global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK>::NP)) void gemm_st
         const int last_u4 = a_k_steps * MG * 64 - 1;
         const int pid = wave - NC;
         // The copy goes through registers (global load, then LDS store): measured faster than the direct L2 -> LDS
-        // path, which slows the weight stream of the same compute unit down when both run (timing lab: weights alone
-        // 27 us, direct copy alone 18 us, both 49 us for 60 workgroups).
+        // path behind the compiler's builtin (timing lab: weights alone 27 us, direct copy alone 18 us, both 49 us for 60
+        // workgroups), where every LDS read waits for all copies in flight; counted waits have not been tried here.
         u32x4_t ra[GG::PVP], rb[GG::PVP];
         auto load_chunk = [&](int c, u32x4_t (&r)[GG::PVP]) {
 #pragma unroll

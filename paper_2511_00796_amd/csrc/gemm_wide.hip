@@ -1,7 +1,8 @@
 // Products for many prompt rows at once: C[R x 256 rows][N] = X W with BOTH operands tiled through LDS, so that a
 // weight is read from HBM once per call instead of once per 256 rows (prompt processing, Section 1 stage (i) of the
-// rollout; the step before decoding).  The streaming kernel of gemm.hip keeps one weight tile per wavefront in
-// registers and is right for up to 256 rows; here a workgroup owns a 256 x 256 (or 256 x 192) tile of the output.
+// rollout; the step before decoding), and for decode batches and prompt chunks of 129 to 256 rows.  The streaming kernel
+// of gemm.hip keeps one weight tile per wavefront in registers and is right for up to 128 rows; here a workgroup owns a
+// tile of the output of 256 rows by 128 to 256 columns.
 //
 // Layouts are the decode step's (hx_internal.h): weights [n_tile][k_step][lane][8], activations of each 256-row block
 // [k_step][8 m-groups][lane][8] in that block's workspace.  Both are already in matrix-core operand order, so
@@ -276,7 +277,9 @@ int launch_wide_epi(int epilogue, dim3 grid, hipStream_t st, const WideArgs &a) 
 // 5: 397), O + down 885 with 7 (8: 951, 8 in 2 splits: 1007), gate|up 1160 with 8 (7: 1199, 6: 1193, 5: 1300).
 // One block of 256 rows (us; in brackets the streaming kernel of gemm.hip, which it replaces beyond 128 rows): 1.5B QKV 14.8
 // (17.4), O 14.8 (16.1), gate|up 27.6 (32.2), down 21.1 (25.3); 7B 20.4 (21.1), 18.4 (19.5), 78.4 (88.6), 46.7 (50.2);
-// 14B 31.2 (32.9), 25.7 (27.3), 90.9 (89.7), 46.6 (51.5).
+// 14B 31.2 (32.9), 25.7 (27.3), 90.9 (89.7), 46.6 (51.5).  The same two in turn on one card, with the packing of the input and the
+// sum of the partials, at 129, 192 and 256 rows: 14B gate|up 95.9, 99.5, 102.2 (98.8, 100.2, 105.5), all other products of the three
+// models 3 to 24 % faster; behind by 1 us (17.2 against 16.1) is only the 43-k-step down product of a hidden size of 256.
 int hx_wide_split_steps(const hx_matrix *m, int splits) { return ((m->k_steps + splits - 1) / splits + 1) & ~1; }
 
 hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, int epilogue, int max_splits) {

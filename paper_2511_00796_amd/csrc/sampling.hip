@@ -12,6 +12,7 @@
 // chip (here, one workgroup per row, drawing again for every kept entry was 90 of 144 us at 64 rows of 152 064 logits).
 // Three reads of the row (from the memory-side cache: the LM head has just written it).
 #include "hx_internal.h"
+#include <type_traits>
 
 #define HX_NUC_THREADS 1024
 #define HX_NUC_BINS 2048
@@ -141,9 +142,10 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
     // The draw: largest z_i - log(-log(u_i)) among the kept entries, smaller index on ties.  The LM head has left the best
     // perturbed score of every 32-column tile: where that entry is kept it is the tile's best kept one, too.  Of the other
     // tiles those whose largest z is not kept hold nothing kept; only the rest are gone through again, by eight lanes each,
-    // 32 tiles requested at a time.  Head + draw, us, 151 936 logits (drawing again for every kept entry | all other tiles gone
-    // through, eight at a time | this): one kept entry 163 | 203 | 166 at 1 row, 210 | 230 | 197 at 64; top_p 0.3 of flat
-    // logits 226 | 241 | 226 and 269 | 269 | 259; 0.95: 226 | 199 | 194 and 269 | 224 | 224.
+    // 32 tiles requested at a time (a wavefront with at most 8 of them: those).  Head + draw, us, 151 936 logits (drawing again for
+    // every kept entry | all other tiles gone through, eight at a time | this): one kept entry 163 | 203 | 166 at 1 row, 210 | 230 | 196
+    // at 64; top_p 0.3 of flat logits 226 | 241 | 224 and 269 | 269 | 255; 0.95: 226 | 199 | 192 and 269 | 224 | 222.  What is left
+    // of the first column's lead, few rows and few kept entries, is the sampling epilogue of the head (10 us at 14B).
     const uint32_t row = row_ids ? (uint32_t)row_ids[m] : (uint32_t)m;
     const uint32_t pos = (uint32_t)positions[m];
     float best = -INFINITY, best_z = 0.f;
@@ -165,18 +167,19 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
         // lanes 0..n-1 get the tiles to go through, in order; the other lanes what is left
         const int rank = __popcll(todo & ((1ull << lane) - 1ull));
         const int packed = __builtin_amdgcn_ds_permute(4 * (again ? rank : n + lane - rank), t);
-        for (int k0 = 0; k0 < n; k0 += 8 * HX_NUC_TILES) {
-            float v[HX_NUC_TILES][4];
-            int q[HX_NUC_TILES];
+        auto look_again = [&](int k0, auto rounds) {                         // tiles k0 .. k0 + 8 * rounds - 1 of them
+            constexpr int U = decltype(rounds)::value;
+            float v[U][4];
+            int q[U];
 #pragma unroll
-            for (int u = 0; u < HX_NUC_TILES; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const int k = k0 + 8 * u + (lane >> 3);
                 const int g = __shfl(packed, min(k, n - 1)) * 8 + (lane & 7);        // a group of four entries
                 q[u] = k < n && g < n_groups ? g : -1;
                 load_group(x, V, min(g, n_groups - 1), vec, v[u]);
             }
 #pragma unroll
-            for (int u = 0; u < HX_NUC_TILES; ++u) {
+            for (int u = 0; u < U; ++u) {
                 if (q[u] < 0) continue;
                 bool keep[4], any = false;
 #pragma unroll
@@ -193,7 +196,9 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
                     }
                 }
             }
-        }
+        };
+        if (n <= 8) look_again(0, std::integral_constant<int, 1>{});
+        else for (int k0 = 0; k0 < n; k0 += 8 * HX_NUC_TILES) look_again(k0, std::integral_constant<int, HX_NUC_TILES>{});
     }
     if (size_out) {                               // the number of kept entries, where it is asked for
         for (int q0 = tid; q0 < n_groups; q0 += HX_NUC_THREADS * HX_NUC_UNROLL) {
