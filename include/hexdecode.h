@@ -223,8 +223,9 @@ int decode_step_top_p(hx_engine *engine, hx_kv *kv, int32_t batch, const int32_t
    before any row attends, so a row sees the rows before it); chunks of a sequence are submitted in position order.
    The last prompt token is then given to decode_step / decode_step_sample, which yields the first generated token.
    Consecutive rows that continue one another (seq_lens one more, the same table row) are attended in groups of up
-   to 128 / G rows (G query heads per KV head) that share one read of the cache, so a call should hold long runs of one sequence rather than one row of many; any row order is correct.  Arguments,
-   ownership and errors as decode_step. */
+   to 128 / G rows (G query heads per KV head) that share one read of the cache, so a call should hold long runs of
+   one sequence rather than one row of many; any row order is correct.  Arguments, ownership and errors as
+   decode_step. */
 int prefill_chunk(hx_engine *engine, hx_kv *kv, int32_t n_rows, const int32_t *tokens, const int32_t *positions,
                   const int32_t *seq_lens, const int32_t *block_table, int32_t max_blocks_per_seq, void *stream);
 
@@ -277,8 +278,8 @@ int hx_attention_waves(const hx_engine *engine); /* wavefronts of the attention 
                             with wk = 1 or 4 with wk = 2 for up to 128 rows, wn 4..8 with wk = 1 beyond; a shape that does
                             not exist for a product is ignored for it.  prefill_rows plans its own
      HX_GEMM_MAX_SPLITS=s   upper bound of the planner's K-splits for a batch (1..9)
-     HX_CHUNK_ATTENTION=0   prefill_chunk attends every row on its own (the decode step's kernel) instead of in groups
-                            of consecutive rows, read at hx_engine_create; for comparison                            */
+     HX_CHUNK_ATTENTION=0   prefill_chunk and prefill_rows attend every row on its own (the decode step's kernel)
+                            instead of in groups of consecutive rows, read at hx_engine_create; for comparison */
 
 /* How the matrix product of n_tiles 32-column tiles and k_steps 16-row steps is launched for `batch` rows (host logic only,
    no GPU work): tiles per workgroup, k-slices per workgroup, and K-splits whose fp32 partial results the consumer kernel
@@ -357,9 +358,9 @@ typedef enum {
     HX_K_GEMM_GATE_UP = 4,
     HX_K_GEMM_DOWN = 5,
     HX_K_GEMM_LM = 6,
-    HX_K_NORM = 7,      /* embedding / split-sum + residual + RMSNorm    */
+    HX_K_NORM = 7,      /* embedding (a decode step: with its set-up) / split-sum + residual + RMSNorm */
     HX_K_ROPE = 8,      /* bias + RoPE + cache append                    */
-    HX_K_SETUP = 9,     /* work list, RoPE angles, final argmax          */
+    HX_K_SETUP = 9,     /* prompt rows: schedule, RoPE angles; final arg-max or draw */
     HX_K_COUNT = 10
 } hx_kernel_class;
 

@@ -13,8 +13,8 @@
 // What bounds it: the matrix cores (24 products of 32 cycles per 32 x 32 scores at D = 128) and the softmax arithmetic
 // beside them, which the second workgroup of a compute unit overlaps.  Measured per layer, kernel + combine, against a
 // kernel that served 8 rows per K/V stream with one wavefront each and 16-row products of half the rate: 7B, one prompt
-// of 2048 tokens 89 + 13 us (214 + 69); 14B, 7 prompts of 5000 tokens, 8-bit cache 125 + 7 us (273 + 136); 1.5B, 200
-// rows behind 3000 cached tokens 18 + 10 us (41 + 9).
+// of 2048 tokens 73 + 13 us (214 + 69); 14B, 7 prompts of 5000 tokens together, 8-bit cache 126 + 6 us (273 + 136);
+// 1.5B, 200 rows behind 3000 cached tokens 18 + 7 us (41 + 9).
 //
 // Schedule: a pair (group, KV head) of more than S steps is cut into equal parts of at most S steps; S follows from the
 // work of the whole call (prompt_sched_kernel), so that a short call with a long cache fills the chip and a long one

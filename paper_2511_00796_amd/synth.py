@@ -7,7 +7,7 @@ available, so everything here is a stand-in: decoder shapes of those model sizes
 weights, uniform / log-uniform ("long-tail") context lengths, random token ids and a randomly
 permuted block table.
 
-This module is the single producer of inputs for both the HIP path and the CPU checker.  It
+This module is the single producer of inputs for both the HIP path and the CPU oracle.  It
 holds none of the decode arithmetic: it only draws numbers (through torch / numpy generators),
 casts them to bf16 with the library cast, and lays out index tables.
 """

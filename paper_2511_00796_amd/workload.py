@@ -4,7 +4,7 @@ the 64-110 GB of cache ever sit on the host), and returns the device-side step i
 
 Pure orchestration of ``synth`` (inputs) and ``binding`` (the library); an optional ``tap`` callback
 sees each layer's tensors as they are produced, which the tests use to hand the same inputs to the
-CPU checker.
+CPU oracle.
 """
 from __future__ import annotations
 
