@@ -23,8 +23,8 @@ HBM_PEAK_GBS = 8000.0     # MI355X published HBM3E bandwidth
 # HBM bytes per attention launch at workload 7b-b128 from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a plain
 # copy (profiles/attn_splitk_7b-b128_hbm_traffic.txt).  Valid only for the kernel source they were taken with.
 PMC_TRAFFIC = {"workload": "7b-b128",
-               "attention_hip_sha256": "be7f62bbfdacff158f776090ec8760f4d67c98b89d3a105873b6663939a0e88e",
-               "fetch_bytes": 2165.41e6, "write_bytes": 9.45e6}
+               "attention_hip_sha256": "00d949e9219073c1fbc531f8c964d025e423429662ce67bd775e14618c750b3f",
+               "fetch_bytes": 2165.38e6, "write_bytes": 9.45e6}
 
 
 def measured_traffic(workload_name):
@@ -318,7 +318,7 @@ def main():
                           "data": "synthetic",
                           "dtype": "bf16",
                           "product_flops_over_call_time_TFLOPs": call_flops / (dt / calls) / 1e12,
-                          "roofline": {"kernel": "gemm_stream_kernel (gate|up product, 256 rows)", "bound": "mfma",
+                          "roofline": {"kernel": "gemm_wide_kernel (gate|up product, 256 rows)", "bound": "mfma",
                                        "achieved": gu_flops / (gu_avg_ms * 1e-3) / 1e12, "peak": 2500.0, "unit": "TFLOP/s",
                                        "frac": gu_flops / (gu_avg_ms * 1e-3) / 1e12 / 2500.0, "traffic": None,
                                        "launches_timed": int(gu_n), "avg_launch_ms": gu_avg_ms,
