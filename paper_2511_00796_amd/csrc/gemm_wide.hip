@@ -11,14 +11,14 @@
 // Workgroup = 8 wavefronts, two per SIMD: 2 x 4 sub-tiles of 128 x 64 (256 columns), 4 x 2 of 64 x 96 or 64 x 64
 // (192, 128 columns), or 8 of 32 rows by all 224 or 160 columns.
 // A chunk is 2 k-steps: 16 pieces of X and 2 WNT of W, each copied global -> LDS directly by one wavefront, requested two
-// chunks ahead into a ring of three stages; one barrier per chunk, passed BEFORE the chunk's last k-step is multiplied,
+// chunks ahead into a ring of three stages (five ahead into six where the tile is narrow); one barrier per chunk, passed BEFORE the chunk's last k-step is multiplied,
 // so that the first operand reads of the next chunk hide behind those products, as the reads of its second k-step hide
 // behind the first.  Reads, copies and products are laid out by hand in groups (sched_barrier).
 // What bounds it is the matrix cores' power: with random operands a loop of 32x32x16 products out of registers reaches
 // 1 550 TFLOP/s on this card (zeros: 2 410).  7B gate|up, 2048 rows, output stores left out: this kernel 1 253 TFLOP/s;
 // with its copies removed 1 442, with its products removed 1 965.  The four-wavefront kernel before it (128 x 128 per
 // wavefront, copies through registers) 1 195, and 951 against 1 086 with fp32 stores, which the second wavefront of a
-// SIMD overlaps.  Four or five stages, or chunks of 4 k-steps in two stages, were not faster (1 095, 1 088, 995).
+// SIMD overlaps.  Four or five stages, or chunks of 4 k-steps in two stages, were not faster there (1 095, 1 088, 995).
 //
 // Workgroup numbering: consecutive workgroup ids go to different XCDs, so XCD x takes the x-th eighth of the work, row
 // blocks fastest, splits slowest: its workgroups take all row blocks of a few column blocks and walk K in step, so each XCD's L2 sees
@@ -35,9 +35,13 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 namespace {
 
 constexpr int WIDE_KC = 2;        // k-steps per chunk
-constexpr int WIDE_STAGES = 3;
 constexpr int WIDE_WAVES = 8;
-constexpr int wide_lds_bytes(int wnt) { return WIDE_STAGES * WIDE_KC * (8 + wnt) * 1024; }
+// Stages of the ring: six of the narrow tiles, three of the others.  The narrow ones run where a product is small or has one
+// block of rows, at a third of the matrix cores' rate, and wait for memory: six stages there, us at 201 rows: 7B gate|up
+// 77 -> 75, down 50 -> 44, 14B gate|up 88 -> 82, O 25 -> 22, QKV 31.5 -> 30 (1.5B, whose weights mostly stay in the
+// memory-side cache: the same).  Beyond 5 tiles the matrix cores bind: 2048 and 4864 rows 0.4 % slower with five stages.
+constexpr int wide_stages(int wnt) { return wnt <= 5 ? 6 : 3; }
+constexpr int wide_lds_bytes(int wnt) { return wide_stages(wnt) * WIDE_KC * (8 + wnt) * 1024; }
 
 struct WideArgs {
     const uint4 *wp;              // packed weights of the matrix
@@ -55,7 +59,7 @@ struct WideArgs {
 // but for the last, whose second k-step is missing.  (As a run-time condition in the loop this cost the narrow tiles 11 %.)
 template <int WNT, int EPI, bool ODD>
 __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) {
-    constexpr int KC = WIDE_KC, NST = WIDE_STAGES, WCOL = WNT == 8 ? 4 : (WNT % 2 ? 1 : 2), WROW = WIDE_WAVES / WCOL, TM = 8 / WROW,
+    constexpr int KC = WIDE_KC, NST = wide_stages(WNT), WCOL = WNT == 8 ? 4 : (WNT % 2 ? 1 : 2), WROW = WIDE_WAVES / WCOL, TM = 8 / WROW,
                   TW = WNT / WCOL;
     constexpr int PIECES = KC * (8 + WNT), STAGE_U4 = PIECES * 64;
     constexpr int LPW = (PIECES + WIDE_WAVES - 1) / WIDE_WAVES, FULL = PIECES - (LPW - 1) * WIDE_WAVES;   // waves < FULL copy LPW pieces, the others one less

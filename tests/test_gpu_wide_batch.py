@@ -64,3 +64,18 @@ def test_forced_plans_beyond_128_rows(hx, batch, max_batch, knob, value, monkeyp
     y = eng.stage_linear(hx.HX_T_WD, 0, x)
     torch.cuda.synchronize()
     assert ((y.double() - x.double() @ wd).abs() <= 1e-5 * (x.double().abs() @ wd.abs())).all()
+
+
+@pytest.mark.parametrize("tiles", [4, 5, 6])
+@pytest.mark.parametrize("k_steps", [1, 2, 9, 10, 11, 12, 13, 14])
+def test_fewer_and_more_chunks_than_stages(hx, k_steps, tiles, monkeypatch):
+    """Products of 1 to 7 chunks: the ring of LDS stages (six of the narrow tiles, three of the others) holds all of them, or not."""
+    s = synth.ModelShape("wb-ring", 1, 192, 2, 1, 64, 16 * k_steps, 64)
+    eng = build(hx, s, 5, 130, 64)
+    wd = synth.layer_weights(s, 0, 5)["wd"].double().cuda()
+    x = torch.randn(130, s.intermediate, generator=torch.Generator(device="cuda").manual_seed(7), device="cuda").bfloat16().float()
+    monkeypatch.setenv("HX_GEMM_SHAPE", "%d,1,1" % tiles)
+    y = eng.stage_linear(hx.HX_T_WD, 0, x)
+    torch.cuda.synchronize()
+    # fp32 sums of exact products, as above
+    assert ((y.double() - x.double() @ wd).abs() <= 1e-5 * (x.double().abs() @ wd.abs())).all()
