@@ -121,15 +121,17 @@ __global__ __launch_bounds__(HX_NORM_THREADS) void norm_kernel(float *__restrict
                                                               const float *__restrict__ ypart, int splits,
                                                               size_t split_stride, const uint16_t *__restrict__ gain,
                                                               int H, float eps, uint16_t *__restrict__ xp, int m_groups,
-                                                              float *__restrict__ y_f32, size_t block_stride) {
+                                                              float *__restrict__ y_f32, int rows, size_t block_stride) {
+    const int b = hx_row_of_workgroup(blockIdx.x, rows);
+    if (b >= rows) return;
     if (blockIdx.y) {               // further row blocks of a wide prompt call: same layout, block_stride bytes apart
         const size_t off = (size_t)blockIdx.y * block_stride;
         x = (float *)((char *)x + off);
         if (ypart) ypart = (const float *)((const char *)ypart + off);
         xp = (uint16_t *)((char *)xp + off);
-        if (tokens) tokens += (size_t)blockIdx.y * gridDim.x;
+        if (tokens) tokens += (size_t)blockIdx.y * rows;
     }
-    norm_row<MODE, MAXS>(blockIdx.x, x, x_in, tokens, embed, ypart, splits, split_stride, gain, H, eps, xp, m_groups, y_f32);
+    norm_row<MODE, MAXS>(b, x, x_in, tokens, embed, ypart, splits, split_stride, gain, H, eps, xp, m_groups, y_f32);
 }
 
 // The start of a decode step in one launch: the embedding and first norm of the rows (blocks 0..batch-1), their angles and
@@ -158,10 +160,10 @@ int hx_launch_step_begin(const hx_engine *e, int batch, const int32_t *tokens, c
 
 int hx_launch_embed_norm(const hx_engine *e, int batch, const int32_t *tokens, size_t gain_off, hipStream_t st, int blocks,
                          size_t block_stride) {
-    hipLaunchKernelGGL((norm_kernel<0, 1>), dim3(batch, blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x),
+    hipLaunchKernelGGL((norm_kernel<0, 1>), dim3(hx_row_workgroups(batch), blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x),
                        (const float *)nullptr, tokens, (const uint16_t *)(e->weights + e->embed),
                        (const float *)nullptr, 0, (size_t)0, (const uint16_t *)(e->weights + gain_off), e->cfg.hidden,
-                       e->cfg.rms_eps, (uint16_t *)(e->ws + e->map.xp), hx_m_groups(batch), (float *)nullptr, block_stride);
+                       e->cfg.rms_eps, (uint16_t *)(e->ws + e->map.xp), hx_m_groups(batch), (float *)nullptr, batch, block_stride);
     HX_CHECK_LAUNCH("embed_norm");
     return HX_OK;
 }
@@ -169,10 +171,10 @@ int hx_launch_embed_norm(const hx_engine *e, int batch, const int32_t *tokens, s
 int hx_launch_reduce_norm(const hx_engine *e, int batch, const float *ypart, int splits, size_t split_stride,
                           size_t gain_off, hipStream_t st, int blocks, size_t block_stride) {
 #define HX_REDUCE_NORM(MAXS)                                                                                      \
-    hipLaunchKernelGGL((norm_kernel<1, MAXS>), dim3(batch, blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x), \
+    hipLaunchKernelGGL((norm_kernel<1, MAXS>), dim3(hx_row_workgroups(batch), blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x), \
                        (const float *)nullptr, (const int32_t *)nullptr, (const uint16_t *)nullptr, ypart, splits, \
                        split_stride, (const uint16_t *)(e->weights + gain_off), e->cfg.hidden, e->cfg.rms_eps,    \
-                       (uint16_t *)(e->ws + e->map.xp), hx_m_groups(batch), (float *)nullptr, block_stride)
+                       (uint16_t *)(e->ws + e->map.xp), hx_m_groups(batch), (float *)nullptr, batch, block_stride)
     if (splits == 1) HX_REDUCE_NORM(1);
     else if (splits == 2) HX_REDUCE_NORM(2);
     else if (splits <= 4) HX_REDUCE_NORM(4);
@@ -183,10 +185,10 @@ int hx_launch_reduce_norm(const hx_engine *e, int batch, const float *ypart, int
 }
 
 int hx_launch_norm_only(const hx_engine *e, int batch, const float *x, size_t gain_off, float *y, hipStream_t st) {
-    hipLaunchKernelGGL((norm_kernel<2, 1>), dim3(batch), dim3(HX_NORM_THREADS), 0, st, (float *)nullptr, x,
+    hipLaunchKernelGGL((norm_kernel<2, 1>), dim3(hx_row_workgroups(batch)), dim3(HX_NORM_THREADS), 0, st, (float *)nullptr, x,
                        (const int32_t *)nullptr, (const uint16_t *)nullptr, (const float *)nullptr, 0, (size_t)0,
                        (const uint16_t *)(e->weights + gain_off), e->cfg.hidden, e->cfg.rms_eps, (uint16_t *)nullptr,
-                       hx_m_groups(batch), y, (size_t)0);
+                       hx_m_groups(batch), y, batch, (size_t)0);
     HX_CHECK_LAUNCH("norm_only");
     return HX_OK;
 }

@@ -113,7 +113,7 @@ int hx_launch_kv_scatter(const hx_kv *kv, int layer, const void *k, const void *
 // One thread per work item of 8 values, two groups of four: for q and k heads, 4 consecutive d of the lower half and the 4
 // matching d of the upper half (both ends of the rotation); for v, 8 consecutive d.  MAXS: split partials that are
 // requested, all before the first is used, and added in split order; those past `splits` repeat the last one, so a row
-// of one or two partials must not pay for nine.  grid (batch, ceil(items / 128)), 128 threads.  Query rows g >= G of the
+// of one or two partials must not pay for nine.  grid (rows, ceil(items / 128)), 128 threads.  Query rows g >= G of the
 // packed operand are never written: they only feed accumulator columns that nobody reads.
 // What bounds it is the latency of its loads on a decode step (hence all of them at once: 16 values per thread took two
 // rounds) and their number on a prompt call.  us: 1.5B, 64 sequences 6.9 -> 4.9, 7B, 128 sequences 7.1 -> 6.3; one partial,
@@ -126,17 +126,18 @@ __global__ __launch_bounds__(128) void rope_append_kernel(const float *__restric
                                                           const int32_t *__restrict__ blk_new,
                                                           char *pool_layer, size_t block_bytes, size_t tile_bytes,
                                                           uint16_t *__restrict__ qp, int n_q, int n_kv, int G,
-                                                          int max_batch, size_t block_stride) {
+                                                          int max_batch, int rows, size_t block_stride) {
     constexpr int HALF = D / 2;
     constexpr int RPH = HALF / 4;                         // rotation items per head
-    const int b = blockIdx.x;
+    const int b = hx_row_of_workgroup(blockIdx.x, rows);
+    if (b >= rows) return;
     if (blockIdx.z) {               // further row blocks of a wide prompt call: same layout, block_stride bytes apart
         const size_t off = (size_t)blockIdx.z * block_stride;
         ypart = (const float *)((const char *)ypart + off);
         cs = (const float *)((const char *)cs + off);
         blk_new = (const int32_t *)((const char *)blk_new + off);
         qp = (uint16_t *)((char *)qp + off);
-        positions += (size_t)blockIdx.z * gridDim.x;
+        positions += (size_t)blockIdx.z * rows;
     }
     const int item = blockIdx.y * blockDim.x + threadIdx.x;
     const int rot_items = (n_q + n_kv) * RPH;
@@ -235,11 +236,11 @@ int hx_launch_rope_append(const hx_engine *e, const hx_kv *kv, int layer, int ba
     const float *cs = (const float *)(e->ws + e->map.cs);
     uint16_t *qp = (uint16_t *)(e->ws + e->map.qp);
     const int items = (e->cfg.n_q_heads + e->cfg.n_kv_heads) * (e->D / 8) + e->cfg.n_kv_heads * (e->D / 8);
-    dim3 grid(batch, (items + 127) / 128, blocks), block(128);
+    dim3 grid(hx_row_workgroups(batch), (items + 127) / 128, blocks), block(128);
 #define HX_ROPE_LAUNCH(DD, F8, MAXS)                                                                            \
     hipLaunchKernelGGL((rope_append_kernel<DD, F8, MAXS>), grid, block, 0, st, ypart, splits, split_stride, bias, \
                        e->cfg.qkv_bias, cs, positions, (const int32_t *)(e->ws + e->map.blk_new), pool_layer, kv->block_bytes, \
-                       kv->tile_bytes, qp, e->cfg.n_q_heads, e->cfg.n_kv_heads, e->G, e->cfg.max_batch, block_stride)
+                       kv->tile_bytes, qp, e->cfg.n_q_heads, e->cfg.n_kv_heads, e->G, e->cfg.max_batch, batch, block_stride)
 #define HX_ROPE_LAUNCH_S(DD, F8)                                                                                \
     do {                                                                                                        \
         if (splits == 1) HX_ROPE_LAUNCH(DD, F8, 1);                                                             \

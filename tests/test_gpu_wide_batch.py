@@ -79,3 +79,17 @@ def test_fewer_and_more_chunks_than_stages(hx, k_steps, tiles, monkeypatch):
     torch.cuda.synchronize()
     # fp32 sums of exact products, as above
     assert ((y.double() - x.double() @ wd).abs() <= 1e-5 * (x.double().abs() @ wd.abs())).all()
+
+
+@pytest.mark.parametrize("rows", [127, 128, 129, 135, 136, 137, 200, 255, 256])
+def test_every_row_is_normalised_once(hx, rows):
+    """Beyond 128 rows the row kernels deal their rows to the XCDs in eighths, the last of which may be short or empty."""
+    s = SHAPES["odd"]
+    eng = build(hx, s, 5, 256, 64)
+    x = torch.randn(rows, s.hidden, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    y = eng.stage_rmsnorm(hx.HX_T_G1, 0, x)
+    torch.cuda.synchronize()
+    xd = x.double()
+    ref = xd * torch.rsqrt((xd * xd).mean(-1, keepdim=True) + s.rms_eps) * synth.layer_weights(s, 0, 5)["g1"].double().cuda()
+    # one bf16 rounding (2^-9 relative) and the fp32 norm's own error
+    assert y.shape == x.shape and ((y.double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-6).all()
