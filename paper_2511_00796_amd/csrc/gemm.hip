@@ -1,5 +1,5 @@
 // Small-M weight-streaming matrix products  Y[M, N] = X[M, K] W[K, N]  (M = batch <= 128;
-// more rows: gemm_wide.hip).
+// more rows: gemm_wide.hip; matrices of few columns: gemm_slice.hip).
 //
 // The weights dominate the bytes, so the kernel is organised around streaming each packed weight
 // tile exactly once, straight from HBM into the A operand of v_mfma_f32_32x32x16_bf16 (32 output
@@ -447,10 +447,10 @@ static int launch_shape(int wn, int wk, int epilogue, dim3 grid, hipStream_t st,
 // Examples: the 1184 tiles of the 7B gate|up matrix make 296 workgroups of 4 (two rounds on 256 compute
 // units) but 237 workgroups of 5 (one round); the 4752 tiles of the LM head make five rounds of 4, four of 5 or
 // two of 10, measured 253 / 244 / 230 us.  Ten tiles per workgroup are twelve wavefronts (three per SIMD): only
-// for products without split partials.  HX_GEMM_SHAPE="wn,wk,splits" overrides (tuning).  Batches of more than 128 rows:
+// for products without split partials.  Matrices of few columns go to gemm_slice.hip.  HX_GEMM_SHAPE="wn,wk,splits" overrides (tuning).  Batches of more than 128 rows:
 // hx_plan_wide, under the same two knobs.
 
-struct gemm_launch { int wn, wk, splits, tile0, tiles; };
+struct gemm_launch { int wn, wk, splits, slice_tiles; };     // slice_tiles > 0: gemm_slice.hip, with these K-splits
 
 // HX_GEMM_MAX_SPLITS, and HX_GEMM_SHAPE="wn,wk,splits"
 static int splits_allowed(int most) {
@@ -462,9 +462,9 @@ static bool forced_shape(int *wn, int *wk, int *splits) {
     return ov && sscanf(ov, "%d,%d,%d", wn, wk, splits) == 3 && *splits >= 1;
 }
 
-static int plan_product(int n_tiles, int k_steps, bool partial, gemm_launch *out) {
+static gemm_launch plan_product(int n_tiles, int k_steps, bool partial) {
     const int cus = hx_device_cus();
-    gemm_launch best{4, 1, 1, 0, n_tiles};
+    gemm_launch best{4, 1, 1, 0};
     double best_cost = 1e300;
     const int max_s = partial ? splits_allowed(HX_MAX_SPLITS) : 1;
     static const int widths[] = {4, 5, 6, 10};
@@ -486,9 +486,11 @@ static int plan_product(int n_tiles, int k_steps, bool partial, gemm_launch *out
     int a, b, c;
     if (forced_shape(&a, &b, &c) && c <= max_s && ((b == 1 && a >= 4 && a <= 6) || (a == 4 && b == 2)) && k_steps / (b * c) >= 1) {
         best.wn = a; best.wk = b; best.splits = c;
+        return best;
     }
-    out[0] = best;
-    return 1;
+    const hx_slice_plan slice = hx_plan_slice(n_tiles, k_steps, partial, max_s);
+    if (slice.tiles) { best.slice_tiles = slice.tiles; best.splits = slice.splits; }
+    return best;
 }
 
 // Beyond 128 rows the workgroup-tiled product of gemm_wide.hip takes over: one block of 256 rows, those past the batch
@@ -517,17 +519,14 @@ extern "C" int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, 
         *wn_out = plan.wnt; *wk_out = 1; *splits_out = plan.splits;
         return HX_OK;
     }
-    gemm_launch plan[2];
-    plan_product(n_tiles, k_steps, partial != 0, plan);
-    *wn_out = plan[0].wn; *wk_out = plan[0].wk; *splits_out = plan[0].splits;
+    const gemm_launch plan = plan_product(n_tiles, k_steps, partial != 0);
+    *wn_out = plan.wn; *wk_out = plan.wk; *splits_out = plan.splits;
     return HX_OK;
 }
 
 int hx_gemm_splits(const hx_engine *e, const hx_matrix *m, int batch) {
     if (wide_rows(batch)) return plan_wide_batch(m, HX_EPI_PARTIAL, e->cfg.max_batch).splits;
-    gemm_launch plan[2];
-    plan_product(m->n_tiles, m->k_steps, true, plan);
-    return plan[0].splits;
+    return plan_product(m->n_tiles, m->k_steps, true).splits;
 }
 size_t hx_gemm_split_stride(const hx_engine *e, const hx_matrix *m, int batch) {
     (void)e;
@@ -539,56 +538,54 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
     if (epilogue == HX_EPI_SAMPLE && !sample) return hx_fail(HX_E_NULL, "sampling parameters missing");
     const int mg = hx_m_groups(batch);
     const bool partial = epilogue == HX_EPI_PARTIAL;
+    const hx_lm_args lm{y, batch, m->N, m->n_tiles, (float *)(e->ws + e->map.amax_val), (int32_t *)(e->ws + e->map.amax_idx),
+                        sample ? sample->positions : nullptr, sample ? sample->row_ids : nullptr,
+                        sample ? sample->inv_temperature : 1.0f, sample ? sample->key0 : 0u, sample ? sample->key1 : 0u,
+                        (float *)(e->ws + e->map.samp_z), (float *)(e->ws + e->map.samp_m), (float *)(e->ws + e->map.samp_s)};
     if (wide_rows(batch)) {
         // The streaming kernel has one wavefront per SIMD with all rows' accumulators, and nothing beside its multiplications
         // or its epilogue; the workgroup-tiled product has two.  LM head, 1.5B, 256 rows, sampled: 327 -> 204 us; the other
         // products: see hx_plan_wide.
-        const hx_lm_args lm{y, batch, m->N, m->n_tiles, (float *)(e->ws + e->map.amax_val), (int32_t *)(e->ws + e->map.amax_idx),
-                            sample ? sample->positions : nullptr, sample ? sample->row_ids : nullptr,
-                            sample ? sample->inv_temperature : 1.0f, sample ? sample->key0 : 0u, sample ? sample->key1 : 0u,
-                            (float *)(e->ws + e->map.samp_z), (float *)(e->ws + e->map.samp_m), (float *)(e->ws + e->map.samp_s)};
         return hx_launch_gemm_wide(e, m, 1, e->ws, 0, (const char *)xp - e->ws, epilogue, partial ? (char *)y - e->ws : 0,
                                    mp_out ? (char *)mp_out - e->ws : 0, plan_wide_batch(m, epilogue, e->cfg.max_batch), st, &lm);
     }
-    gemm_launch plan[2];
-    const int n_launch = plan_product(m->n_tiles, m->k_steps, partial, plan);
-    for (int li = 0; li < n_launch; ++li) {
-        const gemm_launch &pl = plan[li];
-        GemmArgs a;
-        a.wp = (const uint4 *)(e->weights + m->offset);
-        a.xp = (const uint4 *)xp;
-        a.k_steps = m->k_steps;
-        a.n_tiles = m->n_tiles;
-        a.tile0 = pl.tile0;
-        a.tile_end = pl.tile0 + pl.tiles;
-        a.steps_per_split = (m->k_steps + pl.splits - 1) / pl.splits;
-        a.steps_per_wave = (a.steps_per_split + pl.wk - 1) / pl.wk;
-        a.M = batch;
-        a.N = m->N;
-        a.y = y;
-        a.split_stride = (size_t)batch * m->N;
-        a.mp = (uint16_t *)mp_out;
-        a.amax_val = (float *)(e->ws + e->map.amax_val);
-        a.amax_idx = (int32_t *)(e->ws + e->map.amax_idx);
-        a.positions = sample ? sample->positions : nullptr;
-        a.row_ids = sample ? sample->row_ids : nullptr;
-        a.inv_t = sample ? sample->inv_temperature : 1.0f;
-        a.key0 = sample ? sample->key0 : 0u;
-        a.key1 = sample ? sample->key1 : 0u;
-        a.samp_z = (float *)(e->ws + e->map.samp_z);
-        a.samp_m = (float *)(e->ws + e->map.samp_m);
-        a.samp_s = (float *)(e->ws + e->map.samp_s);
-        dim3 grid((pl.tiles + pl.wn - 1) / pl.wn, pl.splits);
-        int rc;
-        switch (mg) {
-            case 1: rc = launch_shape<1>(pl.wn, pl.wk, epilogue, grid, st, a); break;
-            case 2: rc = launch_shape<2>(pl.wn, pl.wk, epilogue, grid, st, a); break;
-            case 4: rc = launch_shape<4>(pl.wn, pl.wk, epilogue, grid, st, a); break;
-            default: return hx_fail(HX_E_RANGE, "%d rows for the streaming product", batch);
-        }
-        if (rc) return rc;
-        HX_CHECK_LAUNCH("gemm_stream");
+    const gemm_launch pl = plan_product(m->n_tiles, m->k_steps, partial);
+    if (pl.slice_tiles)
+        return hx_launch_gemm_slice(e, m, batch, hx_slice_plan{pl.slice_tiles, pl.splits}, xp, epilogue, y, mp_out, lm, st);
+    GemmArgs a;
+    a.wp = (const uint4 *)(e->weights + m->offset);
+    a.xp = (const uint4 *)xp;
+    a.k_steps = m->k_steps;
+    a.n_tiles = m->n_tiles;
+    a.tile0 = 0;
+    a.tile_end = m->n_tiles;
+    a.steps_per_split = (m->k_steps + pl.splits - 1) / pl.splits;
+    a.steps_per_wave = (a.steps_per_split + pl.wk - 1) / pl.wk;
+    a.M = batch;
+    a.N = m->N;
+    a.y = y;
+    a.split_stride = (size_t)batch * m->N;
+    a.mp = (uint16_t *)mp_out;
+    a.amax_val = lm.amax_val;
+    a.amax_idx = lm.amax_idx;
+    a.positions = lm.positions;
+    a.row_ids = lm.row_ids;
+    a.inv_t = lm.inv_t;
+    a.key0 = lm.key0;
+    a.key1 = lm.key1;
+    a.samp_z = lm.samp_z;
+    a.samp_m = lm.samp_m;
+    a.samp_s = lm.samp_s;
+    dim3 grid((m->n_tiles + pl.wn - 1) / pl.wn, pl.splits);
+    int rc;
+    switch (mg) {
+        case 1: rc = launch_shape<1>(pl.wn, pl.wk, epilogue, grid, st, a); break;
+        case 2: rc = launch_shape<2>(pl.wn, pl.wk, epilogue, grid, st, a); break;
+        case 4: rc = launch_shape<4>(pl.wn, pl.wk, epilogue, grid, st, a); break;
+        default: return hx_fail(HX_E_RANGE, "%d rows for the streaming product", batch);
     }
+    if (rc) return rc;
+    HX_CHECK_LAUNCH("gemm_stream");
     return HX_OK;
 }
 

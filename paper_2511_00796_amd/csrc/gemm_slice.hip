@@ -1,0 +1,202 @@
+// Small products of at most 128 rows: those whose matrix has too few column tiles to give the streaming kernel of gemm.hip (four
+// and more tiles per workgroup, at most 9 K-splits) a workgroup for every compute unit.
+//
+// Workgroup = four wavefronts on one 32-column tile (two of a long K): k-step i of the split goes to wavefront i % 4, so the
+// workgroup reads its tile's weights as one contiguous run.  A wavefront loads its weights and activations straight into
+// registers, R steps ahead; no LDS stages, no barrier until the end, where the four sums are added in order through LDS, laid out
+// so that the outputs leave in whole 128-byte lines.
+// What bounds it is the round trips of a launch: a ring's fill, and the end.  That the activations of every tile come through
+// the ring, which returns in order behind the weights, makes it slower than the streaming kernel wherever the weights are
+// many: 14B gate|up at 64 rows 73 us (two tiles per workgroup 56), 48 there.  us, streaming -> this, 1 / 64 / 128 rows:
+// 1.5B QKV 4.3 / 6.7 / 9.7 -> 3.5 / 4.4 / 6.3, O 4.5 / 6.5 / 10.2 -> 3.7 / 4.2 / 5.8, down 11.2 / 13.8 / 16.6 -> 7.2 / 11.1 / 13.0
+// (two tiles; one: 7.7 / 12.6 / 15.0), with weights that are partly in the memory-side cache.
+#include "hx_internal.h"
+#include "lm_epilogue.h"
+#include <algorithm>
+
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+
+namespace {
+
+constexpr int SLICES = 4;         // wavefronts of a workgroup
+
+struct SliceArgs {
+    const uint4 *wp, *xp;         // packed weights, packed activations
+    int k_steps, n_tiles, steps_per_split;
+    int M, N;
+    float *y;                     // PARTIAL: [splits][M][N]
+    size_t split_stride;
+    uint16_t *mp;                 // SWIGLU: packed bf16 output
+    hx_lm_args lm;                // LM head
+};
+
+// TN tiles per workgroup, MG m-groups, R k-steps in flight per wavefront
+template <int MG, int TN, int R, int EPI>
+__global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(SliceArgs a) {
+    constexpr int S = SLICES;
+    constexpr int Q = TN * MG * 4;                       // 16-byte quads of accumulators per lane
+    __shared__ u32x4_t red[S * Q * 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t0 = blockIdx.x * TN;
+    const int split0 = blockIdx.y * a.steps_per_split, split1 = min(a.k_steps, split0 + a.steps_per_split);
+    // step i of this wavefront is k-step split0 + wave + S * i
+    const int n = (split1 - split0 - wave + S - 1) / S;
+    const u32x4_t *wrow[TN];
+#pragma unroll
+    for (int t = 0; t < TN; ++t) wrow[t] = (const u32x4_t *)a.wp + ((size_t)min(t0 + t, a.n_tiles - 1) * a.k_steps + split0 + wave) * 64 + lane;
+    const u32x4_t *xrow = (const u32x4_t *)a.xp + (size_t)(split0 + wave) * MG * 64 + lane;
+    f32x16_t acc[TN][MG];
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+        for (int g = 0; g < MG; ++g)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[t][g][r] = 0.f;
+    if (n > 0) {
+        u32x4_t w[R][TN], x[R][MG];
+        auto request = [&](int r, int i) {
+            const int j = S * min(i, n - 1);
+#pragma unroll
+            for (int t = 0; t < TN; ++t) w[r][t] = __builtin_nontemporal_load(wrow[t] + (size_t)j * 64);
+#pragma unroll
+            for (int g = 0; g < MG; ++g) x[r][g] = xrow[((size_t)j * MG + g) * 64];
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto multiply = [&](int r) {
+#pragma unroll
+            for (int t = 0; t < TN; ++t)
+#pragma unroll
+                for (int g = 0; g < MG; ++g)
+                    acc[t][g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, w[r][t]), __builtin_bit_cast(bf16x8_t, x[r][g]),
+                                                                        acc[t][g], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+#pragma unroll
+        for (int r = 0; r < R; ++r) request(r, r);
+        int i = 0;
+        for (; i + R < n; i += R) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                multiply(r);
+                request(r, i + r + R);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (i + r < n) multiply(r);
+    }
+    // the slices' sums, added in order
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+        for (int g = 0; g < MG; ++g)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const f32x4_t v = {acc[t][g][4 * j], acc[t][g][4 * j + 1], acc[t][g][4 * j + 2], acc[t][g][4 * j + 3]};
+                // the row's place is turned by the quad's column group, so that eight lanes reading one row's eight groups of
+                // columns meet eight different banks
+                const int place = EPI == HX_EPI_PARTIAL ? (lane & 32) | ((lane & 31) ^ (2 * j + (lane >> 5))) : lane;
+                red[(wave * Q + (t * MG + g) * 4 + j) * 64 + place] = __builtin_bit_cast(u32x4_t, v);
+            }
+    __syncthreads();
+    auto sum = [&](int quad, int place) {
+        f32x4_t v = __builtin_bit_cast(f32x4_t, red[quad * 64 + place]);
+#pragma unroll
+        for (int s = 1; s < S; ++s) v += __builtin_bit_cast(f32x4_t, red[(s * Q + quad) * 64 + place]);
+        return v;
+    };
+    if (EPI == HX_EPI_PARTIAL) {
+        // lane = (row of 8, group of 4 columns): 128 contiguous bytes per row
+        float *y = a.y + blockIdx.y * a.split_stride;
+        const int nq = lane & 7;
+        for (int u = wave; u < Q; u += S) {              // 8 rows of one tile
+            const int t = u / (MG * 4), g = u / 4 % MG, ml = (u & 3) * 8 + (lane >> 3);
+            const int m = 32 * g + ml, nn = 32 * (t0 + t) + 4 * nq;
+            if (m < a.M && nn < a.N) {
+                const f32x4_t v = sum((t * MG + g) * 4 + (nq >> 1), (nq & 1) * 32 + (ml ^ nq));
+                *(f32x4_t *)(y + (size_t)m * a.N + nn) = v;
+            }
+        }
+    } else if (EPI == HX_EPI_SWIGLU) {
+        for (int u = wave; u < TN * MG; u += S) {
+            const int t = u / MG, g = u % MG, h = lane >> 5, ml = lane & 31, m = 32 * g + ml;
+            if (m < a.M && t0 + t < a.n_tiles) {
+                uint32_t pk[4];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const f32x4_t gt = sum(u * 4 + h, q * 32 + ml), up = sum(u * 4 + h + 2, q * 32 + ml);
+                    float v[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = (gt[i] / (1.0f + expf(-gt[i]))) * up[i];
+                    pk[2 * q] = hx_cvt_pk_bf16(v[0], v[1]);
+                    pk[2 * q + 1] = hx_cvt_pk_bf16(v[2], v[3]);
+                }
+                *(uint4 *)(a.mp + hx_xp_index(m, 16 * (t0 + t) + 8 * h, MG)) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+            }
+        }
+    } else {
+        for (int u = (wave + blockIdx.x) % S; u < TN * MG; u += S) {
+            const int t = u / MG, g = u % MG;
+            if (32 * g >= a.M || t0 + t >= a.n_tiles) continue;
+            f32x16_t v;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const f32x4_t q = sum(u * 4 + j, lane);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[4 * j + i] = q[i];
+            }
+            if (EPI == HX_EPI_LOGITS) hx_lm_greedy_tile(a.lm, v, 32 * g + (lane & 31), t0 + t, lane);
+            else                      hx_lm_sample_tile(a.lm, v, 32 * g + (lane & 31), t0 + t, lane);
+        }
+    }
+}
+
+template <int MG, int TN, int R>
+void launch_slice(int epilogue, const SliceArgs &a, int splits, hipStream_t st) {
+    const dim3 grid((a.n_tiles + TN - 1) / TN, splits), block(64 * SLICES);
+    if (epilogue == HX_EPI_PARTIAL) hipLaunchKernelGGL((gemm_slice_kernel<MG, TN, R, HX_EPI_PARTIAL>), grid, block, 0, st, a);
+    else if (TN == 2) return;                            // a long K is split: only partial results
+    else if (epilogue == HX_EPI_SWIGLU) hipLaunchKernelGGL((gemm_slice_kernel<MG, 1, R, HX_EPI_SWIGLU>), grid, block, 0, st, a);
+    else if (epilogue == HX_EPI_SAMPLE) hipLaunchKernelGGL((gemm_slice_kernel<MG, 1, R, HX_EPI_SAMPLE>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((gemm_slice_kernel<MG, 1, R, HX_EPI_LOGITS>), grid, block, 0, st, a);
+}
+
+}  // namespace
+
+// Whether a product of at most 128 rows runs here: the streaming kernel's most workgroups, a quarter of the tiles times the
+// most splits, would leave two fifths of the compute units without one (up to 64 tiles on 256; 112 tiles, 7B O: 7.7 / 11.4 us
+// there, 7.9 / 13.7 here at 3 / 37 rows).  K-splits: at least 24 k-steps each (1.5B QKV at 64 rows in 6 / 4 / 2 splits: 5.6 / 4.4 /
+// 5.2 us) and no more workgroups than compute units; two tiles per workgroup where that still leaves long ones.
+hx_slice_plan hx_plan_slice(int n_tiles, int k_steps, bool partial, int max_splits) {
+    const int cus = hx_device_cus();
+    hx_slice_plan p{0, 1};
+    if ((n_tiles + 3) / 4 * HX_MAX_SPLITS * 5 > cus * 3) return p;
+    p.tiles = partial && k_steps > 24 * HX_MAX_SPLITS ? 2 : 1;
+    const int groups = (n_tiles + p.tiles - 1) / p.tiles;
+    if (partial) p.splits = std::max(1, std::min({max_splits, k_steps / 24, cus / groups}));
+    return p;
+}
+
+int hx_launch_gemm_slice(const hx_engine *e, const hx_matrix *m, int batch, hx_slice_plan plan, const void *xp, int epilogue, float *y,
+                         void *mp_out, const hx_lm_args &lm, hipStream_t st) {
+    SliceArgs a;
+    a.wp = (const uint4 *)(e->weights + m->offset);
+    a.xp = (const uint4 *)xp;
+    a.k_steps = m->k_steps; a.n_tiles = m->n_tiles;
+    a.steps_per_split = (m->k_steps + plan.splits - 1) / plan.splits;
+    a.M = batch; a.N = m->N;
+    a.y = y; a.split_stride = (size_t)batch * m->N;
+    a.mp = (uint16_t *)mp_out;
+    a.lm = lm;
+    switch (hx_m_groups(batch) * 10 + plan.tiles) {
+        case 11: launch_slice<1, 1, 8>(epilogue, a, plan.splits, st); break;
+        case 21: launch_slice<2, 1, 6>(epilogue, a, plan.splits, st); break;
+        case 41: launch_slice<4, 1, 4>(epilogue, a, plan.splits, st); break;
+        case 12: launch_slice<1, 2, 6>(epilogue, a, plan.splits, st); break;
+        case 22: launch_slice<2, 2, 6>(epilogue, a, plan.splits, st); break;
+        case 42: launch_slice<4, 2, 3>(epilogue, a, plan.splits, st); break;
+        default: return hx_fail(HX_E_RANGE, "%d rows, %d tiles per workgroup: no such small product", batch, plan.tiles);
+    }
+    HX_CHECK_LAUNCH("gemm_slice");
+    return HX_OK;
+}

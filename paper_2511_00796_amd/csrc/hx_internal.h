@@ -347,9 +347,14 @@ int hx_launch_nucleus(const hx_engine *e, int batch, const float *logits, const 
 int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void *xp, int epilogue,
                    float *y /*partials or logits or NULL*/, void *mp_out, hipStream_t st,
                    const hx_sample_params *sample = nullptr);
+// gemm_slice.hip: small products of at most 128 rows
+struct hx_lm_args;
+struct hx_slice_plan { int tiles, splits; };     // 32-column tiles per workgroup (0: not this kernel), K-splits
+hx_slice_plan hx_plan_slice(int n_tiles, int k_steps, bool partial, int max_splits);
+int hx_launch_gemm_slice(const hx_engine *e, const hx_matrix *m, int batch, hx_slice_plan plan, const void *xp, int epilogue, float *y,
+                         void *mp_out, const hx_lm_args &lm, hipStream_t st);
 // gemm_wide.hip: products over several 256-row blocks at once (prompt rows)
 struct hx_wide_plan { int wnt, splits; };        // 32-column tiles per workgroup, K-splits
-struct hx_lm_args;
 int hx_wide_split_steps(const hx_matrix *m, int splits);      // k-steps of each split but the last: whole chunks of two
 hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, int epilogue, int max_splits = HX_MAX_SPLITS);
 int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, char *ws0, size_t block_stride, size_t xp_off,

@@ -1,0 +1,52 @@
+"""Products of matrices with few columns (gemm_slice.hip): every number of k-steps that leaves wavefronts without work or the ring
+part-filled, odd numbers of tiles, ragged last tiles, both sides of the row groups' edges, one and two tiles per workgroup, and
+the step to the streaming kernel.  Reference: the product in float64."""
+import pytest
+import torch
+
+from paper_2511_00796_amd import synth
+from test_gpu_prefill import build
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hx():
+    from paper_2511_00796_amd import binding
+    binding.load()
+    return binding
+
+
+# hidden x (heads) x intermediate x vocab.  k-steps of the down product: 1, 5, 23, 48 (two splits), 217 (one more than nine
+# splits of 24: two tiles per workgroup); columns: 64 to 2080 (65 tiles: the streaming kernel), 1000 (the last tile holds 8)
+SHAPES = {"k1": synth.ModelShape("sp-k1", 1, 64, 1, 1, 64, 16, 64), "k5": synth.ModelShape("sp-k5", 1, 96, 3, 1, 64, 80, 1000),
+          "k23": synth.ModelShape("sp-k23", 1, 352, 4, 2, 128, 368, 36), "k48": synth.ModelShape("sp-k48", 1, 768, 6, 1, 128, 768, 2048),
+          "k217": synth.ModelShape("sp-k217", 1, 480, 2, 2, 128, 3472, 2080)}
+
+
+@pytest.mark.parametrize("batch", [1, 31, 33, 64, 65, 100, 128])
+@pytest.mark.parametrize("name", sorted(SHAPES))
+def test_products_of_few_columns(hx, name, batch):
+    s = SHAPES[name]
+    eng = build(hx, s, 5, batch, 64)
+    w = {k: v.double().cuda() for k, v in synth.layer_weights(s, 0, 5).items()}
+    head = synth.global_weights(s, 5)["wlm"].double().cuda()
+    g = torch.Generator(device="cuda").manual_seed(7)
+    for kind, mat in ((hx.HX_T_WQKV, w["wqkv"]), (hx.HX_T_WO, w["wo"]), (hx.HX_T_WD, w["wd"]), (hx.HX_T_WG, None), (hx.HX_T_WLM, head)):
+        K = s.hidden if mat is None else mat.shape[0]
+        x = torch.randn(batch, K, generator=g, device="cuda").bfloat16().float()
+        y = eng.stage_linear(kind, 0, x, want_argmax=True) if kind == hx.HX_T_WLM else eng.stage_linear(kind, 0, x)
+        torch.cuda.synchronize()
+        if kind == hx.HX_T_WLM:
+            y, am = y
+            assert (am.long() == y.argmax(-1)).all()
+        xd = x.double()
+        if mat is None:
+            gate = xd @ w["wg"]
+            ref = gate * torch.sigmoid(gate) * (xd @ w["wu"])
+            # one bf16 rounding of the result (2^-8 at most with ties and the fp32 sums' own error)
+            assert y.shape == ref.shape and ((y.double() - ref).abs() <= ref.abs() * 2.0 ** -7 + 1e-5).all(), (name, kind)
+        else:
+            # fp32 sums of exact products: a few units of 2^-24 of the sum of magnitudes
+            ref = xd @ mat
+            assert y.shape == ref.shape and ((y.double() - ref).abs() <= 1e-5 * (xd.abs() @ mat.abs())).all(), (name, kind)
