@@ -114,7 +114,8 @@ __device__ __forceinline__ void norm_row(int b, float *__restrict__ x, const flo
     }
 }
 
-template <int MODE, int MAXS>
+// SPREAD: rows dealt to the XCDs in eighths (hx_row_of_workgroup)
+template <int MODE, int MAXS, bool SPREAD>
 __global__ __launch_bounds__(HX_NORM_THREADS) void norm_kernel(float *__restrict__ x, const float *__restrict__ x_in,
                                                               const int32_t *__restrict__ tokens,
                                                               const uint16_t *__restrict__ embed,
@@ -122,9 +123,9 @@ __global__ __launch_bounds__(HX_NORM_THREADS) void norm_kernel(float *__restrict
                                                               size_t split_stride, const uint16_t *__restrict__ gain,
                                                               int H, float eps, uint16_t *__restrict__ xp, int m_groups,
                                                               float *__restrict__ y_f32, int rows, size_t block_stride) {
-    const int b = hx_row_of_workgroup(blockIdx.x, rows);
-    if (b >= rows) return;
-    if (blockIdx.y) {               // further row blocks of a wide prompt call: same layout, block_stride bytes apart
+    const int b = SPREAD ? hx_row_of_workgroup(blockIdx.x, rows) : blockIdx.x;
+    if (SPREAD && b >= rows) return;
+    if (SPREAD && blockIdx.y) {               // further row blocks of a wide prompt call: same layout, block_stride bytes apart
         const size_t off = (size_t)blockIdx.y * block_stride;
         x = (float *)((char *)x + off);
         if (ypart) ypart = (const float *)((const char *)ypart + off);
@@ -160,7 +161,8 @@ int hx_launch_step_begin(const hx_engine *e, int batch, const int32_t *tokens, c
 
 int hx_launch_embed_norm(const hx_engine *e, int batch, const int32_t *tokens, size_t gain_off, hipStream_t st, int blocks,
                          size_t block_stride) {
-    hipLaunchKernelGGL((norm_kernel<0, 1>), dim3(hx_row_workgroups(batch), blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x),
+    const auto kernel = hx_spread_rows(batch) ? norm_kernel<0, 1, true> : norm_kernel<0, 1, false>;
+    hipLaunchKernelGGL(kernel, dim3(hx_row_workgroups(batch), blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x),
                        (const float *)nullptr, tokens, (const uint16_t *)(e->weights + e->embed),
                        (const float *)nullptr, 0, (size_t)0, (const uint16_t *)(e->weights + gain_off), e->cfg.hidden,
                        e->cfg.rms_eps, (uint16_t *)(e->ws + e->map.xp), hx_m_groups(batch), (float *)nullptr, batch, block_stride);
@@ -171,7 +173,7 @@ int hx_launch_embed_norm(const hx_engine *e, int batch, const int32_t *tokens, s
 int hx_launch_reduce_norm(const hx_engine *e, int batch, const float *ypart, int splits, size_t split_stride,
                           size_t gain_off, hipStream_t st, int blocks, size_t block_stride) {
 #define HX_REDUCE_NORM(MAXS)                                                                                      \
-    hipLaunchKernelGGL((norm_kernel<1, MAXS>), dim3(hx_row_workgroups(batch), blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x), \
+    hipLaunchKernelGGL((hx_spread_rows(batch) ? norm_kernel<1, MAXS, true> : norm_kernel<1, MAXS, false>), dim3(hx_row_workgroups(batch), blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x), \
                        (const float *)nullptr, (const int32_t *)nullptr, (const uint16_t *)nullptr, ypart, splits, \
                        split_stride, (const uint16_t *)(e->weights + gain_off), e->cfg.hidden, e->cfg.rms_eps,    \
                        (uint16_t *)(e->ws + e->map.xp), hx_m_groups(batch), (float *)nullptr, batch, block_stride)
@@ -185,7 +187,7 @@ int hx_launch_reduce_norm(const hx_engine *e, int batch, const float *ypart, int
 }
 
 int hx_launch_norm_only(const hx_engine *e, int batch, const float *x, size_t gain_off, float *y, hipStream_t st) {
-    hipLaunchKernelGGL((norm_kernel<2, 1>), dim3(hx_row_workgroups(batch)), dim3(HX_NORM_THREADS), 0, st, (float *)nullptr, x,
+    hipLaunchKernelGGL((hx_spread_rows(batch) ? norm_kernel<2, 1, true> : norm_kernel<2, 1, false>), dim3(hx_row_workgroups(batch)), dim3(HX_NORM_THREADS), 0, st, (float *)nullptr, x,
                        (const int32_t *)nullptr, (const uint16_t *)nullptr, (const float *)nullptr, 0, (size_t)0,
                        (const uint16_t *)(e->weights + gain_off), e->cfg.hidden, e->cfg.rms_eps, (uint16_t *)nullptr,
                        hx_m_groups(batch), y, batch, (size_t)0);

@@ -161,11 +161,11 @@ __host__ __device__ __forceinline__ int hx_m_groups(int batch) {
 // 16-byte pieces of the same lines (packed activations; in a prompt also V tiles, one or two bytes each): on one XCD its L2
 // merges them, on eight each writes a part of every line.  So workgroup x of more than 128 rows takes row x / 8 of the (x % 8)-th
 // eighth.  us, 14B, 4864 rows: norm 102 -> 85 (two partials), 84 -> 72 (one), of the embedding 63 -> 54; 7B, 2048 rows 31 -> 25,
-// 25 -> 18, rotation + append 17 -> 15.  Up to 128 rows these kernels wait for their loads: 1.5B, 64 rows 4.6 -> 4.8 that way.
-__host__ __device__ __forceinline__ int hx_row_workgroups(int rows) { return rows > 128 ? (rows + 7) / 8 * 8 : rows; }
-__host__ __device__ __forceinline__ int hx_row_of_workgroup(int x, int rows) {
-    return rows > 128 ? (x & 7) * ((rows + 7) / 8) + (x >> 3) : x;
-}
+// 25 -> 18, rotation + append 17 -> 15.  Up to 128 rows these kernels wait for their loads: 1.5B, 64 rows 4.6 -> 4.8 that way, and
+// even the question at run time costs 0.2 us a launch (the row count is one more load before the first), so it is a template's.
+__host__ __device__ __forceinline__ bool hx_spread_rows(int rows) { return rows > 128; }
+__host__ __device__ __forceinline__ int hx_row_workgroups(int rows) { return hx_spread_rows(rows) ? (rows + 7) / 8 * 8 : rows; }
+__host__ __device__ __forceinline__ int hx_row_of_workgroup(int x, int rows) { return (x & 7) * ((rows + 7) / 8) + (x >> 3); }
 
 // element offset (in bf16) of activation (m, k) inside a packed X buffer with m_groups groups
 __host__ __device__ __forceinline__ size_t hx_xp_index(int m, int k, int m_groups) {

@@ -118,7 +118,8 @@ int hx_launch_kv_scatter(const hx_kv *kv, int layer, const void *k, const void *
 // What bounds it is the latency of its loads on a decode step (hence all of them at once: 16 values per thread took two
 // rounds) and their number on a prompt call.  us: 1.5B, 64 sequences 6.9 -> 4.9, 7B, 128 sequences 7.1 -> 6.3; one partial,
 // 7B, 2048 rows 25 -> 18, 14B, 4864 rows, 8-bit cache 88 -> 58.
-template <int D, bool FP8, int MAXS>
+// SPREAD: rows dealt to the XCDs in eighths (hx_row_of_workgroup)
+template <int D, bool FP8, int MAXS, bool SPREAD>
 __global__ __launch_bounds__(128) void rope_append_kernel(const float *__restrict__ ypart, int splits,
                                                           size_t split_stride, const uint16_t *__restrict__ bias,
                                                           int has_bias, const float *__restrict__ cs,
@@ -129,9 +130,9 @@ __global__ __launch_bounds__(128) void rope_append_kernel(const float *__restric
                                                           int max_batch, int rows, size_t block_stride) {
     constexpr int HALF = D / 2;
     constexpr int RPH = HALF / 4;                         // rotation items per head
-    const int b = hx_row_of_workgroup(blockIdx.x, rows);
-    if (b >= rows) return;
-    if (blockIdx.z) {               // further row blocks of a wide prompt call: same layout, block_stride bytes apart
+    const int b = SPREAD ? hx_row_of_workgroup(blockIdx.x, rows) : blockIdx.x;
+    if (SPREAD && b >= rows) return;
+    if (SPREAD && blockIdx.z) {               // further row blocks of a wide prompt call: same layout, block_stride bytes apart
         const size_t off = (size_t)blockIdx.z * block_stride;
         ypart = (const float *)((const char *)ypart + off);
         cs = (const float *)((const char *)cs + off);
@@ -238,7 +239,7 @@ int hx_launch_rope_append(const hx_engine *e, const hx_kv *kv, int layer, int ba
     const int items = (e->cfg.n_q_heads + e->cfg.n_kv_heads) * (e->D / 8) + e->cfg.n_kv_heads * (e->D / 8);
     dim3 grid(hx_row_workgroups(batch), (items + 127) / 128, blocks), block(128);
 #define HX_ROPE_LAUNCH(DD, F8, MAXS)                                                                            \
-    hipLaunchKernelGGL((rope_append_kernel<DD, F8, MAXS>), grid, block, 0, st, ypart, splits, split_stride, bias, \
+    hipLaunchKernelGGL((hx_spread_rows(batch) ? rope_append_kernel<DD, F8, MAXS, true> : rope_append_kernel<DD, F8, MAXS, false>), grid, block, 0, st, ypart, splits, split_stride, bias, \
                        e->cfg.qkv_bias, cs, positions, (const int32_t *)(e->ws + e->map.blk_new), pool_layer, kv->block_bytes, \
                        kv->tile_bytes, qp, e->cfg.n_q_heads, e->cfg.n_kv_heads, e->G, e->cfg.max_batch, batch, block_stride)
 #define HX_ROPE_LAUNCH_S(DD, F8)                                                                                \
