@@ -14,8 +14,10 @@ SOURCES = ["api.hip", "kv_cache.hip", "attention.hip", "attention_prompt.hip", "
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # -ffp-contract=off: products and sums round separately unless fmaf is written out;
 # packed fp32 instructions are switched off for the device pass.
+# Kernel arguments: the first 14 registers' worth (56 bytes) arrive with the launch instead of being loaded by every
+# wavefront, so the kernels of a step have the arguments of their first loads in front, and no structs there.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16", "-Wall", "-Wno-unused-function"]
 
 
 # host-side sanitizers (address + undefined behaviour) for the CPU check of the library's host logic; device code is

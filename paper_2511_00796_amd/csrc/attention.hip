@@ -175,14 +175,11 @@ __device__ __forceinline__ void stream_tiles(AttnState<D> &st, const bf16x8_t (&
 }
 
 template <int D, int PF>
-__global__ __launch_bounds__(64) void attn_splitk_kernel(const char *__restrict__ pool_layer, size_t block_bytes,
-                                                         const uint16_t *__restrict__ qp,
-                                                         const int32_t *__restrict__ table, int max_blocks,
-                                                         const int32_t *__restrict__ pre,
-                                                         const int32_t *__restrict__ lens,
-                                                         const int32_t *__restrict__ sched, int n_kv, int G,
-                                                         float scale_log2e, float *__restrict__ part_ml,
-                                                         float *__restrict__ part_o) {
+__global__ __launch_bounds__(64) void attn_splitk_kernel(const int32_t *__restrict__ sched, const int32_t *__restrict__ pre,
+                                         const int32_t *__restrict__ lens, const char *__restrict__ pool_layer, size_t block_bytes,
+                                         const uint16_t *__restrict__ qp, const int32_t *__restrict__ table, int max_blocks,
+                                         int n_kv, int G, float scale_log2e, float *__restrict__ part_ml,
+                                         float *__restrict__ part_o) {
     const int w = blockIdx.x;
     const int lane = threadIdx.x;
     const int S = sched[0], Nt = sched[1];
@@ -399,13 +396,12 @@ int hx_launch_attention(const hx_engine *e, const hx_kv *kv, int layer, int batc
     const char *pool_layer = kv->pool + (size_t)layer * kv->layer_bytes;
     const hx_attn_bufs own = hx_attn_bufs_of(e);
     const hx_attn_bufs &a = bufs ? *bufs : own;
-    const int n_kv = e->cfg.n_kv_heads;
     const float scale_log2e = (float)(1.4426950408889634 / sqrt((double)e->D));
     (void)seq_lens; (void)batch;
     dim3 grid(e->attn_waves), block(64);
 #define HX_ATTN_ARGS                                                                                             \
-    pool_layer, kv->block_bytes, (const uint16_t *)a.qp, table, max_blocks, (const int32_t *)a.pre,              \
-        (const int32_t *)a.lens, (const int32_t *)a.sched, n_kv, e->G, scale_log2e, a.part_ml, a.part_o
+    (const int32_t *)a.sched, (const int32_t *)a.pre, (const int32_t *)a.lens, pool_layer, kv->block_bytes,      \
+        (const uint16_t *)a.qp, table, max_blocks, e->cfg.n_kv_heads, e->G, scale_log2e, a.part_ml, a.part_o
     if (e->D == 128) hipLaunchKernelGGL((attn_splitk_kernel<128, 3>), grid, block, 0, st, HX_ATTN_ARGS);
     else             hipLaunchKernelGGL((attn_splitk_kernel<64, 4>), grid, block, 0, st, HX_ATTN_ARGS);
 #undef HX_ATTN_ARGS

@@ -125,14 +125,11 @@ __device__ __forceinline__ void stream_tiles8(AttnState8<D> &st, const bf16x8_t 
 }
 
 template <int D, int PF>
-__global__ __launch_bounds__(64) void attn_splitk_fp8_kernel(const char *__restrict__ pool_layer, size_t block_bytes,
-                                                             const uint16_t *__restrict__ qp,
-                                                             const int32_t *__restrict__ table, int max_blocks,
-                                                             const int32_t *__restrict__ pre,
-                                                             const int32_t *__restrict__ lens,
-                                                             const int32_t *__restrict__ sched, int n_kv, int G,
-                                                             float scale_log2e, float *__restrict__ part_ml,
-                                                             float *__restrict__ part_o) {
+__global__ __launch_bounds__(64) void attn_splitk_fp8_kernel(const int32_t *__restrict__ sched, const int32_t *__restrict__ pre,
+                                         const int32_t *__restrict__ lens, const char *__restrict__ pool_layer, size_t block_bytes,
+                                         const uint16_t *__restrict__ qp, const int32_t *__restrict__ table, int max_blocks,
+                                         int n_kv, int G, float scale_log2e, float *__restrict__ part_ml,
+                                         float *__restrict__ part_o) {
     const int w = blockIdx.x;
     const int lane = threadIdx.x;
     const int S = sched[0], Nt = sched[1];
@@ -219,9 +216,9 @@ int hx_launch_attention_fp8(const hx_engine *e, const hx_kv *kv, int layer, cons
     const hx_attn_bufs &a = bufs ? *bufs : own;
     const float scale_log2e = (float)(1.4426950408889634 / sqrt((double)e->D));
     dim3 grid(e->attn_waves), block(64);
-#define HX_ATTN8_ARGS                                                                                            \
-    pool_layer, kv->block_bytes, (const uint16_t *)a.qp, table, max_blocks, (const int32_t *)a.pre,              \
-        (const int32_t *)a.lens, (const int32_t *)a.sched, e->cfg.n_kv_heads, e->G, scale_log2e, a.part_ml, a.part_o
+#define HX_ATTN8_ARGS                                                                                             \
+    (const int32_t *)a.sched, (const int32_t *)a.pre, (const int32_t *)a.lens, pool_layer, kv->block_bytes,      \
+        (const uint16_t *)a.qp, table, max_blocks, e->cfg.n_kv_heads, e->G, scale_log2e, a.part_ml, a.part_o
     // ring depths: 128: see the header; 64: depth 6 (every depth from 2 to 12 is right since the operand hold is
     // ordered behind the products; the tests cover long runs)
     if (e->D == 128) hipLaunchKernelGGL((attn_splitk_fp8_kernel<128, 4>), grid, block, 0, st, HX_ATTN8_ARGS);

@@ -116,13 +116,12 @@ __device__ __forceinline__ void norm_row(int b, float *__restrict__ x, const flo
 
 // SPREAD: rows dealt to the XCDs in eighths (hx_row_of_workgroup)
 template <int MODE, int MAXS, bool SPREAD>
-__global__ __launch_bounds__(HX_NORM_THREADS) void norm_kernel(float *__restrict__ x, const float *__restrict__ x_in,
-                                                              const int32_t *__restrict__ tokens,
-                                                              const uint16_t *__restrict__ embed,
-                                                              const float *__restrict__ ypart, int splits,
-                                                              size_t split_stride, const uint16_t *__restrict__ gain,
-                                                              int H, float eps, uint16_t *__restrict__ xp, int m_groups,
-                                                              float *__restrict__ y_f32, int rows, size_t block_stride) {
+__global__ __launch_bounds__(HX_NORM_THREADS) void norm_kernel(float *__restrict__ x, const float *__restrict__ ypart, size_t split_stride,
+                                                              int splits, int H, const uint16_t *__restrict__ gain,
+                                                              uint16_t *__restrict__ xp, float eps, int m_groups,
+                                                              const float *__restrict__ x_in, const int32_t *__restrict__ tokens,
+                                                              const uint16_t *__restrict__ embed, float *__restrict__ y_f32,
+                                                              int rows, size_t block_stride) {
     const int b = SPREAD ? hx_row_of_workgroup(blockIdx.x, rows) : blockIdx.x;
     if (SPREAD && b >= rows) return;
     if (SPREAD && blockIdx.y) {               // further row blocks of a wide prompt call: same layout, block_stride bytes apart
@@ -163,9 +162,9 @@ int hx_launch_embed_norm(const hx_engine *e, int batch, const int32_t *tokens, s
                          size_t block_stride) {
     const auto kernel = hx_spread_rows(batch) ? norm_kernel<0, 1, true> : norm_kernel<0, 1, false>;
     hipLaunchKernelGGL(kernel, dim3(hx_row_workgroups(batch), blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x),
-                       (const float *)nullptr, tokens, (const uint16_t *)(e->weights + e->embed),
-                       (const float *)nullptr, 0, (size_t)0, (const uint16_t *)(e->weights + gain_off), e->cfg.hidden,
-                       e->cfg.rms_eps, (uint16_t *)(e->ws + e->map.xp), hx_m_groups(batch), (float *)nullptr, batch, block_stride);
+                       (const float *)nullptr, (size_t)0, 0, e->cfg.hidden, (const uint16_t *)(e->weights + gain_off),
+                       (uint16_t *)(e->ws + e->map.xp), e->cfg.rms_eps, hx_m_groups(batch), (const float *)nullptr, tokens,
+                       (const uint16_t *)(e->weights + e->embed), (float *)nullptr, batch, block_stride);
     HX_CHECK_LAUNCH("embed_norm");
     return HX_OK;
 }
@@ -173,10 +172,11 @@ int hx_launch_embed_norm(const hx_engine *e, int batch, const int32_t *tokens, s
 int hx_launch_reduce_norm(const hx_engine *e, int batch, const float *ypart, int splits, size_t split_stride,
                           size_t gain_off, hipStream_t st, int blocks, size_t block_stride) {
 #define HX_REDUCE_NORM(MAXS)                                                                                      \
-    hipLaunchKernelGGL((hx_spread_rows(batch) ? norm_kernel<1, MAXS, true> : norm_kernel<1, MAXS, false>), dim3(hx_row_workgroups(batch), blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x), \
-                       (const float *)nullptr, (const int32_t *)nullptr, (const uint16_t *)nullptr, ypart, splits, \
-                       split_stride, (const uint16_t *)(e->weights + gain_off), e->cfg.hidden, e->cfg.rms_eps,    \
-                       (uint16_t *)(e->ws + e->map.xp), hx_m_groups(batch), (float *)nullptr, batch, block_stride)
+    hipLaunchKernelGGL((hx_spread_rows(batch) ? norm_kernel<1, MAXS, true> : norm_kernel<1, MAXS, false>),       \
+                       dim3(hx_row_workgroups(batch), blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x), \
+                       ypart, split_stride, splits, e->cfg.hidden, (const uint16_t *)(e->weights + gain_off),     \
+                       (uint16_t *)(e->ws + e->map.xp), e->cfg.rms_eps, hx_m_groups(batch), (const float *)nullptr, \
+                       (const int32_t *)nullptr, (const uint16_t *)nullptr, (float *)nullptr, batch, block_stride)
     if (splits == 1) HX_REDUCE_NORM(1);
     else if (splits == 2) HX_REDUCE_NORM(2);
     else if (splits <= 4) HX_REDUCE_NORM(4);
@@ -187,10 +187,10 @@ int hx_launch_reduce_norm(const hx_engine *e, int batch, const float *ypart, int
 }
 
 int hx_launch_norm_only(const hx_engine *e, int batch, const float *x, size_t gain_off, float *y, hipStream_t st) {
-    hipLaunchKernelGGL((hx_spread_rows(batch) ? norm_kernel<2, 1, true> : norm_kernel<2, 1, false>), dim3(hx_row_workgroups(batch)), dim3(HX_NORM_THREADS), 0, st, (float *)nullptr, x,
-                       (const int32_t *)nullptr, (const uint16_t *)nullptr, (const float *)nullptr, 0, (size_t)0,
-                       (const uint16_t *)(e->weights + gain_off), e->cfg.hidden, e->cfg.rms_eps, (uint16_t *)nullptr,
-                       hx_m_groups(batch), y, batch, (size_t)0);
+    hipLaunchKernelGGL((hx_spread_rows(batch) ? norm_kernel<2, 1, true> : norm_kernel<2, 1, false>), dim3(hx_row_workgroups(batch)),
+                       dim3(HX_NORM_THREADS), 0, st, (float *)nullptr, (const float *)nullptr, (size_t)0, 0, e->cfg.hidden,
+                       (const uint16_t *)(e->weights + gain_off), (uint16_t *)nullptr, e->cfg.rms_eps, hx_m_groups(batch), x,
+                       (const int32_t *)nullptr, (const uint16_t *)nullptr, y, batch, (size_t)0);
     HX_CHECK_LAUNCH("norm_only");
     return HX_OK;
 }

@@ -20,31 +20,24 @@ namespace {
 
 constexpr int SLICES = 4;         // wavefronts of a workgroup
 
-struct SliceArgs {
-    const uint4 *wp, *xp;         // packed weights, packed activations
-    int k_steps, n_tiles, steps_per_split;
-    int M, N;
-    float *y;                     // PARTIAL: [splits][M][N]
-    size_t split_stride;
-    uint16_t *mp;                 // SWIGLU: packed bf16 output
-    hx_lm_args lm;                // LM head
-};
-
 // TN tiles per workgroup, MG m-groups, R k-steps in flight per wavefront
 template <int MG, int TN, int R, int EPI>
-__global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(SliceArgs a) {
+__global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(const uint4 *__restrict__ a_wp, const uint4 *__restrict__ a_xp,
+                                                               int a_k_steps, int a_n_tiles, int a_steps_per_split, int a_M, int a_N,
+                                                               int a_split_stride, float *__restrict__ a_y, uint16_t *__restrict__ a_mp,
+                                                               hx_lm_args a_lm) {
     constexpr int S = SLICES;
     constexpr int Q = TN * MG * 4;                       // 16-byte quads of accumulators per lane
     __shared__ u32x4_t red[S * Q * 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int t0 = blockIdx.x * TN;
-    const int split0 = blockIdx.y * a.steps_per_split, split1 = min(a.k_steps, split0 + a.steps_per_split);
+    const int split0 = blockIdx.y * a_steps_per_split, split1 = min(a_k_steps, split0 + a_steps_per_split);
     // step i of this wavefront is k-step split0 + wave + S * i
     const int n = (split1 - split0 - wave + S - 1) / S;
     const u32x4_t *wrow[TN];
 #pragma unroll
-    for (int t = 0; t < TN; ++t) wrow[t] = (const u32x4_t *)a.wp + ((size_t)min(t0 + t, a.n_tiles - 1) * a.k_steps + split0 + wave) * 64 + lane;
-    const u32x4_t *xrow = (const u32x4_t *)a.xp + (size_t)(split0 + wave) * MG * 64 + lane;
+    for (int t = 0; t < TN; ++t) wrow[t] = (const u32x4_t *)a_wp + ((size_t)min(t0 + t, a_n_tiles - 1) * a_k_steps + split0 + wave) * 64 + lane;
+    const u32x4_t *xrow = (const u32x4_t *)a_xp + (size_t)(split0 + wave) * MG * 64 + lane;
     f32x16_t acc[TN][MG];
 #pragma unroll
     for (int t = 0; t < TN; ++t)
@@ -107,20 +100,20 @@ __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(SliceArgs a) {
     };
     if (EPI == HX_EPI_PARTIAL) {
         // lane = (row of 8, group of 4 columns): 128 contiguous bytes per row
-        float *y = a.y + blockIdx.y * a.split_stride;
+        float *y = a_y + (size_t)blockIdx.y * a_split_stride;
         const int nq = lane & 7;
         for (int u = wave; u < Q; u += S) {              // 8 rows of one tile
             const int t = u / (MG * 4), g = u / 4 % MG, ml = (u & 3) * 8 + (lane >> 3);
             const int m = 32 * g + ml, nn = 32 * (t0 + t) + 4 * nq;
-            if (m < a.M && nn < a.N) {
+            if (m < a_M && nn < a_N) {
                 const f32x4_t v = sum((t * MG + g) * 4 + (nq >> 1), (nq & 1) * 32 + (ml ^ nq));
-                *(f32x4_t *)(y + (size_t)m * a.N + nn) = v;
+                *(f32x4_t *)(y + (size_t)m * a_N + nn) = v;
             }
         }
     } else if (EPI == HX_EPI_SWIGLU) {
         for (int u = wave; u < TN * MG; u += S) {
             const int t = u / MG, g = u % MG, h = lane >> 5, ml = lane & 31, m = 32 * g + ml;
-            if (m < a.M && t0 + t < a.n_tiles) {
+            if (m < a_M && t0 + t < a_n_tiles) {
                 uint32_t pk[4];
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
@@ -131,13 +124,13 @@ __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(SliceArgs a) {
                     pk[2 * q] = hx_cvt_pk_bf16(v[0], v[1]);
                     pk[2 * q + 1] = hx_cvt_pk_bf16(v[2], v[3]);
                 }
-                *(uint4 *)(a.mp + hx_xp_index(m, 16 * (t0 + t) + 8 * h, MG)) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+                *(uint4 *)(a_mp + hx_xp_index(m, 16 * (t0 + t) + 8 * h, MG)) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
             }
         }
     } else {
         for (int u = (wave + blockIdx.x) % S; u < TN * MG; u += S) {
             const int t = u / MG, g = u % MG;
-            if (32 * g >= a.M || t0 + t >= a.n_tiles) continue;
+            if (32 * g >= a_M || t0 + t >= a_n_tiles) continue;
             f32x16_t v;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -145,20 +138,32 @@ __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(SliceArgs a) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[4 * j + i] = q[i];
             }
-            if (EPI == HX_EPI_LOGITS) hx_lm_greedy_tile(a.lm, v, 32 * g + (lane & 31), t0 + t, lane);
-            else                      hx_lm_sample_tile(a.lm, v, 32 * g + (lane & 31), t0 + t, lane);
+            if (EPI == HX_EPI_LOGITS) hx_lm_greedy_tile(a_lm, v, 32 * g + (lane & 31), t0 + t, lane);
+            else                      hx_lm_sample_tile(a_lm, v, 32 * g + (lane & 31), t0 + t, lane);
         }
     }
 }
 
+struct SliceArgs {
+    const uint4 *wp, *xp;         // packed weights, packed activations
+    int k_steps, n_tiles, steps_per_split, M, N, split_stride;      // split_stride: elements between the splits of y
+    float *y;                     // PARTIAL: [splits][M][N]
+    uint16_t *mp;                 // SWIGLU: packed bf16 output
+    hx_lm_args lm;                // LM head
+};
+
 template <int MG, int TN, int R>
 void launch_slice(int epilogue, const SliceArgs &a, int splits, hipStream_t st) {
     const dim3 grid((a.n_tiles + TN - 1) / TN, splits), block(64 * SLICES);
-    if (epilogue == HX_EPI_PARTIAL) hipLaunchKernelGGL((gemm_slice_kernel<MG, TN, R, HX_EPI_PARTIAL>), grid, block, 0, st, a);
+#define HX_SLICE(TT, EPI)                                                                                                  \
+    hipLaunchKernelGGL((gemm_slice_kernel<MG, TT, R, EPI>), grid, block, 0, st, a.wp, a.xp, a.k_steps, a.n_tiles, a.steps_per_split, \
+                       a.M, a.N, a.split_stride, a.y, a.mp, a.lm)
+    if (epilogue == HX_EPI_PARTIAL) HX_SLICE(TN, HX_EPI_PARTIAL);
     else if (TN == 2) return;                            // a long K is split: only partial results
-    else if (epilogue == HX_EPI_SWIGLU) hipLaunchKernelGGL((gemm_slice_kernel<MG, 1, R, HX_EPI_SWIGLU>), grid, block, 0, st, a);
-    else if (epilogue == HX_EPI_SAMPLE) hipLaunchKernelGGL((gemm_slice_kernel<MG, 1, R, HX_EPI_SAMPLE>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((gemm_slice_kernel<MG, 1, R, HX_EPI_LOGITS>), grid, block, 0, st, a);
+    else if (epilogue == HX_EPI_SWIGLU) HX_SLICE(1, HX_EPI_SWIGLU);
+    else if (epilogue == HX_EPI_SAMPLE) HX_SLICE(1, HX_EPI_SAMPLE);
+    else HX_SLICE(1, HX_EPI_LOGITS);
+#undef HX_SLICE
 }
 
 }  // namespace
@@ -185,7 +190,7 @@ int hx_launch_gemm_slice(const hx_engine *e, const hx_matrix *m, int batch, hx_s
     a.k_steps = m->k_steps; a.n_tiles = m->n_tiles;
     a.steps_per_split = (m->k_steps + plan.splits - 1) / plan.splits;
     a.M = batch; a.N = m->N;
-    a.y = y; a.split_stride = (size_t)batch * m->N;
+    a.y = y; a.split_stride = batch * m->N;
     a.mp = (uint16_t *)mp_out;
     a.lm = lm;
     switch (hx_m_groups(batch) * 10 + plan.tiles) {

@@ -120,14 +120,13 @@ int hx_launch_kv_scatter(const hx_kv *kv, int layer, const void *k, const void *
 // 7B, 2048 rows 25 -> 18, 14B, 4864 rows, 8-bit cache 88 -> 58.
 // SPREAD: rows dealt to the XCDs in eighths (hx_row_of_workgroup)
 template <int D, bool FP8, int MAXS, bool SPREAD>
-__global__ __launch_bounds__(128) void rope_append_kernel(const float *__restrict__ ypart, int splits,
-                                                          size_t split_stride, const uint16_t *__restrict__ bias,
-                                                          int has_bias, const float *__restrict__ cs,
+__global__ __launch_bounds__(128) void rope_append_kernel(const float *__restrict__ ypart, int split_stride, int splits, int n_q,
+                                                          int n_kv, const float *__restrict__ cs,
+                                                          const uint16_t *__restrict__ bias, int has_bias, int max_batch,
                                                           const int32_t *__restrict__ positions,
                                                           const int32_t *__restrict__ blk_new,
                                                           char *pool_layer, size_t block_bytes, size_t tile_bytes,
-                                                          uint16_t *__restrict__ qp, int n_q, int n_kv, int G,
-                                                          int max_batch, int rows, size_t block_stride) {
+                                                          uint16_t *__restrict__ qp, int G, int rows, size_t block_stride) {
     constexpr int HALF = D / 2;
     constexpr int RPH = HALF / 4;                         // rotation items per head
     const int b = SPREAD ? hx_row_of_workgroup(blockIdx.x, rows) : blockIdx.x;
@@ -155,7 +154,7 @@ __global__ __launch_bounds__(128) void rope_append_kernel(const float *__restric
     const float *src = ypart + (size_t)b * qkv_dim + col;
 #pragma unroll
     for (int sp = 0; sp < MAXS; ++sp) {
-        const float *p = src + min(sp, splits - 1) * split_stride;
+        const float *p = src + (size_t)min(sp, splits - 1) * split_stride;
         ya[sp] = *(const f32x4_t *)p;
         yc[sp] = *(const f32x4_t *)(p + gap);
     }
@@ -239,9 +238,10 @@ int hx_launch_rope_append(const hx_engine *e, const hx_kv *kv, int layer, int ba
     const int items = (e->cfg.n_q_heads + e->cfg.n_kv_heads) * (e->D / 8) + e->cfg.n_kv_heads * (e->D / 8);
     dim3 grid(hx_row_workgroups(batch), (items + 127) / 128, blocks), block(128);
 #define HX_ROPE_LAUNCH(DD, F8, MAXS)                                                                            \
-    hipLaunchKernelGGL((hx_spread_rows(batch) ? rope_append_kernel<DD, F8, MAXS, true> : rope_append_kernel<DD, F8, MAXS, false>), grid, block, 0, st, ypart, splits, split_stride, bias, \
-                       e->cfg.qkv_bias, cs, positions, (const int32_t *)(e->ws + e->map.blk_new), pool_layer, kv->block_bytes, \
-                       kv->tile_bytes, qp, e->cfg.n_q_heads, e->cfg.n_kv_heads, e->G, e->cfg.max_batch, batch, block_stride)
+    hipLaunchKernelGGL((hx_spread_rows(batch) ? rope_append_kernel<DD, F8, MAXS, true> : rope_append_kernel<DD, F8, MAXS, false>), grid, block, 0, st, \
+                       ypart, (int)split_stride, splits, e->cfg.n_q_heads, e->cfg.n_kv_heads, cs, bias, e->cfg.qkv_bias, e->cfg.max_batch, \
+                       positions, (const int32_t *)(e->ws + e->map.blk_new), pool_layer, kv->block_bytes, kv->tile_bytes, qp, e->G, \
+                       batch, block_stride)
 #define HX_ROPE_LAUNCH_S(DD, F8)                                                                                \
     do {                                                                                                        \
         if (splits == 1) HX_ROPE_LAUNCH(DD, F8, 1);                                                             \
