@@ -152,6 +152,7 @@ static size_t map_workspace(hx_engine *e) {
     m->samp_z = take(B * e->wlm.n_tiles * 4);
     m->samp_m = take(B * e->wlm.n_tiles * 4);
     m->samp_s = take(B * e->wlm.n_tiles * 4);
+    m->nucleus = take(hx_nucleus_bytes(c->vocab, c->max_batch));
     size_t widest = wide;
     if ((size_t)c->intermediate > widest) widest = c->intermediate;
     if ((size_t)e->q_dim > widest) widest = e->q_dim;

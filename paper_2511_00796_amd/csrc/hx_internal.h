@@ -238,6 +238,7 @@ struct hx_ws_map {          // byte offsets in the workspace
     size_t prompt_part_o;   // fp32 [slots][4][16][D]
     size_t amax_val, amax_idx;  // fp32 / int32 [max_batch][lm n_tiles]   (sampling: best perturbed score and its column)
     size_t samp_z, samp_m, samp_s;  // fp32 [max_batch][lm n_tiles]: scaled logit of the candidate, tile max, tile sum of exp
+    size_t nucleus;         // bins and lists of a nucleus draw (sampling.hip)
     size_t scratch_f32;     // fp32 [max_batch][max(hidden, q_dim, inter, qkv_dim)] stage-hook staging
     size_t total;
 };
@@ -342,6 +343,7 @@ int hx_launch_attention_fp8(const hx_engine *e, const hx_kv *kv, int layer, cons
                             hipStream_t st, const hx_attn_bufs *bufs = nullptr);
 
 // sampling.hip
+size_t hx_nucleus_bytes(int vocab, int max_batch);
 int hx_launch_nucleus(const hx_engine *e, int batch, const float *logits, const hx_sample_params *sample,
                       int32_t *tokens_out, float *logprobs_out, hipStream_t st);
 int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void *xp, int epilogue,

@@ -1,0 +1,62 @@
+"""Nucleus selection by bins: rows at the edges of one and several workgroups per row, with so many equal logits that no list
+takes the cut bin's entries, that one list of several overflows, or that the cut falls on a bin of one entry.  Logits are planted
+through the LM head (one input column is 1, so column j's logit is the weight of row 0); the oracle is the sort of the definition."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2511_00796_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hx():
+    from paper_2511_00796_amd import binding
+    binding.load()
+    return binding
+
+
+def planted(law, V):
+    r = np.random.default_rng(V)
+    if law == "normal":
+        return r.normal(0, 2, V)
+    if law == "equal":                       # one bin holds the whole row
+        return np.zeros(V)
+    if law == "two_levels":                  # 5 000 equal entries in front, more than a part's list, spread or together
+        z = np.full(V, -3.0)
+        z[: min(5000, V // 2)] = 1.0
+        return z
+    z = r.normal(0, 1, V)                     # peaked: one entry carries nearly everything
+    z[V // 3] = 30.0
+    return z
+
+
+@pytest.mark.parametrize("law", ["normal", "equal", "two_levels", "peaked"])
+@pytest.mark.parametrize("vocab", [8, 1000, 32764, 32768, 65540, 300000])
+def test_kept_sets_of_planted_rows(hx, vocab, law):
+    s = synth.ModelShape("nb", 1, 32, 1, 1, 64, 16, vocab)
+    rows = 3
+    eng = hx.Engine(s, rows, 64)
+    z = torch.from_numpy(planted(law, vocab)).to(torch.bfloat16)
+    wlm = torch.zeros(s.hidden, vocab, dtype=torch.bfloat16)
+    wlm[0] = z
+    eng.pack_globals({"embed": torch.zeros(vocab, s.hidden, dtype=torch.bfloat16).cuda(),
+                      "gf": torch.ones(s.hidden, dtype=torch.bfloat16).cuda(), "wlm": wlm.cuda()})
+    x = torch.zeros(rows, s.hidden, device="cuda")
+    x[:, 0] = torch.tensor([1.0, 0.5, 2.0])
+    pos = torch.tensor([3, 4, 5], dtype=torch.int32, device="cuda")
+    compared = 0
+    for share in (0.05, 0.5, 0.97):
+        top_p = (int(share * vocab) + 0.5) / vocab          # between two multiples of 1 / vocab: never on a cut of equal entries
+        y, tok, lp, n = [t.cpu().numpy() for t in eng.stage_lm_head_top_p(x, pos, 1.0, top_p, 99)]
+        assert np.array_equal(y, x[:, :1].cpu().numpy() * z.float().numpy()[None])
+        otok, olp, on, margin, gap = oracle.sample_top_p(y, 1.0, top_p, 99, np.arange(rows), pos.cpu().numpy())
+        firm = margin > 1e-6                  # further from the cut than a sum of 3e5 fp32 exponentials is exact
+        assert np.array_equal(n[firm], on[firm]), (top_p, n, on, margin)
+        same = firm & (gap > 1e-4)            # fp32 perturbed scores on both sides
+        assert np.array_equal(tok[same], otok[same])
+        assert np.abs(lp[same] - olp[same]).max(initial=0.0) <= 2e-4
+        compared += int(same.sum())
+    assert compared >= 3
