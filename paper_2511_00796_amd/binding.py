@@ -20,7 +20,7 @@ HX_OK, HX_E_NULL, HX_E_CONFIG, HX_E_SHAPE, HX_E_ALIGN, HX_E_TOO_SMALL, HX_E_RANG
  HX_T_WLM) = range(11)
 
 EXPORTS = ["hx_last_error", "hx_weights_bytes", "hx_workspace_bytes", "hx_kv_bytes", "hx_engine_create",
-           "hx_engine_destroy", "hx_weights_pack", "kv_alloc", "kv_free", "prefill_fill", "hx_kv_gather",
+           "hx_engine_destroy", "hx_weights_pack", "hx_weights_pack_many", "kv_alloc", "kv_free", "prefill_fill", "hx_kv_gather",
            "decode_step", "decode_step_sample", "decode_step_top_p", "prefill_chunk", "prefill_rows", "hx_prefill_workspace_bytes",
            "hx_validate_step_inputs", "hx_set_attn_capture", "hx_stage_schedule", "hx_attention_waves", "hx_plan_product",
            "hx_stage_rope_append", "hx_stage_attention", "hx_stage_attention_static", "hx_stage_rmsnorm", "hx_stage_linear", "hx_stage_linear_rows", "hx_stage_lm_head_top_p",
@@ -70,6 +70,7 @@ def load():
         "hx_engine_create": [cfgp, vp, sz, vp, sz, C.POINTER(vp)],
         "hx_engine_destroy": [vp],
         "hx_weights_pack": [vp, C.c_int, C.c_int, vp, i64, i64, vp],
+        "hx_weights_pack_many": [vp, i32, C.POINTER(i32), C.c_int, C.POINTER(vp), C.POINTER(i64), C.POINTER(i64), vp],
         "kv_alloc": [vp, vp, sz, i64, C.POINTER(vp)],
         "kv_free": [vp],
         "prefill_fill": [vp, C.c_int, vp, vp, vp, vp, i32, i32, i64, vp],
@@ -190,14 +191,29 @@ class Engine:
         rows, cols = (src.shape[0], 1) if src.dim() == 1 else src.shape
         _check(load().hx_weights_pack(self.handle, kind, layer, _ptr(src), rows, cols, _stream()))
 
+    def _pack(self, layer: int, tensors) -> None:
+        """tensors: (kind, tensor).  Those on the device go in one launch; one that has to be copied there first goes alone, so
+        that the copies are not all held at once."""
+        here = [(k, t) for k, t in tensors if t.device == self.weights.device]
+        for kind, t in tensors:
+            if t.device != self.weights.device:
+                self.weights_pack(kind, layer, t.to(self.device))
+        n = len(here)
+        if n == 0:
+            return
+        for _, t in here:
+            assert t.dtype == torch.bfloat16 and t.is_cuda and t.is_contiguous() and t.dim() in (1, 2)
+        _check(load().hx_weights_pack_many(self.handle, n, (C.c_int32 * n)(*[k for k, _ in here]), layer,
+                                           (C.c_void_p * n)(*[t.data_ptr() for _, t in here]), (C.c_int64 * n)(*[t.shape[0] for _, t in here]),
+                                           (C.c_int64 * n)(*[t.shape[1] if t.dim() == 2 else 1 for _, t in here]), _stream()))
+
     def pack_layer(self, layer: int, w: Dict[str, torch.Tensor]) -> None:
-        for name, kind in (("g1", HX_T_G1), ("wqkv", HX_T_WQKV), ("bqkv", HX_T_BQKV), ("wo", HX_T_WO),
-                           ("g2", HX_T_G2), ("wg", HX_T_WG), ("wu", HX_T_WU), ("wd", HX_T_WD)):
-            self.weights_pack(kind, layer, w[name].to(self.device))
+        self._pack(layer, [(kind, w[name]) for name, kind in (
+            ("wg", HX_T_WG), ("wu", HX_T_WU), ("wd", HX_T_WD), ("wqkv", HX_T_WQKV), ("wo", HX_T_WO), ("g1", HX_T_G1), ("g2", HX_T_G2),
+            ("bqkv", HX_T_BQKV))])
 
     def pack_globals(self, w: Dict[str, torch.Tensor]) -> None:
-        for name, kind in (("embed", HX_T_EMBED), ("gf", HX_T_GF), ("wlm", HX_T_WLM)):
-            self.weights_pack(kind, 0, w[name].to(self.device))
+        self._pack(0, [(kind, w[name]) for name, kind in (("wlm", HX_T_WLM), ("embed", HX_T_EMBED), ("gf", HX_T_GF))])
 
     # -- decode
     def decode_step(self, kv: "KVCache", tokens, positions, seq_lens, block_table, logits: Optional[torch.Tensor],

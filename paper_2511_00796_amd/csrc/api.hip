@@ -263,10 +263,9 @@ extern "C" int hx_set_attn_capture(hx_engine *e, float *attn_dev) {
 }
 
 // ---- weight packing ----------------------------------------------------------------------------------------------
-extern "C" int hx_weights_pack(hx_engine *e, int kind, int layer, const void *src, int64_t rows, int64_t cols, void *stream) {
-    if (!e) return hx_fail(HX_E_NULL, "engine is NULL");
+// checks one tensor and says where it goes
+static int pack_target(const hx_engine *e, int kind, int layer, const void *src, int64_t rows, int64_t cols, hx_pack_tensor *t) {
     if (!src) return hx_fail(HX_E_NULL, "src is NULL");
-    hipStream_t st = (hipStream_t)stream;
     const hx_model_config *c = &e->cfg;
     const bool per_layer = !(kind == HX_T_EMBED || kind == HX_T_GF || kind == HX_T_WLM);
     if (per_layer && (layer < 0 || layer >= c->n_layers)) return hx_fail(HX_E_SHAPE, "layer %d out of range", layer);
@@ -277,25 +276,55 @@ extern "C" int hx_weights_pack(hx_engine *e, int kind, int layer, const void *sr
                            (long long)cols, (long long)r, (long long)cc);
         return HX_OK;
     };
-    auto copy_vec = [&](size_t off, size_t n) -> int {
-        HX_CHECK_HIP(hipMemcpyAsync(e->weights + off, src, n * 2, hipMemcpyDeviceToDevice, st));
+    auto vec = [&](size_t off, int64_t n) -> int {
+        *t = hx_pack_tensor{src, rows, cols, nullptr, off, 3};
+        int rc;
+        if ((rc = want(n, 1)) && (rc = want(1, n))) return rc;
         return HX_OK;
     };
-    int rc;
+    auto matrix = [&](const hx_matrix *m, int64_t r, int64_t cc, int phase) -> int {
+        *t = hx_pack_tensor{src, rows, cols, m, m->offset, phase};
+        return want(r, cc);
+    };
     switch (kind) {
-        case HX_T_EMBED: if ((rc = want(c->vocab, c->hidden))) return rc; return copy_vec(e->embed, (size_t)c->vocab * c->hidden);
-        case HX_T_GF:    if ((rc = want(c->hidden, 1)) && (rc = want(1, c->hidden))) return rc; return copy_vec(e->gf, c->hidden);
-        case HX_T_G1:    if ((rc = want(c->hidden, 1)) && (rc = want(1, c->hidden))) return rc; return copy_vec(lm->g1, c->hidden);
-        case HX_T_G2:    if ((rc = want(c->hidden, 1)) && (rc = want(1, c->hidden))) return rc; return copy_vec(lm->g2, c->hidden);
-        case HX_T_BQKV:  if ((rc = want(e->qkv_dim, 1)) && (rc = want(1, e->qkv_dim))) return rc; return copy_vec(lm->bqkv, e->qkv_dim);
-        case HX_T_WQKV:  if ((rc = want(c->hidden, e->qkv_dim))) return rc; return hx_launch_pack_matrix(e, &lm->wqkv, src, rows, cols, 0, st);
-        case HX_T_WO:    if ((rc = want(e->q_dim, c->hidden))) return rc; return hx_launch_pack_matrix(e, &lm->wo, src, rows, cols, 0, st);
-        case HX_T_WG:    if ((rc = want(c->hidden, c->intermediate))) return rc; return hx_launch_pack_matrix(e, &lm->wgu, src, rows, cols, 1, st);
-        case HX_T_WU:    if ((rc = want(c->hidden, c->intermediate))) return rc; return hx_launch_pack_matrix(e, &lm->wgu, src, rows, cols, 2, st);
-        case HX_T_WD:    if ((rc = want(c->intermediate, c->hidden))) return rc; return hx_launch_pack_matrix(e, &lm->wd, src, rows, cols, 0, st);
-        case HX_T_WLM:   if ((rc = want(c->hidden, c->vocab))) return rc; return hx_launch_pack_matrix(e, &e->wlm, src, rows, cols, 0, st);
+        case HX_T_EMBED: *t = hx_pack_tensor{src, rows, cols, nullptr, e->embed, 3}; return want(c->vocab, c->hidden);
+        case HX_T_GF:    return vec(e->gf, c->hidden);
+        case HX_T_G1:    return vec(lm->g1, c->hidden);
+        case HX_T_G2:    return vec(lm->g2, c->hidden);
+        case HX_T_BQKV:  return vec(lm->bqkv, e->qkv_dim);
+        case HX_T_WQKV:  return matrix(&lm->wqkv, c->hidden, e->qkv_dim, 0);
+        case HX_T_WO:    return matrix(&lm->wo, e->q_dim, c->hidden, 0);
+        case HX_T_WG:    return matrix(&lm->wgu, c->hidden, c->intermediate, 1);
+        case HX_T_WU:    return matrix(&lm->wgu, c->hidden, c->intermediate, 2);
+        case HX_T_WD:    return matrix(&lm->wd, c->intermediate, c->hidden, 0);
+        case HX_T_WLM:   return matrix(&e->wlm, c->hidden, c->vocab, 0);
         default: return hx_fail(HX_E_SHAPE, "unknown tensor kind %d", kind);
     }
+}
+
+extern "C" int hx_weights_pack(hx_engine *e, int kind, int layer, const void *src, int64_t rows, int64_t cols, void *stream) {
+    if (!e) return hx_fail(HX_E_NULL, "engine is NULL");
+    hx_pack_tensor t;
+    int rc = pack_target(e, kind, layer, src, rows, cols, &t);
+    if (rc) return rc;
+    hipStream_t st = (hipStream_t)stream;
+    if (t.phase == 3) {
+        HX_CHECK_HIP(hipMemcpyAsync(e->weights + t.offset, src, (size_t)(rows * cols) * 2, hipMemcpyDeviceToDevice, st));
+        return HX_OK;
+    }
+    return hx_launch_pack(e, &t, 1, st);
+}
+
+extern "C" int hx_weights_pack_many(hx_engine *e, int32_t n, const int32_t *kinds, int layer, const void *const *srcs, const int64_t *rows,
+                                    const int64_t *cols, void *stream) {
+    if (!e || !kinds || !srcs || !rows || !cols) return hx_fail(HX_E_NULL, "a pointer argument is NULL");
+    if (n < 1 || n > HX_PACK_MANY) return hx_fail(HX_E_RANGE, "%d tensors in one call, 1 to %d", n, HX_PACK_MANY);
+    hx_pack_tensor t[HX_PACK_MANY];
+    for (int i = 0; i < n; ++i) {
+        const int rc = pack_target(e, kinds[i], layer, srcs[i], rows[i], cols[i], &t[i]);
+        if (rc) return rc;
+    }
+    return hx_launch_pack(e, t, n, (hipStream_t)stream);
 }
 
 // ---- KV cache ------------------------------------------------------------------------------------------------------

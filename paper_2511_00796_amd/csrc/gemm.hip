@@ -16,6 +16,9 @@
 #include <algorithm>
 #include <mutex>
 
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));     // at any element
+
 // ---- weight packing ------------------------------------------------------------------------------------------
 // A workgroup turns 32 k x 512 columns of the row-major source (two k-steps) into operand order.  Thread = 8 k x 8
 // columns: eight 16-byte loads, a wavefront's each 1 KiB of one source row; transposed in registers to one 16-byte unit
@@ -23,21 +26,22 @@
 // PHASE 0: tile column c = source column 32 * nt + c; PHASE 1 / 2 (gate / up): columns 0..15 / 16..31 of a tile, from
 // source column 16 * nt + c % 16 (runs of 256 bytes).  What bounds it is memory: see hx_launch_pack_matrix.
 #define HX_PACK_COLS 512
-// The source may lie at any element: the 16-byte loads are written as copies from a 2-byte-aligned address (one load
+// The source may lie at any element: the 16-byte loads are from a 2-byte-aligned type (one load
 // instruction, which the hardware takes at any alignment), and only a group of columns that ends past the row goes by elements.
+// Loads and stores are non-temporal: everything passes once, and the globals take 764 us with them, 1020 without (see below).
+// bx, by: 512 columns, two k-steps
 template <int PHASE>
-__global__ __launch_bounds__(256) void pack_matrix_kernel(const uint16_t *__restrict__ src, int64_t rows, int64_t cols,
-                                                          uint4 *__restrict__ dst, int k_steps, int n_tiles) {
-    __shared__ uint4 lds[2048];                         // unit of column c, k-step s, half kh: see place() below
+__device__ __forceinline__ void pack_matrix_block(const uint16_t *__restrict__ src, int64_t rows, int64_t cols, uint4 *__restrict__ dst,
+                                                  int k_steps, int n_tiles, int bx, int by, uint4 *lds) {
     constexpr int TC = PHASE == 0 ? 32 : 16;            // source columns per tile
     const int tid = threadIdx.x, cg = tid & 63, rg = tid >> 6;            // rg = 2 * k-step + half
-    const int64_t c0 = (int64_t)blockIdx.x * HX_PACK_COLS, col = c0 + 8 * cg, k0 = (int64_t)blockIdx.y * 32 + 8 * rg;
+    const int64_t c0 = (int64_t)bx * HX_PACK_COLS, col = c0 + 8 * cg, k0 = (int64_t)by * 32 + 8 * rg;
     uint4 in[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
         in[r] = make_uint4(0u, 0u, 0u, 0u);
         const uint16_t *p = src + (k0 + r) * cols + col;
-        if (k0 + r < rows && col + 8 <= cols) __builtin_memcpy(&in[r], p, 16);
+        if (k0 + r < rows && col + 8 <= cols) in[r] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_any_t *)p));
     }
     if (col < cols && col + 8 > cols) {
 #pragma unroll
@@ -70,27 +74,75 @@ __global__ __launch_bounds__(256) void pack_matrix_kernel(const uint16_t *__rest
         const int u = i * 256 + tid;
         const int c = u % TC, kh = (u / TC) & 1, s = (u / (2 * TC)) & 1;
         const int64_t nt = c0 / TC + u / (4 * TC);
-        const int ks = 2 * (int)blockIdx.y + s;
+        const int ks = 2 * by + s;
         if (nt < n_tiles && ks < k_steps)
-            dst[((size_t)nt * k_steps + ks) * 64 + kh * 32 + (PHASE == 2 ? 16 : 0) + c] = lds[place(u)];
+            __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, lds[place(u)]), (u32x4_t *)dst + ((size_t)nt * k_steps + ks) * 64 + kh * 32 + (PHASE == 2 ? 16 : 0) + c);
     }
 }
 
-// us per matrix, 7B, source read and packed copy written (a thread per 8 k of one column, 64-byte pieces of the source rows,
-// before): gate 53 = 5.1 TB/s (104), QKV 14 (19), down 57 (65), LM head 411 = 5.3 TB/s (531); a device copy moves 4.8-5.3.
-// From a source one element off a 16-byte boundary, same matrix again and again: O 9.7 (16.2; element loads in this kernel
-// 20.7), gate 49 (138; 82), LM head 403 (700; 619), and with 152 068 columns 423 (578; 628).
-int hx_launch_pack_matrix(const hx_engine *e, const hx_matrix *m, const void *src, int64_t rows, int64_t cols,
-                          int col_phase, hipStream_t st) {
-    const int64_t all = (int64_t)m->n_tiles * (col_phase ? 16 : 32);      // columns of the tiles, zeros beyond `cols` included
-    dim3 grid((unsigned)((all + HX_PACK_COLS - 1) / HX_PACK_COLS), (m->k_steps + 1) / 2), block(256);
-    uint4 *dst = (uint4 *)(e->weights + m->offset);
-#define HX_PACK(P) hipLaunchKernelGGL((pack_matrix_kernel<P>), grid, block, 0, st, (const uint16_t *)src, rows, cols, dst, m->k_steps, m->n_tiles)
-    if (col_phase == 0) HX_PACK(0);
-    else if (col_phase == 1) HX_PACK(1);
-    else HX_PACK(2);
-#undef HX_PACK
-    HX_CHECK_LAUNCH("pack_matrix");
+// One tensor of a call.  first: its first workgroup; across: workgroups per two k-steps (vectors: all of them).
+struct PackItem {
+    const uint16_t *src;
+    char *dst;
+    int64_t rows, cols;
+    int k_steps, n_tiles, phase, across;      // phase 0 plain, 1 gate, 2 up, 3 vector (copied)
+    unsigned first;
+};
+struct PackList { PackItem item[HX_PACK_MANY]; int n; };
+#define HX_PACK_COPY 4096                    // elements of a vector per workgroup
+
+// All tensors of a call in one launch: the small ones fill the end of the large ones, and nothing waits between them.
+__global__ __launch_bounds__(256) void pack_kernel(PackList list) {
+    __shared__ uint4 lds[2048];               // unit of column c, k-step s, half kh: see place() above
+    int i = 0;
+    while (i + 1 < list.n && blockIdx.x >= list.item[i + 1].first) ++i;
+    const PackItem &t = list.item[i];
+    const unsigned blk = blockIdx.x - t.first;
+    if (t.phase == 3) {
+        const int64_t n = t.rows * t.cols, e0 = (int64_t)blk * HX_PACK_COPY + threadIdx.x * 8;
+        uint16_t *dst = (uint16_t *)t.dst;
+        constexpr int U = HX_PACK_COPY / 2048;
+        u32x4_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) if (e0 + u * 2048 + 8 <= n) v[u] = __builtin_nontemporal_load((const u32x4_any_t *)(t.src + e0 + u * 2048));
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t e = e0 + u * 2048;
+            if (e + 8 <= n) __builtin_nontemporal_store(v[u], (u32x4_t *)(dst + e));
+            else for (int64_t k = e; k < n; ++k) dst[k] = t.src[k];
+        }
+        return;
+    }
+    const int by = (int)(blk / (unsigned)t.across), bx = (int)(blk % (unsigned)t.across);
+    if (t.phase == 0) pack_matrix_block<0>(t.src, t.rows, t.cols, (uint4 *)t.dst, t.k_steps, t.n_tiles, bx, by, lds);
+    else if (t.phase == 1) pack_matrix_block<1>(t.src, t.rows, t.cols, (uint4 *)t.dst, t.k_steps, t.n_tiles, bx, by, lds);
+    else pack_matrix_block<2>(t.src, t.rows, t.cols, (uint4 *)t.dst, t.k_steps, t.n_tiles, bx, by, lds);
+}
+
+// 7B, source read and packed copy written: a layer 178 us = 5.2 TB/s (eight launches and copies 203, and as many boundaries),
+// the globals 764 us = 5.7 TB/s (pack 412, the runtime's copy of the embedding 429, and a boundary; copying 16 384 elements per
+// workgroup instead of 4 096: 827).  A device copy moves 4.8-5.3 here.
+int hx_launch_pack(const hx_engine *e, const hx_pack_tensor *tensors, int n, hipStream_t st) {
+    if (n < 1 || n > HX_PACK_MANY) return hx_fail(HX_E_RANGE, "%d tensors in one call, 1 to %d", n, HX_PACK_MANY);
+    PackList list;
+    list.n = n;
+    int64_t at = 0;
+    for (int i = 0; i < n; ++i) {
+        const hx_pack_tensor &t = tensors[i];
+        PackItem &o = list.item[i];
+        o = PackItem{(const uint16_t *)t.src, e->weights + t.offset, t.rows, t.cols, 0, 0, t.phase, 1, (unsigned)at};
+        if (t.phase == 3) {
+            at += (t.rows * t.cols + HX_PACK_COPY - 1) / HX_PACK_COPY;
+        } else {
+            o.k_steps = t.m->k_steps; o.n_tiles = t.m->n_tiles;
+            const int64_t all = (int64_t)t.m->n_tiles * (t.phase ? 16 : 32);      // columns of the tiles, zeros beyond `cols` included
+            o.across = (int)((all + HX_PACK_COLS - 1) / HX_PACK_COLS);
+            at += (int64_t)o.across * ((t.m->k_steps + 1) / 2);
+        }
+        if (at > 0x7fffffff) return hx_fail(HX_E_RANGE, "the tensors need %lld workgroups", (long long)at);
+    }
+    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)at), dim3(256), 0, st, list);
+    HX_CHECK_LAUNCH("pack");
     return HX_OK;
 }
 
@@ -123,7 +175,6 @@ struct GemmArgs {
     float *samp_z, *samp_m, *samp_s;   // [M][n_tiles]
 };
 
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ u32x4_t hx_stream_load(const uint4 *p) {   // read-once data: non-temporal
     return __builtin_nontemporal_load((const u32x4_t *)p);
 }

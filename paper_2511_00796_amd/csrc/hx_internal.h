@@ -304,8 +304,14 @@ int hx_launch_attention(const hx_engine *e, const hx_kv *kv, int layer, int batc
 int hx_launch_combine(const hx_engine *e, int batch, float *attn_f32_out, hipStream_t st, const hx_attn_bufs *bufs = nullptr);
 
 // gemm.hip
-int hx_launch_pack_matrix(const hx_engine *e, const hx_matrix *m, const void *src, int64_t rows, int64_t cols,
-                          int col_phase /*0 plain, 1 gate, 2 up*/, hipStream_t st);
+struct hx_pack_tensor {      // phase 0 plain matrix, 1 gate, 2 up: into m; 3: copied to the offset
+    const void *src;
+    int64_t rows, cols;
+    const hx_matrix *m;
+    size_t offset;
+    int phase;
+};
+int hx_launch_pack(const hx_engine *e, const hx_pack_tensor *tensors, int n, hipStream_t st);
 enum { HX_EPI_PARTIAL = 0, HX_EPI_SWIGLU = 1, HX_EPI_LOGITS = 2, HX_EPI_SAMPLE = 3 };
 
 // parameters of a sampled step (NULL = greedy)

@@ -45,6 +45,45 @@ def test_products_of_packed_weights(hx, intermediate, vocab, shift):
             assert ((y - xd @ w.double()).abs() <= 1e-5 * (xd.abs() @ w.double().abs())).all()   # fp32 sums of exact products
 
 
+@pytest.mark.parametrize("shift", [0, 1, 4])
+@pytest.mark.parametrize("intermediate,vocab", [(688, 1000), (16, 132), (2064, 40004)])
+def test_tensors_packed_together_and_one_by_one(hx, intermediate, vocab, shift):
+    """One launch for all tensors of a layer, or of the model, leaves the bytes that one call per tensor leaves; tensors on the
+    host go along; a refused tensor keeps the others from being packed."""
+    s = synth.ModelShape("many", 2, 96, 3, 1, 64, intermediate, vocab)
+    nbytes = hx.Engine(s, 4, 64).weights.numel()
+    one, many, mixed = [hx.Engine(s, 4, 64, weights=torch.zeros(nbytes, dtype=torch.uint8, device="cuda")) for _ in range(3)]
+    g = torch.Generator(device="cuda").manual_seed(5)
+
+    def fresh(*shape):
+        n = int(np.prod(shape))
+        return torch.empty(n + 8, dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.05, generator=g)[shift:shift + n].view(*shape)
+
+    kinds = {"g1": (hx.HX_T_G1, (96,)), "wqkv": (hx.HX_T_WQKV, (96, 320)), "bqkv": (hx.HX_T_BQKV, (320,)), "wo": (hx.HX_T_WO, (192, 96)),
+             "g2": (hx.HX_T_G2, (96,)), "wg": (hx.HX_T_WG, (96, intermediate)), "wu": (hx.HX_T_WU, (96, intermediate)),
+             "wd": (hx.HX_T_WD, (intermediate, 96))}
+    top = {"embed": (hx.HX_T_EMBED, (vocab, 96)), "gf": (hx.HX_T_GF, (96,)), "wlm": (hx.HX_T_WLM, (96, vocab))}
+    for layer, group in ((0, kinds), (1, kinds), (None, top)):
+        w = {n: fresh(*sh) for n, (_, sh) in group.items()}
+        for n, (k, _) in group.items():
+            one.weights_pack(k, layer or 0, w[n])
+        half = {n: t.cpu() if i % 2 else t for i, (n, t) in enumerate(w.items())}
+        if layer is None:
+            many.pack_globals(w)
+            mixed.pack_globals(half)
+        else:
+            many.pack_layer(layer, w)
+            mixed.pack_layer(layer, half)
+    torch.cuda.synchronize()
+    assert torch.equal(one.weights, many.weights) and torch.equal(one.weights, mixed.weights)
+    bad = {n: fresh(*sh) for n, (_, sh) in kinds.items()}
+    bad["wd"] = fresh(intermediate, 95)
+    with pytest.raises(hx.HexError):
+        many.pack_layer(1, bad)
+    torch.cuda.synchronize()
+    assert torch.equal(one.weights, many.weights)
+
+
 @pytest.mark.parametrize("cache", ["bf16", "fp8"])
 @pytest.mark.parametrize("d,lens", [(128, [500]), (128, [520]), (128, [8000, 17, 3000]), (64, [4096]), (64, [1, 900])])
 def test_combine_of_many_partials(hx, d, lens, cache, monkeypatch):
