@@ -102,6 +102,13 @@ __device__ __forceinline__ void hx_hold_operands(const unsigned int __attribute_
     else if constexpr (N == 2) asm volatile("s_nop 3" : "+v"(acc) : "v"(op[0]), "v"(op[1]));
     else static_assert(N == 2 || N == 4, "operand steps of head sizes 64 and 128");
 }
+// Behind 16x16x32 products of four operands, each with the high and the low part of the probabilities, into four accumulators.
+__device__ __forceinline__ void hx_hold_operands(const unsigned int __attribute__((ext_vector_type(4))) (&v)[4],
+                                                 const unsigned int __attribute__((ext_vector_type(4))) &hi,
+                                                 const unsigned int __attribute__((ext_vector_type(4))) &lo, f32x4_t &a0, f32x4_t &a1,
+                                                 f32x4_t &a2, f32x4_t &a3) {
+    asm volatile("s_nop 3" : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3) : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(hi), "v"(lo));
+}
 // The same for 32x32x16 products (attention_prompt.hip), which have never been seen to suffer (in builds without these statements
 // the kernel had a hundred such writes 2 to 6 slots behind them, and its results were right): free of cost, and one rule for
 // all attention kernels.  Behind a chain over D / 16 operand steps, and behind the products of the
