@@ -80,10 +80,12 @@ struct AttnState {
 
 // Streams `nblk` (1..128) consecutive blocks of one pair: tokens [t0, t1), t0 a multiple of 16.  blk_lo / blk_hi
 // hold the physical ids: lane i of blk_lo = block i, lane i of blk_hi = block 64 + i.
-// PF = tiles in flight (register ring).  The loop has no prologue and no conditional load: it starts PF tiles
-// early (those iterations see only masked-out tokens and zero operands) and every iteration requests the tile
-// PF ahead into the slot it has just finished with; past the end of the run the request goes to the packed
-// query (small, cache-resident, finite), so the load stream is unconditional and the compiler keeps exactly
+// PF = tiles in flight (register ring): 8 KiB per wavefront, 64 KiB per compute unit, which is what a compute unit keeps
+// outstanding; more only queues up, and a run of few tiles asks for more past its end.  us per launch with 3 / 2 / 1 tiles of
+// 8 KiB: 7B, 128 sequences 351 / 347 / 339, 1.5B, 256 of them 157.5 / 151.5 / 147.5, 64 53.4 / 51.1 / 49.3; 7B, 8 short ones 15.6 / - / 9.2.
+// The loop has no prologue and no conditional load: it starts PF tiles early (iterations that only request) and every
+// iteration requests the tile PF ahead into the slot it has just finished with; past the end of the run the request goes to the
+// packed query (small, cache-resident, finite), so the load stream is unconditional and the compiler keeps exactly
 // PF - 1 tiles outstanding behind every wait.
 template <int D, int PF>
 __device__ __forceinline__ void stream_tiles(AttnState<D> &st, const bf16x8_t (&qop)[D / 32], const char *pool_layer,
@@ -102,6 +104,7 @@ __device__ __forceinline__ void stream_tiles(AttnState<D> &st, const bf16x8_t (&
         for (int s = 0; s < PF; ++s) {
             const int i = (rd - 1) * PF + s;                   // tile of this iteration; < 0 while the ring fills
             const int tok0 = t0 + i * 16 + qd * 4;             // this lane's 4 tokens
+            if (rd > 0) {
             // scores of 16 tokens x 16 query heads
             f32x4_t sc = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -124,8 +127,8 @@ __device__ __forceinline__ void stream_tiles(AttnState<D> &st, const bf16x8_t (&
             u32x4_t vv[D / 32];
 #pragma unroll
             for (int q = 0; q < D / 32; ++q) vv[q] = ring[s][D / 32 + q];
-            if (i < 0 || t0 + (i + 1) * 16 > t1) {             // wave-uniform: a tile with missing tokens
-                const int valid = (i < 0) ? 0 : (t1 - tok0);
+            if (t0 + (i + 1) * 16 > t1) {                      // wave-uniform: a tile with missing tokens
+                const int valid = t1 - tok0;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) s4[r] = r < valid ? s4[r] : -INFINITY;
                 const uint32_t m01 = valid >= 2 ? 0xffffffffu : (valid == 1 ? 0x0000ffffu : 0u);
@@ -164,6 +167,7 @@ __device__ __forceinline__ void stream_tiles(AttnState<D> &st, const bf16x8_t (&
                 uint2 lo = make_uint2(vv[q].x, vv[q].y), hi = make_uint2(vv[q].z, vv[q].w);
                 st.o[2 * q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, lo), pop_lo, st.o[2 * q], 0, 0, 0);
                 st.o[2 * q + 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, hi), pop_lo, st.o[2 * q + 1], 0, 0, 0);
+            }
             }
             // the slot is free: request tile i + PF into it (or the query once the run is exhausted)
             const int nx = i + PF;
@@ -402,8 +406,8 @@ int hx_launch_attention(const hx_engine *e, const hx_kv *kv, int layer, int batc
 #define HX_ATTN_ARGS                                                                                             \
     (const int32_t *)a.sched, (const int32_t *)a.pre, (const int32_t *)a.lens, pool_layer, kv->block_bytes,      \
         (const uint16_t *)a.qp, table, max_blocks, e->cfg.n_kv_heads, e->G, scale_log2e, a.part_ml, a.part_o
-    if (e->D == 128) hipLaunchKernelGGL((attn_splitk_kernel<128, 3>), grid, block, 0, st, HX_ATTN_ARGS);
-    else             hipLaunchKernelGGL((attn_splitk_kernel<64, 4>), grid, block, 0, st, HX_ATTN_ARGS);
+    if (e->D == 128) hipLaunchKernelGGL((attn_splitk_kernel<128, 1>), grid, block, 0, st, HX_ATTN_ARGS);
+    else             hipLaunchKernelGGL((attn_splitk_kernel<64, 2>), grid, block, 0, st, HX_ATTN_ARGS);
 #undef HX_ATTN_ARGS
     HX_CHECK_LAUNCH("attn_splitk");
     return HX_OK;
