@@ -179,31 +179,40 @@ __device__ __forceinline__ u32x4_t hx_stream_load(const uint4 *p) {   // read-on
     return __builtin_nontemporal_load((const u32x4_t *)p);
 }
 
-template <int MG, int WK> struct GemmGeom {
+// Weight tiles in flight per consumer.  A compute unit keeps about 64 KiB outstanding: what goes beyond only queues up in front
+// of the activations, and splits of few k-steps run in whole revolutions.  So 8, but for two shapes that lose by it: the four and
+// five consumers of 128 rows, which wait for activations more than for weights, and four tiles of gate|up.  us, 16 -> 8: 7B at 3
+// rows gate|up 44.0 -> 41.7, down 24.2 -> 22.5, QKV 7.8 -> 7.0, O 7.8 -> 7.1; at 37 rows 45.2 -> 44.2, 27.6 -> 26.6, 10.5 -> 9.7, 11.1 -> 10.2,
+// LM head 188 -> 185, at 128 rows 227 -> 220; kept: 7B at 128 rows gate|up 54.0 (57.2), down 37.1 (39.4), 14B gate|up at 64 47.4 (48.4).
+template <int MG, int WN, int EPI> constexpr int gemm_ring() {
+    return WN == 10 || MG == 1 || (MG == 2 && !(WN == 4 && EPI == HX_EPI_SWIGLU)) ? HX_GEMM_RING / 2 : HX_GEMM_RING;
+}
+
+template <int MG, int WK, int RING> struct GemmGeom {
     static constexpr int NBUF = 4;                                  // stages of at most 32 KiB
     static constexpr int KC0 = 32 / (WK * MG);
-    static constexpr int KC = KC0 > 8 ? 8 : (KC0 < 1 ? 1 : KC0);   // k-steps per LDS chunk
+    static constexpr int KC = KC0 > RING / 2 ? RING / 2 : (KC0 < 1 ? 1 : KC0);   // k-steps per LDS chunk
     static constexpr int SLICE_U4 = KC * MG * 64;                   // uint4 per k-slice per stage
     static constexpr int PVT = WK * KC * MG;                        // 1-KiB copies per stage
     static constexpr int NP = PVT > 16 ? 2 : 1;                     // producer wavefronts
     static constexpr int PVP = PVT / NP;                            // copies per producer per stage
     static constexpr int STAGE_BYTES = WK * SLICE_U4 * 16;
 };
-template <int MG, int WN, int WK> constexpr int gemm_lds_bytes() {
-    constexpr int stages = GemmGeom<MG, WK>::NBUF * GemmGeom<MG, WK>::STAGE_BYTES;
+template <int MG, int WN, int WK, int RING> constexpr int gemm_lds_bytes() {
+    constexpr int stages = GemmGeom<MG, WK, RING>::NBUF * GemmGeom<MG, WK, RING>::STAGE_BYTES;
     constexpr int red = (WK - 1) * WN * MG * 4096;
     return stages > red ? stages : red;
 }
 
 template <int MG, int WN, int WK, int EPI>
-__global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK>::NP)) void gemm_stream_kernel(
+__global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK, gemm_ring<MG, WN, EPI>()>::NP)) void gemm_stream_kernel(
     const uint4 *__restrict__ a_wp, const uint4 *__restrict__ a_xp, int a_k_steps, int a_n_tiles, int a_tile0,
     int a_tile_end, int a_steps_per_split, int a_steps_per_wave, int a_M, int a_N, float *__restrict__ a_y, size_t a_split_stride,
     uint16_t *__restrict__ a_mp, float *__restrict__ a_amax_val, int32_t *__restrict__ a_amax_idx,
     const int32_t *__restrict__ a_positions, const int32_t *__restrict__ a_row_ids, float a_inv_t, uint32_t a_key0,
     uint32_t a_key1, float *__restrict__ a_samp_z, float *__restrict__ a_samp_m, float *__restrict__ a_samp_s) {
-    using GG = GemmGeom<MG, WK>;
-    constexpr int RING = HX_GEMM_RING;
+    constexpr int RING = gemm_ring<MG, WN, EPI>();
+    using GG = GemmGeom<MG, WK, RING>;
     constexpr int NBUF = GG::NBUF;
     constexpr int KC = GG::KC, CPR = RING / KC, SLICE_U4 = GG::SLICE_U4, NC = WN * WK;
     // with at most 8 wavefronts per workgroup each may use 256 registers: enough to read B operands ahead
@@ -446,7 +455,8 @@ __global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK>::NP)) void gemm_st
 
 template <int MG, int WN, int WK, int EPI>
 static int launch_one(dim3 grid, hipStream_t st, const GemmArgs &a) {
-    constexpr int lds = gemm_lds_bytes<MG, WN, WK>();
+    constexpr int RING = gemm_ring<MG, WN, EPI>();
+    constexpr int lds = gemm_lds_bytes<MG, WN, WK, RING>();
     // the opt-in for more than 64 KiB of LDS is per kernel: once per instantiation, whichever thread comes first
     static std::once_flag once;
     static hipError_t configured = hipSuccess;
@@ -455,7 +465,7 @@ static int launch_one(dim3 grid, hipStream_t st, const GemmArgs &a) {
                                          hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (configured != hipSuccess) return hx_fail(HX_E_HIP, "hipFuncSetAttribute: %s", hipGetErrorString(configured));
-    dim3 block(64 * (WN * WK + GemmGeom<MG, WK>::NP));
+    dim3 block(64 * (WN * WK + GemmGeom<MG, WK, RING>::NP));
     hipLaunchKernelGGL((gemm_stream_kernel<MG, WN, WK, EPI>), grid, block, lds, st, HX_GEMM_ARGS);
     return HX_OK;
 }
