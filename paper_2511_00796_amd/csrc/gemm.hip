@@ -528,6 +528,11 @@ static gemm_launch plan_product(int n_tiles, int k_steps, bool partial) {
     gemm_launch best{4, 1, 1, 0};
     double best_cost = 1e300;
     const int max_s = partial ? splits_allowed(HX_MAX_SPLITS) : 1;
+    int a, b, c;
+    if (forced_shape(&a, &b, &c) && c <= max_s && ((b == 1 && a >= 4 && a <= 6) || (a == 4 && b == 2)) && k_steps / (b * c) >= 1)
+        return gemm_launch{a, b, c, 0};
+    const hx_slice_plan slice = hx_plan_slice(n_tiles, k_steps, partial, max_s);
+    if (slice.tiles) return gemm_launch{4, 1, slice.splits, slice.tiles};
     static const int widths[] = {4, 5, 6, 10};
     for (int wn : widths) {
         if (wn == 10 && partial) continue;
@@ -544,13 +549,6 @@ static gemm_launch plan_product(int n_tiles, int k_steps, bool partial) {
             if (cost < best_cost - 1e-9) { best_cost = cost; best.wn = wn; best.splits = s; }
         }
     }
-    int a, b, c;
-    if (forced_shape(&a, &b, &c) && c <= max_s && ((b == 1 && a >= 4 && a <= 6) || (a == 4 && b == 2)) && k_steps / (b * c) >= 1) {
-        best.wn = a; best.wk = b; best.splits = c;
-        return best;
-    }
-    const hx_slice_plan slice = hx_plan_slice(n_tiles, k_steps, partial, max_s);
-    if (slice.tiles) { best.slice_tiles = slice.tiles; best.splits = slice.splits; }
     return best;
 }
 
