@@ -16,7 +16,6 @@
 // The draw takes the tile winners that the LM head's sampling epilogue has left, on the whole
 // chip (here, one workgroup per row, drawing again for every kept entry was 90 of 144 us at 64 rows of 152 064 logits).
 #include "hx_internal.h"
-#include "lm_epilogue.h"
 #include <algorithm>
 
 #define HX_NUC_THREADS 1024
@@ -55,8 +54,9 @@ __device__ __forceinline__ void load_groups(const float *__restrict__ x, int V, 
     for (int u = 0; u < HX_NUC_UNROLL; ++u) load_group(x, V, min(q0 + u * HX_NUC_THREADS, n_groups - 1), vec, v[u]);
 }
 
-// an entry's mass, and its bin: rounding is monotone, so a larger z is never in a later bin
-__device__ __forceinline__ unsigned long long nucleus_mass(float z, float zmax) { return (unsigned long long)(hx_exp_nonpositive(z - zmax) * HX_NUC_SCALE); }
+// An entry's mass, and its bin: rounding is monotone, so a larger z is never in a later bin.  expf, within 0.86 units in the last
+// place (0.30 root mean square) of the exact value; the LM head's hx_exp_nonpositive, 1.26 (0.41), would move entries at the cut.
+__device__ __forceinline__ unsigned long long nucleus_mass(float z, float zmax) { return (unsigned long long)(expf(z - zmax) * HX_NUC_SCALE); }
 __device__ __forceinline__ uint32_t nucleus_bin(float z, float zmax) {
     return min((uint32_t)(int32_t)((zmax - z) * (HX_NUC_BINS / 32.0f)), (uint32_t)(HX_NUC_BINS - 1));
 }

@@ -60,3 +60,37 @@ def test_kept_sets_of_planted_rows(hx, vocab, law):
         assert np.abs(lp[same] - olp[same]).max(initial=0.0) <= 2e-4
         compared += int(same.sum())
     assert compared >= 3
+
+
+def test_masses_are_the_exponentials_of_the_definition(hx):
+    """Rows of two entries that count, z = 0 and z = t: the second is kept unless the first alone reaches top_p of the sum, so the
+    kept set turns over at one value of t.  128 neighbouring values around it, for many top_p: the sizes are those of the masses
+    floor(exp(t) 2^40) of the device's fp32 exponential, not of one that is a unit in the last place away."""
+    s = synth.ModelShape("nm", 1, 32, 1, 1, 64, 16, 4)
+    rows = 128
+    eng = hx.Engine(s, rows, 64)
+    wlm = torch.zeros(s.hidden, s.vocab, dtype=torch.bfloat16)
+    wlm[0:3, 1] = 1.0                         # logit 1 = x0 + x1 + x2: any fp32 number, as three bf16 pieces
+    wlm[3, 2:] = 1.0
+    eng.pack_globals({"embed": torch.zeros(s.vocab, s.hidden, dtype=torch.bfloat16).cuda(),
+                      "gf": torch.ones(s.hidden, dtype=torch.bfloat16).cuda(), "wlm": wlm.cuda()})
+    pos = torch.zeros(rows, dtype=torch.int32, device="cuda")
+    turned = 0
+    for top_p in np.linspace(0.51, 0.999, 64).astype(np.float32):
+        mid = np.float32(np.log(1.0 / float(top_p) - 1.0))
+        t = (np.full(rows, mid).view(np.int32) + np.arange(rows, dtype=np.int32) - rows // 2).view(np.float32)
+        x = torch.zeros(rows, s.hidden, device="cuda")
+        left = torch.from_numpy(t).cuda()
+        for i in range(3):
+            x[:, i] = left.bfloat16().float()
+            left = left - x[:, i]
+        assert not left.any()
+        x[:, 3] = -100.0                      # no mass
+        y, _, _, n = eng.stage_lm_head_top_p(x, pos, 1.0, float(top_p), 7)
+        assert np.array_equal(y[:, 1].cpu().numpy(), t) and not y[:, 0].any()
+        w = (torch.exp(y[:, :2]) * 2.0 ** 40).to(torch.int64).cpu().numpy()
+        target = np.ceil(float(top_p) * w.sum(1).astype(np.float64))
+        want = np.where(w[:, 0] >= target, 1, 2)
+        assert np.array_equal(n.cpu().numpy(), want), (float(top_p), np.nonzero(n.cpu().numpy() != want)[0])
+        turned += len(set(want.tolist())) == 2
+    assert turned >= 48
