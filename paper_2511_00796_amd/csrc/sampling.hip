@@ -5,10 +5,11 @@
 //
 // Mass is 40-bit fixed point, w_i = floor(exp(z_i - max z) * 2^40), added with integer LDS atomics: the sums are exact, so the
 // kept set does not depend on the order of the additions and the result is deterministic.  tau is found in two steps.  The
-// entries' mass is summed in 2048 bins of 1/64 of max z - z (beyond 27.7 the mass is 0), and the bins are walked from the largest
-// z down to the one where the running mass reaches the target.  The entries of that bin, a thousand of 152 064 or fewer, are
-// then collected in LDS and selected among by their order-preserving 32-bit keys, up to 11 bits of their range at a time; a bin
-// of more than HX_NUC_LIST entries (many equal logits) is read from the row again for each digit instead.
+// entries' mass is summed in 2048 bins of max z - z, as wide as the row's spread asks for (nucleus_scale), and the bins are walked
+// from the largest z down to the one where the running mass reaches the target.  The entries of that bin, a thousand of 152 064 or
+// fewer, are then collected in LDS and selected among by their order-preserving 32-bit keys, up to 11 bits of their range at a
+// time; a bin of more than HX_NUC_LIST entries (many equal logits, or a cut far below the bulk) is read from the row again for each
+// digit instead.
 // A row of less than two times HX_NUC_PART entries is one workgroup's.  Of longer ones the bins are filled and the bin's keys
 // listed by as many workgroups per row as give the chip two on every compute unit: exponentials and atomics of the whole row,
 // three times over, by one workgroup were four fifths of the time.  64 rows of 152 064 logits: 94 -> 16 + 17 + 24 us, bound by
@@ -57,24 +58,29 @@ __device__ __forceinline__ void load_groups(const float *__restrict__ x, int V, 
 // An entry's mass, and its bin: rounding is monotone, so a larger z is never in a later bin.  expf, within 0.86 units in the last
 // place (0.30 root mean square) of the exact value; the LM head's hx_exp_nonpositive, 1.26 (0.41), would move entries at the cut.
 __device__ __forceinline__ unsigned long long nucleus_mass(float z, float zmax) { return (unsigned long long)(expf(z - zmax) * HX_NUC_SCALE); }
-__device__ __forceinline__ uint32_t nucleus_bin(float z, float zmax) {
-    return min((uint32_t)(int32_t)((zmax - z) * (HX_NUC_BINS / 32.0f)), (uint32_t)(HX_NUC_BINS - 1));
+struct NucleusScale { float zmax, per_z; };       // largest z of the row; bins per unit of z below it
+__device__ __forceinline__ uint32_t nucleus_bin(float z, const NucleusScale &s) {
+    return (uint32_t)fminf((s.zmax - z) * s.per_z, (float)(HX_NUC_BINS - 1));
 }
 
-// largest z of the row, from the LM head's per-tile maxima
-__device__ __forceinline__ float nucleus_zmax(const float *__restrict__ tile_zmax, int n_tiles, float *redf) {
+// The row's scale, from the LM head's per-tile maxima.  The bins reach 32 below the largest z, where the mass has long been 0, or
+// six times as far as the smallest of the tiles' maxima: of normally distributed logits that is 22 standard deviations, so that a
+// bin holds the same few entries whatever their spread (with bins of 1/64 always, the cut bin of a flat row overflowed the lists:
+// 128 and 256 rows of 151 936, standard deviation 0.2, took 330 and 401 us with the head, 175 and 238 now).  Entries further
+// down are the last bin's.
+__device__ __forceinline__ NucleusScale nucleus_scale(const float *__restrict__ tile_zmax, int n_tiles, float (*redf)[HX_NUC_THREADS / 64]) {
     const int tid = threadIdx.x;
-    float mx = -INFINITY;
-    for (int t = tid; t < n_tiles; t += HX_NUC_THREADS) mx = fmaxf(mx, tile_zmax[t]);
+    float mx = -INFINITY, mn = INFINITY;
+    for (int t = tid; t < n_tiles; t += HX_NUC_THREADS) { mx = fmaxf(mx, tile_zmax[t]); mn = fminf(mn, tile_zmax[t]); }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-    if ((tid & 63) == 0) redf[tid >> 6] = mx;
+    for (int off = 32; off > 0; off >>= 1) { mx = fmaxf(mx, __shfl_xor(mx, off)); mn = fminf(mn, __shfl_xor(mn, off)); }
+    if ((tid & 63) == 0) { redf[0][tid >> 6] = mx; redf[1][tid >> 6] = mn; }
     __syncthreads();
-    mx = redf[0];
+    mx = redf[0][0]; mn = redf[1][0];
 #pragma unroll
-    for (int w = 1; w < HX_NUC_THREADS / 64; ++w) mx = fmaxf(mx, redf[w]);
+    for (int w = 1; w < HX_NUC_THREADS / 64; ++w) { mx = fmaxf(mx, redf[0][w]); mn = fminf(mn, redf[1][w]); }
     __syncthreads();
-    return mx;
+    return NucleusScale{mx, HX_NUC_BINS / fmaxf(fminf(6.0f * (mx - mn), 32.0f), 1e-30f)};
 }
 
 // f(z) for the entries of groups [q0, q1) of the row.  One copy of f per entry of a group, the groups moved up behind it: with
@@ -99,12 +105,12 @@ __device__ __forceinline__ void each_entry(const float *__restrict__ x, int V, i
 
 // the bins of one part of a row (hist is cleared here; the caller synchronises)
 __device__ __forceinline__ void fill_bins(unsigned long long *hist, const float *__restrict__ x, int V, int q0, int q1, bool vec, float inv_t,
-                                          float zmax) {
+                                          const NucleusScale &scale) {
     for (int i = threadIdx.x; i < HX_NUC_BINS; i += HX_NUC_THREADS) hist[i] = 0ull;
     __syncthreads();
     each_entry(x, V, q0, q1, vec, inv_t, [&](float z) {
-        const unsigned long long w = nucleus_mass(z, zmax);
-        if (w) atomicAdd(&hist[nucleus_bin(z, zmax)], w);
+        const unsigned long long w = nucleus_mass(z, scale.zmax);
+        if (w) atomicAdd(&hist[nucleus_bin(z, scale)], w);
     });
 }
 
@@ -112,22 +118,22 @@ __device__ __forceinline__ void fill_bins(unsigned long long *hist, const float 
 struct NucleusState { unsigned long long before, through, target; uint32_t digit; };
 
 // What the two kernels before nucleus_kernel leave of a row, beside the lists
-struct NucleusRow { NucleusState st; float zmax; uint32_t count[HX_NUC_MAX_PARTS]; };
+struct NucleusRow { NucleusState st; NucleusScale scale; uint32_t count[HX_NUC_MAX_PARTS]; };
 
-// grid (rows, parts), so that the parts of a row mostly share an XCD's L2: bins of each part, to be added by nucleus_collect_kernel; zmax of each row
+// grid (rows, parts), so that the parts of a row mostly share an XCD's L2: bins of each part, to be added by nucleus_collect_kernel; the scale of each row
 __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_bins_kernel(const float *__restrict__ logits, const float *__restrict__ tile_zmax,
                                                                       int V, int n_tiles, float inv_t, int part_groups,
                                                                       unsigned long long *__restrict__ bins, NucleusRow *__restrict__ heads) {
     __shared__ unsigned long long hist[HX_NUC_BINS];
-    __shared__ float redf[HX_NUC_THREADS / 64];
+    __shared__ float redf[2][HX_NUC_THREADS / 64];
     const int m = blockIdx.x, part = blockIdx.y;
-    const float zmax = nucleus_zmax(tile_zmax + (size_t)m * n_tiles, n_tiles, redf);
+    const NucleusScale scale = nucleus_scale(tile_zmax + (size_t)m * n_tiles, n_tiles, redf);
     const int q0 = part * part_groups, q1 = min((V + 3) >> 2, q0 + part_groups);
-    fill_bins(hist, logits + (size_t)m * V, V, q0, q1, (V & 3) == 0, inv_t, zmax);
+    fill_bins(hist, logits + (size_t)m * V, V, q0, q1, (V & 3) == 0, inv_t, scale);
     __syncthreads();
     unsigned long long *out = bins + ((size_t)m * gridDim.y + part) * HX_NUC_BINS;
     for (int i = threadIdx.x; i < HX_NUC_BINS; i += HX_NUC_THREADS) out[i] = hist[i];
-    if (part == 0 && threadIdx.x == 0) heads[m].zmax = zmax;
+    if (part == 0 && threadIdx.x == 0) heads[m].scale = scale;
 }
 
 // The bin, two per thread, in which the running mass from st.before on reaches st.target; `first`: the total of all bins fixes the
@@ -188,13 +194,13 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_collect_kernel(const f
         hist[k * HX_NUC_THREADS + tid] = h;
     }
     if (tid == 0) { sh = NucleusState{0ull, 0ull, 0ull, 0u}; n = 0; }
-    const float zmax = heads[m].zmax;
+    const NucleusScale scale = heads[m].scale;
     __syncthreads();
     const NucleusState st = walk_bins(hist, wave_sum, &sh, NucleusState{0ull, 0ull, 0ull, 0u}, true, top_p);
     uint32_t *list = lists + ((size_t)m * HX_NUC_MAX_PARTS + part) * HX_NUC_PART_LIST;
     const int q0 = part * part_groups, q1 = min((V + 3) >> 2, q0 + part_groups);
     each_entry(logits + (size_t)m * V, V, q0, q1, (V & 3) == 0, inv_t, [&](float z) {
-        if (nucleus_bin(z, zmax) == st.digit && nucleus_mass(z, zmax)) {
+        if (nucleus_bin(z, scale) == st.digit && nucleus_mass(z, scale.zmax)) {
             const uint32_t at = atomicAdd(&n, 1u);
             if (at < HX_NUC_PART_LIST) list[at] = nucleus_key(z);
         }
@@ -219,7 +225,7 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
     __shared__ unsigned long long hist[HX_NUC_BINS];
     __shared__ unsigned long long wave_sum[NW];
     __shared__ uint32_t list[HX_NUC_LIST];
-    __shared__ float redf[NW];
+    __shared__ float redf[2][NW];
     __shared__ int32_t redi[NW], redc[NW];
     __shared__ float redz[NW];
     __shared__ NucleusState sh;
@@ -238,12 +244,12 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
         pz[u] = cand_z[o]; py[u] = cand_y[o]; pm[u] = tile_zmax[o]; pi[u] = cand_i[o];
     }
     if (tid == 0) { sh = NucleusState{0ull, 0ull, 0ull, 0u}; sh_lo = 0xffffffffu; sh_hi = 0; sh_n = 0; }
-    float zmax;
+    NucleusScale scale;
     NucleusState st{0ull, 0ull, 0ull, 0u};
     uint32_t bin, n_in_bin;
     bool listed = true;                           // `list` holds all keys of the bin
     if (PARTS) {
-        zmax = heads[m].zmax;
+        scale = heads[m].scale;
         st = heads[m].st;
         bin = st.digit;
         n_in_bin = 0;
@@ -263,13 +269,13 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
         __syncthreads();                          // `sh` was cleared by one thread above
         if (tid == 0) sh = st;
     } else {
-        zmax = nucleus_zmax(tile_zmax + (size_t)m * n_tiles, n_tiles, redf);
-        fill_bins(hist, x, V, 0, n_groups, vec, inv_t, zmax);
+        scale = nucleus_scale(tile_zmax + (size_t)m * n_tiles, n_tiles, redf);
+        fill_bins(hist, x, V, 0, n_groups, vec, inv_t, scale);
         __syncthreads();
         st = walk_bins(hist, wave_sum, &sh, st, true, top_p);
         bin = st.digit;
         each_entry(x, V, 0, n_groups, vec, inv_t, [&](float z) {
-            if (nucleus_bin(z, zmax) == bin && nucleus_mass(z, zmax)) {
+            if (nucleus_bin(z, scale) == bin && nucleus_mass(z, scale.zmax)) {
                 const uint32_t at = atomicAdd(&sh_n, 1u);
                 if (at < HX_NUC_LIST) list[at] = nucleus_key(z);
             }
@@ -285,7 +291,7 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
             for (uint32_t i = tid; i < n_in_bin; i += HX_NUC_THREADS) f(list[i], key_value(list[i]));
         } else {
             each_entry(x, V, 0, n_groups, vec, inv_t, [&](float z) {
-                if (nucleus_bin(z, zmax) == bin && nucleus_mass(z, zmax)) f(nucleus_key(z), z);
+                if (nucleus_bin(z, scale) == bin && nucleus_mass(z, scale.zmax)) f(nucleus_key(z), z);
             });
         }
     };
@@ -305,7 +311,7 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
         __syncthreads();
         each_key([&](uint32_t key, float z) {
             const uint32_t d = key - key_lo;
-            if (hi_shift == 32 || (d >> hi_shift) == prefix) atomicAdd(&hist[(d >> shift) & ((1u << bits) - 1u)], nucleus_mass(z, zmax));
+            if (hi_shift == 32 || (d >> hi_shift) == prefix) atomicAdd(&hist[(d >> shift) & ((1u << bits) - 1u)], nucleus_mass(z, scale.zmax));
         });
         __syncthreads();
         st = walk_bins(hist, wave_sum, &sh, st, false, top_p);
@@ -383,16 +389,16 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
         if (oy > best || (oy == best && oi < best_i)) { best = oy; best_i = oi; best_z = oz; }
         count += __shfl_xor(count, off);
     }
-    if (lane == 0) { redf[wave] = best; redi[wave] = best_i; redz[wave] = best_z; redc[wave] = count; }
+    if (lane == 0) { redf[0][wave] = best; redi[wave] = best_i; redz[wave] = best_z; redc[wave] = count; }
     __syncthreads();
     if (tid == 0) {
 #pragma unroll 1
         for (int w = 1; w < HX_NUC_THREADS / 64; ++w) {
-            if (redf[w] > best || (redf[w] == best && redi[w] < best_i)) { best = redf[w]; best_i = redi[w]; best_z = redz[w]; }
+            if (redf[0][w] > best || (redf[0][w] == best && redi[w] < best_i)) { best = redf[0][w]; best_i = redi[w]; best_z = redz[w]; }
             count += redc[w];
         }
         tok_out[m] = best_i;
-        lp_out[m] = (float)((double)best_z - ((double)zmax + log((double)mass * (1.0 / 1099511627776.0))));
+        lp_out[m] = (float)((double)best_z - ((double)scale.zmax + log((double)mass * (1.0 / 1099511627776.0))));
         if (size_out) size_out[m] = count;
     }
 }
