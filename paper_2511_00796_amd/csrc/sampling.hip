@@ -10,7 +10,7 @@
 // fewer, are then collected in LDS and selected among by their order-preserving 32-bit keys, up to 11 bits of their range at a
 // time; a bin of more than HX_NUC_LIST entries (many equal logits, or a cut far below the bulk) is read from the row again for each
 // digit instead.
-// A row of less than two times HX_NUC_PART entries is one workgroup's.  Of longer ones the bins are filled and the bin's keys
+// A short row, or one of many, is one workgroup's (nucleus_parts).  Of others the bins are filled and the bin's keys
 // listed by as many workgroups per row as give the chip two on every compute unit: exponentials and atomics of the whole row,
 // three times over, by one workgroup were four fifths of the time.  64 rows of 152 064 logits: 94 -> 16 + 17 + 24 us, bound by
 // the LDS atomics, the chains of small steps, and the launches.
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_collect_kernel(const f
     const NucleusScale scale = heads[m].scale;
     __syncthreads();
     const NucleusState st = walk_bins(hist, wave_sum, &sh, NucleusState{0ull, 0ull, 0ull, 0u}, true, top_p);
-    uint32_t *list = lists + ((size_t)m * HX_NUC_MAX_PARTS + part) * HX_NUC_PART_LIST;
+    uint32_t *list = lists + ((size_t)m * parts + part) * HX_NUC_PART_LIST;
     const int q0 = part * part_groups, q1 = min((V + 3) >> 2, q0 + part_groups);
     each_entry(logits + (size_t)m * V, V, q0, q1, (V & 3) == 0, inv_t, [&](float z) {
         if (nucleus_bin(z, scale) == st.digit && nucleus_mass(z, scale.zmax)) {
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
         for (int p = 0; p < HX_NUC_MAX_PARTS; ++p) n[p] = p < parts ? heads[m].count[p] : 0u;
 #pragma unroll
         for (int p = 0; p < HX_NUC_MAX_PARTS; ++p)
-            if ((uint32_t)tid < min(n[p], (uint32_t)HX_NUC_PART_LIST)) key[p] = lists[((size_t)m * HX_NUC_MAX_PARTS + p) * HX_NUC_PART_LIST + tid];
+            if ((uint32_t)tid < min(n[p], (uint32_t)HX_NUC_PART_LIST)) key[p] = lists[((size_t)m * parts + p) * HX_NUC_PART_LIST + tid];
 #pragma unroll
         for (int p = 0; p < HX_NUC_MAX_PARTS; ++p) {
             listed = listed && n[p] <= HX_NUC_PART_LIST && n_in_bin + n[p] <= HX_NUC_LIST;
@@ -403,22 +403,29 @@ __global__ __launch_bounds__(HX_NUC_THREADS) void nucleus_kernel(
     }
 }
 
-// Workgroups per row that fill the bins and list the keys: two on every compute unit, parts of HX_NUC_PART entries or more.
+// Workgroups per row that fill the bins and list the keys: two on every compute unit, parts of HX_NUC_PART entries or more.  One
+// workgroup does it all in one launch where the row is short or the rows alone fill the chip: beyond a row per two compute units, or
+// 768 entries for each row.  us with the head, one workgroup -> several: 151 936 entries 1 row 114 -> 81, 64 rows 138 -> 114, 128 rows
+// 158 -> 150, 170 rows 194 -> 191, 256 rows 208 -> 216; 65 536 entries 64 rows 75.3 -> 70.1, 96 rows 81.2 -> 80.9, 128 rows 85.2 -> 88.5;
+// 49 152 entries 1 row 54.5 -> 50.6, 64 rows 62.8 -> 61.5, 96 rows 69.1 -> 71.9; 32 768 entries 1 row 42.6 -> 45.8, 128 rows 59.1 -> 64.3.
 static int nucleus_parts(int vocab, int batch) {
-    return std::max(1, std::min({HX_NUC_MAX_PARTS, 2 * hx_device_cus() / batch, vocab / HX_NUC_PART}));
+    const int cus = hx_device_cus();
+    if (vocab < 3 * HX_NUC_PART || batch > cus / 2 || vocab / batch < 768) return 1;
+    return std::max(1, std::min({HX_NUC_MAX_PARTS, 2 * cus / batch, vocab / HX_NUC_PART}));
 }
 
-// heads and lists of `max_batch` rows, then the bins
-static size_t nucleus_bins_offset(int max_batch) {
-    return (size_t)max_batch * (sizeof(NucleusRow) + HX_NUC_MAX_PARTS * HX_NUC_PART_LIST * sizeof(uint32_t));
-}
-size_t hx_nucleus_bytes(int vocab, int max_batch) {
+// heads of `max_batch` rows, then lists and bins of at most `most` parts
+static size_t nucleus_most_parts(int vocab, int max_batch) {
     size_t most = 0;
     for (int b = 1; b <= max_batch; ++b) {
         const int parts = nucleus_parts(vocab, b);
         if (parts > 1) most = std::max(most, (size_t)parts * b);
     }
-    return most ? nucleus_bins_offset(max_batch) + most * HX_NUC_BINS * sizeof(unsigned long long) : 0;
+    return most;
+}
+size_t hx_nucleus_bytes(int vocab, int max_batch) {
+    const size_t most = nucleus_most_parts(vocab, max_batch);
+    return most ? (size_t)max_batch * sizeof(NucleusRow) + most * (HX_NUC_BINS * sizeof(unsigned long long) + HX_NUC_PART_LIST * sizeof(uint32_t)) : 0;
 }
 
 int hx_launch_nucleus(const hx_engine *e, int batch, const float *logits, const hx_sample_params *sample,
@@ -427,9 +434,9 @@ int hx_launch_nucleus(const hx_engine *e, int batch, const float *logits, const 
     const float *tile_zmax = (const float *)(e->ws + e->map.samp_m);
     char *ws = e->ws + e->map.nucleus;
     NucleusRow *heads = (NucleusRow *)ws;
-    uint32_t *lists = (uint32_t *)(ws + (size_t)e->cfg.max_batch * sizeof(NucleusRow));
+    unsigned long long *bins = (unsigned long long *)(ws + (size_t)e->cfg.max_batch * sizeof(NucleusRow));
+    uint32_t *lists = (uint32_t *)(bins + (size_t)batch * parts * HX_NUC_BINS);
     if (parts > 1) {
-        unsigned long long *bins = (unsigned long long *)(ws + nucleus_bins_offset(e->cfg.max_batch));
         const int part_groups = ((V + 3) / 4 + parts - 1) / parts;
         hipLaunchKernelGGL(nucleus_bins_kernel, dim3(batch, parts), dim3(HX_NUC_THREADS), 0, st, logits, tile_zmax, V, n_tiles,
                            sample->inv_temperature, part_groups, bins, heads);

@@ -126,3 +126,16 @@ def test_flat_rows_cost_what_others_do(hx):
     usual = us(1.0)
     for temperature in (5.0, 30.0, 1000.0):
         assert us(temperature) <= 1.4 * usual, (temperature, usual)
+
+
+@pytest.mark.parametrize("vocab,rows", [(49148, 8), (49152, 8), (49152, 64), (49152, 65), (98304, 128), (98304, 129), (151936, 200)])
+def test_kept_sets_beside_the_edges_of_the_split(hx, vocab, rows):
+    """One workgroup per row and several: both sides of the row's length and of the number of rows where it turns."""
+    eng, x, pos = top_p_engine(hx, rows, vocab, 2.0)
+    for top_p in (0.2, 0.9):
+        y, tok, lp, n = [t.cpu().numpy() for t in eng.stage_lm_head_top_p(x, pos, 0.7, top_p, 5)]
+        otok, olp, on, margin, gap = oracle.sample_top_p(y, 0.7, top_p, 5, np.arange(rows), pos.cpu().numpy())
+        firm = margin > 1e-7                  # as in test_gpu_top_p.py: a sum of 1e5 fp32 exponentials
+        same = firm & (gap > 1e-4)
+        assert firm.sum() > rows // 2 and np.array_equal(n[firm], on[firm])
+        assert np.array_equal(tok[same], otok[same]) and np.abs(lp[same] - olp[same]).max(initial=0.0) <= 2e-4
