@@ -2,6 +2,7 @@
 // All device work is enqueued on the caller's stream; nothing here allocates device memory.
 #include "hx_internal.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -146,13 +147,14 @@ static size_t map_workspace(hx_engine *e) {
     m->prompt_ginfo = take(256 * 4);
     m->prompt_gslot = take(256 * 4);
     m->prompt_part_ml = take(slots * 4 * 32 * 4);
-    m->prompt_part_o = take(slots * 4 * 16 * e->D * 4);
+    // a nucleus draw comes behind all attention of its step, and prompt rows never draw: its bins and lists share this area
+    m->prompt_part_o = take(std::max(slots * 4 * 16 * e->D * 4, hx_nucleus_bytes(c->vocab, c->max_batch)));
+    m->nucleus = m->prompt_part_o;
     m->amax_val = take(B * e->wlm.n_tiles * 4);
     m->amax_idx = take(B * e->wlm.n_tiles * 4);
     m->samp_z = take(B * e->wlm.n_tiles * 4);
     m->samp_m = take(B * e->wlm.n_tiles * 4);
     m->samp_s = take(B * e->wlm.n_tiles * 4);
-    m->nucleus = take(hx_nucleus_bytes(c->vocab, c->max_batch));
     size_t widest = wide;
     if ((size_t)c->intermediate > widest) widest = c->intermediate;
     if ((size_t)e->q_dim > widest) widest = e->q_dim;

@@ -243,9 +243,9 @@ struct hx_ws_map {          // byte offsets in the workspace
     size_t prompt_gslot;    // int32 [256]  group: first partial slot
     size_t prompt_part_ml;  // fp32 [slots][4][32]
     size_t prompt_part_o;   // fp32 [slots][4][16][D]
+    size_t nucleus;         // bins and lists of a nucleus draw (sampling.hip): the same bytes, dead when a draw runs
     size_t amax_val, amax_idx;  // fp32 / int32 [max_batch][lm n_tiles]   (sampling: best perturbed score and its column)
     size_t samp_z, samp_m, samp_s;  // fp32 [max_batch][lm n_tiles]: scaled logit of the candidate, tile max, tile sum of exp
-    size_t nucleus;         // bins and lists of a nucleus draw (sampling.hip)
     size_t scratch_f32;     // fp32 [max_batch][max(hidden, q_dim, inter, qkv_dim)] stage-hook staging
     size_t total;
 };

@@ -1,6 +1,7 @@
 """Host-side checks of the C-ABI library that need no GPU: it loads, exports every symbol the header
 declares, its pure-host entry points (size queries, argument validation) behave as documented."""
 import ctypes as C
+import dataclasses
 import os
 import re
 
@@ -151,3 +152,18 @@ def test_product_plans_fill_the_chip_and_respect_their_limits(monkeypatch):
     assert lib.hx_plan_product(0, 10, 4, 1, C.byref(none), C.byref(none), C.byref(none)) == binding.HX_E_RANGE
     assert lib.hx_plan_product(10, 10, 300, 1, C.byref(none), C.byref(none), C.byref(none)) == binding.HX_E_RANGE
     assert lib.hx_plan_product(10, 10, 4, 1, None, C.byref(none), C.byref(none)) == binding.HX_E_NULL
+
+
+def test_a_nucleus_draw_takes_no_workspace_of_its_own():
+    """The vocabulary enters the workspace by the LM head's five arrays of one number per row and tile, nothing else: neither an
+    engine's nor that of a prompt call, which holds one per 256 rows and never draws."""
+    def arrays(vocab, batch):
+        return 5 * ((batch * ((vocab + 31) // 32) * 4 + 255) // 256 * 256)
+    for shape in (synth.QWEN_1P5B, synth.QWEN_14B):
+        for batch in (1, 3, 64, 128, 256):
+            small, large = [binding.make_config(dataclasses.replace(shape, vocab=v), batch, 1024) for v in (1024, 152064)]
+            more = arrays(152064, batch) - arrays(1024, batch)
+            assert binding.workspace_bytes(large) - binding.workspace_bytes(small) == more
+            if batch == 256:
+                blocks = [binding.prefill_workspace_bytes(c, 256) for c in (small, large)]
+                assert abs(blocks[1] - blocks[0] - more) < 4096            # blocks are a multiple of 4096 bytes

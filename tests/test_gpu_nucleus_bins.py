@@ -7,6 +7,7 @@ import torch
 
 import oracle
 from paper_2511_00796_amd import synth
+from test_gpu_prefill import build
 
 pytestmark = pytest.mark.gpu
 
@@ -139,3 +140,34 @@ def test_kept_sets_beside_the_edges_of_the_split(hx, vocab, rows):
         same = firm & (gap > 1e-4)
         assert firm.sum() > rows // 2 and np.array_equal(n[firm], on[firm])
         assert np.array_equal(tok[same], otok[same]) and np.abs(lp[same] - olp[same]).max(initial=0.0) <= 2e-4
+
+
+def test_draws_between_prompt_chunks(hx):
+    """A draw's lists lie where prompt attention keeps its partial results: chunks and draws of one engine in turn, each as alone."""
+    s = synth.ModelShape("nd", 2, 64, 2, 1, 64, 96, 65536)
+    eng = build(hx, s, 11, 256, 4096)
+    n = 3000
+    kv = hx.KVCache(eng, 200)
+    table = torch.arange(200, dtype=torch.int32, device="cuda").flip(0)[None].contiguous()
+    start = torch.tensor([0, n], dtype=torch.int32, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    for l in range(s.n_layers):
+        k, v = torch.randn(2, n, s.n_kv_heads, s.head_dim, generator=g, device="cuda").bfloat16()
+        kv.prefill_fill(l, k, v, start, table)
+    pos = torch.arange(n - 256, n, dtype=torch.int32, device="cuda")
+    toks = torch.arange(256, dtype=torch.int32, device="cuda")
+    rows_table = table.expand(256, -1).contiguous()
+    x = torch.randn(16, s.hidden, generator=g, device="cuda")
+    step = torch.arange(16, dtype=torch.int32, device="cuda")
+
+    def chunk():
+        eng.prefill_chunk(kv, toks, pos, pos + 1, rows_table)
+        return torch.stack(kv.gather(s.n_layers - 1, n, start, table)).clone()
+
+    def draw():
+        return [t.clone() for t in eng.stage_lm_head_top_p(x, step, 1.0, 0.9, 3)]
+    alone = chunk()
+    drawn = draw()
+    for _ in range(3):
+        assert torch.equal(chunk(), alone)
+        assert all(torch.equal(a, b) for a, b in zip(draw(), drawn))
