@@ -11,7 +11,7 @@
 // Workgroup = 8 wavefronts, two per SIMD: 2 x 4 sub-tiles of 128 x 64 (256 columns), 4 x 2 of 64 x 96 or 64 x 64
 // (192, 128 columns), or 8 of 32 rows by all 224 or 160 columns.
 // A chunk is 2 k-steps: 16 pieces of X and 2 WNT of W, each copied global -> LDS directly by one wavefront, requested two
-// chunks ahead into a ring of three stages (five ahead into six where the tile is narrow); one barrier per chunk, passed BEFORE the chunk's last k-step is multiplied,
+// chunks ahead into a ring of three stages (five ahead into six: wide_stages); one barrier per chunk, passed BEFORE the chunk's last k-step is multiplied,
 // so that the first operand reads of the next chunk hide behind those products, as the reads of its second k-step hide
 // behind the first.  Reads, copies and products are laid out by hand in groups (sched_barrier).
 // What bounds it is the matrix cores' power: with random operands a loop of 32x32x16 products out of registers reaches
@@ -38,10 +38,13 @@ constexpr int WIDE_KC = 2;        // k-steps per chunk
 constexpr int WIDE_WAVES = 8;
 // Stages of the ring: six of the narrow tiles, three of the others.  The narrow ones run where a product is small or has one
 // block of rows, at a third of the matrix cores' rate, and wait for memory: six stages there, us at 201 rows: 7B gate|up
-// 77 -> 75, down 50 -> 44, 14B gate|up 88 -> 82, O 25 -> 22, QKV 31.5 -> 30 (1.5B, whose weights mostly stay in the
-// memory-side cache: the same).  Beyond 5 tiles the matrix cores bind: 2048 and 4864 rows 0.4 % slower with five stages.
-constexpr int wide_stages(int wnt) { return wnt <= 5 ? 6 : 3; }
-constexpr int wide_lds_bytes(int wnt) { return wide_stages(wnt) * WIDE_KC * (8 + wnt) * 1024; }
+// 77 -> 75, down 50 -> 44, 14B gate|up 88 -> 82, O 25 -> 22, QKV 31.5 -> 30; 7B O, 1024 rows 34 -> 31.  Beyond 5 tiles the matrix
+// cores bind: 2048 and 4864 rows 0.4 % slower with five stages.  Gate|up of more workgroups than compute units has three, too:
+// five stages are requested anew at the start of every workgroup, which its few k-steps do not repay (us, three | six stages:
+// 1.5B, 1024 rows 60.1 | 62.7; hidden size 896, 2048 rows 38.9 | 43.2; 2048, 768 rows 75.4 | 77.1; one workgroup for a compute
+// unit: 1.5B, 256 rows 28 | 26).  The others of more than one round, whose k-steps are many, gain: 7B QKV, 4096 rows 141 | 135.
+constexpr int wide_stages(int wnt, bool rounds) { return wnt <= 5 && !rounds ? 6 : 3; }
+constexpr int wide_lds_bytes(int wnt, int stages) { return stages * WIDE_KC * (8 + wnt) * 1024; }
 
 struct WideArgs {
     const uint4 *wp;              // packed weights of the matrix
@@ -57,9 +60,9 @@ struct WideArgs {
 
 // WNT: 32-column tiles per workgroup, 4 to 8 (a 256 x 128 to 256 x 256 output tile).  Splits hold whole chunks; ODD:
 // but for the last, whose second k-step is missing.  (As a run-time condition in the loop this cost the narrow tiles 11 %.)
-template <int WNT, int EPI, bool ODD>
+template <int WNT, int EPI, bool ODD, int NST>
 __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) {
-    constexpr int KC = WIDE_KC, NST = wide_stages(WNT), WCOL = WNT == 8 ? 4 : (WNT % 2 ? 1 : 2), WROW = WIDE_WAVES / WCOL, TM = 8 / WROW,
+    constexpr int KC = WIDE_KC, WCOL = WNT == 8 ? 4 : (WNT % 2 ? 1 : 2), WROW = WIDE_WAVES / WCOL, TM = 8 / WROW,
                   TW = WNT / WCOL;
     constexpr int PIECES = KC * (8 + WNT), STAGE_U4 = PIECES * 64;
     constexpr int LPW = (PIECES + WIDE_WAVES - 1) / WIDE_WAVES, FULL = PIECES - (LPW - 1) * WIDE_WAVES;   // waves < FULL copy LPW pieces, the others one less
@@ -244,16 +247,16 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
     }
 }
 
-template <int WNT, int EPI, bool ODD>
+template <int WNT, int EPI, bool ODD, bool ROUNDS = false>
 int launch_wide(dim3 grid, hipStream_t st, const WideArgs &a) {
+    constexpr int NST = wide_stages(WNT, ROUNDS), LDS = wide_lds_bytes(WNT, NST);
     static std::once_flag once;
     static hipError_t configured = hipSuccess;
     std::call_once(once, [] {
-        configured = hipFuncSetAttribute((const void *)gemm_wide_kernel<WNT, EPI, ODD>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         wide_lds_bytes(WNT));
+        configured = hipFuncSetAttribute((const void *)gemm_wide_kernel<WNT, EPI, ODD, NST>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     });
     if (configured != hipSuccess) return hx_fail(HX_E_HIP, "hipFuncSetAttribute: %s", hipGetErrorString(configured));
-    hipLaunchKernelGGL((gemm_wide_kernel<WNT, EPI, ODD>), grid, dim3(64 * WIDE_WAVES), wide_lds_bytes(WNT), st, a);
+    hipLaunchKernelGGL((gemm_wide_kernel<WNT, EPI, ODD, NST>), grid, dim3(64 * WIDE_WAVES), LDS, st, a);
     return HX_OK;
 }
 
@@ -265,6 +268,7 @@ int launch_wide_epi(int epilogue, dim3 grid, hipStream_t st, const WideArgs &a) 
     }
     if (epilogue == HX_EPI_LOGITS) return launch_wide<WNT, HX_EPI_LOGITS, false>(grid, st, a);
     if (epilogue == HX_EPI_SAMPLE) return launch_wide<WNT, HX_EPI_SAMPLE, false>(grid, st, a);
+    if ((int)grid.x > hx_device_cus()) return launch_wide<WNT, HX_EPI_SWIGLU, false, true>(grid, st, a);
     return launch_wide<WNT, HX_EPI_SWIGLU, false>(grid, st, a);
 }
 

@@ -93,3 +93,20 @@ def test_every_row_is_normalised_once(hx, rows):
     ref = xd * torch.rsqrt((xd * xd).mean(-1, keepdim=True) + s.rms_eps) * synth.layer_weights(s, 0, 5)["g1"].double().cuda()
     # one bf16 rounding (2^-9 relative) and the fp32 norm's own error
     assert y.shape == x.shape and ((y.double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-6).all()
+
+
+@pytest.mark.parametrize("tiles,blocks,hidden", [(512, 2, 32), (338, 6, 32), (640, 2, 32), (640, 2, 192), (1026, 2, 32), (1026, 2, 96), (1026, 2, 192)])
+def test_gate_up_of_one_and_two_rounds(hx, tiles, blocks, hidden):
+    """Narrow tiles of gate|up on as many workgroups as compute units (256 of 4 and of 5 tiles), and on more (510 of 4, 412 of 5),
+    which have another number of LDS stages: products of 1, 3 and 6 chunks."""
+    s = synth.ModelShape("wb-gu", 1, hidden, 1, 1, 64, 16 * tiles, 64)
+    eng = build(hx, s, 5, 256, 64)
+    w = {k: v.double().cuda() for k, v in synth.layer_weights(s, 0, 5).items()}
+    ws = torch.empty(hx.prefill_workspace_bytes(eng.cfg, 256 * blocks), dtype=torch.uint8, device="cuda")
+    x = torch.randn(256 * blocks, hidden, generator=torch.Generator(device="cuda").manual_seed(7), device="cuda").bfloat16().float()
+    y = eng.stage_linear_rows(hx.HX_T_WG, 0, x, ws)
+    torch.cuda.synchronize()
+    gate = x.double() @ w["wg"]
+    ref = gate * torch.sigmoid(gate) * (x.double() @ w["wu"])
+    # one bf16 rounding of the result and the fp32 sums' own error
+    assert y.shape == ref.shape and ((y.double() - ref).abs() <= ref.abs() * 2.0 ** -7 + 1e-5).all()
