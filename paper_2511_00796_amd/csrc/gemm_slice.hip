@@ -153,17 +153,23 @@ struct SliceArgs {
 };
 
 template <int MG, int TN, int R>
-void launch_slice(int epilogue, const SliceArgs &a, int splits, hipStream_t st) {
+int launch_slice(int epilogue, const SliceArgs &a, int splits, hipStream_t st) {
     const dim3 grid((a.n_tiles + TN - 1) / TN, splits), block(64 * SLICES);
-#define HX_SLICE(TT, EPI)                                                                                                  \
-    hipLaunchKernelGGL((gemm_slice_kernel<MG, TT, R, EPI>), grid, block, 0, st, a.wp, a.xp, a.k_steps, a.n_tiles, a.steps_per_split, \
+#define HX_SLICE(EPI)                                                                                                      \
+    hipLaunchKernelGGL((gemm_slice_kernel<MG, TN, R, EPI>), grid, block, 0, st, a.wp, a.xp, a.k_steps, a.n_tiles, a.steps_per_split, \
                        a.M, a.N, a.split_stride, a.y, a.mp, a.lm)
-    if (epilogue == HX_EPI_PARTIAL) HX_SLICE(TN, HX_EPI_PARTIAL);
-    else if (TN == 2) return;                            // a long K is split: only partial results
-    else if (epilogue == HX_EPI_SWIGLU) HX_SLICE(1, HX_EPI_SWIGLU);
-    else if (epilogue == HX_EPI_SAMPLE) HX_SLICE(1, HX_EPI_SAMPLE);
-    else HX_SLICE(1, HX_EPI_LOGITS);
+    if (epilogue == HX_EPI_PARTIAL) {
+        HX_SLICE(HX_EPI_PARTIAL);
+    } else if constexpr (TN == 1) {
+        if (epilogue == HX_EPI_SWIGLU) HX_SLICE(HX_EPI_SWIGLU);
+        else if (epilogue == HX_EPI_SAMPLE) HX_SLICE(HX_EPI_SAMPLE);
+        else HX_SLICE(HX_EPI_LOGITS);
+    } else {                                             // a long K is split: only partial results
+        return hx_fail(HX_E_RANGE, "epilogue %d with %d tiles per workgroup: no such small product", epilogue, TN);
+    }
 #undef HX_SLICE
+    HX_CHECK_LAUNCH("gemm_slice");
+    return HX_OK;
 }
 
 }  // namespace
@@ -196,14 +202,12 @@ int hx_launch_gemm_slice(const hx_engine *e, const hx_matrix *m, int batch, hx_s
     // k-steps in flight: with eight of the fewest rows the first products wait for loads past the split's end (1.5B, 16 rows, QKV
     // 4.7 -> 4.1 us, O 4.5 -> 3.7 with four); at more rows 2 to 6 are alike, but for two tiles of 128 rows (2: 13.3, 3: 12.4)
     switch (hx_m_groups(batch) * 10 + plan.tiles) {
-        case 11: launch_slice<1, 1, 4>(epilogue, a, plan.splits, st); break;
-        case 21: launch_slice<2, 1, 6>(epilogue, a, plan.splits, st); break;
-        case 41: launch_slice<4, 1, 4>(epilogue, a, plan.splits, st); break;
-        case 12: launch_slice<1, 2, 4>(epilogue, a, plan.splits, st); break;
-        case 22: launch_slice<2, 2, 6>(epilogue, a, plan.splits, st); break;
-        case 42: launch_slice<4, 2, 3>(epilogue, a, plan.splits, st); break;
+        case 11: return launch_slice<1, 1, 4>(epilogue, a, plan.splits, st);
+        case 21: return launch_slice<2, 1, 6>(epilogue, a, plan.splits, st);
+        case 41: return launch_slice<4, 1, 4>(epilogue, a, plan.splits, st);
+        case 12: return launch_slice<1, 2, 4>(epilogue, a, plan.splits, st);
+        case 22: return launch_slice<2, 2, 6>(epilogue, a, plan.splits, st);
+        case 42: return launch_slice<4, 2, 3>(epilogue, a, plan.splits, st);
         default: return hx_fail(HX_E_RANGE, "%d rows, %d tiles per workgroup: no such small product", batch, plan.tiles);
     }
-    HX_CHECK_LAUNCH("gemm_slice");
-    return HX_OK;
 }
