@@ -289,7 +289,7 @@ int hx_attention_waves(const hx_engine *engine); /* wavefronts of the attention 
 /* How the matrix product of n_tiles 32-column tiles and k_steps 16-row steps is launched for `batch` rows (host logic only,
    no GPU work): tiles per workgroup, k-slices per workgroup, and K-splits whose fp32 partial results the consumer kernel
    adds (only if `partial` != 0; products with a fused epilogue are never split).  Up to 128 rows that is the streaming
-   product -- of a matrix of few columns (up to 64 tiles on 256 compute units) only the K-splits hold: its tiles go to single
+   product -- of a matrix of few columns (up to 68 tiles on 256 compute units) only the K-splits hold: its tiles go to single
    workgroups, one or two each, unless HX_GEMM_SHAPE forces the streaming product --, beyond them the workgroup-tiled one of prefill_rows over one block of 256 rows, as an engine with max_batch 256
    runs it (one for fewer rows may split less).  HX_E_RANGE for sizes < 1 or batch > 256, HX_E_NULL for NULL outputs. */
 int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, int32_t partial, int32_t *tiles_per_workgroup_out,

@@ -175,8 +175,10 @@ int launch_slice(int epilogue, const SliceArgs &a, int splits, hipStream_t st) {
 }  // namespace
 
 // Whether a product of at most 128 rows runs here: the streaming kernel's most workgroups, a quarter of the tiles times the
-// most splits, would leave two fifths of the compute units without one (up to 64 tiles on 256; 112 tiles, 7B O: 7.7 / 11.4 us
-// there, 7.9 / 13.7 here at 3 / 37 rows).  K-splits: at least 24 k-steps each (1.5B QKV at 64 rows in 6 / 4 / 2 splits: 5.6 / 4.4 /
+// most splits, would leave two fifths of the compute units without one (up to 68 tiles on 256: 17 workgroups of four in 9 splits are
+// 153).  us at 1 / 64 / 128 rows, 68 tiles, there with its best splits -> here: 128 k-steps 4.4 / 7.4 / 11.9 -> 4.0 / 5.4 / 7.3, 544 k-steps
+// 10.2 / 15.7 / 18.7 -> 8.4 / 13.3 / 16.6, LM head 11.5 / 20.1 / 23.1 -> 5.2 / 8.7 / 11.0; 112 tiles, 7B O, at 3 / 37 rows 7.7 / 11.4 there,
+// 7.9 / 13.7 here.  K-splits: at least 24 k-steps each (1.5B QKV at 64 rows in 6 / 4 / 2 splits: 5.6 / 4.4 /
 // 5.2 us) and no more workgroups than compute units; two tiles per workgroup where that still leaves long ones.
 hx_slice_plan hx_plan_slice(int n_tiles, int k_steps, bool partial, int max_splits) {
     const int cus = hx_device_cus();

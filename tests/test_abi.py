@@ -167,3 +167,17 @@ def test_a_nucleus_draw_takes_no_workspace_of_its_own():
             if batch == 256:
                 blocks = [binding.prefill_workspace_bytes(c, 256) for c in (small, large)]
                 assert abs(blocks[1] - blocks[0] - more) < 4096            # blocks are a multiple of 4096 bytes
+
+
+def test_the_step_from_few_columns_to_the_streaming_product():
+    """68 tiles are the last whose product gets one workgroup per tile and splits of 24 k-steps; 69 take the streaming plan, in
+    splits of whole revolutions of 16 (256 compute units: no device is asked here)."""
+    lib = binding.load()
+    out = [C.c_int32() for _ in range(3)]
+
+    def splits(n_tiles, k_steps, batch=64):
+        assert lib.hx_plan_product(n_tiles, k_steps, batch, 1, *[C.byref(o) for o in out]) == binding.HX_OK
+        return out[2].value
+    for batch in (1, 64, 128):
+        assert [splits(t, 48, batch) for t in (64, 65, 68, 69)] == [2, 2, 2, 3]
+        assert [splits(t, 128, batch) for t in (68, 69)] == [3, 8]

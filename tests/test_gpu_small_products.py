@@ -1,6 +1,6 @@
 """Products of matrices with few columns (gemm_slice.hip): every number of k-steps that leaves wavefronts without work or the ring
 part-filled, odd numbers of tiles, ragged last tiles, both sides of the row groups' edges, one and two tiles per workgroup, and
-the step to the streaming kernel.  Reference: the product in float64."""
+the step to the streaming kernel (68 | 69 tiles on 256 compute units).  Reference: the product in float64."""
 import pytest
 import torch
 
@@ -18,10 +18,13 @@ def hx():
 
 
 # hidden x (heads) x intermediate x vocab.  k-steps of the down product: 1, 5, 23, 48 (two splits), 217 (one more than nine
-# splits of 24: two tiles per workgroup); columns: 64 to 2080 (65 tiles: the streaming kernel), 1000 (the last tile holds 8)
+# splits of 24: two tiles per workgroup); columns: 64 to 2080, 1000 (the last tile holds 8)
 SHAPES = {"k1": synth.ModelShape("sp-k1", 1, 64, 1, 1, 64, 16, 64), "k5": synth.ModelShape("sp-k5", 1, 96, 3, 1, 64, 80, 1000),
           "k23": synth.ModelShape("sp-k23", 1, 352, 4, 2, 128, 368, 36), "k48": synth.ModelShape("sp-k48", 1, 768, 6, 1, 128, 768, 2048),
           "k217": synth.ModelShape("sp-k217", 1, 480, 2, 2, 128, 3472, 2080)}
+# 68 and 69 tiles: a head of 2176 and of 2180 columns (its last tile holds 4), O and down products (split) of hidden sizes 2176 and 2208
+for hidden, vocab in ((2176, 2180), (2208, 2176)):
+    SHAPES["t%d" % (hidden // 32)] = synth.ModelShape("sp-t%d" % (hidden // 32), 1, hidden, 6, 1, 128, 800, vocab)
 
 
 @pytest.mark.parametrize("batch", [1, 31, 33, 64, 65, 100, 128])
