@@ -161,7 +161,7 @@ int hx_launch_pack(const hx_engine *e, const hx_pack_tensor *tensors, int n, hip
 struct GemmArgs {
     const uint4 *wp;      // packed weights
     const uint4 *xp;      // packed activations
-    int k_steps, n_tiles, tile0, tile_end, steps_per_split, steps_per_wave;   // n_tiles: whole matrix; [tile0, tile_end): this launch
+    int k_steps, n_tiles, steps_per_split, steps_per_wave;
     int M, N;
     float *y;             // PARTIAL: [splits][M][N]; LOGITS: [M][N] or NULL
     size_t split_stride;  // elements between splits of y
@@ -206,8 +206,8 @@ template <int MG, int WN, int WK, int RING> constexpr int gemm_lds_bytes() {
 
 template <int MG, int WN, int WK, int EPI>
 __global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK, gemm_ring<MG, WN, EPI>()>::NP)) void gemm_stream_kernel(
-    const uint4 *__restrict__ a_wp, const uint4 *__restrict__ a_xp, int a_k_steps, int a_n_tiles, int a_tile0,
-    int a_tile_end, int a_steps_per_split, int a_steps_per_wave, int a_M, int a_N, float *__restrict__ a_y, size_t a_split_stride,
+    const uint4 *__restrict__ a_wp, const uint4 *__restrict__ a_xp, int a_k_steps, int a_n_tiles,
+    int a_steps_per_split, int a_steps_per_wave, int a_M, int a_N, float *__restrict__ a_y, size_t a_split_stride,
     uint16_t *__restrict__ a_mp, float *__restrict__ a_amax_val, int32_t *__restrict__ a_amax_idx,
     const int32_t *__restrict__ a_positions, const int32_t *__restrict__ a_row_ids, float a_inv_t, uint32_t a_key0,
     uint32_t a_key1, float *__restrict__ a_samp_z, float *__restrict__ a_samp_m, float *__restrict__ a_samp_s) {
@@ -225,8 +225,8 @@ __global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK, gemm_ring<MG, WN, 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);       // wave-uniform, kept in a scalar register
     const bool producer = wave >= NC;                    // the last wavefronts only stage activations
     const int wn = producer ? 0 : wave % WN, wk = producer ? 0 : wave / WN;
-    const int nt = a_tile0 + blockIdx.x * WN + wn;
-    const bool active = !producer && nt < a_tile_end;
+    const int nt = blockIdx.x * WN + wn;
+    const bool active = !producer && nt < a_n_tiles;
     const int split0 = blockIdx.y * a_steps_per_split;
     const int split1 = min(a_k_steps, split0 + a_steps_per_split);
     // every wavefront of the grid runs the same number of chunks: whole ring revolutions.  Steps past the end
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK, gemm_ring<MG, WN, 
     const int n_valid = active ? max(0, ke - kb0) : 0;               // steps that are multiplied
     const int kb = min(kb0, a_k_steps - 1);
     const int last = max(0, min(a_k_steps, kb + a_steps_per_wave) - kb - 1);   // last step whose tile may be read
-    const uint4 *wrow = a_wp + ((size_t)(active ? nt : a_tile0) * a_k_steps + kb) * 64 + lane;
+    const uint4 *wrow = a_wp + ((size_t)(active ? nt : 0) * a_k_steps + kb) * 64 + lane;
 
     f32x16_t acc[MG];
 #pragma unroll
@@ -449,9 +449,8 @@ __global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK, gemm_ring<MG, WN, 
 }
 
 // ---- host side: one launch of a given shape -----------------------------------------------------------------------
-#define HX_GEMM_ARGS a.wp, a.xp, a.k_steps, a.n_tiles, a.tile0, a.tile_end, a.steps_per_split, a.steps_per_wave, a.M, a.N, a.y, \
-                     a.split_stride, a.mp, a.amax_val, a.amax_idx, a.positions, a.row_ids, a.inv_t, a.key0, a.key1, a.samp_z, a.samp_m, \
-                     a.samp_s
+#define HX_GEMM_ARGS a.wp, a.xp, a.k_steps, a.n_tiles, a.steps_per_split, a.steps_per_wave, a.M, a.N, a.y, a.split_stride, a.mp, \
+                     a.amax_val, a.amax_idx, a.positions, a.row_ids, a.inv_t, a.key0, a.key1, a.samp_z, a.samp_m, a.samp_s
 
 template <int MG, int WN, int WK, int EPI>
 static int launch_one(dim3 grid, hipStream_t st, const GemmArgs &a) {
@@ -616,8 +615,6 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
     a.xp = (const uint4 *)xp;
     a.k_steps = m->k_steps;
     a.n_tiles = m->n_tiles;
-    a.tile0 = 0;
-    a.tile_end = m->n_tiles;
     a.steps_per_split = (m->k_steps + pl.splits - 1) / pl.splits;
     a.steps_per_wave = (a.steps_per_split + pl.wk - 1) / pl.wk;
     a.M = batch;
