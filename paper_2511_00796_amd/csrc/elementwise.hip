@@ -124,7 +124,7 @@ __global__ __launch_bounds__(HX_NORM_THREADS) void norm_kernel(float *__restrict
                                                               int rows, size_t block_stride) {
     const int b = SPREAD ? hx_row_of_workgroup(blockIdx.x, rows) : blockIdx.x;
     if (SPREAD && b >= rows) return;
-    if (SPREAD && blockIdx.y) {               // further row blocks of a wide prompt call: same layout, block_stride bytes apart
+    if (SPREAD && blockIdx.y) {     // further row blocks of a wide prompt call: same layout, block_stride bytes apart
         const size_t off = (size_t)blockIdx.y * block_stride;
         x = (float *)((char *)x + off);
         if (ypart) ypart = (const float *)((const char *)ypart + off);
@@ -160,6 +160,7 @@ int hx_launch_step_begin(const hx_engine *e, int batch, const int32_t *tokens, c
 
 int hx_launch_embed_norm(const hx_engine *e, int batch, const int32_t *tokens, size_t gain_off, hipStream_t st, int blocks,
                          size_t block_stride) {
+    HX_CHECK_ROW_BLOCKS(batch, blocks);
     const auto kernel = hx_spread_rows(batch) ? norm_kernel<0, 1, true> : norm_kernel<0, 1, false>;
     hipLaunchKernelGGL(kernel, dim3(hx_row_workgroups(batch), blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x),
                        (const float *)nullptr, (size_t)0, 0, e->cfg.hidden, (const uint16_t *)(e->weights + gain_off),
@@ -171,6 +172,7 @@ int hx_launch_embed_norm(const hx_engine *e, int batch, const int32_t *tokens, s
 
 int hx_launch_reduce_norm(const hx_engine *e, int batch, const float *ypart, int splits, size_t split_stride,
                           size_t gain_off, hipStream_t st, int blocks, size_t block_stride) {
+    HX_CHECK_ROW_BLOCKS(batch, blocks);
 #define HX_REDUCE_NORM(MAXS)                                                                                      \
     hipLaunchKernelGGL((hx_spread_rows(batch) ? norm_kernel<1, MAXS, true> : norm_kernel<1, MAXS, false>),       \
                        dim3(hx_row_workgroups(batch), blocks), dim3(HX_NORM_THREADS), 0, st, (float *)(e->ws + e->map.x), \

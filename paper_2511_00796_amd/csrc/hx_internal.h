@@ -172,6 +172,11 @@ __host__ __device__ __forceinline__ int hx_m_groups(int batch) {
 // even the question at run time costs 0.2 us a launch (the row count is one more load before the first), so it is a template's.
 __host__ __device__ __forceinline__ bool hx_spread_rows(int rows) { return rows > 128; }
 __host__ __device__ __forceinline__ int hx_row_workgroups(int rows) { return hx_spread_rows(rows) ? (rows + 7) / 8 * 8 : rows; }
+// Several blocks of rows go in one launch only where they are spread: the others' kernels do not look at the block's index.
+#define HX_CHECK_ROW_BLOCKS(rows, blocks)                                                                                 \
+    do {                                                                                                                 \
+        if ((blocks) > 1 && !hx_spread_rows(rows)) return hx_fail(HX_E_RANGE, "%d blocks of %d rows: no such row kernel", (int)(blocks), (int)(rows)); \
+    } while (0)
 __host__ __device__ __forceinline__ int hx_row_of_workgroup(int x, int rows) { return (x & 7) * ((rows + 7) / 8) + (x >> 3); }
 
 // element offset (in bf16) of activation (m, k) inside a packed X buffer with m_groups groups

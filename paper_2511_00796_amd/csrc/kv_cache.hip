@@ -131,7 +131,7 @@ __global__ __launch_bounds__(128) void rope_append_kernel(const float *__restric
     constexpr int RPH = HALF / 4;                         // rotation items per head
     const int b = SPREAD ? hx_row_of_workgroup(blockIdx.x, rows) : blockIdx.x;
     if (SPREAD && b >= rows) return;
-    if (SPREAD && blockIdx.z) {               // further row blocks of a wide prompt call: same layout, block_stride bytes apart
+    if (SPREAD && blockIdx.z) {     // further row blocks of a wide prompt call: same layout, block_stride bytes apart
         const size_t off = (size_t)blockIdx.z * block_stride;
         ypart = (const float *)((const char *)ypart + off);
         cs = (const float *)((const char *)cs + off);
@@ -230,6 +230,7 @@ __global__ __launch_bounds__(128) void rope_append_kernel(const float *__restric
 int hx_launch_rope_append(const hx_engine *e, const hx_kv *kv, int layer, int batch, const float *ypart,
                           int splits, size_t split_stride, const int32_t *positions, hipStream_t st, int blocks,
                           size_t block_stride) {
+    HX_CHECK_ROW_BLOCKS(batch, blocks);
     const hx_layer_map &lm = e->layers[layer];
     char *pool_layer = kv->pool + (size_t)layer * kv->layer_bytes;
     const uint16_t *bias = (const uint16_t *)(e->weights + lm.bqkv);

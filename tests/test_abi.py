@@ -181,3 +181,23 @@ def test_the_step_from_few_columns_to_the_streaming_product():
     for batch in (1, 64, 128):
         assert [splits(t, 48, batch) for t in (64, 65, 68, 69)] == [2, 2, 2, 3]
         assert [splits(t, 128, batch) for t in (68, 69)] == [3, 8]
+
+
+def test_row_kernels_take_several_blocks_only_beyond_128_rows():
+    """The row kernels of at most 128 rows do not look at the block's index: several blocks of so few rows are refused instead of
+    the first being written again and again.  Internal launches, over an engine of zeros: nothing is read behind the check."""
+    lib = binding.load()
+    zeros = C.create_string_buffer(1 << 14)
+    e, none, size = C.cast(zeros, C.c_void_p), C.c_void_p(), C.c_size_t
+
+    def launch(name, *args):
+        f = getattr(lib, name)
+        f.restype = C.c_int
+        return f(*args)
+    for blocks, rows in ((2, 128), (3, 1)):
+        for rc in (launch("_Z20hx_launch_embed_normPK9hx_engineiPKimP12ihipStream_tim", e, rows, none, size(0), none, blocks, size(4096)),
+                   launch("_Z21hx_launch_reduce_normPK9hx_engineiPKfimmP12ihipStream_tim", e, rows, none, 1, size(0), size(0), none, blocks,
+                          size(4096)),
+                   launch("_Z21hx_launch_rope_appendPK9hx_enginePK5hx_kviiPKfimPKiP12ihipStream_tim", e, e, 0, rows, none, 1, size(0), none,
+                          none, blocks, size(4096))):
+            assert rc == binding.HX_E_RANGE and "blocks of" in lib.hx_last_error().decode()
