@@ -127,7 +127,7 @@ int hx_engine_destroy(hx_engine *engine);
 int hx_weights_pack(hx_engine *engine, int tensor_kind, int layer, const void *src_dev,
                     int64_t rows, int64_t cols, void *stream);
 /* The same for up to HX_PACK_MANY tensors in one launch (HOST arrays of length `n`; `layer` for those that belong to one).
-   Nothing is packed if any of them is refused. */
+   Nothing is packed if any of them is refused; a kind given twice is (HX_E_SHAPE). */
 #define HX_PACK_MANY 8
 int hx_weights_pack_many(hx_engine *engine, int32_t n, const int32_t *tensor_kinds, int layer, const void *const *srcs_dev,
                          const int64_t *rows, const int64_t *cols, void *stream);

@@ -325,6 +325,8 @@ extern "C" int hx_weights_pack_many(hx_engine *e, int32_t n, const int32_t *kind
     for (int i = 0; i < n; ++i) {
         const int rc = pack_target(e, kinds[i], layer, srcs[i], rows[i], cols[i], &t[i]);
         if (rc) return rc;
+        for (int j = 0; j < i; ++j)          // two writers of one place, in no order
+            if (kinds[j] == kinds[i]) return hx_fail(HX_E_SHAPE, "tensor kind %d twice in one call", kinds[i]);
     }
     return hx_launch_pack(e, t, n, (hipStream_t)stream);
 }

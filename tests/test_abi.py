@@ -201,3 +201,25 @@ def test_row_kernels_take_several_blocks_only_beyond_128_rows():
                    launch("_Z21hx_launch_rope_appendPK9hx_enginePK5hx_kviiPKfimPKiP12ihipStream_tim", e, e, 0, rows, none, 1, size(0), none,
                           none, blocks, size(4096))):
             assert rc == binding.HX_E_RANGE and "blocks of" in lib.hx_last_error().decode()
+
+
+def test_packing_many_refuses_a_tensor_given_twice():
+    """All tensors of a call are written by one launch, in no order.  Refused on the host: the buffers are never touched."""
+    lib = binding.load()
+    s = synth.TINY
+    cfg = binding.make_config(s, 4, 64)
+    engine = C.c_void_p()
+    at = C.c_void_p(1 << 20)
+    assert lib.hx_engine_create(C.byref(cfg), at, binding.weights_bytes(cfg), at, binding.workspace_bytes(cfg), C.byref(engine)) == binding.HX_OK
+    try:
+        def pack(*kinds):
+            n = len(kinds)
+            rows = [s.intermediate if k == binding.HX_T_WD else s.hidden for k in kinds]
+            cols = [s.hidden if k == binding.HX_T_WD else s.intermediate for k in kinds]
+            return lib.hx_weights_pack_many(engine, n, (C.c_int32 * n)(*kinds), 0, (C.c_void_p * n)(*[1 << 20] * n), (C.c_int64 * n)(*rows),
+                                            (C.c_int64 * n)(*cols), None)
+        assert pack(binding.HX_T_WG, binding.HX_T_WU, binding.HX_T_WG) == binding.HX_E_SHAPE
+        assert pack(binding.HX_T_WD, binding.HX_T_WD) == binding.HX_E_SHAPE
+        assert lib.hx_weights_pack_many(engine, 0, None, 0, None, None, None, None) == binding.HX_E_NULL
+    finally:
+        lib.hx_engine_destroy(engine)
