@@ -4,10 +4,11 @@
 // tile (K and V of 16 tokens of one KV head) holds 1-byte elements in the operand order of the bf16 tile with the bytes
 // of two operand steps side by side (hx_ktile8_index / hx_vtile8_index), so it is half as many 1-KiB loads.  Each
 // operand is converted to bf16 in registers right before its product -- exactly, every E4M3 value is a bf16 value --
-// and from there on the arithmetic is the bf16 kernel's, over two tiles at a time: one maximum, one rescaling and 16x16x32
-// products of 32 tokens for both.  The ring holds the raw bytes of one pair, 8 KiB per wavefront and 64 KiB per compute unit, as
-// in the bf16 kernel (why: there).  What bounds it is the memory system: 7B, 128 sequences 179 us per launch = 5.97 TB/s, the
-// same loads without any arithmetic 178; rings of 4 and 6 tiles 184 and 186, tile by tile with a ring of 4 187.
+// and from there on the arithmetic is the bf16 kernel's, tile by tile.  The ring holds the raw bytes of two tiles, 8 KiB per
+// wavefront and 64 KiB per compute unit, as in the bf16 kernel (why: there).  What bounds it is the memory system: us per launch
+// with rings of 2 / 3 / 4 tiles, 7B, 128 sequences 182 = 5.9 TB/s / 187 / 188, 14B, 64 of them 174 / 177 / 178, 1.5B, 256 of them 84 / 88 / 90,
+// 7B, 3 long ones 13.7 / 15.4 / 17.0; the loads of the first without any arithmetic 178.  Two tiles at a time, with one maximum and one
+// rescaling for both, took 180 / 171 / 82 / 14.4, but left the result further from exact: 1.84e-6 instead of 1.79e-6 at 9 001 tokens.
 #include "hx_internal.h"
 
 #define HX_NEG_BIG (-1.0e30f)
@@ -42,97 +43,85 @@ __device__ __forceinline__ void stream_tiles8(AttnState8<D> &st, const bf16x8_t 
 #pragma unroll
         for (int i = 0; i < D / 32; ++i) ring[s][i] = u32x4_t{0u, 0u, 0u, 0u};
 
-    static_assert(PF % 2 == 0, "tiles go in pairs");
     const int n_rounds = (nblk + PF - 1) / PF + 1;
     for (int rd = 0; rd < n_rounds; ++rd) {
 #pragma unroll
-        for (int s = 0; s < PF; s += 2) {
-            const int i = (rd - 1) * PF + s;                   // first tile of the pair; < 0 while the ring fills
-            float s8[8];                                       // this lane's 4 tokens of either tile
+        for (int s = 0; s < PF; ++s) {
+            const int i = (rd - 1) * PF + s;                   // tile of this iteration; < 0 while the ring fills
+            const int tok0 = t0 + i * 16 + qd * 4;             // this lane's 4 tokens
+            // scores of 16 tokens x 16 query heads; operand step kk = dwords 2 (kk % 2), 2 (kk % 2) + 1 of load kk / 2
+            u32x4_t kop[D / 32];
+            f32x4_t sc = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                // scores of 16 tokens x 16 query heads; operand step kk = dwords 2 (kk % 2), 2 (kk % 2) + 1 of load kk / 2
-                u32x4_t kop[D / 32];
-                f32x4_t sc = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kk = 0; kk < D / 32; ++kk) {
-                    const u32x4_t raw = ring[s + e][kk >> 1];
-                    const uint2 a = hx_e4m3x4_to_bf16x4((kk & 1) ? raw.z : raw.x);
-                    const uint2 b = hx_e4m3x4_to_bf16x4((kk & 1) ? raw.w : raw.y);
-                    kop[kk] = u32x4_t{a.x, a.y, b.x, b.y};
-                    sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kop[kk]), qop[kk], sc, 0, 0, 0);
-                }
-                hx_hold_operands(kop, sc);                     // converted operands outlive the products that read them
-#pragma unroll
-                for (int r = 0; r < 4; ++r) s8[4 * e + r] = sc[r] * scale_log2e;
+            for (int kk = 0; kk < D / 32; ++kk) {
+                const u32x4_t raw = ring[s][kk >> 1];
+                const uint2 a = hx_e4m3x4_to_bf16x4((kk & 1) ? raw.z : raw.x);
+                const uint2 b = hx_e4m3x4_to_bf16x4((kk & 1) ? raw.w : raw.y);
+                kop[kk] = u32x4_t{a.x, a.y, b.x, b.y};
+                sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kop[kk]), qop[kk], sc, 0, 0, 0);
             }
+            hx_hold_operands(kop, sc);                         // converted operands outlive the products that read them
+            float s4[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s4[r] = sc[r] * scale_log2e;
             // V: operand step q = dwords 2 (q % 2) (rows d < 16 of the step) and 2 (q % 2) + 1 (rows d >= 16) of load
             // D/64 + q / 2; a dword holds this lane's 4 tokens, one byte each.  Bytes of positions that do not
             // exist may hold anything (also NaN codes): they are cleared before the conversion.
-            uint32_t vraw[2][2][D / 32];                       // [tile][d >= 16][step]
+            uint32_t vlo[D / 32], vhi[D / 32];
 #pragma unroll
-            for (int e = 0; e < 2; ++e)
-#pragma unroll
-                for (int q = 0; q < D / 32; ++q) {
-                    const u32x4_t raw = ring[s + e][D / 64 + (q >> 1)];
-                    vraw[e][0][q] = (q & 1) ? raw.z : raw.x;
-                    vraw[e][1][q] = (q & 1) ? raw.w : raw.y;
-                }
-            if (i < 0 || t0 + (i + 2) * 16 > t1) {             // wave-uniform: a pair with missing tokens
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const int valid = (i < 0) ? 0 : t1 - (t0 + (i + e) * 16 + qd * 4);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) s8[4 * e + r] = r < valid ? s8[4 * e + r] : -INFINITY;
-                    const uint32_t keep = valid >= 4 ? 0xffffffffu : (valid <= 0 ? 0u : ((1u << (8 * valid)) - 1u));
-#pragma unroll
-                    for (int q = 0; q < D / 32; ++q) { vraw[e][0][q] &= keep; vraw[e][1][q] &= keep; }
-                }
+            for (int q = 0; q < D / 32; ++q) {
+                const u32x4_t raw = ring[s][D / 64 + (q >> 1)];
+                vlo[q] = (q & 1) ? raw.z : raw.x;
+                vhi[q] = (q & 1) ? raw.w : raw.y;
             }
-            float mx = fmaxf(fmaxf(fmaxf(s8[0], s8[1]), fmaxf(s8[2], s8[3])), fmaxf(fmaxf(s8[4], s8[5]), fmaxf(s8[6], s8[7])));
+            if (i < 0 || t0 + (i + 1) * 16 > t1) {             // wave-uniform: a tile with missing tokens
+                const int valid = (i < 0) ? 0 : (t1 - tok0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s4[r] = r < valid ? s4[r] : -INFINITY;
+                const uint32_t keep = valid >= 4 ? 0xffffffffu : (valid <= 0 ? 0u : ((1u << (8 * valid)) - 1u));
+#pragma unroll
+                for (int q = 0; q < D / 32; ++q) { vlo[q] &= keep; vhi[q] &= keep; }
+            }
+            float mx = fmaxf(fmaxf(s4[0], s4[1]), fmaxf(s4[2], s4[3]));
             mx = hx_max_of_16_lane_groups(mx);
             const float m_new = fmaxf(st.m, mx);
             const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
-            float p[8];
+            float p[4];
 #pragma unroll
-            for (int r = 0; r < 8; ++r) p[r] = __builtin_amdgcn_exp2f(s8[r] - m_new);
-            st.l = st.l * alpha + (((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])));
+            for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(s4[r] - m_new);
+            st.l = st.l * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
             // the accumulators are rescaled only when some maximum moved (else alpha is exactly 1 in every lane)
             if (__builtin_amdgcn_ballot_w64(m_new != st.m) != 0ull) {
 #pragma unroll
                 for (int nn = 0; nn < D / 16; ++nn) st.o[nn] *= alpha;
             }
             st.m = m_new;
-            // probabilities as a high + low bf16 pair, as in the bf16 kernel.  The contraction index of the second product is
-            // numbered so that a lane's eight are its four tokens of the first tile, then of the second: what it holds.
-            u32x4_t ph, pl;
+            // probabilities as a high + low bf16 pair, as in the bf16 kernel
+            uint2 ph, pl;
+            ph.x = hx_cvt_pk_bf16(p[0], p[1]);
+            ph.y = hx_cvt_pk_bf16(p[2], p[3]);
+            pl.x = hx_cvt_pk_bf16(p[0] - __uint_as_float(ph.x << 16), p[1] - __uint_as_float(ph.x & 0xffff0000u));
+            pl.y = hx_cvt_pk_bf16(p[2] - __uint_as_float(ph.y << 16), p[3] - __uint_as_float(ph.y & 0xffff0000u));
+            const s16x4_t pop_hi = __builtin_bit_cast(s16x4_t, ph);
+            const s16x4_t pop_lo = __builtin_bit_cast(s16x4_t, pl);
+            u32x4_t vop[D / 32];                               // x, y: rows d < 16 of the step; z, w: rows d >= 16
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                ph[r] = hx_cvt_pk_bf16(p[2 * r], p[2 * r + 1]);
-                pl[r] = hx_cvt_pk_bf16(p[2 * r] - __uint_as_float(ph[r] << 16), p[2 * r + 1] - __uint_as_float(ph[r] & 0xffff0000u));
+            for (int q = 0; q < D / 32; ++q) {
+                const uint2 lo2 = hx_e4m3x4_to_bf16x4(vlo[q]), hi2 = hx_e4m3x4_to_bf16x4(vhi[q]);
+                vop[q] = u32x4_t{lo2.x, lo2.y, hi2.x, hi2.y};
+                const s16x4_t lo = __builtin_bit_cast(s16x4_t, make_uint2(vop[q].x, vop[q].y));
+                const s16x4_t hi = __builtin_bit_cast(s16x4_t, make_uint2(vop[q].z, vop[q].w));
+                st.o[2 * q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(lo, pop_hi, st.o[2 * q], 0, 0, 0);
+                st.o[2 * q + 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(hi, pop_hi, st.o[2 * q + 1], 0, 0, 0);
+                st.o[2 * q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(lo, pop_lo, st.o[2 * q], 0, 0, 0);
+                st.o[2 * q + 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(hi, pop_lo, st.o[2 * q + 1], 0, 0, 0);
             }
-            const bf16x8_t pop_hi = __builtin_bit_cast(bf16x8_t, ph), pop_lo = __builtin_bit_cast(bf16x8_t, pl);
-#pragma unroll
-            for (int q = 0; q < D / 32; q += 2) {
-                u32x4_t vop[4];                                // steps q, q + 1: rows d < 16, d >= 16
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const uint2 a = hx_e4m3x4_to_bf16x4(vraw[0][k & 1][q + (k >> 1)]), b = hx_e4m3x4_to_bf16x4(vraw[1][k & 1][q + (k >> 1)]);
-                    vop[k] = u32x4_t{a.x, a.y, b.x, b.y};
-                    f32x4_t &o = st.o[2 * q + k];
-                    o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vop[k]), pop_hi, o, 0, 0, 0);
-                    o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vop[k]), pop_lo, o, 0, 0, 0);
-                }
-                hx_hold_operands(vop, ph, pl, st.o[2 * q], st.o[2 * q + 1], st.o[2 * q + 2], st.o[2 * q + 3]);
-            }
-            // the slots are free: request tiles i + PF and the next into them (or the query once the run is exhausted)
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const int nx = i + e + PF;
-                const int32_t blk = (nx < 64) ? __builtin_amdgcn_readlane(blk_lo, nx & 63) : __builtin_amdgcn_readlane(blk_hi, nx & 63);
-                const char *src = (nx < nblk) ? pool_layer + (size_t)blk * block_bytes + head_off : qtile;
-                load_tile8<D>(ring[s + e], src, lane);
-            }
+            hx_hold_operands(vop, ph, pl, st.o);
+            // the slot is free: request tile i + PF into it (or the query once the run is exhausted)
+            const int nx = i + PF;
+            const int32_t blk = (nx < 64) ? __builtin_amdgcn_readlane(blk_lo, nx & 63) : __builtin_amdgcn_readlane(blk_hi, nx & 63);
+            const char *src = (nx < nblk) ? pool_layer + (size_t)blk * block_bytes + head_off : qtile;
+            load_tile8<D>(ring[s], src, lane);
         }
     }
 }
@@ -232,9 +221,9 @@ int hx_launch_attention_fp8(const hx_engine *e, const hx_kv *kv, int layer, cons
 #define HX_ATTN8_ARGS                                                                                             \
     (const int32_t *)a.sched, (const int32_t *)a.pre, (const int32_t *)a.lens, pool_layer, kv->block_bytes,      \
         (const uint16_t *)a.qp, table, max_blocks, e->cfg.n_kv_heads, e->G, scale_log2e, a.part_ml, a.part_o
-    // 8 KiB in flight per wavefront; head size 64, 256 sequences of 4000 to 16 000: depths 2 / 4 / 6 114 / 108 / 121 us
+    // ring depths: 128: see the header; 64: 256 sequences of 4 000 to 16 000: 2 / 4 / 6 tiles 117 / 118 / 125 us
     if (e->D == 128) hipLaunchKernelGGL((attn_splitk_fp8_kernel<128, 2>), grid, block, 0, st, HX_ATTN8_ARGS);
-    else             hipLaunchKernelGGL((attn_splitk_fp8_kernel<64, 4>), grid, block, 0, st, HX_ATTN8_ARGS);
+    else             hipLaunchKernelGGL((attn_splitk_fp8_kernel<64, 2>), grid, block, 0, st, HX_ATTN8_ARGS);
 #undef HX_ATTN8_ARGS
     HX_CHECK_LAUNCH("attn_splitk_fp8");
     return HX_OK;

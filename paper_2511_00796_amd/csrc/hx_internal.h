@@ -102,12 +102,16 @@ __device__ __forceinline__ void hx_hold_operands(const unsigned int __attribute_
     else if constexpr (N == 2) asm volatile("s_nop 3" : "+v"(acc) : "v"(op[0]), "v"(op[1]));
     else static_assert(N == 2 || N == 4, "operand steps of head sizes 64 and 128");
 }
-// Behind 16x16x32 products of four operands, each with the high and the low part of the probabilities, into four accumulators.
-__device__ __forceinline__ void hx_hold_operands(const unsigned int __attribute__((ext_vector_type(4))) (&v)[4],
-                                                 const unsigned int __attribute__((ext_vector_type(4))) &hi,
-                                                 const unsigned int __attribute__((ext_vector_type(4))) &lo, f32x4_t &a0, f32x4_t &a1,
-                                                 f32x4_t &a2, f32x4_t &a3) {
-    asm volatile("s_nop 3" : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3) : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(hi), "v"(lo));
+// Behind the 16x16x16 products of an 8-bit tile's V, into all accumulators, with the high and the low part of the probabilities.
+template <int N>
+__device__ __forceinline__ void hx_hold_operands(const unsigned int __attribute__((ext_vector_type(4))) (&v)[N], const uint2 &hi, const uint2 &lo,
+                                                 f32x4_t (&o)[2 * N]) {
+    if constexpr (N == 4)
+        asm volatile("s_nop 3" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]), "+v"(o[4]), "+v"(o[5]), "+v"(o[6]), "+v"(o[7])
+                     : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(hi.x), "v"(hi.y), "v"(lo.x), "v"(lo.y));
+    else if constexpr (N == 2)
+        asm volatile("s_nop 3" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]) : "v"(v[0]), "v"(v[1]), "v"(hi.x), "v"(hi.y), "v"(lo.x), "v"(lo.y));
+    else static_assert(N == 2 || N == 4, "operand steps of head sizes 64 and 128");
 }
 // The same for 32x32x16 products (attention_prompt.hip), which have never been seen to suffer (in builds without these statements
 // the kernel had a hundred such writes 2 to 6 slots behind them, and its results were right): free of cost, and one rule for

@@ -254,3 +254,35 @@ def test_attention_stage_over_the_8_bit_cache_matches_oracle(hx, name, waves, mo
         assert err <= ATTN_TOL, (name, b, int(T), err)
         worst = max(worst, err)
     print("attention over the 8-bit cache, %s: max abs err %.2e" % (name, worst))
+
+
+def test_long_attention_over_the_8_bit_cache_is_as_near_to_exact_as_tile_by_tile(hx):
+    """9 001 tokens, 7B heads, four draws of K, V and queries: relative error (2-norm) against float64 on the bytes the cache holds.
+    With each tile's own maximum its mean is 1.803e-6, with one maximum for two tiles at a time it was 1.854e-6, both the same in every
+    run (the inputs are seeded and the kernel is deterministic), so the bound lies between the two."""
+    import math
+    s = dataclasses.replace(synth.QWEN_7B, n_layers=1, vocab=64)
+    B, T = 4, 9001
+    nb = (T + 15) // 16
+    eng = hx.Engine(s, B, T + 1, kv_dtype=hx.HX_KV_FP8_E4M3)
+    kv = hx.KVCache(eng, B * nb)
+    table = torch.randperm(B * nb, generator=torch.Generator().manual_seed(1)).int().view(B, nb).cuda()
+    start = (torch.arange(B + 1) * T).int().cuda()
+    lens = torch.full((B,), T, dtype=torch.int32, device="cuda")
+    errs = []
+    for seed in range(4):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        k, v = torch.randn(2, B * T, s.n_kv_heads, s.head_dim, generator=g, device="cuda").bfloat16()
+        kv.prefill_fill(0, k, v, start, table)
+        q = torch.randn(B, s.q_dim, generator=g, device="cuda").bfloat16().float()
+        o = eng.stage_attention(kv, 0, q, lens, table).double().view(B, s.n_q_heads, s.head_dim)
+        k, v = [t.float().to(torch.float8_e4m3fn).double().view(B, T, s.n_kv_heads, s.head_dim) for t in (k, v)]
+        ref = torch.empty_like(o)
+        for b in range(B):
+            for h in range(s.n_q_heads):
+                kh, vh = k[b, :, h // s.group].contiguous(), v[b, :, h // s.group].contiguous()
+                p = torch.softmax(kh @ q[b].double().view(s.n_q_heads, -1)[h] / math.sqrt(s.head_dim), 0)
+                ref[b, h] = p @ vh
+        errs.append(float((o - ref).norm() / ref.norm()))
+    print("long attention over the 8-bit cache: relative errors", errs)
+    assert sum(errs) / len(errs) <= 1.828e-6
