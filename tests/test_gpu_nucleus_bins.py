@@ -1,5 +1,6 @@
 """Nucleus selection by bins: rows at the edges of one and several workgroups per row, with so many equal logits that no list
-takes the cut bin's entries, that one list of several overflows, or that the cut falls on a bin of one entry.  Logits are planted
+takes the cut bin's entries, that one list of several overflows, that each takes its own but all are too many together, or that the
+cut falls on a bin of one entry.  Logits are planted
 through the LM head (one input column is 1, so column j's logit is the weight of row 0); the oracle is the sort of the definition."""
 import numpy as np
 import pytest
@@ -25,16 +26,25 @@ def planted(law, V):
         return r.normal(0, 2, V)
     if law == "equal":                       # one bin holds the whole row
         return np.zeros(V)
-    if law == "two_levels":                  # 5 000 equal entries in front, more than a part's list, spread or together
+    if law == "two_levels":                  # 5 000 equal entries in front, more than a part's list
         z = np.full(V, -3.0)
         z[: min(5000, V // 2)] = 1.0
+        return z
+    if law == "spread":                      # as many all over the row, which every part's list takes
+        z = np.full(V, -3.0)
+        z[:: max(2, V // 5000)] = 1.0
+        return z
+    if law == "two_in_a_bin":                # two in every other tile of 32 columns, neighbouring bf16 values that share a bin: in the
+        z = np.full(V, -20.0)                # longest row 9 376, which every part's list takes its own of, but all together are too many
+        z[::64] = 1.0
+        z[7::64] = 1.0078125
         return z
     z = r.normal(0, 1, V)                     # peaked: one entry carries nearly everything
     z[V // 3] = 30.0
     return z
 
 
-@pytest.mark.parametrize("law", ["normal", "equal", "two_levels", "peaked"])
+@pytest.mark.parametrize("law", ["normal", "equal", "two_levels", "spread", "two_in_a_bin", "peaked"])
 @pytest.mark.parametrize("vocab", [8, 1000, 32764, 32768, 65540, 300000])
 def test_kept_sets_of_planted_rows(hx, vocab, law):
     s = synth.ModelShape("nb", 1, 32, 1, 1, 64, 16, vocab)
