@@ -105,69 +105,69 @@ __device__ __forceinline__ void stream_tiles(AttnState<D> &st, const bf16x8_t (&
             const int i = (rd - 1) * PF + s;                   // tile of this iteration; < 0 while the ring fills
             const int tok0 = t0 + i * 16 + qd * 4;             // this lane's 4 tokens
             if (rd > 0) {
-            // scores of 16 tokens x 16 query heads
-            f32x4_t sc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                // scores of 16 tokens x 16 query heads
+                f32x4_t sc = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int kk = 0; kk < D / 32; ++kk)
-                sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ring[s][kk]), qop[kk], sc, 0, 0, 0);
-            {
-                // The K operands of the slot die with these products, so the compiler may hand their registers to the
-                // next vector instruction (at head size 64 it did: the mask arithmetic of a ragged tile, a few
-                // instructions behind the product that was still to read them).  Keep them live past the products
-                // (hx_hold_operands) at both head sizes.
-                u32x4_t kheld[D / 32];
+                for (int kk = 0; kk < D / 32; ++kk)
+                    sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ring[s][kk]), qop[kk], sc, 0, 0, 0);
+                {
+                    // The K operands of the slot die with these products, so the compiler may hand their registers to the
+                    // next vector instruction (at head size 64 it did: the mask arithmetic of a ragged tile, a few
+                    // instructions behind the product that was still to read them).  Keep them live past the products
+                    // (hx_hold_operands) at both head sizes.
+                    u32x4_t kheld[D / 32];
 #pragma unroll
-                for (int kk = 0; kk < D / 32; ++kk) kheld[kk] = ring[s][kk];
-                hx_hold_operands(kheld, sc);
-            }
-            float s4[4];
+                    for (int kk = 0; kk < D / 32; ++kk) kheld[kk] = ring[s][kk];
+                    hx_hold_operands(kheld, sc);
+                }
+                float s4[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) s4[r] = sc[r] * scale_log2e;
-            // V of positions that do not exist must not reach the product as NaN/Inf
-            u32x4_t vv[D / 32];
+                for (int r = 0; r < 4; ++r) s4[r] = sc[r] * scale_log2e;
+                // V of positions that do not exist must not reach the product as NaN/Inf
+                u32x4_t vv[D / 32];
 #pragma unroll
-            for (int q = 0; q < D / 32; ++q) vv[q] = ring[s][D / 32 + q];
-            if (t0 + (i + 1) * 16 > t1) {                      // wave-uniform: a tile with missing tokens
-                const int valid = t1 - tok0;
+                for (int q = 0; q < D / 32; ++q) vv[q] = ring[s][D / 32 + q];
+                if (t0 + (i + 1) * 16 > t1) {                      // wave-uniform: a tile with missing tokens
+                    const int valid = t1 - tok0;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) s4[r] = r < valid ? s4[r] : -INFINITY;
-                const uint32_t m01 = valid >= 2 ? 0xffffffffu : (valid == 1 ? 0x0000ffffu : 0u);
-                const uint32_t m23 = valid >= 4 ? 0xffffffffu : (valid == 3 ? 0x0000ffffu : 0u);
+                    for (int r = 0; r < 4; ++r) s4[r] = r < valid ? s4[r] : -INFINITY;
+                    const uint32_t m01 = valid >= 2 ? 0xffffffffu : (valid == 1 ? 0x0000ffffu : 0u);
+                    const uint32_t m23 = valid >= 4 ? 0xffffffffu : (valid == 3 ? 0x0000ffffu : 0u);
 #pragma unroll
-                for (int q = 0; q < D / 32; ++q) { vv[q].x &= m01; vv[q].y &= m23; vv[q].z &= m01; vv[q].w &= m23; }
-            }
-            float mx = fmaxf(fmaxf(s4[0], s4[1]), fmaxf(s4[2], s4[3]));
-            mx = hx_max_of_16_lane_groups(mx);
-            const float m_new = fmaxf(st.m, mx);
-            const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
-            float p[4];
+                    for (int q = 0; q < D / 32; ++q) { vv[q].x &= m01; vv[q].y &= m23; vv[q].z &= m01; vv[q].w &= m23; }
+                }
+                float mx = fmaxf(fmaxf(s4[0], s4[1]), fmaxf(s4[2], s4[3]));
+                mx = hx_max_of_16_lane_groups(mx);
+                const float m_new = fmaxf(st.m, mx);
+                const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
+                float p[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(s4[r] - m_new);
-            st.l = st.l * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
-            st.m = m_new;
+                for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(s4[r] - m_new);
+                st.l = st.l * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
+                st.m = m_new;
 #pragma unroll
-            for (int nn = 0; nn < D / 16; ++nn) st.o[nn] *= alpha;
-            // P enters the matrix core as bf16; split it into a high and a low bf16 part so that the
-            // product keeps ~16 significant bits of every probability
-            uint2 ph, pl;
-            ph.x = hx_cvt_pk_bf16(p[0], p[1]);
-            ph.y = hx_cvt_pk_bf16(p[2], p[3]);
-            pl.x = hx_cvt_pk_bf16(p[0] - __uint_as_float(ph.x << 16), p[1] - __uint_as_float(ph.x & 0xffff0000u));
-            pl.y = hx_cvt_pk_bf16(p[2] - __uint_as_float(ph.y << 16), p[3] - __uint_as_float(ph.y & 0xffff0000u));
-            const s16x4_t pop_hi = __builtin_bit_cast(s16x4_t, ph);
-            const s16x4_t pop_lo = __builtin_bit_cast(s16x4_t, pl);
+                for (int nn = 0; nn < D / 16; ++nn) st.o[nn] *= alpha;
+                // P enters the matrix core as bf16; split it into a high and a low bf16 part so that the
+                // product keeps ~16 significant bits of every probability
+                uint2 ph, pl;
+                ph.x = hx_cvt_pk_bf16(p[0], p[1]);
+                ph.y = hx_cvt_pk_bf16(p[2], p[3]);
+                pl.x = hx_cvt_pk_bf16(p[0] - __uint_as_float(ph.x << 16), p[1] - __uint_as_float(ph.x & 0xffff0000u));
+                pl.y = hx_cvt_pk_bf16(p[2] - __uint_as_float(ph.y << 16), p[3] - __uint_as_float(ph.y & 0xffff0000u));
+                const s16x4_t pop_hi = __builtin_bit_cast(s16x4_t, ph);
+                const s16x4_t pop_lo = __builtin_bit_cast(s16x4_t, pl);
 #pragma unroll
-            for (int q = 0; q < D / 32; ++q) {
-                uint2 lo = make_uint2(vv[q].x, vv[q].y), hi = make_uint2(vv[q].z, vv[q].w);
-                st.o[2 * q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, lo), pop_hi, st.o[2 * q], 0, 0, 0);
-                st.o[2 * q + 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, hi), pop_hi, st.o[2 * q + 1], 0, 0, 0);
-            }
+                for (int q = 0; q < D / 32; ++q) {
+                    uint2 lo = make_uint2(vv[q].x, vv[q].y), hi = make_uint2(vv[q].z, vv[q].w);
+                    st.o[2 * q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, lo), pop_hi, st.o[2 * q], 0, 0, 0);
+                    st.o[2 * q + 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, hi), pop_hi, st.o[2 * q + 1], 0, 0, 0);
+                }
 #pragma unroll
-            for (int q = 0; q < D / 32; ++q) {
-                uint2 lo = make_uint2(vv[q].x, vv[q].y), hi = make_uint2(vv[q].z, vv[q].w);
-                st.o[2 * q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, lo), pop_lo, st.o[2 * q], 0, 0, 0);
-                st.o[2 * q + 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, hi), pop_lo, st.o[2 * q + 1], 0, 0, 0);
-            }
+                for (int q = 0; q < D / 32; ++q) {
+                    uint2 lo = make_uint2(vv[q].x, vv[q].y), hi = make_uint2(vv[q].z, vv[q].w);
+                    st.o[2 * q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, lo), pop_lo, st.o[2 * q], 0, 0, 0);
+                    st.o[2 * q + 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, hi), pop_lo, st.o[2 * q + 1], 0, 0, 0);
+                }
             }
             // the slot is free: request tile i + PF into it (or the query once the run is exhausted)
             const int nx = i + PF;

@@ -147,13 +147,13 @@ int hx_launch_pack(const hx_engine *e, const hx_pack_tensor *tensors, int n, hip
 }
 
 // ---- the streaming product ------------------------------------------------------------------------------------
-// Workgroup = WN x WK consumer wavefronts + NP producer wavefronts, one workgroup per compute unit.
+// Workgroup = WN x WK consumer wavefronts + NP producer wavefronts.
 // Consumers: WN adjacent n-tiles, each split into WK k-slices that are summed in slice order through LDS at
-// the end.  Every consumer keeps RING weight loads (1 KiB each, non-temporal) in flight in a register ring
-// and issues no other vector-memory load, so the in-order load counter never makes it wait for anything but
-// the tile it is about to use.  Producers stage the activations of the coming chunks (KC k-steps of every
-// k-slice, 32 KiB per stage, four stages) in LDS through their own registers; one workgroup barrier per chunk
-// hands a stage over.
+// the end.  Every consumer keeps RING weight loads (1 KiB each, non-temporal; 8 or 16: gemm_ring) in flight in a
+// register ring and issues no other vector-memory load, so the in-order load counter never makes it wait for anything
+// but the tile it is about to use.  Producers stage the activations of the coming chunks (KC k-steps of every
+// k-slice, half a ring at most; four stages) in LDS through their own registers; one workgroup barrier per chunk
+// hands a stage over.  A stage of one k-slice: 128 rows 32 KiB (16 with a ring of 8), 64 rows 16 (8), 32 rows 4.
 #ifndef HX_GEMM_RING
 #define HX_GEMM_RING 16
 #endif
@@ -183,7 +183,9 @@ __device__ __forceinline__ u32x4_t hx_stream_load(const uint4 *p) {   // read-on
 // of the activations, and splits of few k-steps run in whole revolutions.  So 8, but for two shapes that lose by it: the four and
 // five consumers of 128 rows, which wait for activations more than for weights, and four tiles of gate|up.  us, 16 -> 8: 7B at 3
 // rows gate|up 44.0 -> 41.7, down 24.2 -> 22.5, QKV 7.8 -> 7.0, O 7.8 -> 7.1; at 37 rows 45.2 -> 44.2, 27.6 -> 26.6, 10.5 -> 9.7, 11.1 -> 10.2,
-// LM head 188 -> 185, at 128 rows 227 -> 220; kept: 7B at 128 rows gate|up 54.0 (57.2), down 37.1 (39.4), 14B gate|up at 64 47.4 (48.4).
+// LM head 188 -> 185, at 128 rows 227 -> 220; kept, at 16 (8): 7B at 128 rows gate|up 54.0 (57.2), down 37.1 (39.4); gate|up of four tiles
+// at 33 / 48 / 64 rows 1.5B 16.6 / 16.1 / 16.3 (17.1 / 16.4 / 17.1), hidden 2048 22.6 / 21.6 / 22.7 (22.7 / 22.2 / 22.8), 14B 48.8 / 47.2 / 47.0
+// (49.0 / 48.1 / 47.8).
 template <int MG, int WN, int EPI> constexpr int gemm_ring() {
     return WN == 10 || MG == 1 || (MG == 2 && !(WN == 4 && EPI == HX_EPI_SWIGLU)) ? HX_GEMM_RING / 2 : HX_GEMM_RING;
 }
@@ -495,20 +497,22 @@ static int launch_shape(int wn, int wk, int epilogue, dim3 grid, hipStream_t st,
 }
 
 // ---- host side: how to cut one product into launches ---------------------------------------------------------------
-// A workgroup occupies a whole compute unit (128 KiB of LDS), so a launch runs in rounds of as many workgroups as
-// the device has compute units (hx_device_cus) and a partly filled last round costs a full one.  Measured on MI355X, wn x 1 shapes (wn n-tiles
-// sharing one activation stream, 32 KiB stages, a barrier every 8 k-steps) are the fastest.  The planner
-// picks wn in {4, 5, 6, 10} -- and, for products whose consumer kernel sums split partials, the number of
-// K-splits (at most HX_MAX_SPLITS, at least 16 k-steps each) -- that minimises the time of the busiest compute
-// unit: rounds x (wn tiles + 3 tile-times for the round's own copy of the activations, which every workgroup
-// draws from the L2 whatever its width) x whole ring revolutions; split products, which run in one round and
-// read only a K-slice of the activations, keep a small charge per extra tile instead (five
-// consumers on four SIMDs); ties go to the smaller wn and fewer splits.
+// Measured on MI355X, wn x 1 shapes (wn n-tiles sharing one activation stream) are the fastest.  The planner picks wn in
+// {4, 5, 6, 10} -- and, for products whose consumer kernel sums split partials, the number of K-splits (at most
+// HX_MAX_SPLITS, at least 16 k-steps each) -- that minimises the time of the busiest compute unit in a model fitted at 128 rows,
+// where a workgroup occupies a compute unit (128 KiB of LDS), a launch runs in rounds of as many workgroups as the device has
+// compute units (hx_device_cus) and a partly filled last round costs a full one: rounds x (wn tiles + 3 tile-times for the
+// round's own copy of the activations, which every workgroup draws from the L2 whatever its width) x revolutions of
+// PLAN_STEPS k-steps; split products, which run in one round and read only a K-slice of the activations, keep a small charge
+// per extra tile instead (five consumers on four SIMDs); ties go to the smaller wn and fewer splits.  Fewer rows take
+// the same plan, though their rings are of 8 and their workgroups take a quarter of the LDS or less: the splits decide
+// in which order a row's products are added, and so a row comes out alike in every batch of up to 128.
 // Examples: the 1184 tiles of the 7B gate|up matrix make 296 workgroups of 4 (two rounds on 256 compute
 // units) but 237 workgroups of 5 (one round); the 4752 tiles of the LM head make five rounds of 4, four of 5 or
 // two of 10, measured 253 / 244 / 230 us.  Ten tiles per workgroup are twelve wavefronts (three per SIMD): only
-// for products without split partials.  Matrices of few columns go to gemm_slice.hip.  HX_GEMM_SHAPE="wn,wk,splits" overrides (tuning).  Batches of more than 128 rows:
-// hx_plan_wide, under the same two knobs.
+// for products without split partials.  Matrices of few columns go to gemm_slice.hip.  HX_GEMM_SHAPE="wn,wk,splits" overrides
+// (tuning).  Batches of more than 128 rows: hx_plan_wide, under the same two knobs.
+constexpr int PLAN_STEPS = 16;
 
 struct gemm_launch { int wn, wk, splits, slice_tiles; };     // slice_tiles > 0: gemm_slice.hip, with these K-splits
 
@@ -540,9 +544,9 @@ static gemm_launch plan_product(int n_tiles, int k_steps, bool partial) {
             const int wgs = ((n_tiles + wn - 1) / wn) * s;
             const int rounds = (wgs + cus - 1) / cus;
             const int sps = (k_steps + s - 1) / s;
-            // busiest compute unit: rounds x (wn tiles + the activations) x whole ring revolutions (one more to fill
+            // busiest compute unit: rounds x (wn tiles + the activations) x whole revolutions (one more to fill
             // the ring), plus a small charge per split for writing and re-reading its partial tile
-            const int revolutions = (sps + HX_GEMM_RING - 1) / HX_GEMM_RING + 1;
+            const int revolutions = (sps + PLAN_STEPS - 1) / PLAN_STEPS + 1;
             const double width = partial ? wn + 0.35 * (wn - 4) : wn + 3.0;   // as measured on each kind
             const double cost = (double)rounds * width * revolutions * (1.0 + 0.02 * (s - 1));
             if (cost < best_cost - 1e-9) { best_cost = cost; best.wn = wn; best.splits = s; }

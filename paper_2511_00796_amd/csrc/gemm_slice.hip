@@ -8,8 +8,8 @@
 // What bounds it is the round trips of a launch: a ring's fill, and the end.  That the activations of every tile come through
 // the ring, which returns in order behind the weights, makes it slower than the streaming kernel wherever the weights are
 // many: 14B gate|up at 64 rows 73 us (two tiles per workgroup 56), 48 there.  us, streaming -> this, 1 / 64 / 128 rows:
-// 1.5B QKV 4.3 / 6.7 / 9.7 -> 3.5 / 4.4 / 6.3, O 4.5 / 6.5 / 10.2 -> 3.7 / 4.2 / 5.8, down 11.2 / 13.8 / 16.6 -> 7.2 / 11.1 / 13.0
-// (two tiles; one: 7.7 / 12.6 / 15.0), with weights that are partly in the memory-side cache.
+// 1.5B QKV 3.9 / 7.5 / 10.5 -> 2.7 / 4.3 / 7.0, O 4.5 / 7.1 / 9.5 -> 3.4 / 4.1 / 6.0, down 10.0 / 14.3 / 16.8 -> 8.6 / 11.2 / 13.0
+// (two tiles; one: 7.6 / 10.4 / 13.6), with weights that are partly in the memory-side cache.
 #include "hx_internal.h"
 #include "lm_epilogue.h"
 #include <algorithm>

@@ -111,7 +111,7 @@ def test_product_plans_fill_the_chip_and_respect_their_limits(monkeypatch):
     """Host-side launch planner: every plan keeps at least 16 k-steps per split, never splits a product whose epilogue
     needs the whole sum, stays within 9 splits and 4..6 tiles per workgroup (10 only for unsplit products; 4..8 beyond 128 rows),
     and for the 7B shapes picks the plans the design rests on (gate|up: 237 workgroups of 5 = one round on 256 compute
-    units; O and QKV: 7 splits of exactly two ring revolutions; down: 9 splits; LM head: two rounds of 10 tiles)."""
+    units; O and QKV: 7 splits of exactly two revolutions of 16 k-steps, the planner's unit; down: 9 splits; LM head: two rounds of 10 tiles)."""
     lib = binding.load()
 
     def plan(n_tiles, k_steps, batch, partial):
