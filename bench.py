@@ -23,8 +23,8 @@ HBM_PEAK_GBS = 8000.0     # MI355X published HBM3E bandwidth
 # HBM bytes per attention launch at workload 7b-b128 from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a plain
 # copy (profiles/attn_splitk_7b-b128_hbm_traffic.txt).  Valid only for the kernel source they were taken with.
 PMC_TRAFFIC = {"workload": "7b-b128",
-               "attention_hip_sha256": "7c92c9342a46bc9edf999d95e950ce9a51d17eada7940b85ba9a7619a0d807ad",
-               "fetch_bytes": 2150.31e6, "write_bytes": 9.45e6}
+               "attention_hip_sha256": "65b376a2d7e347f6733e0bf45e3775782fa7d541a2820f213db81216a91edf96",
+               "fetch_bytes": 2150.25e6, "write_bytes": 9.45e6}
 
 
 def measured_traffic(workload_name):

@@ -12,7 +12,7 @@
 // digit instead.
 // A short row, or one of many, is one workgroup's (nucleus_parts).  Of others the bins are filled and the bin's keys
 // listed by as many workgroups per row as give the chip two on every compute unit: exponentials and atomics of the whole row,
-// three times over, by one workgroup were four fifths of the time.  64 rows of 152 064 logits: 94 -> 16 + 17 + 24 us, bound by
+// three times over, by one workgroup were four fifths of the time.  64 rows of 152 064 logits: 94 -> 17 + 17 + 24 us, bound by
 // the LDS atomics, the chains of small steps, and the launches.
 // The draw takes the tile winners that the LM head's sampling epilogue has left, on the whole
 // chip (here, one workgroup per row, drawing again for every kept entry was 90 of 144 us at 64 rows of 152 064 logits).
