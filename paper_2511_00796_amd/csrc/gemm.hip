@@ -24,7 +24,7 @@ typedef unsigned int u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)))
 // columns: eight 16-byte loads, a wavefront's each 1 KiB of one source row; transposed in registers to one 16-byte unit
 // (8 k of a column) per column, through LDS into output order, and stored 1 KiB per wavefront and instruction.
 // PHASE 0: tile column c = source column 32 * nt + c; PHASE 1 / 2 (gate / up): columns 0..15 / 16..31 of a tile, from
-// source column 16 * nt + c % 16 (runs of 256 bytes).  What bounds it is memory: see hx_launch_pack_matrix.
+// source column 16 * nt + c % 16 (runs of 256 bytes).  What bounds it is memory: see hx_launch_pack.
 #define HX_PACK_COLS 512
 // The source may lie at any element: the 16-byte loads are from a 2-byte-aligned type (one load
 // instruction, which the hardware takes at any alignment), and only a group of columns that ends past the row goes by elements.
