@@ -12,14 +12,17 @@
 // (192, 128 columns), or 8 of 32 rows by all 224 or 160 columns.
 // A chunk is 2 k-steps: 16 pieces of X and 2 WNT of W, each copied global -> LDS directly by one wavefront, requested two
 // chunks ahead into a ring of three stages (five ahead into six: wide_stages); one barrier per chunk, passed BEFORE the chunk's last k-step is multiplied,
-// so that the first operand reads of the next chunk hide behind those products, as the reads of its second k-step hide
-// behind the first.  Reads, copies and products are laid out by hand in groups (sched_barrier).
-// What bounds it is the matrix cores' power: with random operands a loop of 32x32x16 products out of registers reaches
-// 1 550 TFLOP/s on this card (zeros: 2 410).  7B gate|up, 2048 rows, output stores left out: this kernel 1 253 TFLOP/s;
-// with its copies removed 1 442, with its products removed 1 965.  The four-wavefront kernel before it (128 x 128 per
-// wavefront, copies through registers) 1 195, and 951 against 1 086 with fp32 stores, which the second wavefront of a
-// SIMD overlaps.  Four or five stages, or chunks of 4 k-steps in two stages, were not faster there (1 095, 1 088, 995).
-//
+// so that the first operand reads of the next chunk hide behind those products, as the reads of its second k-step (16x16x32: of the
+// second half of the longer operand) hide behind the first.  Reads, copies and products are laid out by hand in groups (sched_barrier).
+// What bounds it is the matrix cores' power, and 16x16x32 products need less of it than 32x32x16 ones: with random operands a
+// loop out of registers reaches 2 080 TFLOP/s with the former and 1 810 with the latter, on one card.  A chunk of two k-steps is one
+// 16x16x32 product's k, and its operands are read from the same stages (lane l: row l % 16 of a half group, k octet l / 16), so
+// the layouts stay; the sums come out the same, bit for bit.  Six and more tiles per workgroup use them, us, 32x32x16 -> 16x16x32 in turn:
+// 7B, 2048 rows gate|up 453 -> 422 (1.28 PFLOP/s), down 227 -> 215, O 52.3 -> 49.4; 14B, 4864 rows gate|up 1146 -> 1096, down 551 -> 501
+// (1.38), QKV 322 -> 305.  Narrower tiles wait for memory and keep 32x32x16 (1.5B gate|up 25.5 | 26.5 at 256 rows, 63.5 | 65.5 at 1024),
+// and so does the LM head, whose epilogue is written for that accumulator.
+// Four wavefronts of 128 x 128, one per SIMD, move a quarter less through LDS and are slower (575 against 437 in one session).
+
 // Workgroup numbering: consecutive workgroup ids go to different XCDs, so XCD x takes the x-th eighth of the work, row
 // blocks fastest, splits slowest: its workgroups take all row blocks of a few column blocks and walk K in step, so each XCD's L2 sees
 // (nearly) every weight once, and all XCDs have the same number of workgroups.  (Whole column blocks dealt to the XCDs
@@ -118,6 +121,126 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
         __builtin_amdgcn_sched_barrier(0);
     };
     const int wm = wave / WCOL, wn = wave % WCOL;
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s) {
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) copy_one(i);
+        advance();
+    }
+    hand_over();                                        // chunk 0 is in its stage
+    if constexpr (WNT >= 6 && EPI <= HX_EPI_SWIGLU) {
+        // 16x16x32 products: a chunk is their k; a 32-row group or a column tile is two fragments.  The longer operand is held once and
+        // read half by half, the shorter one twice.
+        constexpr int XF = 2 * TM, WF = 2 * TW;
+        constexpr bool XL = XF >= WF;
+        constexpr int NL = XL ? XF : WF, NS = XL ? WF : XF, H = NL / 2;
+        static_assert(NS == 2 || NS == 4, "the hold behind the last products names every fragment of the shorter operand");
+        f32x4_t acc[XF][WF];
+#pragma unroll
+        for (int i = 0; i < XF; ++i)
+#pragma unroll
+            for (int j = 0; j < WF; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        u32x4_t lo[NL], sh[2][NS];
+        // lane l of a fragment: row l % 16 of its half, k octet l / 16 (k-step l / 32 of the chunk, half l / 16 % 2 of it)
+        const int row = lane & 15, oct = lane >> 4;
+        const u32x4_t *xbase = lds + ((oct >> 1) * 8 + TM * wm) * 64 + (oct & 1) * 32 + row;
+        const u32x4_t *wbase = lds + (KC * 8 + (oct >> 1) * WNT + wn * TW) * 64 + (oct & 1) * 32 + row;
+        auto frag = [&](bool x, uint32_t stage, int f) { return (x ? xbase : wbase)[stage * STAGE_U4 + (f >> 1) * 64 + (f & 1) * 16]; };
+        auto read_l = [&](uint32_t stage, int f) { lo[f] = frag(XL, stage, f); };
+        auto read_s = [&](uint32_t stage, int set, int f) { sh[set][f] = frag(!XL, stage, f); };
+        auto multiply = [&](int l, int set) {
+#pragma unroll
+            for (int f = 0; f < NS; ++f) {
+                f32x4_t &d = XL ? acc[l][f] : acc[f][l];
+                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, XL ? sh[set][f] : lo[l]),
+                                                            __builtin_bit_cast(bf16x8_t, XL ? lo[l] : sh[set][f]), d, 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        // the second k-step of an odd split's last chunk may hold anything: its lanes of both operands are zero
+        auto clear = [&](u32x4_t &v) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = lane < 32 ? v[k] : 0u;
+        };
+#pragma unroll
+        for (int f = 0; f < NS; ++f) read_s(0, 0, f);
+#pragma unroll
+        for (int l = 0; l < H; ++l) read_l(0, l);
+        uint32_t rd = 0;                                // stage of chunk c
+        auto chunk = [&](int c, int set) {
+            const uint32_t nrd = rd + 1 == NST ? 0 : rd + 1;
+            const bool odd = ODD && 2 * c + 1 >= k1 - k0;
+            if (odd) {
+#pragma unroll
+                for (int f = 0; f < NS; ++f) clear(sh[set][f]);
+#pragma unroll
+                for (int l = 0; l < H; ++l) clear(lo[l]);
+            }
+            // first half: beside its products the reads of the second, and the copies of chunk c + NST - 1 into the stage of
+            // chunk c - 1, which everybody has left
+#pragma unroll
+            for (int l = 0; l < H; ++l) {
+                read_l(rd, H + l);
+#pragma unroll
+                for (int q = 0; q < LPW; ++q) if (q * H / LPW == l) copy_one(q);
+                multiply(l, set);
+            }
+            advance();
+            hand_over();
+            if (odd) {
+#pragma unroll
+                for (int l = H; l < NL; ++l) clear(lo[l]);
+            }
+            // second half: beside its products the first reads of chunk c + 1
+#pragma unroll
+            for (int l = H; l < NL; ++l) {
+#pragma unroll
+                for (int f = 0; f < NS; ++f) if (f * H / NS == l - H) read_s(nrd, set ^ 1, f);
+                read_l(nrd, l - H);
+                multiply(l, set);
+            }
+            rd = nrd;
+        };
+        int c = 0;
+        for (; c + 1 < n_chunks; c += 2) { chunk(c, 0); chunk(c + 1, 1); }
+        if (c < n_chunks) chunk(c, 0);
+        // nothing may be written into the last products' operands a few slots behind them (hx_hold_operands)
+        f32x4_t &end = XL ? acc[NL - 1][NS - 1] : acc[NS - 1][NL - 1];
+        asm volatile("s_nop 7" : "+v"(end) : "v"(lo[NL - 1]), "v"(lo[NL - 2]), "v"(lo[NL - 3]), "v"(sh[0][0]), "v"(sh[0][NS / 2 - 1]), "v"(sh[0][NS / 2]),
+                     "v"(sh[0][NS - 1]), "v"(sh[1][0]), "v"(sh[1][NS / 2 - 1]), "v"(sh[1][NS / 2]), "v"(sh[1][NS - 1]));
+        __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT(0));    // no copy is in flight when the workgroup gives its LDS back
+
+        // register r of lane l of acc[i][j]: batch row 32 * TM * wm + 16 * i + l % 16, column 32 * (nt0 + wn * TW) + 16 * j + 4 * (l / 16) + r
+        const int nt1 = nt0 + wn * TW, m0 = 32 * TM * wm + row;
+        if (EPI == HX_EPI_PARTIAL) {
+            float *y = a.y0 + ((size_t)b * a.block_stride) / 4 + (size_t)split * 256 * a.N;
+#pragma unroll
+            for (int i = 0; i < XF; ++i)
+#pragma unroll
+                for (int j = 0; j < WF; ++j) {
+                    const int n = 32 * nt1 + 16 * j + 4 * oct;
+                    if (n < a.N) *(f32x4_t *)(y + (size_t)(m0 + 16 * i) * a.N + n) = acc[i][j];
+                }
+        } else {
+            // SiLU(gate) * up: the first 16 columns of a tile are gate columns 16 * nt + p, the others the matching up columns
+            uint16_t *mp = a.mp0 + ((size_t)b * a.block_stride) / 2;
+#pragma unroll
+            for (int i = 0; i < XF; ++i)
+#pragma unroll
+                for (int j = 0; j < TW; ++j) {
+                    if (nt1 + j >= a.n_tiles) continue;
+                    float v[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float gt = acc[i][2 * j][q], up = acc[i][2 * j + 1][q];
+                        v[q] = (gt / (1.0f + expf(-gt))) * up;
+                    }
+                    *(uint2 *)(mp + hx_xp_index(m0 + 16 * i, 16 * (nt1 + j) + 4 * oct, 8)) =
+                        make_uint2(hx_cvt_pk_bf16(v[0], v[1]), hx_cvt_pk_bf16(v[2], v[3]));
+                }
+        }
+        return;
+    }
     f32x16_t acc[TM][TW];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -129,13 +252,6 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
     const u32x4_t *base = lds + lane;
     auto read_x = [&](uint32_t stage, int kc, int i) { x[kc & 1][i] = base[stage * STAGE_U4 + (kc * 8 + TM * wm + i) * 64]; };
     auto read_w = [&](uint32_t stage, int kc, int j) { wt[kc & 1][j] = base[stage * STAGE_U4 + (KC * 8 + kc * WNT + wn * TW + j) * 64]; };
-#pragma unroll
-    for (int s = 0; s < NST - 1; ++s) {
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) copy_one(i);
-        advance();
-    }
-    hand_over();                                        // chunk 0 is in its stage
 #pragma unroll
     for (int j = 0; j < TW; ++j) read_w(0, 0, j);
 #pragma unroll

@@ -110,3 +110,26 @@ def test_gate_up_of_one_and_two_rounds(hx, tiles, blocks, hidden):
     ref = gate * torch.sigmoid(gate) * (x.double() @ w["wu"])
     # one bf16 rounding of the result and the fp32 sums' own error
     assert y.shape == ref.shape and ((y.double() - ref).abs() <= ref.abs() * 2.0 ** -7 + 1e-5).all()
+
+
+@pytest.mark.parametrize("tiles", [6, 7, 8])
+@pytest.mark.parametrize("k_steps,batch", [(1, 129), (2, 130), (3, 255), (5, 256), (8, 129), (13, 256)])
+def test_wide_tiles(hx, k_steps, batch, tiles, monkeypatch):
+    """Six and more column tiles per workgroup (16x16x32 products): 1 to 7 chunks, the last of them half empty (what lies behind it
+    is not a number here), column blocks that end inside a workgroup, and gate|up."""
+    s = synth.ModelShape("wb-wide", 1, 288, 2, 1, 64, 16 * k_steps, 64)
+    eng = build(hx, s, 5, 256, 64)
+    w = {k: v.double().cuda() for k, v in synth.layer_weights(s, 0, 5).items()}
+    monkeypatch.setenv("HX_GEMM_SHAPE", "%d,1,1" % tiles)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    eng.workspace.fill_(0xFF)
+    x = torch.randn(batch, s.intermediate, generator=g, device="cuda").bfloat16().float()
+    y = eng.stage_linear(hx.HX_T_WD, 0, x)
+    u = torch.randn(batch, s.hidden, generator=g, device="cuda").bfloat16().float()
+    m = eng.stage_linear(hx.HX_T_WG, 0, u)
+    torch.cuda.synchronize()
+    # fp32 sums of exact products; one bf16 rounding of gate|up's result and the fp32 sums' own error
+    assert ((y.double() - x.double() @ w["wd"]).abs() <= 1e-5 * (x.double().abs() @ w["wd"].abs())).all()
+    gate = u.double() @ w["wg"]
+    ref = gate * torch.sigmoid(gate) * (u.double() @ w["wu"])
+    assert m.shape == ref.shape and ((m.double() - ref).abs() <= ref.abs() * 2.0 ** -7 + 1e-5).all()
