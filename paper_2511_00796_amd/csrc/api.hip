@@ -465,6 +465,7 @@ static int run_step(hx_engine *e, hx_kv *kv, int32_t batch, const int32_t *token
     char *ws = e->ws;
     float *ypart = (float *)(ws + e->map.ypart);
     const size_t attn_stride = (size_t)batch * e->q_dim;
+    hx_partials part;
 
     // prompt rows: consecutive rows of a sequence share one K/V stream (their schedule replaces the decode step's)
     const bool prompt = !with_head && e->chunk_attention;
@@ -476,9 +477,8 @@ static int run_step(hx_engine *e, hx_kv *kv, int32_t batch, const int32_t *token
     }
     for (int l = 0; l < c->n_layers; ++l) {
         const hx_layer_map *lm = &e->layers[l];
-        HX_TIMED(HX_K_GEMM_QKV, hx_launch_gemm(e, &lm->wqkv, batch, ws + e->map.xp, HX_EPI_PARTIAL, ypart, nullptr, st));
-        HX_TIMED(HX_K_ROPE, hx_launch_rope_append(e, kv, l, batch, ypart, hx_gemm_splits(e, &lm->wqkv, batch), hx_gemm_split_stride(e, &lm->wqkv, batch),
-                                                 positions, st));
+        HX_TIMED(HX_K_GEMM_QKV, hx_launch_gemm(e, &lm->wqkv, batch, ws + e->map.xp, HX_EPI_PARTIAL, ypart, nullptr, st, nullptr, &part));
+        HX_TIMED(HX_K_ROPE, hx_launch_rope_append(e, kv, l, batch, ypart, part.splits, part.stride, positions, st));
         if (!with_head && l + 1 == c->n_layers) break;   // prompt rows: of the last layer only its K and V are needed
         float *capture = e->attn_capture ? e->attn_capture + l * attn_stride : nullptr;
         if (prompt) {
@@ -489,12 +489,12 @@ static int run_step(hx_engine *e, hx_kv *kv, int32_t batch, const int32_t *token
             else HX_TIMED(HX_K_ATTENTION, hx_launch_attention(e, kv, l, batch, seq_lens, block_table, max_blocks, st));
             HX_TIMED(HX_K_COMBINE, hx_launch_combine(e, batch, capture, st));
         }
-        HX_TIMED(HX_K_GEMM_O, hx_launch_gemm(e, &lm->wo, batch, ws + e->map.ap, HX_EPI_PARTIAL, ypart, nullptr, st));
-        HX_TIMED(HX_K_NORM, hx_launch_reduce_norm(e, batch, ypart, hx_gemm_splits(e, &lm->wo, batch), hx_gemm_split_stride(e, &lm->wo, batch), lm->g2, st));
+        HX_TIMED(HX_K_GEMM_O, hx_launch_gemm(e, &lm->wo, batch, ws + e->map.ap, HX_EPI_PARTIAL, ypart, nullptr, st, nullptr, &part));
+        HX_TIMED(HX_K_NORM, hx_launch_reduce_norm(e, batch, ypart, part.splits, part.stride, lm->g2, st));
         HX_TIMED(HX_K_GEMM_GATE_UP, hx_launch_gemm(e, &lm->wgu, batch, ws + e->map.xp, HX_EPI_SWIGLU, nullptr, ws + e->map.mp, st));
-        HX_TIMED(HX_K_GEMM_DOWN, hx_launch_gemm(e, &lm->wd, batch, ws + e->map.mp, HX_EPI_PARTIAL, ypart, nullptr, st));
+        HX_TIMED(HX_K_GEMM_DOWN, hx_launch_gemm(e, &lm->wd, batch, ws + e->map.mp, HX_EPI_PARTIAL, ypart, nullptr, st, nullptr, &part));
         const size_t next_gain = (l + 1 < c->n_layers) ? e->layers[l + 1].g1 : e->gf;
-        HX_TIMED(HX_K_NORM, hx_launch_reduce_norm(e, batch, ypart, hx_gemm_splits(e, &lm->wd, batch), hx_gemm_split_stride(e, &lm->wd, batch), next_gain, st));
+        HX_TIMED(HX_K_NORM, hx_launch_reduce_norm(e, batch, ypart, part.splits, part.stride, next_gain, st));
     }
     if (!with_head) return HX_OK;
     if (sample && sample->top_p < 1.0f) {
@@ -545,6 +545,20 @@ extern "C" int hx_prefill_workspace_bytes(const hx_model_config *cfg, int32_t ma
     return HX_OK;
 }
 
+// One product over the R blocks.  A single block takes what a batch of 256 rows takes (matrices of few columns: gemm_slice.hip).
+// v0: the engine with the first block's workspace.
+static int launch_rows_product(const hx_engine *v0, const hx_matrix *w, int R, size_t stride, size_t in_off, int epilogue, hipStream_t st,
+                               hx_partials *part) {
+    const hx_ws_map &m = v0->map;
+    const bool partial = epilogue == HX_EPI_PARTIAL;
+    if (R == 1)
+        return hx_launch_gemm(v0, w, 256, v0->ws + in_off, epilogue, partial ? (float *)(v0->ws + m.ypart) : nullptr, partial ? nullptr : v0->ws + m.mp,
+                              st, nullptr, part);
+    const hx_wide_plan plan = hx_plan_wide(w, R, epilogue);
+    *part = hx_partials{plan.splits, (size_t)256 * w->N};
+    return hx_launch_gemm_wide(v0, w, R, v0->ws, stride, in_off, epilogue, partial ? m.ypart : 0, partial ? 0 : m.mp, plan, st);
+}
+
 extern "C" int prefill_rows(hx_engine *e, hx_kv *kv, int32_t n_rows, const int32_t *tokens, const int32_t *positions,
                             const int32_t *seq_lens, const int32_t *block_table, int32_t max_blocks, void *workspace_dev,
                             size_t workspace_bytes, void *stream) {
@@ -580,6 +594,11 @@ extern "C" int prefill_rows(hx_engine *e, hx_kv *kv, int32_t n_rows, const int32
     // workspaces), as do the products.
     const hx_engine *v0 = &view[0];
     const float *ypart0 = (const float *)(ws0 + m.ypart);
+    hx_partials part;
+    auto product = [&](int klass, const hx_matrix *w, size_t in_off, int epilogue) {
+        timed_launch t(e, klass, st);
+        return launch_rows_product(v0, w, R, stride, in_off, epilogue, st, &part);
+    };
     if (grouped) {
         HX_TIMED(HX_K_SETUP, hx_launch_prompt_setup(v0, n_rows, positions, seq_lens, block_table, max_blocks, st, stride));
     } else {
@@ -589,12 +608,9 @@ extern "C" int prefill_rows(hx_engine *e, hx_kv *kv, int32_t n_rows, const int32
     HX_TIMED(HX_K_NORM, hx_launch_embed_norm(v0, 256, tokens, e->layers[0].g1, st, R, stride));
     for (int l = 0; l < c->n_layers; ++l) {
         const hx_layer_map *lm = &e->layers[l];
-        const hx_wide_plan p_qkv = hx_plan_wide(&lm->wqkv, R, HX_EPI_PARTIAL), p_o = hx_plan_wide(&lm->wo, R, HX_EPI_PARTIAL),
-                           p_gu = hx_plan_wide(&lm->wgu, R, HX_EPI_SWIGLU), p_d = hx_plan_wide(&lm->wd, R, HX_EPI_PARTIAL);
-        const int s_qkv = p_qkv.splits, s_o = p_o.splits, s_d = p_d.splits;
-        HX_TIMED(HX_K_GEMM_QKV, hx_launch_gemm_wide(e, &lm->wqkv, R, ws0, stride, m.xp, HX_EPI_PARTIAL, m.ypart, 0, p_qkv, st));
+        if ((rc = product(HX_K_GEMM_QKV, &lm->wqkv, m.xp, HX_EPI_PARTIAL))) return rc;
         // K and V of every row of the call enter the cache before any row attends
-        HX_TIMED(HX_K_ROPE, hx_launch_rope_append(v0, kv, l, 256, ypart0, s_qkv, (size_t)256 * e->qkv_dim, positions, st, R, stride));
+        HX_TIMED(HX_K_ROPE, hx_launch_rope_append(v0, kv, l, 256, ypart0, part.splits, part.stride, positions, st, R, stride));
         if (l + 1 == c->n_layers) break;     // of the last layer only its K and V are needed
         float *capture = e->attn_capture ? e->attn_capture + l * attn_stride : nullptr;
         if (grouped) {
@@ -608,12 +624,12 @@ extern "C" int prefill_rows(hx_engine *e, hx_kv *kv, int32_t n_rows, const int32
                 HX_TIMED(HX_K_COMBINE, hx_launch_combine(vb, 256, capture ? capture + (size_t)b * 256 * e->q_dim : nullptr, st));
             }
         }
-        HX_TIMED(HX_K_GEMM_O, hx_launch_gemm_wide(e, &lm->wo, R, ws0, stride, m.ap, HX_EPI_PARTIAL, m.ypart, 0, p_o, st));
-        HX_TIMED(HX_K_NORM, hx_launch_reduce_norm(v0, 256, ypart0, s_o, (size_t)256 * c->hidden, lm->g2, st, R, stride));
-        HX_TIMED(HX_K_GEMM_GATE_UP, hx_launch_gemm_wide(e, &lm->wgu, R, ws0, stride, m.xp, HX_EPI_SWIGLU, 0, m.mp, p_gu, st));
-        HX_TIMED(HX_K_GEMM_DOWN, hx_launch_gemm_wide(e, &lm->wd, R, ws0, stride, m.mp, HX_EPI_PARTIAL, m.ypart, 0, p_d, st));
+        if ((rc = product(HX_K_GEMM_O, &lm->wo, m.ap, HX_EPI_PARTIAL))) return rc;
+        HX_TIMED(HX_K_NORM, hx_launch_reduce_norm(v0, 256, ypart0, part.splits, part.stride, lm->g2, st, R, stride));
+        if ((rc = product(HX_K_GEMM_GATE_UP, &lm->wgu, m.xp, HX_EPI_SWIGLU))) return rc;
+        if ((rc = product(HX_K_GEMM_DOWN, &lm->wd, m.mp, HX_EPI_PARTIAL))) return rc;
         const size_t next_gain = (l + 1 < c->n_layers) ? e->layers[l + 1].g1 : e->gf;
-        HX_TIMED(HX_K_NORM, hx_launch_reduce_norm(v0, 256, ypart0, s_d, (size_t)256 * c->hidden, next_gain, st, R, stride));
+        HX_TIMED(HX_K_NORM, hx_launch_reduce_norm(v0, 256, ypart0, part.splits, part.stride, next_gain, st, R, stride));
     }
     return HX_OK;
 }
@@ -892,19 +908,20 @@ extern "C" int hx_stage_linear_rows(hx_engine *e, int kind, int layer, int32_t n
         default: return hx_fail(HX_E_SHAPE, "tensor kind %d has no wide product", kind);
     }
     const bool swiglu = kind == HX_T_WG;
-    const hx_wide_plan plan = hx_plan_wide(w, R, swiglu ? HX_EPI_SWIGLU : HX_EPI_PARTIAL);
+    hx_partials part;
     hx_engine view = *e;
     int rc;
     for (int b = 0; b < R; ++b) {
         view.ws = ws0 + (size_t)b * stride;
         if ((rc = hx_launch_pack_x(&view, 256, x_dev + (size_t)b * 256 * K, K, view.ws + in_off, st))) return rc;
     }
-    if ((rc = hx_launch_gemm_wide(e, w, R, ws0, stride, in_off, swiglu ? HX_EPI_SWIGLU : HX_EPI_PARTIAL, m.ypart, m.mp, plan, st))) return rc;
+    view.ws = ws0;
+    if ((rc = launch_rows_product(&view, w, R, stride, in_off, swiglu ? HX_EPI_SWIGLU : HX_EPI_PARTIAL, st, &part))) return rc;
     for (int b = 0; b < R; ++b) {
         view.ws = ws0 + (size_t)b * stride;
         float *y = y_dev + (size_t)b * 256 * N;
         if (swiglu) rc = hx_launch_unpack_x(&view, 256, view.ws + m.mp, N, y, st);
-        else rc = hx_launch_sum_partials(&view, 256, (const float *)(view.ws + m.ypart), plan.splits, (size_t)256 * N, N, y, st);
+        else rc = hx_launch_sum_partials(&view, 256, (const float *)(view.ws + m.ypart), part.splits, part.stride, N, y, st);
         if (rc) return rc;
     }
     return HX_OK;
@@ -922,23 +939,24 @@ extern "C" int hx_stage_linear(hx_engine *e, int kind, int layer, int32_t batch,
     char *ws = e->ws;
     float *ypart = (float *)(ws + e->map.ypart);
     const hx_layer_map *lm = (kind == HX_T_WLM) ? nullptr : &e->layers[layer];
+    hx_partials part;
     switch (kind) {
         case HX_T_WQKV:
             if ((rc = hx_launch_pack_x(e, batch, x_dev, c->hidden, ws + e->map.xp, st))) return rc;
-            if ((rc = hx_launch_gemm(e, &lm->wqkv, batch, ws + e->map.xp, HX_EPI_PARTIAL, ypart, nullptr, st))) return rc;
-            return hx_launch_sum_partials(e, batch, ypart, hx_gemm_splits(e, &lm->wqkv, batch), hx_gemm_split_stride(e, &lm->wqkv, batch), e->qkv_dim, y_dev, st);
+            if ((rc = hx_launch_gemm(e, &lm->wqkv, batch, ws + e->map.xp, HX_EPI_PARTIAL, ypart, nullptr, st, nullptr, &part))) return rc;
+            return hx_launch_sum_partials(e, batch, ypart, part.splits, part.stride, e->qkv_dim, y_dev, st);
         case HX_T_WO:
             if ((rc = hx_launch_pack_x(e, batch, x_dev, e->q_dim, ws + e->map.ap, st))) return rc;
-            if ((rc = hx_launch_gemm(e, &lm->wo, batch, ws + e->map.ap, HX_EPI_PARTIAL, ypart, nullptr, st))) return rc;
-            return hx_launch_sum_partials(e, batch, ypart, hx_gemm_splits(e, &lm->wo, batch), hx_gemm_split_stride(e, &lm->wo, batch), c->hidden, y_dev, st);
+            if ((rc = hx_launch_gemm(e, &lm->wo, batch, ws + e->map.ap, HX_EPI_PARTIAL, ypart, nullptr, st, nullptr, &part))) return rc;
+            return hx_launch_sum_partials(e, batch, ypart, part.splits, part.stride, c->hidden, y_dev, st);
         case HX_T_WG:
             if ((rc = hx_launch_pack_x(e, batch, x_dev, c->hidden, ws + e->map.xp, st))) return rc;
             if ((rc = hx_launch_gemm(e, &lm->wgu, batch, ws + e->map.xp, HX_EPI_SWIGLU, nullptr, ws + e->map.mp, st))) return rc;
             return hx_launch_unpack_x(e, batch, ws + e->map.mp, c->intermediate, y_dev, st);
         case HX_T_WD:
             if ((rc = hx_launch_pack_x(e, batch, x_dev, c->intermediate, ws + e->map.mp, st))) return rc;
-            if ((rc = hx_launch_gemm(e, &lm->wd, batch, ws + e->map.mp, HX_EPI_PARTIAL, ypart, nullptr, st))) return rc;
-            return hx_launch_sum_partials(e, batch, ypart, hx_gemm_splits(e, &lm->wd, batch), hx_gemm_split_stride(e, &lm->wd, batch), c->hidden, y_dev, st);
+            if ((rc = hx_launch_gemm(e, &lm->wd, batch, ws + e->map.mp, HX_EPI_PARTIAL, ypart, nullptr, st, nullptr, &part))) return rc;
+            return hx_launch_sum_partials(e, batch, ypart, part.splits, part.stride, c->hidden, y_dev, st);
         case HX_T_WLM:
             if ((rc = hx_launch_pack_x(e, batch, x_dev, c->hidden, ws + e->map.xp, st))) return rc;
             if ((rc = hx_launch_gemm(e, &e->wlm, batch, ws + e->map.xp, HX_EPI_LOGITS, y_dev, nullptr, st))) return rc;

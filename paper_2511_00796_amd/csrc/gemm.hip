@@ -526,6 +526,7 @@ static bool forced_shape(int *wn, int *wk, int *splits) {
     return ov && sscanf(ov, "%d,%d,%d", wn, wk, splits) == 3 && *splits >= 1;
 }
 
+// Up to 128 rows.
 static gemm_launch plan_product(int n_tiles, int k_steps, bool partial) {
     const int cus = hx_device_cus();
     gemm_launch best{4, 1, 1, 0};
@@ -534,7 +535,7 @@ static gemm_launch plan_product(int n_tiles, int k_steps, bool partial) {
     int a, b, c;
     if (forced_shape(&a, &b, &c) && c <= max_s && ((b == 1 && a >= 4 && a <= 6) || (a == 4 && b == 2)) && k_steps / (b * c) >= 1)
         return gemm_launch{a, b, c, 0};
-    const hx_slice_plan slice = hx_plan_slice(n_tiles, k_steps, partial, max_s);
+    const hx_slice_plan slice = hx_plan_slice(n_tiles, k_steps, 128, partial, max_s);
     if (slice.tiles) return gemm_launch{4, 1, slice.splits, slice.tiles};
     static const int widths[] = {4, 5, 6, 10};
     for (int wn : widths) {
@@ -555,17 +556,20 @@ static gemm_launch plan_product(int n_tiles, int k_steps, bool partial) {
     return best;
 }
 
-// Beyond 128 rows the workgroup-tiled product of gemm_wide.hip takes over: one block of 256 rows, those past the batch
-// computed and never read.  Its partials are 256 rows apart, so fewer splits fit the buffer of an engine for fewer rows.
+// Beyond 128 rows: the workgroup-tiled product of gemm_wide.hip, one block of 256 rows, those past the batch computed and never
+// read; its partials are 256 rows apart, so fewer splits fit the buffer of an engine for fewer rows.  Matrices of few columns
+// (slice.tiles > 0): gemm_slice.hip, unless a shape is forced.
 static bool wide_rows(int batch) { return batch > 128; }
-static hx_wide_plan plan_wide_batch(const hx_matrix *m, int epilogue, int max_batch) {
-    const int max_s = epilogue == HX_EPI_PARTIAL ? splits_allowed(HX_MAX_SPLITS * max_batch / 256) : 1;
-    hx_wide_plan plan = hx_plan_wide(m, 1, epilogue, max_s);
+struct batch_plan { hx_wide_plan wide; hx_slice_plan slice; };
+static batch_plan plan_wide_batch(const hx_matrix *m, int epilogue, int max_batch) {
+    const bool partial = epilogue == HX_EPI_PARTIAL;
+    const int max_s = partial ? splits_allowed(HX_MAX_SPLITS * max_batch / 256) : 1;
+    batch_plan plan{hx_plan_wide(m, 1, epilogue, max_s), hx_slice_plan{0, 1}};
     int wn, wk, sp;                                      // forced: 4 to 8 tiles, no k-slices, no split without k-steps
-    if (forced_shape(&wn, &wk, &sp) && wk == 1 && wn >= 4 && wn <= 8 && sp <= max_s && (sp - 1) * hx_wide_split_steps(m, sp) < m->k_steps) {
-        plan.wnt = wn;
-        plan.splits = sp;
-    }
+    if (forced_shape(&wn, &wk, &sp) && wk == 1 && wn >= 4 && wn <= 8 && sp <= max_s && (sp - 1) * hx_wide_split_steps(m, sp) < m->k_steps)
+        plan.wide = hx_wide_plan{wn, sp};
+    else
+        plan.slice = hx_plan_slice(m->n_tiles, m->k_steps, 256, partial, partial ? splits_allowed(HX_MAX_SPLITS) : 1);
     return plan;
 }
 
@@ -577,8 +581,8 @@ extern "C" int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, 
     if (n_tiles < 1 || k_steps < 1 || batch < 1 || batch > 256) return hx_fail(HX_E_RANGE, "product %d x %d for batch %d", n_tiles, k_steps, batch);
     if (wide_rows(batch)) {
         const hx_matrix m{0, 16 * k_steps, 32 * n_tiles, k_steps, n_tiles};
-        const hx_wide_plan plan = plan_wide_batch(&m, partial ? HX_EPI_PARTIAL : HX_EPI_SWIGLU, 256);
-        *wn_out = plan.wnt; *wk_out = 1; *splits_out = plan.splits;
+        const batch_plan plan = plan_wide_batch(&m, partial ? HX_EPI_PARTIAL : HX_EPI_SWIGLU, 256);
+        *wn_out = plan.slice.tiles ? 4 : plan.wide.wnt; *wk_out = 1; *splits_out = plan.slice.tiles ? plan.slice.splits : plan.wide.splits;
         return HX_OK;
     }
     const gemm_launch plan = plan_product(n_tiles, k_steps, partial != 0);
@@ -586,17 +590,8 @@ extern "C" int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, 
     return HX_OK;
 }
 
-int hx_gemm_splits(const hx_engine *e, const hx_matrix *m, int batch) {
-    if (wide_rows(batch)) return plan_wide_batch(m, HX_EPI_PARTIAL, e->cfg.max_batch).splits;
-    return plan_product(m->n_tiles, m->k_steps, true).splits;
-}
-size_t hx_gemm_split_stride(const hx_engine *e, const hx_matrix *m, int batch) {
-    (void)e;
-    return (size_t)(wide_rows(batch) ? 256 : batch) * m->N;
-}
-
 int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void *xp, int epilogue, float *y,
-                   void *mp_out, hipStream_t st, const hx_sample_params *sample) {
+                   void *mp_out, hipStream_t st, const hx_sample_params *sample, hx_partials *parts) {
     if (epilogue == HX_EPI_SAMPLE && !sample) return hx_fail(HX_E_NULL, "sampling parameters missing");
     const int mg = hx_m_groups(batch);
     const bool partial = epilogue == HX_EPI_PARTIAL;
@@ -605,13 +600,17 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
                         sample ? sample->inv_temperature : 1.0f, sample ? sample->key0 : 0u, sample ? sample->key1 : 0u,
                         (float *)(e->ws + e->map.samp_z), (float *)(e->ws + e->map.samp_m), (float *)(e->ws + e->map.samp_s)};
     if (wide_rows(batch)) {
+        const batch_plan plan = plan_wide_batch(m, epilogue, e->cfg.max_batch);
+        if (parts) *parts = plan.slice.tiles ? hx_partials{plan.slice.splits, (size_t)batch * m->N} : hx_partials{plan.wide.splits, (size_t)256 * m->N};
+        if (plan.slice.tiles) return hx_launch_gemm_slice(e, m, batch, plan.slice, xp, epilogue, y, mp_out, lm, st);
         // The streaming kernel has one wavefront per SIMD with all rows' accumulators, and nothing beside its multiplications
         // or its epilogue; the workgroup-tiled product has two.  LM head, 1.5B, 256 rows, sampled: 327 -> 204 us; the other
         // products: see hx_plan_wide.
         return hx_launch_gemm_wide(e, m, 1, e->ws, 0, (const char *)xp - e->ws, epilogue, partial ? (char *)y - e->ws : 0,
-                                   mp_out ? (char *)mp_out - e->ws : 0, plan_wide_batch(m, epilogue, e->cfg.max_batch), st, &lm);
+                                   mp_out ? (char *)mp_out - e->ws : 0, plan.wide, st, &lm);
     }
     const gemm_launch pl = plan_product(m->n_tiles, m->k_steps, partial);
+    if (parts) *parts = hx_partials{pl.splits, (size_t)batch * m->N};
     if (pl.slice_tiles)
         return hx_launch_gemm_slice(e, m, batch, hx_slice_plan{pl.slice_tiles, pl.splits}, xp, epilogue, y, mp_out, lm, st);
     GemmArgs a;

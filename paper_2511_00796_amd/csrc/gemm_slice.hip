@@ -1,4 +1,4 @@
-// Small products of at most 128 rows: those whose matrix has too few column tiles to give the streaming kernel of gemm.hip (four
+// Small products: those whose matrix has too few column tiles to give the streaming kernel of gemm.hip (four
 // and more tiles per workgroup, at most 9 K-splits) a workgroup for every compute unit.
 //
 // Workgroup = four wavefronts on one 32-column tile (two of a long K): k-step i of the split goes to wavefront i % 4, so the
@@ -10,6 +10,10 @@
 // many: 14B gate|up at 64 rows 73 us (two tiles per workgroup 56), 48 there.  us, streaming -> this, 1 / 64 / 128 rows:
 // 1.5B QKV 3.9 / 7.5 / 10.5 -> 2.7 / 4.3 / 7.0, O 4.5 / 7.1 / 9.5 -> 3.4 / 4.1 / 6.0, down 10.0 / 14.3 / 16.8 -> 8.6 / 11.2 / 13.0
 // (two tiles; one: 7.6 / 10.4 / 13.6), with weights that are partly in the memory-side cache.
+// Beyond 128 rows a workgroup takes 64 of them (two tiles: 128), and the row blocks read the weights again, from the L2.  The
+// workgroup-tiled kernel of gemm_wide.hip would give these matrices 40 to 112 of 256 compute units a workgroup.  us, there -> this, 160 / 256
+// rows, weights from memory: 1.5B QKV 14.1 / 14.6 -> 7.4 / 7.7, O 14.1 / 15.0 -> 7.2 / 7.3, down 22.2 / 22.1 -> 15.6 / 16.6 (five splits; nine 21.2 / 22.2,
+// one tile per workgroup 23.9 / 23.8); the tiny model's 9 to 13 -> 3 to 4.
 #include "hx_internal.h"
 #include "lm_epilogue.h"
 #include <algorithm>
@@ -20,8 +24,8 @@ namespace {
 
 constexpr int SLICES = 4;         // wavefronts of a workgroup
 
-// TN tiles per workgroup, MG m-groups, R k-steps in flight per wavefront
-template <int MG, int TN, int R, int EPI>
+// TN tiles per workgroup, MG of XG m-groups (blockIdx.z), R k-steps in flight per wavefront
+template <int MG, int XG, int TN, int R, int EPI>
 __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(const uint4 *__restrict__ a_wp, const uint4 *__restrict__ a_xp,
                                                                int a_k_steps, int a_n_tiles, int a_steps_per_split, int a_M, int a_N,
                                                                int a_split_stride, float *__restrict__ a_y, uint16_t *__restrict__ a_mp,
@@ -31,13 +35,14 @@ __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(const uint4 *__
     __shared__ u32x4_t red[S * Q * 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int t0 = blockIdx.x * TN;
+    const int g0 = XG > MG ? MG * blockIdx.z : 0;
     const int split0 = blockIdx.y * a_steps_per_split, split1 = min(a_k_steps, split0 + a_steps_per_split);
     // step i of this wavefront is k-step split0 + wave + S * i
     const int n = (split1 - split0 - wave + S - 1) / S;
     const u32x4_t *wrow[TN];
 #pragma unroll
     for (int t = 0; t < TN; ++t) wrow[t] = (const u32x4_t *)a_wp + ((size_t)min(t0 + t, a_n_tiles - 1) * a_k_steps + split0 + wave) * 64 + lane;
-    const u32x4_t *xrow = (const u32x4_t *)a_xp + (size_t)(split0 + wave) * MG * 64 + lane;
+    const u32x4_t *xrow = (const u32x4_t *)a_xp + ((size_t)(split0 + wave) * XG + g0) * 64 + lane;
     f32x16_t acc[TN][MG];
 #pragma unroll
     for (int t = 0; t < TN; ++t)
@@ -52,7 +57,7 @@ __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(const uint4 *__
 #pragma unroll
             for (int t = 0; t < TN; ++t) w[r][t] = __builtin_nontemporal_load(wrow[t] + (size_t)j * 64);
 #pragma unroll
-            for (int g = 0; g < MG; ++g) x[r][g] = xrow[((size_t)j * MG + g) * 64];
+            for (int g = 0; g < MG; ++g) x[r][g] = xrow[((size_t)j * XG + g) * 64];
             __builtin_amdgcn_sched_barrier(0);
         };
         auto multiply = [&](int r) {
@@ -104,7 +109,7 @@ __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(const uint4 *__
         const int nq = lane & 7;
         for (int u = wave; u < Q; u += S) {              // 8 rows of one tile
             const int t = u / (MG * 4), g = u / 4 % MG, ml = (u & 3) * 8 + (lane >> 3);
-            const int m = 32 * g + ml, nn = 32 * (t0 + t) + 4 * nq;
+            const int m = 32 * (g0 + g) + ml, nn = 32 * (t0 + t) + 4 * nq;
             if (m < a_M && nn < a_N) {
                 const f32x4_t v = sum((t * MG + g) * 4 + (nq >> 1), (nq & 1) * 32 + (ml ^ nq));
                 *(f32x4_t *)(y + (size_t)m * a_N + nn) = v;
@@ -112,7 +117,7 @@ __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(const uint4 *__
         }
     } else if (EPI == HX_EPI_SWIGLU) {
         for (int u = wave; u < TN * MG; u += S) {
-            const int t = u / MG, g = u % MG, h = lane >> 5, ml = lane & 31, m = 32 * g + ml;
+            const int t = u / MG, g = u % MG, h = lane >> 5, ml = lane & 31, m = 32 * (g0 + g) + ml;
             if (m < a_M && t0 + t < a_n_tiles) {
                 uint32_t pk[4];
 #pragma unroll
@@ -124,13 +129,13 @@ __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(const uint4 *__
                     pk[2 * q] = hx_cvt_pk_bf16(v[0], v[1]);
                     pk[2 * q + 1] = hx_cvt_pk_bf16(v[2], v[3]);
                 }
-                *(uint4 *)(a_mp + hx_xp_index(m, 16 * (t0 + t) + 8 * h, MG)) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+                *(uint4 *)(a_mp + hx_xp_index(m, 16 * (t0 + t) + 8 * h, XG)) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
             }
         }
     } else {
         for (int u = (wave + blockIdx.x) % S; u < TN * MG; u += S) {
             const int t = u / MG, g = u % MG;
-            if (32 * g >= a_M || t0 + t >= a_n_tiles) continue;
+            if (32 * (g0 + g) >= a_M || t0 + t >= a_n_tiles) continue;
             f32x16_t v;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -138,8 +143,8 @@ __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(const uint4 *__
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[4 * j + i] = q[i];
             }
-            if (EPI == HX_EPI_LOGITS) hx_lm_greedy_tile(a_lm, v, 32 * g + (lane & 31), t0 + t, lane);
-            else                      hx_lm_sample_tile(a_lm, v, 32 * g + (lane & 31), t0 + t, lane);
+            if (EPI == HX_EPI_LOGITS) hx_lm_greedy_tile(a_lm, v, 32 * (g0 + g) + (lane & 31), t0 + t, lane);
+            else                      hx_lm_sample_tile(a_lm, v, 32 * (g0 + g) + (lane & 31), t0 + t, lane);
         }
     }
 }
@@ -152,11 +157,11 @@ struct SliceArgs {
     hx_lm_args lm;                // LM head
 };
 
-template <int MG, int TN, int R>
+template <int MG, int XG, int TN, int R>
 int launch_slice(int epilogue, const SliceArgs &a, int splits, hipStream_t st) {
-    const dim3 grid((a.n_tiles + TN - 1) / TN, splits), block(64 * SLICES);
+    const dim3 grid((a.n_tiles + TN - 1) / TN, splits, XG > MG ? (a.M + 32 * MG - 1) / (32 * MG) : 1), block(64 * SLICES);
 #define HX_SLICE(EPI)                                                                                                      \
-    hipLaunchKernelGGL((gemm_slice_kernel<MG, TN, R, EPI>), grid, block, 0, st, a.wp, a.xp, a.k_steps, a.n_tiles, a.steps_per_split, \
+    hipLaunchKernelGGL((gemm_slice_kernel<MG, XG, TN, R, EPI>), grid, block, 0, st, a.wp, a.xp, a.k_steps, a.n_tiles, a.steps_per_split, \
                        a.M, a.N, a.split_stride, a.y, a.mp, a.lm)
     if (epilogue == HX_EPI_PARTIAL) {
         HX_SLICE(HX_EPI_PARTIAL);
@@ -174,18 +179,19 @@ int launch_slice(int epilogue, const SliceArgs &a, int splits, hipStream_t st) {
 
 }  // namespace
 
-// Whether a product of at most 128 rows runs here: the streaming kernel's most workgroups, a quarter of the tiles times the
+// Whether a product runs here: the streaming kernel's most workgroups, a quarter of the tiles times the
 // most splits, would leave two fifths of the compute units without one (up to 68 tiles on 256: 17 workgroups of four in 9 splits are
 // 153).  us at 1 / 64 / 128 rows, 68 tiles, there with its best splits -> here: 128 k-steps 4.4 / 7.4 / 11.9 -> 4.0 / 5.4 / 7.3, 544 k-steps
 // 10.2 / 15.7 / 18.7 -> 8.4 / 13.3 / 16.6, LM head 11.5 / 20.1 / 23.1 -> 5.2 / 8.7 / 11.0; 112 tiles, 7B O, at 3 / 37 rows 7.7 / 11.4 there,
 // 7.9 / 13.7 here.  K-splits: at least 24 k-steps each (1.5B QKV at 64 rows in 6 / 4 / 2 splits: 5.6 / 4.4 /
-// 5.2 us) and no more workgroups than compute units; two tiles per workgroup where that still leaves long ones.
-hx_slice_plan hx_plan_slice(int n_tiles, int k_steps, bool partial, int max_splits) {
+// 5.2 us) and no more workgroups than compute units; two tiles per workgroup where that still leaves long ones.  Up to 128 rows are one
+// block; more are four of 64 or two of 128, whatever their number, so that a row's sums are added in one order in all such batches.
+hx_slice_plan hx_plan_slice(int n_tiles, int k_steps, int rows, bool partial, int max_splits) {
     const int cus = hx_device_cus();
     hx_slice_plan p{0, 1};
     if ((n_tiles + 3) / 4 * HX_MAX_SPLITS * 5 > cus * 3) return p;
     p.tiles = partial && k_steps > 24 * HX_MAX_SPLITS ? 2 : 1;
-    const int groups = (n_tiles + p.tiles - 1) / p.tiles;
+    const int groups = (n_tiles + p.tiles - 1) / p.tiles * (rows <= 128 ? 1 : 4 / p.tiles);
     if (partial) p.splits = std::max(1, std::min({max_splits, k_steps / 24, cus / groups}));
     return p;
 }
@@ -204,12 +210,14 @@ int hx_launch_gemm_slice(const hx_engine *e, const hx_matrix *m, int batch, hx_s
     // k-steps in flight: with eight of the fewest rows the first products wait for loads past the split's end (1.5B, 16 rows, QKV
     // 4.7 -> 4.1 us, O 4.5 -> 3.7 with four); at more rows 2 to 6 are alike, but for two tiles of 128 rows (2: 13.3, 3: 12.4)
     switch (hx_m_groups(batch) * 10 + plan.tiles) {
-        case 11: return launch_slice<1, 1, 4>(epilogue, a, plan.splits, st);
-        case 21: return launch_slice<2, 1, 6>(epilogue, a, plan.splits, st);
-        case 41: return launch_slice<4, 1, 4>(epilogue, a, plan.splits, st);
-        case 12: return launch_slice<1, 2, 4>(epilogue, a, plan.splits, st);
-        case 22: return launch_slice<2, 2, 6>(epilogue, a, plan.splits, st);
-        case 42: return launch_slice<4, 2, 3>(epilogue, a, plan.splits, st);
+        case 11: return launch_slice<1, 1, 1, 4>(epilogue, a, plan.splits, st);
+        case 21: return launch_slice<2, 2, 1, 6>(epilogue, a, plan.splits, st);
+        case 41: return launch_slice<4, 4, 1, 4>(epilogue, a, plan.splits, st);
+        case 81: return launch_slice<2, 8, 1, 6>(epilogue, a, plan.splits, st);
+        case 12: return launch_slice<1, 1, 2, 4>(epilogue, a, plan.splits, st);
+        case 22: return launch_slice<2, 2, 2, 6>(epilogue, a, plan.splits, st);
+        case 42: return launch_slice<4, 4, 2, 3>(epilogue, a, plan.splits, st);
+        case 82: return launch_slice<4, 8, 2, 3>(epilogue, a, plan.splits, st);
         default: return hx_fail(HX_E_RANGE, "%d rows, %d tiles per workgroup: no such small product", batch, plan.tiles);
     }
 }

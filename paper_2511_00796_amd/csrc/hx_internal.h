@@ -368,13 +368,15 @@ int hx_launch_attention_fp8(const hx_engine *e, const hx_kv *kv, int layer, cons
 size_t hx_nucleus_bytes(int vocab, int max_batch);
 int hx_launch_nucleus(const hx_engine *e, int batch, const float *logits, const hx_sample_params *sample,
                       int32_t *tokens_out, float *logprobs_out, hipStream_t st);
+// a product with split partials: its K-splits, and the elements between their outputs
+struct hx_partials { int splits; size_t stride; };
 int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void *xp, int epilogue,
                    float *y /*partials or logits or NULL*/, void *mp_out, hipStream_t st,
-                   const hx_sample_params *sample = nullptr);
-// gemm_slice.hip: small products of at most 128 rows
+                   const hx_sample_params *sample = nullptr, hx_partials *parts = nullptr);
+// gemm_slice.hip: products of matrices with few columns
 struct hx_lm_args;
 struct hx_slice_plan { int tiles, splits; };     // 32-column tiles per workgroup (0: not this kernel), K-splits
-hx_slice_plan hx_plan_slice(int n_tiles, int k_steps, bool partial, int max_splits);
+hx_slice_plan hx_plan_slice(int n_tiles, int k_steps, int rows, bool partial, int max_splits);
 int hx_launch_gemm_slice(const hx_engine *e, const hx_matrix *m, int batch, hx_slice_plan plan, const void *xp, int epilogue, float *y,
                          void *mp_out, const hx_lm_args &lm, hipStream_t st);
 // gemm_wide.hip: products over several 256-row blocks at once (prompt rows)
@@ -385,9 +387,6 @@ int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, 
                         int epilogue, size_t y_off, size_t mp_off, hx_wide_plan plan, hipStream_t st, const hx_lm_args *lm = nullptr);
 
 int hx_launch_sample_final(const hx_engine *e, int batch, int32_t *tokens_out, float *logprobs_out, hipStream_t st);
-// a product with split partials: the K-splits hx_launch_gemm uses, and the elements between their outputs
-int hx_gemm_splits(const hx_engine *e, const hx_matrix *m, int batch);
-size_t hx_gemm_split_stride(const hx_engine *e, const hx_matrix *m, int batch);
 int hx_launch_argmax_final(const hx_engine *e, int batch, int32_t *tokens_out, hipStream_t st);
 
 // elementwise.hip

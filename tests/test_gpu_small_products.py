@@ -53,3 +53,30 @@ def test_products_of_few_columns(hx, name, batch):
             # fp32 sums of exact products: a few units of 2^-24 of the sum of magnitudes
             ref = xd @ mat
             assert y.shape == ref.shape and ((y.double() - ref).abs() <= 1e-5 * (xd.abs() @ mat.abs())).all(), (name, kind)
+
+
+@pytest.mark.parametrize("batch,max_batch", [(129, 129), (192, 256), (193, 193), (256, 256)])
+@pytest.mark.parametrize("name", ["k1", "k5", "k23", "k48", "k217", "t68"])
+def test_products_of_few_columns_beyond_128_rows(hx, name, batch, max_batch):
+    """Blocks of 64 rows (two tiles per workgroup: 128), the last of which may hold one row; what lies behind the rows is not a number."""
+    s = SHAPES[name]
+    eng = build(hx, s, 5, max_batch, 64)
+    w = {k: v.double().cuda() for k, v in synth.layer_weights(s, 0, 5).items()}
+    head = synth.global_weights(s, 5)["wlm"].double().cuda()
+    g = torch.Generator(device="cuda").manual_seed(7)
+    eng.workspace.fill_(0xFF)
+    for kind, mat in ((hx.HX_T_WQKV, w["wqkv"]), (hx.HX_T_WO, w["wo"]), (hx.HX_T_WD, w["wd"]), (hx.HX_T_WG, None), (hx.HX_T_WLM, head)):
+        x = torch.randn(batch, s.hidden if mat is None else mat.shape[0], generator=g, device="cuda").bfloat16().float()
+        y, am = eng.stage_linear(kind, 0, x, want_argmax=True) if kind == hx.HX_T_WLM else (eng.stage_linear(kind, 0, x), None)
+        torch.cuda.synchronize()
+        assert am is None or (am.long() == y.argmax(-1)).all()
+        xd = x.double()
+        if mat is None:
+            gate = xd @ w["wg"]
+            ref = gate * torch.sigmoid(gate) * (xd @ w["wu"])
+            # one bf16 rounding of the result and the fp32 sums' own error
+            assert y.shape == ref.shape and ((y.double() - ref).abs() <= ref.abs() * 2.0 ** -7 + 1e-5).all(), (name, kind)
+        else:
+            # fp32 sums of exact products
+            ref = xd @ mat
+            assert y.shape == ref.shape and ((y.double() - ref).abs() <= 1e-5 * (xd.abs() @ mat.abs())).all(), (name, kind)
