@@ -506,11 +506,12 @@ static int launch_shape(int wn, int wk, int epilogue, dim3 grid, hipStream_t st,
 // PLAN_STEPS k-steps; split products, which run in one round and read only a K-slice of the activations, keep a small charge
 // per extra tile instead (five consumers on four SIMDs); ties go to the smaller wn and fewer splits.  Fewer rows take
 // the same plan, though their rings are of 8 and their workgroups take a quarter of the LDS or less: the splits decide
-// in which order a row's products are added, and so a row comes out alike in every batch of up to 128.
+// in which order a row's products are added, and so a row comes out alike in every batch of up to 128 (of up to 64, and of 65 to 128,
+// where gate|up has a workgroup of gemm_slice.hip for every three tiles up to 64 rows).
 // Examples: the 1184 tiles of the 7B gate|up matrix make 296 workgroups of 4 (two rounds on 256 compute
 // units) but 237 workgroups of 5 (one round); the 4752 tiles of the LM head make five rounds of 4, four of 5 or
 // two of 10, measured 253 / 244 / 230 us.  Ten tiles per workgroup are twelve wavefronts (three per SIMD): only
-// for products without split partials.  Matrices of few columns go to gemm_slice.hip.  HX_GEMM_SHAPE="wn,wk,splits" overrides
+// for products without split partials.  Matrices of few columns go to gemm_slice.hip (hx_plan_slice).  HX_GEMM_SHAPE="wn,wk,splits" overrides
 // (tuning).  Batches of more than 128 rows: hx_plan_wide, under the same two knobs.
 constexpr int PLAN_STEPS = 16;
 
@@ -527,15 +528,16 @@ static bool forced_shape(int *wn, int *wk, int *splits) {
 }
 
 // Up to 128 rows.
-static gemm_launch plan_product(int n_tiles, int k_steps, bool partial) {
+static gemm_launch plan_product(int n_tiles, int k_steps, int rows, int epilogue) {
     const int cus = hx_device_cus();
+    const bool partial = epilogue == HX_EPI_PARTIAL;
     gemm_launch best{4, 1, 1, 0};
     double best_cost = 1e300;
     const int max_s = partial ? splits_allowed(HX_MAX_SPLITS) : 1;
     int a, b, c;
     if (forced_shape(&a, &b, &c) && c <= max_s && ((b == 1 && a >= 4 && a <= 6) || (a == 4 && b == 2)) && k_steps / (b * c) >= 1)
         return gemm_launch{a, b, c, 0};
-    const hx_slice_plan slice = hx_plan_slice(n_tiles, k_steps, 128, partial, max_s);
+    const hx_slice_plan slice = hx_plan_slice(n_tiles, k_steps, rows, epilogue, max_s);
     if (slice.tiles) return gemm_launch{4, 1, slice.splits, slice.tiles};
     static const int widths[] = {4, 5, 6, 10};
     for (int wn : widths) {
@@ -569,7 +571,7 @@ static batch_plan plan_wide_batch(const hx_matrix *m, int epilogue, int max_batc
     if (forced_shape(&wn, &wk, &sp) && wk == 1 && wn >= 4 && wn <= 8 && sp <= max_s && (sp - 1) * hx_wide_split_steps(m, sp) < m->k_steps)
         plan.wide = hx_wide_plan{wn, sp};
     else
-        plan.slice = hx_plan_slice(m->n_tiles, m->k_steps, 256, partial, partial ? splits_allowed(HX_MAX_SPLITS) : 1);
+        plan.slice = hx_plan_slice(m->n_tiles, m->k_steps, 256, epilogue, partial ? splits_allowed(HX_MAX_SPLITS) : 1);
     return plan;
 }
 
@@ -585,7 +587,7 @@ extern "C" int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, 
         *wn_out = plan.slice.tiles ? 4 : plan.wide.wnt; *wk_out = 1; *splits_out = plan.slice.tiles ? plan.slice.splits : plan.wide.splits;
         return HX_OK;
     }
-    const gemm_launch plan = plan_product(n_tiles, k_steps, partial != 0);
+    const gemm_launch plan = plan_product(n_tiles, k_steps, batch, partial ? HX_EPI_PARTIAL : HX_EPI_SWIGLU);
     *wn_out = plan.wn; *wk_out = plan.wk; *splits_out = plan.splits;
     return HX_OK;
 }
@@ -609,7 +611,7 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
         return hx_launch_gemm_wide(e, m, 1, e->ws, 0, (const char *)xp - e->ws, epilogue, partial ? (char *)y - e->ws : 0,
                                    mp_out ? (char *)mp_out - e->ws : 0, plan.wide, st, &lm);
     }
-    const gemm_launch pl = plan_product(m->n_tiles, m->k_steps, partial);
+    const gemm_launch pl = plan_product(m->n_tiles, m->k_steps, batch, epilogue);
     if (parts) *parts = hx_partials{pl.splits, (size_t)batch * m->N};
     if (pl.slice_tiles)
         return hx_launch_gemm_slice(e, m, batch, hx_slice_plan{pl.slice_tiles, pl.splits}, xp, epilogue, y, mp_out, lm, st);

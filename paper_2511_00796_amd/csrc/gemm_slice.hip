@@ -1,7 +1,7 @@
 // Small products: those whose matrix has too few column tiles to give the streaming kernel of gemm.hip (four
-// and more tiles per workgroup, at most 9 K-splits) a workgroup for every compute unit.
+// and more tiles per workgroup, at most 9 K-splits, none of gate|up) a workgroup for every compute unit.
 //
-// Workgroup = four wavefronts on one 32-column tile (two of a long K): k-step i of the split goes to wavefront i % 4, so the
+// Workgroup = four wavefronts on one to three 32-column tiles: k-step i of the split goes to wavefront i % 4, so the
 // workgroup reads its tile's weights as one contiguous run.  A wavefront loads its weights and activations straight into
 // registers, R steps ahead; no LDS stages, no barrier until the end, where the four sums are added in order through LDS, laid out
 // so that the outputs leave in whole 128-byte lines.
@@ -165,11 +165,12 @@ int launch_slice(int epilogue, const SliceArgs &a, int splits, hipStream_t st) {
                        a.M, a.N, a.split_stride, a.y, a.mp, a.lm)
     if (epilogue == HX_EPI_PARTIAL) {
         HX_SLICE(HX_EPI_PARTIAL);
+    } else if (epilogue == HX_EPI_SWIGLU) {
+        HX_SLICE(HX_EPI_SWIGLU);
     } else if constexpr (TN == 1) {
-        if (epilogue == HX_EPI_SWIGLU) HX_SLICE(HX_EPI_SWIGLU);
-        else if (epilogue == HX_EPI_SAMPLE) HX_SLICE(HX_EPI_SAMPLE);
+        if (epilogue == HX_EPI_SAMPLE) HX_SLICE(HX_EPI_SAMPLE);
         else HX_SLICE(HX_EPI_LOGITS);
-    } else {                                             // a long K is split: only partial results
+    } else {                                             // small heads are planned with one
         return hx_fail(HX_E_RANGE, "epilogue %d with %d tiles per workgroup: no such small product", epilogue, TN);
     }
 #undef HX_SLICE
@@ -186,9 +187,19 @@ int launch_slice(int epilogue, const SliceArgs &a, int splits, hipStream_t st) {
 // 7.9 / 13.7 here.  K-splits: at least 24 k-steps each (1.5B QKV at 64 rows in 6 / 4 / 2 splits: 5.6 / 4.4 /
 // 5.2 us) and no more workgroups than compute units; two tiles per workgroup where that still leaves long ones.  Up to 128 rows are one
 // block; more are four of 64 or two of 128, whatever their number, so that a row's sums are added in one order in all such batches.
-hx_slice_plan hx_plan_slice(int n_tiles, int k_steps, int rows, bool partial, int max_splits) {
+// Gate|up, which is not split, runs here in one round of one or two tiles per workgroup, up to 64 rows also of three, where its activations
+// are few.  us, streaming -> this, 1 / 33 / 128 rows: 256 tiles of 128 k-steps 16.8 / 18.6 / 23.6 -> 8.8 / 10.5 / 14.4, 512 of 128 18.7 / 20.6 / 25.2 ->
+// 13.5 / 14.6 / 19.6, 384 of 192 24.0 / 26.6 / 33.7 -> 17.0 / 18.2 / 25.2, 560 of 96 (1.5B) 15.2 / 17.0 / 21.8 -> 13.2 / 14.8 / 26, 768 of 192 26.9 / 30.2 /
+// 38.0 -> 25.3 / 26.4 / 46; 816 tiles, in two rounds of two, 21.7 / 25.4 / 29.8 -> 21.6 / 24.9 / 34.2.
+hx_slice_plan hx_plan_slice(int n_tiles, int k_steps, int rows, int epilogue, int max_splits) {
     const int cus = hx_device_cus();
+    const bool partial = epilogue == HX_EPI_PARTIAL;
     hx_slice_plan p{0, 1};
+    if (epilogue == HX_EPI_SWIGLU && rows <= 128) {
+        const int t = (n_tiles + cus - 1) / cus;
+        if (t <= (rows <= 64 ? 3 : 2)) p.tiles = t;
+        return p;
+    }
     if ((n_tiles + 3) / 4 * HX_MAX_SPLITS * 5 > cus * 3) return p;
     p.tiles = partial && k_steps > 24 * HX_MAX_SPLITS ? 2 : 1;
     const int groups = (n_tiles + p.tiles - 1) / p.tiles * (rows <= 128 ? 1 : 4 / p.tiles);
@@ -214,7 +225,9 @@ int hx_launch_gemm_slice(const hx_engine *e, const hx_matrix *m, int batch, hx_s
         case 21: return launch_slice<2, 2, 1, 6>(epilogue, a, plan.splits, st);
         case 41: return launch_slice<4, 4, 1, 4>(epilogue, a, plan.splits, st);
         case 81: return launch_slice<2, 8, 1, 6>(epilogue, a, plan.splits, st);
-        case 12: return launch_slice<1, 1, 2, 4>(epilogue, a, plan.splits, st);
+        case 13: return launch_slice<1, 1, 3, 4>(epilogue, a, plan.splits, st);
+        case 23: return launch_slice<2, 2, 3, 4>(epilogue, a, plan.splits, st);
+        case 12: return launch_slice<1, 1, 2, 6>(epilogue, a, plan.splits, st);
         case 22: return launch_slice<2, 2, 2, 6>(epilogue, a, plan.splits, st);
         case 42: return launch_slice<4, 4, 2, 3>(epilogue, a, plan.splits, st);
         case 82: return launch_slice<4, 8, 2, 3>(epilogue, a, plan.splits, st);

@@ -376,7 +376,7 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
 // gemm_slice.hip: products of matrices with few columns
 struct hx_lm_args;
 struct hx_slice_plan { int tiles, splits; };     // 32-column tiles per workgroup (0: not this kernel), K-splits
-hx_slice_plan hx_plan_slice(int n_tiles, int k_steps, int rows, bool partial, int max_splits);
+hx_slice_plan hx_plan_slice(int n_tiles, int k_steps, int rows, int epilogue, int max_splits);
 int hx_launch_gemm_slice(const hx_engine *e, const hx_matrix *m, int batch, hx_slice_plan plan, const void *xp, int epilogue, float *y,
                          void *mp_out, const hx_lm_args &lm, hipStream_t st);
 // gemm_wide.hip: products over several 256-row blocks at once (prompt rows)

@@ -80,3 +80,21 @@ def test_products_of_few_columns_beyond_128_rows(hx, name, batch, max_batch):
             # fp32 sums of exact products
             ref = xd @ mat
             assert y.shape == ref.shape and ((y.double() - ref).abs() <= 1e-5 * (xd.abs() @ mat.abs())).all(), (name, kind)
+
+
+@pytest.mark.parametrize("batch", [1, 32, 33, 64, 65, 128])
+@pytest.mark.parametrize("tiles,hidden", [(69, 32), (256, 96), (257, 192), (512, 160), (513, 96), (770, 64)])
+def test_gate_up_of_one_to_three_tiles_per_workgroup(hx, tiles, hidden, batch):
+    """Both sides of the steps between one, two and three tiles per workgroup (256, 512 on 256 compute units) and to the streaming
+    kernel (768 up to 64 rows, 512 beyond), last workgroups with tiles that do not exist, fewer k-steps than wavefronts."""
+    s = synth.ModelShape("sp-gu", 1, hidden, 1, 1, 64, 16 * tiles, 64)
+    eng = build(hx, s, 5, batch, 64)
+    w = {k: v.double().cuda() for k, v in synth.layer_weights(s, 0, 5).items()}
+    eng.workspace.fill_(0xFF)
+    x = torch.randn(batch, hidden, generator=torch.Generator(device="cuda").manual_seed(7), device="cuda").bfloat16().float()
+    y = eng.stage_linear(hx.HX_T_WG, 0, x)
+    torch.cuda.synchronize()
+    gate = x.double() @ w["wg"]
+    ref = gate * torch.sigmoid(gate) * (x.double() @ w["wu"])
+    # one bf16 rounding of the result and the fp32 sums' own error
+    assert y.shape == ref.shape and ((y.double() - ref).abs() <= ref.abs() * 2.0 ** -7 + 1e-5).all()
