@@ -283,30 +283,27 @@ __global__ __launch_bounds__(64) void attn_splitk_kernel(const int32_t *__restri
 // done by its first wavefront as with WPP = 1, bit for bit.
 #define HX_COMBINE_FEW 32
 template <int D, int WPP>
-__global__ __launch_bounds__(WPP == 1 ? 256 : 64 * WPP) void attn_combine_kernel(int batch, int n_q, int n_kv, int G,
+__global__ __launch_bounds__(WPP == 1 ? 256 : 64 * WPP) void attn_combine_kernel(const int32_t *__restrict__ sched,
                                                            const int32_t *__restrict__ pre,
-                                                           const int32_t *__restrict__ lens,
-                                                           const int32_t *__restrict__ sched,
+                                                           const int32_t *__restrict__ lens, int n_q, int n_kv, int G,
                                                            const float *__restrict__ part_ml,
                                                            const float *__restrict__ part_o,
                                                            uint16_t *__restrict__ ap, int m_groups,
                                                            float *__restrict__ attn_f32) {
     __shared__ float part[WPP == 1 ? 1 : WPP][WPP == 1 ? 1 : D];
-    const int wave = threadIdx.x >> 6, pw = WPP == 1 ? 0 : wave;         // wavefront of the workgroup / of the pair
-    const int bh = WPP == 1 ? blockIdx.x * 4 + wave : blockIdx.x;
-    if (bh >= batch * n_q) return;                       // whole wavefronts; for WPP > 1 the grid is exact
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), pw = WPP == 1 ? 0 : wave;   // of the workgroup / of the pair
+    const int b = blockIdx.y, h = WPP == 1 ? blockIdx.x * 4 + wave : blockIdx.x;
+    if (h >= n_q) return;                                // whole wavefronts; for WPP > 1 the grid is exact
     const int lane = threadIdx.x & 63, d8 = lane & 15, ph = lane >> 4;
     const bool has_d = d8 < D / 8;
-    const int b = bh / n_q, h = bh % n_q;
-    const int kvh = h / G, g = h % G;
-    const int S = sched[0];
-    const int nblk_b = (lens[b] + 15) >> 4;
-    const int start = pre[b] * n_kv + kvh * nblk_b;      // tiles of this pair: [start, start + nblk_b)
+    const int T = lens[b], P = pre[b];
+    const unsigned S = sched[0];
+    __builtin_amdgcn_sched_barrier(0);                   // three loads in one round trip, beside the division by G
+    const int kvh = (unsigned)h / (unsigned)G, g = h - kvh * G;
+    const int nblk_b = (T + 15) >> 4;
+    const int start = P * n_kv + kvh * nblk_b;           // tiles of this pair: [start, start + nblk_b)
     const int pair = b * n_kv + kvh;
-    const int s0 = start / S + pair, s1 = (start + nblk_b - 1) / S + pair;   // its slots, inclusive
-    // More than 8 partials per pair (a short batch of long sequences has a hundred): maximum and denominator take one
-    // partial per lane, 64 at a time; the weighted sum of the o vectors four partials per 16-lane group and iteration,
-    // all requested before the first is used.
+    const int s0 = (unsigned)start / S + pair, s1 = (unsigned)(start + nblk_b - 1) / S + pair;   // its slots, inclusive
     const int n = s1 - s0 + 1;
     const int waves = WPP > 1 && n > HX_COMBINE_FEW ? WPP : 1;      // that share the pair: the same for the whole workgroup
     if (pw >= waves) return;
@@ -314,52 +311,65 @@ __global__ __launch_bounds__(WPP == 1 ? 256 : 64 * WPP) void attn_combine_kernel
     float acc[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+    // U partials of this 16-lane group, four slots apart; past the end the last again, with weight 0
+    constexpr int U = 4;
+    float m[U], l[U];
+    f32x4_t a[U], c[U];
+    auto request = [&](int it, int u) {
+        const int iu = min(it + 4 * u, s1);
+        const float *ml = part_ml + (size_t)iu * 32 + g;
+        m[u] = ml[0]; l[u] = ml[16];
+        if (has_d) {
+            const float *po = part_o + ((size_t)iu * G + g) * D + d8 * 8;
+            a[u] = *(const f32x4_t *)po; c[u] = *(const f32x4_t *)(po + 4);
+        }
+    };
+    auto add = [&](float w, int u) {
+        if (has_d) {
+            acc[0] += w * a[u][0]; acc[1] += w * a[u][1]; acc[2] += w * a[u][2]; acc[3] += w * a[u][3];
+            acc[4] += w * c[u][0]; acc[5] += w * c[u][1]; acc[6] += w * c[u][2]; acc[7] += w * c[u][3];
+        }
+    };
     if (n <= 8) {       // the usual case (a few partials per pair): each 16-lane group takes every fourth
-        for (int it = s0 + ph; it <= s1; it += 4) M = fmaxf(M, part_ml[(size_t)it * 32 + g]);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) request(s0 + ph, u);
+        M = fmaxf(m[0], m[1]);
         M = fmaxf(M, __shfl_xor(M, 16));
         M = fmaxf(M, __shfl_xor(M, 32));
-        for (int it = s0 + ph; it <= s1; it += 4) {
-            const float w = __builtin_amdgcn_exp2f(part_ml[(size_t)it * 32 + g] - M);
-            den += w * part_ml[(size_t)it * 32 + 16 + g];
-            if (has_d) {
-                const float *po = part_o + ((size_t)it * G + g) * D + d8 * 8;
-                const f32x4_t a = *(const f32x4_t *)po, c = *(const f32x4_t *)(po + 4);
-                acc[0] += w * a[0]; acc[1] += w * a[1]; acc[2] += w * a[2]; acc[3] += w * a[3];
-                acc[4] += w * c[0]; acc[5] += w * c[1]; acc[6] += w * c[2]; acc[7] += w * c[3];
-            }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const float w = s0 + ph + 4 * u <= s1 ? __builtin_amdgcn_exp2f(m[u] - M) : 0.f;
+            den += w * l[u];
+            add(w, u);
         }
         den += __shfl_xor(den, 16);
         den += __shfl_xor(den, 32);
     } else {
-        for (int i = lane; i < n; i += 64) M = fmaxf(M, part_ml[(size_t)(s0 + i) * 32 + g]);
+        // More than 8 partials (a short batch of long sequences has a hundred): maximum and denominator take one
+        // partial per lane, 64 at a time; the weighted sum four per 16-lane group and round, the first round's requested with them.
+        const int first = s0 + 16 * pw + ph;
+        const float *ml = part_ml + (size_t)(s0 + min(lane, n - 1)) * 32 + g;
+        const float m0 = ml[0], l0 = lane < n ? ml[16] : 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u) request(first, u);
+        M = m0;
+        for (int i = lane + 64; i < n; i += 64) M = fmaxf(M, part_ml[(size_t)(s0 + i) * 32 + g]);
 #pragma unroll
         for (int sh = 1; sh < 64; sh <<= 1) M = fmaxf(M, __shfl_xor(M, sh));
-        for (int i = lane; i < n; i += 64) {
-            const float *ml = part_ml + (size_t)(s0 + i) * 32;
-            den += __builtin_amdgcn_exp2f(ml[g] - M) * ml[16 + g];
+        den = __builtin_amdgcn_exp2f(m0 - M) * l0;
+        for (int i = lane + 64; i < n; i += 64) {
+            const float *mi = part_ml + (size_t)(s0 + i) * 32 + g;
+            den += __builtin_amdgcn_exp2f(mi[0] - M) * mi[16];
         }
 #pragma unroll
         for (int sh = 1; sh < 64; sh <<= 1) den += __shfl_xor(den, sh);
-        for (int it = s0 + 16 * pw + ph; it <= s1; it += 16 * waves) {
-            float w[4];
-            f32x4_t a[4], c[4];
+        for (int it = first; it <= s1; it += 16 * waves) {
+            if (it != first) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int iu = min(it + 4 * u, s1);                   // past the end: re-read the last, weight 0
-                w[u] = part_ml[(size_t)iu * 32 + g];
-                if (has_d) {
-                    const float *po = part_o + ((size_t)iu * G + g) * D + d8 * 8;
-                    a[u] = *(const f32x4_t *)po; c[u] = *(const f32x4_t *)(po + 4);
-                }
+                for (int u = 0; u < U; ++u) request(it, u);
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float wu = it + 4 * u <= s1 ? __builtin_amdgcn_exp2f(w[u] - M) : 0.f;
-                if (has_d) {
-                    acc[0] += wu * a[u][0]; acc[1] += wu * a[u][1]; acc[2] += wu * a[u][2]; acc[3] += wu * a[u][3];
-                    acc[4] += wu * c[u][0]; acc[5] += wu * c[u][1]; acc[6] += wu * c[u][2]; acc[7] += wu * c[u][3];
-                }
-            }
+            for (int u = 0; u < U; ++u) add(it + 4 * u <= s1 ? __builtin_amdgcn_exp2f(m[u] - M) : 0.f, u);
         }
     }
 #pragma unroll
@@ -423,9 +433,9 @@ int hx_launch_combine(const hx_engine *e, int batch, float *attn_f32_out, hipStr
     // for shorter sequences the seven that leave at once cost nothing (1 to 8 rows, 20 to 400 tokens: 17.3-18.3 us with the
     // attention kernel either way).
     const bool many = e->attn_waves > HX_COMBINE_FEW * batch * n_kv;
-    dim3 cgrid(many ? batch * n_q : (batch * n_q + 3) / 4), cblock(many ? 512 : 256);
+    dim3 cgrid(many ? n_q : (n_q + 3) / 4, batch), cblock(many ? 512 : 256);
 #define HX_COMB_ARGS                                                                                             \
-    batch, n_q, n_kv, e->G, (const int32_t *)a.pre, (const int32_t *)a.lens, (const int32_t *)a.sched,            \
+    (const int32_t *)a.sched, (const int32_t *)a.pre, (const int32_t *)a.lens, n_q, n_kv, e->G,                  \
         (const float *)a.part_ml, (const float *)a.part_o, a.ap, m_groups, attn_f32_out
 #define HX_COMB_LAUNCH(DD)                                                                                         \
     do {                                                                                                         \
