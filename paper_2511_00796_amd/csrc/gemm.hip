@@ -186,7 +186,14 @@ __device__ __forceinline__ u32x4_t hx_stream_load(const uint4 *p) {   // read-on
 // LM head 188 -> 185, at 128 rows 227 -> 220; kept, at 16 (8): 7B at 128 rows gate|up 54.0 (57.2), down 37.1 (39.4); gate|up of four tiles
 // at 33 / 48 / 64 rows 1.5B 16.6 / 16.1 / 16.3 (17.1 / 16.4 / 17.1), hidden 2048 22.6 / 21.6 / 22.7 (22.7 / 22.2 / 22.8), 14B 48.8 / 47.2 / 47.0
 // (49.0 / 48.1 / 47.8).
+// Ten tiles per workgroup (the LM head, in two rounds) of up to 64 rows: with at most 80 registers a compute unit holds two workgroups,
+// and all run in one round.  So six wavefronts per SIMD are asked for, and a ring of 4.  Head, us, before -> now: 7B at 3 rows, drawn
+// (136 registers before) 166 -> 162, 16 rows 179 -> 172, 37 rows (133) 195 -> 184, greedy (87) 187 -> 175; 64 rows greedy 1.5B 92 -> 88, 7B 190 -> 184,
+// 14B 263 -> 255, drawn 270 -> 265.  Rings of 8 | 4 up to 32 rows 162.5 | 161.7 and 175.5 | 172.2, of 6 | 4 at 64 rows 14B 269 | 265.
+template <int MG, int WN, int EPI> constexpr int gemm_resident() { return WN == 10 && MG <= 2 ? 6 : 1; }
+
 template <int MG, int WN, int EPI> constexpr int gemm_ring() {
+    if (WN == 10 && MG <= 2) return HX_GEMM_RING / 4;
     return WN == 10 || MG == 1 || (MG == 2 && !(WN == 4 && EPI == HX_EPI_SWIGLU)) ? HX_GEMM_RING / 2 : HX_GEMM_RING;
 }
 
@@ -207,7 +214,7 @@ template <int MG, int WN, int WK, int RING> constexpr int gemm_lds_bytes() {
 }
 
 template <int MG, int WN, int WK, int EPI>
-__global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK, gemm_ring<MG, WN, EPI>()>::NP)) void gemm_stream_kernel(
+__global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK, gemm_ring<MG, WN, EPI>()>::NP), (gemm_resident<MG, WN, EPI>())) void gemm_stream_kernel(
     const uint4 *__restrict__ a_wp, const uint4 *__restrict__ a_xp, int a_k_steps, int a_n_tiles,
     int a_steps_per_split, int a_steps_per_wave, int a_M, int a_N, float *__restrict__ a_y, size_t a_split_stride,
     uint16_t *__restrict__ a_mp, float *__restrict__ a_amax_val, int32_t *__restrict__ a_amax_idx,
@@ -439,13 +446,16 @@ __global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK, gemm_ring<MG, WN, 
         const hx_lm_args lm{a_y, a_M, a_N, a_n_tiles, a_amax_val, a_amax_idx, a_positions, a_row_ids, a_inv_t, a_key0, a_key1,
                             a_samp_z, a_samp_m, a_samp_s};
         // one copy of the tile's code, the accumulators moved up behind it (unrolled it spills and leaves the instruction
-        // cache); m-groups that only pad the batch are left out
+        // cache; the last is cleared, or it would stay live); m-groups that only pad the batch are left out
 #pragma unroll 1
-        for (int g = 0; 32 * g < a_M; ++g) {
-            if (EPI == HX_EPI_LOGITS) hx_lm_greedy_tile(lm, acc[0], 32 * g + ml, nt, lane);
-            else                      hx_lm_sample_tile(lm, acc[0], 32 * g + ml, nt, lane);
+        for (int g = 0; g < MG && 32 * g < a_M; ++g) {
+            const f32x16_t now = acc[0];
 #pragma unroll
             for (int k = 0; k + 1 < MG; ++k) acc[k] = acc[k + 1];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[MG - 1][r] = 0.f;
+            if (EPI == HX_EPI_LOGITS) hx_lm_greedy_tile(lm, now, 32 * g + ml, nt, lane);
+            else                      hx_lm_sample_tile<(MG <= 2)>(lm, now, 32 * g + ml, nt, lane);
         }
     }
 }

@@ -144,7 +144,7 @@ __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(const uint4 *__
                 for (int i = 0; i < 4; ++i) v[4 * j + i] = q[i];
             }
             if (EPI == HX_EPI_LOGITS) hx_lm_greedy_tile(a_lm, v, 32 * (g0 + g) + (lane & 31), t0 + t, lane);
-            else                      hx_lm_sample_tile(a_lm, v, 32 * (g0 + g) + (lane & 31), t0 + t, lane);
+            else                      hx_lm_sample_tile<true>(a_lm, v, 32 * (g0 + g) + (lane & 31), t0 + t, lane);
         }
     }
 }

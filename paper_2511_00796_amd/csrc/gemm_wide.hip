@@ -354,7 +354,7 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
                 const int nt = nt0 + wn * TW + j;
                 if (nt < a.n_tiles && m0 < a.lm.M) {
                     if (EPI == HX_EPI_LOGITS) hx_lm_greedy_tile(a.lm, acc[0][0], m0 + ml, nt, lane);
-                    else                      hx_lm_sample_tile(a.lm, acc[0][0], m0 + ml, nt, lane);
+                    else                      hx_lm_sample_tile<false>(a.lm, acc[0][0], m0 + ml, nt, lane);
                 }
 #pragma unroll
                 for (int k = 0; k + 1 < TM * TW; ++k) acc[k / TW][k % TW] = acc[(k + 1) / TW][(k + 1) % TW];

@@ -58,20 +58,24 @@ __device__ __forceinline__ void hx_lm_greedy_tile(const hx_lm_args &a, const f32
 // are within 2e-5 of the exact score, and only the winner's score is computed exactly; where a lane's second best comes
 // within a margin above twice that error, the whole tile is done exactly.  So the candidate is always the exact one.
 // 7B head: 128 rows 249 -> 240 us, 37 rows 207 -> 200.
-template <bool WHOLE>             // every column of the tile exists
-__device__ __forceinline__ void hx_lm_sample_columns(const hx_lm_args &a, const f32x16_t &acc, uint32_t row, uint32_t pos, int nt, int hl,
-                                                     float (&z)[16], float &best, int &best_n, float &best_z, float &zmax) {
+// LEAN, for kernels whose registers decide how many workgroups a compute unit holds (gemm_resident): the generator's blocks are kept
+// one behind the other, and none of their products moves out of the caller's loop over rows; z takes the logits' registers, the exact
+// pass is a loop, and a ragged tile has no copy of the code (136 registers -> 70).  With two or three wavefronts per SIMD the blocks
+// hide each other's latencies: 7B at 128 rows 231 us, LEAN 234; 1.5B at 256 rows 187, LEAN 194.
+template <bool LEAN>
+__device__ __forceinline__ void hx_lm_sample_columns(const hx_lm_args &a, f32x16_t &z, uint32_t row, uint32_t pos, int n0,
+                                                     float &best, int &best_n, float &best_z, float &zmax) {
     const auto uniform = [](uint32_t w) { return ((float)(w >> 9) + 0.5f) * (1.0f / 8388608.0f); };
     float top = -INFINITY, second = -INFINITY, top_u = 0.5f;
 #pragma unroll
     for (int j4 = 0; j4 < 4; ++j4) {
-        const int n = 32 * nt + 8 * j4 + 4 * hl;
+        const int n = n0 + 8 * j4;
         uint32_t w[4];
         hx_philox4x32_10((uint32_t)(n >> 2), row, pos, 0x53414D50u, a.key0, a.key1, w);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int r = 4 * j4 + i;
-            z[r] = (WHOLE || n + i < a.N) ? acc[r] * a.inv_t : -INFINITY;
+            z[r] *= a.inv_t;
             const float u = uniform(w[i]);
             const float g2 = __builtin_amdgcn_logf(-__builtin_amdgcn_logf(u));          // log2(-log2(u))
             const float ya = fmaf(-0.693147182f, g2, z[r]);                             // y, less the constant log(log 2)
@@ -79,41 +83,49 @@ __device__ __forceinline__ void hx_lm_sample_columns(const hx_lm_args &a, const 
             if (ya > top) { top = ya; top_u = u; best_z = z[r]; best_n = n + i; }
             zmax = fmaxf(zmax, z[r]);
         }
+        if (LEAN) __builtin_amdgcn_sched_barrier(0);
     }
     best = best_z - logf(-logf(top_u));
     if (__any(second >= top - (1e-4f + 1e-6f * fabsf(top)))) {         // also both -inf, or a lane with an infinite score
         best = -INFINITY; best_z = 0.f; best_n = 0x7fffffff;          // rare: the numbers are generated again, not kept
-#pragma unroll
+#pragma unroll 1
         for (int j4 = 0; j4 < 4; ++j4) {
-            const int n = 32 * nt + 8 * j4 + 4 * hl;
-            uint32_t w[4], c0 = (uint32_t)(n >> 2);
-            asm volatile("" : "+v"(c0));                                // opaque, or the compiler keeps all 16 after all
-            hx_philox4x32_10(c0, row, pos, 0x53414D50u, a.key0, a.key1, w);
+            const int n = n0 + 8 * j4;
+            uint32_t w[4];
+            hx_philox4x32_10((uint32_t)(n >> 2), row, pos, 0x53414D50u, a.key0, a.key1, w);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float y = z[4 * j4 + i] - logf(-logf(uniform(w[i])));
-                if (y > best) { best = y; best_z = z[4 * j4 + i]; best_n = n + i; }
+                const float zi = j4 == 0 ? z[i] : j4 == 1 ? z[4 + i] : j4 == 2 ? z[8 + i] : z[12 + i];
+                const float y = zi - logf(-logf(uniform(w[i])));
+                if (y > best) { best = y; best_z = zi; best_n = n + i; }
             }
         }
     }
 }
 
-__device__ __forceinline__ void hx_lm_sample_tile(const hx_lm_args &a, const f32x16_t &acc, int m, int nt, int lane) {
+template <bool LEAN>
+__device__ __forceinline__ void hx_lm_sample_tile(const hx_lm_args &a, f32x16_t z, int m, int nt, int lane) {
     const int hl = lane >> 5;
+    int n0 = 32 * nt + 4 * hl;
+    if (LEAN) asm volatile("" : "+v"(n0));               // opaque
     const bool row_ok = m < a.M;
     const uint32_t row = row_ok ? (a.row_ids ? (uint32_t)a.row_ids[m] : (uint32_t)m) : 0u;
     const uint32_t pos = row_ok ? (uint32_t)a.positions[m] : 0u;
-    float z[16], best = -INFINITY, best_z = 0.f, zmax = -INFINITY;
+    float best = -INFINITY, best_z = 0.f, zmax = -INFINITY;
     int best_n = 0x7fffffff;
-    if (32 * nt + 32 <= a.N) hx_lm_sample_columns<true>(a, acc, row, pos, nt, hl, z, best, best_n, best_z, zmax);
-    else                     hx_lm_sample_columns<false>(a, acc, row, pos, nt, hl, z, best, best_n, best_z, zmax);
     if (a.y != nullptr && row_ok) {
 #pragma unroll
         for (int j4 = 0; j4 < 4; ++j4) {
-            const int n = 32 * nt + 8 * j4 + 4 * hl;
-            if (n < a.N) *(f32x4_t *)(a.y + (size_t)m * a.N + n) = f32x4_t{acc[4 * j4], acc[4 * j4 + 1], acc[4 * j4 + 2], acc[4 * j4 + 3]};
+            const int n = n0 + 8 * j4;
+            if (n < a.N) *(f32x4_t *)(a.y + (size_t)m * a.N + n) = f32x4_t{z[4 * j4], z[4 * j4 + 1], z[4 * j4 + 2], z[4 * j4 + 3]};
         }
     }
+    if (32 * nt + 32 > a.N) {                            // columns that do not exist: neither drawn nor weighed
+#pragma unroll
+        for (int r = 0; r < 16; ++r) if (n0 + 8 * (r >> 2) + (r & 3) >= a.N) z[r] = -INFINITY;
+    }
+    if (LEAN) __builtin_amdgcn_sched_barrier(0);
+    hx_lm_sample_columns<LEAN>(a, z, row, pos, n0, best, best_n, best_z, zmax);
     // the two half-wavefronts hold the two halves of the tile's 32 columns
     const float tmax = fmaxf(zmax, __shfl_xor(zmax, 32));
     float sum = 0.f;
