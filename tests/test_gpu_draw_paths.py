@@ -62,3 +62,21 @@ def test_kept_sets_of_every_size(hx, vocab, batch, temperature, top_p):
     y, tok, lp, n = (t.cpu().numpy() for t in eng.stage_lm_head_top_p(x, pos, temperature, top_p, 31))
     print("kept %d..%d of %d" % (n.min(), n.max(), vocab))
     test_gpu_top_p.check_against_oracle(tok, lp, n, y, temperature, top_p, 31, np.arange(batch), pos.cpu().numpy(), "kept")
+
+
+@pytest.mark.parametrize("vocab,batch", [(70000, 5), (70000, 37), (70000, 100), (33324, 200)])
+def test_near_ties_are_decided_exactly(hx, vocab, batch):
+    """All logits of a row equal and large, so the noise alone decides and one wavefront in twenty meets a second best within the
+    margin of the fast scores: its tiles are scored again, exactly.  Ten tiles per workgroup (up to 32, 64, 128 rows) and the
+    workgroup-tiled head."""
+    s = synth.ModelShape("near", 1, 256, 4, 2, 64, 688, vocab)
+    eng = hx.Engine(s, batch if batch <= 128 else 256, 64)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    column = torch.empty(256, 1, dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02, generator=g)
+    eng.weights_pack(hx.HX_T_WLM, 0, column.expand(256, vocab).contiguous())
+    x = torch.randn(batch, 256, generator=g, device="cuda")
+    pos = torch.arange(100, 100 + batch, dtype=torch.int32, device="cuda")
+    for seed in (31, 32):
+        y, tok, lp, n = (t.cpu().numpy() for t in eng.stage_lm_head_top_p(x, pos, 1e-3, 0.5, seed))
+        assert (n == vocab).all()
+        test_gpu_top_p.check_against_oracle(tok, lp, n, y, 1e-3, 0.5, seed, np.arange(batch), pos.cpu().numpy(), "near")
