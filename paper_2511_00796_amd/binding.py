@@ -119,7 +119,9 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream's handle, without the Stream object that torch.cuda.current_stream() builds: 0.2 against 2.8 us, of the
+    85 that the smallest step takes on the host (21 launches)."""
+    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
 
 
 def make_config(shape, max_batch: int, max_seq_len: int, kv_dtype: int = HX_KV_BF16) -> ModelConfig:
