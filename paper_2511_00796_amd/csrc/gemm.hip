@@ -619,7 +619,7 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
         // or its epilogue; the workgroup-tiled product has two.  LM head, 1.5B, 256 rows, sampled: 327 -> 204 us; the other
         // products: see hx_plan_wide.
         return hx_launch_gemm_wide(e, m, 1, e->ws, 0, (const char *)xp - e->ws, epilogue, partial ? (char *)y - e->ws : 0,
-                                   mp_out ? (char *)mp_out - e->ws : 0, plan.wide, st, &lm);
+                                   mp_out ? (char *)mp_out - e->ws : 0, plan.wide, st, &lm, batch);
     }
     const gemm_launch pl = plan_product(m->n_tiles, m->k_steps, batch, epilogue);
     if (parts) *parts = hx_partials{pl.splits, (size_t)batch * m->N};

@@ -46,6 +46,13 @@ constexpr int WIDE_WAVES = 8;
 // five stages are requested anew at the start of every workgroup, which its few k-steps do not repay (us, three | six stages:
 // 1.5B, 1024 rows 60.1 | 62.7; hidden size 896, 2048 rows 38.9 | 43.2; 2048, 768 rows 75.4 | 77.1; one workgroup for a compute
 // unit: 1.5B, 256 rows 28 | 26).  The others of more than one round, whose k-steps are many, gain: 7B QKV, 4096 rows 141 | 135.
+// A single block of at most 192 rows (narrow tiles: what such blocks get): the m-groups without rows are neither copied nor
+// multiplied nor stored.  us at 129 / 192 rows, weights from memory: 14B gate|up 80.8 / 81.1 -> 68.5 / 73.4, down 45.0 / 46.6 -> 40.6 / 43.8, QKV 29.9 /
+// 29.8 -> 25.6 / 26.1, O 25.1 / 24.4 -> 21.8 / 22.0; 7B gate|up 73.9 / 73.4 -> 65.9 / 68.9, down 45.9 / 44.8 -> 38.5 / 40.5; at 193 to 224 rows, where one
+// group is left out, alike.  And its gate|up of 128 and more k-steps copies the weights non-temporally (a single block is all that reads
+// them): 14B 68.5 / 73.4 / 82.6 at 129 / 192 / 256 rows -> 62.2 / 68.0 / 79.5, 7B 65.9 / 68.9 / 75.3 -> 63.7 / 63.2 / 70.0, 192 k-steps 43.4 / 48.6 / 50.7 -> 39.8 /
+// 43.2 / 47.6, 128 30.7 / 35.6 / 41.0 -> 31.0 / 34.0 / 39.2, but 96 23.4 / 24.6 / 25.9 -> 24.6 / 25.6 / 27.1, and the split products 1 to 3 us slower.
+constexpr int WIDE_PART_GROUPS = 6, WIDE_ONCE_STEPS = 128;
 constexpr int wide_stages(int wnt, bool rounds) { return wnt <= 5 && !rounds ? 6 : 3; }
 constexpr int wide_lds_bytes(int wnt, int stages) { return stages * WIDE_KC * (8 + wnt) * 1024; }
 
@@ -58,12 +65,14 @@ struct WideArgs {
     float *y0;                    // fp32 output of block 0 ([splits][256][N]), same stride between blocks
     int steps_per_split, splits;
     uint16_t *mp0;                // SiLU(gate)*up output of block 0 (packed activations, 8 m-groups)
+    int groups;                   // m-groups that hold rows: 8, of a single block 5 to 8
     hx_lm_args lm;                // LM head (one block)
 };
 
 // WNT: 32-column tiles per workgroup, 4 to 8 (a 256 x 128 to 256 x 256 output tile).  Splits hold whole chunks; ODD:
 // but for the last, whose second k-step is missing.  (As a run-time condition in the loop this cost the narrow tiles 11 %.)
-template <int WNT, int EPI, bool ODD, int NST>
+// PART: one block whose last m-groups hold no rows; wavefronts that have no others only copy.  ONCE: weights non-temporally.
+template <int WNT, int EPI, bool ODD, int NST, bool PART = false, bool ONCE = false>
 __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) {
     constexpr int KC = WIDE_KC, WCOL = WNT == 8 ? 4 : (WNT % 2 ? 1 : 2), WROW = WIDE_WAVES / WCOL, TM = 8 / WROW,
                   TW = WNT / WCOL;
@@ -82,20 +91,22 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
     const int k0 = split * a.steps_per_split, k1 = min(k_steps, k0 + a.steps_per_split);
     const int n_chunks = (k1 - k0 + 1) / KC;            // an odd last k-step (a down product): its partner counts as zero
     const u32x4_t *xp = (const u32x4_t *)(a.xp0 + (size_t)b * a.block_stride);
-    // this wavefront's share of the copies of a chunk: wave-uniform pointers that advance by a fixed step per chunk and
-    // stop at the split's last one (requests past the end repeat it: never used)
-    const bool full = FULL == WIDE_WAVES || wave < FULL;
+    // This wavefront's share of the copies of a chunk: piece 8 i + wave, the 2 RG of X in the first two rounds and those of W behind;
+    // wave-uniform pointers that advance by a fixed step per chunk and stop at the split's last one (requests past the end repeat
+    // it: never used).  PART: X ends within the second round.
+    const int RG = PART ? a.groups : 8;
+    const bool full = FULL == WIDE_WAVES || wave < FULL, second = !PART || wave < KC * RG - WIDE_WAVES;
     const u32x4_t *ptr[LPW];
     int step[LPW];
     uint32_t dst[LPW];
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
-        const int p = min(i * WIDE_WAVES + wave, PIECES - 1);
-        if (p < KC * 8) {
-            const int kc = p >> 3, mg = p & 7;
+        const int p = i * WIDE_WAVES + wave;
+        if (i < 2) {
+            const int x = min(p, KC * RG - 1), kc = PART ? x >= RG : x >> 3, mg = x - kc * RG;
             ptr[i] = xp + ((size_t)(k0 + kc) * 8 + mg) * 64; step[i] = KC * 8 * 64; dst[i] = (kc * 8 + mg) * 1024;
         } else {
-            const int q = p - KC * 8, t = q / KC, kc = q % KC;
+            const int q = min(p, PIECES - 1) - KC * 8, t = q / KC, kc = q % KC;
             const int nt = min(nt0 + t, a.n_tiles - 1);
             ptr[i] = (const u32x4_t *)a.wp + ((size_t)nt * k_steps + k0 + kc) * 64; step[i] = KC * 64; dst[i] = (KC * 8 + kc * WNT + t) * 1024;
         }
@@ -103,7 +114,10 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
     int next_c = 0;                                     // chunk the pointers stand at, and the stage it goes to
     uint32_t next_stage = 0;
     auto copy_one = [&](int i) {
-        if (i + 1 < LPW || full) hx_copy_to_lds(ptr[i], lane * 16, next_stage * (STAGE_U4 * 16) + dst[i]);
+        if (i == 1 ? second : i + 1 < LPW || full) {
+            if (ONCE && i >= 2) hx_copy_to_lds_once(ptr[i], lane * 16, next_stage * (STAGE_U4 * 16) + dst[i]);
+            else hx_copy_to_lds(ptr[i], lane * 16, next_stage * (STAGE_U4 * 16) + dst[i]);
+        }
     };
     auto advance = [&]() {
         ++next_c;
@@ -114,8 +128,9 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
     };
     // this wavefront's copies of the chunk before the last requested one have landed, its LDS reads are done; then everyone's
     auto hand_over = [&]() {
-        if (full) __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT((NST - 2) * LPW));
-        else __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT((NST - 2) * (LPW - 1)));
+        if (full && second) __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT((NST - 2) * LPW));
+        else if (!PART || full || second) __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT((NST - 2) * (LPW - 1)));
+        else __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT((NST - 2) * (LPW - 2)));
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
@@ -250,6 +265,16 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
     u32x4_t x[2][TM], wt[2][TW];
     const u32x4_t *base = lds + lane;
+    if (PART && TM * wm >= RG) {                        // no rows: its copies, and everyone's barriers
+        for (int c = 0; c < n_chunks; ++c) {
+#pragma unroll
+            for (int q = 0; q < LPW; ++q) copy_one(q);
+            advance();
+            hand_over();
+        }
+        __builtin_amdgcn_s_waitcnt(HX_COPY_WAIT(0));
+        return;
+    }
     auto read_x = [&](uint32_t stage, int kc, int i) { x[kc & 1][i] = base[stage * STAGE_U4 + (kc * 8 + TM * wm + i) * 64]; };
     auto read_w = [&](uint32_t stage, int kc, int j) { wt[kc & 1][j] = base[stage * STAGE_U4 + (KC * 8 + kc * WNT + wn * TW + j) * 64]; };
 #pragma unroll
@@ -304,6 +329,7 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int m = 32 * (TM * wm + i) + ml;
+            if (PART && TM * wm + i >= RG) continue;
 #pragma unroll
             for (int j = 0; j < TW; ++j) {
                 const int nt = nt0 + wn * TW + j;
@@ -324,6 +350,7 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int m = 32 * (TM * wm + i) + ml;
+            if (PART && TM * wm + i >= RG) continue;
 #pragma unroll
             for (int j = 0; j < TW; ++j) {
                 const int nt = nt0 + wn * TW + j;
@@ -363,16 +390,16 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void gemm_wide_kernel(WideArgs a) 
     }
 }
 
-template <int WNT, int EPI, bool ODD, bool ROUNDS = false>
+template <int WNT, int EPI, bool ODD, bool ROUNDS = false, bool PART = false, bool ONCE = false>
 int launch_wide(dim3 grid, hipStream_t st, const WideArgs &a) {
     constexpr int NST = wide_stages(WNT, ROUNDS), LDS = wide_lds_bytes(WNT, NST);
     static std::once_flag once;
     static hipError_t configured = hipSuccess;
     std::call_once(once, [] {
-        configured = hipFuncSetAttribute((const void *)gemm_wide_kernel<WNT, EPI, ODD, NST>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        configured = hipFuncSetAttribute((const void *)gemm_wide_kernel<WNT, EPI, ODD, NST, PART, ONCE>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     });
     if (configured != hipSuccess) return hx_fail(HX_E_HIP, "hipFuncSetAttribute: %s", hipGetErrorString(configured));
-    hipLaunchKernelGGL((gemm_wide_kernel<WNT, EPI, ODD, NST>), grid, dim3(64 * WIDE_WAVES), LDS, st, a);
+    hipLaunchKernelGGL((gemm_wide_kernel<WNT, EPI, ODD, NST, PART, ONCE>), grid, dim3(64 * WIDE_WAVES), LDS, st, a);
     return HX_OK;
 }
 
@@ -380,11 +407,20 @@ template <int WNT>
 int launch_wide_epi(int epilogue, dim3 grid, hipStream_t st, const WideArgs &a) {
     if (epilogue == HX_EPI_PARTIAL) {
         if (a.k_steps & 1) return launch_wide<WNT, HX_EPI_PARTIAL, true>(grid, st, a);
+        if constexpr (WNT <= 5) if (a.groups <= WIDE_PART_GROUPS) return launch_wide<WNT, HX_EPI_PARTIAL, false, false, true>(grid, st, a);
         return launch_wide<WNT, HX_EPI_PARTIAL, false>(grid, st, a);
     }
     if (epilogue == HX_EPI_LOGITS) return launch_wide<WNT, HX_EPI_LOGITS, false>(grid, st, a);
     if (epilogue == HX_EPI_SAMPLE) return launch_wide<WNT, HX_EPI_SAMPLE, false>(grid, st, a);
     if ((int)grid.x > hx_device_cus()) return launch_wide<WNT, HX_EPI_SWIGLU, false, true>(grid, st, a);
+    if constexpr (WNT <= 5) {
+        const bool once = a.R == 1 && a.k_steps >= WIDE_ONCE_STEPS;
+        if (a.groups <= WIDE_PART_GROUPS) {
+            if (once) return launch_wide<WNT, HX_EPI_SWIGLU, false, false, true, true>(grid, st, a);
+            return launch_wide<WNT, HX_EPI_SWIGLU, false, false, true>(grid, st, a);
+        }
+        if (once) return launch_wide<WNT, HX_EPI_SWIGLU, false, false, false, true>(grid, st, a);
+    }
     return launch_wide<WNT, HX_EPI_SWIGLU, false>(grid, st, a);
 }
 
@@ -435,7 +471,7 @@ hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, int epilogue, int 
 // the fp32 output ([splits][256][N]) and the SiLU*mul output inside each block's workspace; ws0 = block 0's
 // workspace, block_stride bytes between blocks.
 int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, char *ws0, size_t block_stride, size_t xp_off,
-                        int epilogue, size_t y_off, size_t mp_off, hx_wide_plan plan, hipStream_t st, const hx_lm_args *lm) {
+                        int epilogue, size_t y_off, size_t mp_off, hx_wide_plan plan, hipStream_t st, const hx_lm_args *lm, int rows) {
     int splits = plan.splits;
     const int wnt = plan.wnt;
     if (wnt < 4 || wnt > 8) return hx_fail(HX_E_RANGE, "%d tiles per workgroup: no such wide product", wnt);
@@ -451,6 +487,7 @@ int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, 
     a.xp0 = ws0 + xp_off; a.block_stride = block_stride; a.R = row_blocks;
     a.y0 = (float *)(ws0 + y_off);
     a.mp0 = (uint16_t *)(ws0 + mp_off);
+    a.groups = row_blocks == 1 && rows > 128 ? (rows + 31) / 32 : 8;
     a.lm = head ? *lm : hx_lm_args{};
     a.steps_per_split = hx_wide_split_steps(m, splits);
     const int NB = (m->n_tiles + wnt - 1) / wnt;

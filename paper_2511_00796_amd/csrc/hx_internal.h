@@ -217,6 +217,10 @@ __host__ __device__ __forceinline__ int hx_vtile8_index(int t, int d) {
 __device__ __forceinline__ void hx_copy_to_lds(const void *src, uint32_t lane_off, uint32_t lds_off) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_off), "s"(src), "s"(lds_off) : "memory");
 }
+// the same, non-temporally: what is read once
+__device__ __forceinline__ void hx_copy_to_lds_once(const void *src, uint32_t lane_off, uint32_t lds_off) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" : : "v"(lane_off), "s"(src), "s"(lds_off) : "memory");
+}
 // s_waitcnt immediate: at most n vector-memory operations outstanding, all LDS operations done
 #define HX_COPY_WAIT(n) (((n) & 15) | (((n) >> 4) << 14) | 0x0070)
 
@@ -384,7 +388,8 @@ struct hx_wide_plan { int wnt, splits; };        // 32-column tiles per workgrou
 int hx_wide_split_steps(const hx_matrix *m, int splits);      // k-steps of each split but the last: whole chunks of two
 hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, int epilogue, int max_splits = HX_MAX_SPLITS);
 int hx_launch_gemm_wide(const hx_engine *e, const hx_matrix *m, int row_blocks, char *ws0, size_t block_stride, size_t xp_off,
-                        int epilogue, size_t y_off, size_t mp_off, hx_wide_plan plan, hipStream_t st, const hx_lm_args *lm = nullptr);
+                        int epilogue, size_t y_off, size_t mp_off, hx_wide_plan plan, hipStream_t st, const hx_lm_args *lm = nullptr,
+                        int rows = 256);         // rows that exist of a single block
 
 int hx_launch_sample_final(const hx_engine *e, int batch, int32_t *tokens_out, float *logprobs_out, hipStream_t st);
 int hx_launch_argmax_final(const hx_engine *e, int batch, int32_t *tokens_out, hipStream_t st);

@@ -133,3 +133,32 @@ def test_wide_tiles(hx, k_steps, batch, tiles, monkeypatch):
     gate = u.double() @ w["wg"]
     ref = gate * torch.sigmoid(gate) * (u.double() @ w["wu"])
     assert m.shape == ref.shape and ((m.double() - ref).abs() <= ref.abs() * 2.0 ** -7 + 1e-5).all()
+
+
+@pytest.mark.parametrize("tiles", [4, 5])
+@pytest.mark.parametrize("batch", [129, 160, 161, 192, 193])
+@pytest.mark.parametrize("hidden,k_steps", [(96, 2), (160, 14), (2080, 26)])
+def test_blocks_with_groups_that_hold_no_rows(hx, hidden, k_steps, batch, tiles, monkeypatch):
+    """Five and six m-groups of a single block (seven and eight: the kernel of full blocks), few and many chunks, splits, column blocks
+    that end inside a workgroup; gate|up of 128 and more k-steps copies its weights non-temporally.  What lies behind the rows is not
+    a number."""
+    s = synth.ModelShape("wb-part", 1, hidden, 2, 1, 64, 16 * k_steps, 64)
+    eng = build(hx, s, 5, 256, 64)
+    w = {k: v.double().cuda() for k, v in synth.layer_weights(s, 0, 5).items()}
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randn(batch, s.intermediate, generator=g, device="cuda").bfloat16().float()
+    u = torch.randn(batch, s.hidden, generator=g, device="cuda").bfloat16().float()
+    for splits in (1, 2):
+        monkeypatch.setenv("HX_GEMM_SHAPE", "%d,1,%d" % (tiles, splits))
+        eng.workspace.fill_(0xFF)
+        y = eng.stage_linear(hx.HX_T_WD, 0, x)
+        # fp32 sums of exact products
+        assert ((y.double() - x.double() @ w["wd"]).abs() <= 1e-5 * (x.double().abs() @ w["wd"].abs())).all()
+    monkeypatch.setenv("HX_GEMM_SHAPE", "%d,1,1" % tiles)
+    eng.workspace.fill_(0xFF)
+    m = eng.stage_linear(hx.HX_T_WG, 0, u)
+    torch.cuda.synchronize()
+    gate = u.double() @ w["wg"]
+    ref = gate * torch.sigmoid(gate) * (u.double() @ w["wu"])
+    # one bf16 rounding of the result and the fp32 sums' own error
+    assert m.shape == ref.shape and ((m.double() - ref).abs() <= ref.abs() * 2.0 ** -7 + 1e-5).all()
