@@ -19,7 +19,9 @@
 // Schedule: a pair (group, KV head) of more than S steps is cut into equal parts of at most S steps; S follows from the
 // work of the whole call (prompt_sched_kernel), so that a short call with a long cache fills the chip and a long one
 // writes few partial results.  An uncut pair writes its output itself; the parts of a cut one are merged by
-// prompt_combine_kernel.  Items run from the last group to the first: of one prompt the longest come first.
+// prompt_combine_kernel.  Groups are numbered by the length of their parts, items run from the last group to the first, and every
+// second round of the workgroups takes its items in reverse: who had a long part gets a short one.  (By the last row, and every
+// round alike: 512 workgroups had between 15 and 50 steps of a 2048-token prompt, TIMES.)
 //
 // Per-group arrays live where the 256-row workspaces keep their per-row ones: entry g in block g / 256 at g % 256.
 #include "hx_internal.h"
@@ -102,12 +104,15 @@ __device__ __forceinline__ int scan_1024(int v, int *red, int *total) {
     return MAX ? max(v, before) : v + before;
 }
 
+// Groups in the order of their parts' lengths, shortest first.
 // pre[g] = items (group, KV head, part) of the groups before g, lens[g] = keys of the group's last row, ginfo[g] = first
 // row | rows << 16, gslot[g] = first partial slot of a cut group, glist = the cut groups; sched (block 0) = {S, items,
 // cut groups}.  n_rows <= 8192: up to 8 rows (later: groups) per thread.
 __global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const int32_t *__restrict__ seq_lens, size_t o_cont,
                                                             int group_rows, int n_wgs) {
-    extern __shared__ int32_t sT[];                     // [n_rows] keys of each group's last row
+    extern __shared__ int32_t sT[];                     // [n_rows] keys of each group's last row; then [n_rows] 16-bit groups in order
+    uint16_t *order = (uint16_t *)(sT + a.n_rows);
+    __shared__ int bin[1024];
     __shared__ int red[16];
     __shared__ long long redl[16];
     const int tid = threadIdx.x, E = (a.n_rows + 1023) >> 10, r0 = tid * E, r1 = min(a.n_rows, r0 + E);
@@ -135,9 +140,7 @@ __global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const 
         gid += local == 0;
         const bool last = r + 1 == a.n_rows || !cont(r + 1) || local + 1 == group_rows;
         if (last) {
-            const int T = seq_lens[r];
-            sT[gid] = T;
-            *group_entry<int32_t>(a, a.o_lens, gid) = T;
+            sT[gid] = seq_lens[r];
             *group_entry<int32_t>(a, a.o_ginfo, gid) = (r - local) | ((local + 1) << 16);
         }
     }
@@ -157,12 +160,49 @@ __global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const 
     // workgroup the queries and a partial result of 64 KiB), and long enough for the partial slots: a cut pair has at
     // most 2 steps / S parts.
     const long long cap = (long long)a.slots_per_block * a.n_blocks;
-    long long S = (units + n_wgs - 1) / n_wgs;
-    if (S < HX_PROMPT_MIN_STEPS) S = HX_PROMPT_MIN_STEPS;
-    if (S < (2 * units + cap - 1) / cap) S = (2 * units + cap - 1) / cap;
+    long long longest = (units + n_wgs - 1) / n_wgs;
+    if (longest < HX_PROMPT_MIN_STEPS) longest = HX_PROMPT_MIN_STEPS;
+    if (longest < (2 * units + cap - 1) / cap) longest = (2 * units + cap - 1) / cap;
+    const int S = (int)longest;                         // 32 bits: the quotients by it are what this kernel's end takes
+    auto parts = [&](int g) { return (((sT[g] + 31) >> 5) + S - 1) / S; };
+    int want = 0;
+    for (int g = g0; g < g1; ++g) want += parts(g);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) want += __shfl_xor(want, off);
+    if ((tid & 63) == 0) red[tid >> 6] = want;
+    bin[tid] = 0;
+    __syncthreads();
+    want = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) want += red[w];
+    // Items in one round of the workgroups are not ordered.  Otherwise the groups by the length of their parts, in 1024 steps of
+    // it; which of two equal ones comes first decides no result.
+    if (want * a.n_kv > n_wgs) {
+        auto length = [&](int g) { const int st = (sT[g] + 31) >> 5, np = parts(g); return (st + np - 1) / np * 1023 / S; };
+        for (int g = g0; g < g1; ++g) atomicAdd(&bin[length(g)], 1);
+        __syncthreads();
+        int all;
+        const int count = bin[tid], below = scan_1024<false>(count, red, &all) - count;
+        bin[tid] = below;
+        __syncthreads();
+        for (int g = g0; g < g1; ++g) order[atomicAdd(&bin[length(g)], 1)] = (uint16_t)g;
+    } else {
+        for (int g = g0; g < g1; ++g) order[g] = (uint16_t)g;
+    }
+    __syncthreads();
+    int info[HX_PREFILL_MAX_ROWS / 1024];
+#pragma unroll
+    for (int k = 0; k < HX_PREFILL_MAX_ROWS / 1024; ++k) info[k] = g0 + k < g1 ? *group_entry<int32_t>(a, a.o_ginfo, order[g0 + k]) : 0;
+    __syncthreads();                                    // read by everybody, before the entries move
+#pragma unroll
+    for (int k = 0; k < HX_PREFILL_MAX_ROWS / 1024; ++k)
+        if (g0 + k < g1) {
+            *group_entry<int32_t>(a, a.o_ginfo, g0 + k) = info[k];
+            *group_entry<int32_t>(a, a.o_lens, g0 + k) = sT[order[g0 + k]];
+        }
     int items = 0, slots = 0, cut = 0;
     for (int g = g0; g < g1; ++g) {
-        const int np = (int)((((sT[g] + 31) >> 5) + S - 1) / S);
+        const int np = parts(order[g]);
         items += np * a.n_kv;
         if (np > 1) { slots += np * a.n_kv; ++cut; }
     }
@@ -171,7 +211,7 @@ __global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const 
     int slot = scan_1024<false>(slots, red, &n_slots) - slots;
     int ci = scan_1024<false>(cut, red, &n_cut) - cut;
     for (int g = g0; g < g1; ++g) {
-        const int np = (int)((((sT[g] + 31) >> 5) + S - 1) / S);
+        const int np = parts(order[g]);
         *group_entry<int32_t>(a, a.o_pre, g) = at;
         at += np * a.n_kv;
         if (np > 1) {
@@ -183,7 +223,7 @@ __global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const 
     for (int g = n_groups + tid; g < a.n_blocks * 256; g += 1024) *group_entry<int32_t>(a, a.o_pre, g) = n_items;
     if (tid == 0) {
         int32_t *sched = (int32_t *)(a.ws0 + a.o_sched);
-        sched[0] = (int)S;
+        sched[0] = S;
         sched[1] = n_items;
         sched[2] = n_cut;
     }
@@ -264,7 +304,9 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_kernel(PromptArgs a, const
     const int rl_w = (wave * 32 + c32) / G, gq_w = wave * 32 + c32 - rl_w * G, rl_n = c32 / G, gq_n = c32 - rl_n * G;
     // this wavefront's part of a step: half a block (K or V) at most
     constexpr int PER_TILE = TILE / 1024;               // copies per tile: 4, 2 or 1
-    for (int w = blockIdx.x; w < n_items; w += gridDim.x) {
+    for (int round = 0, w0 = 0; w0 < n_items; ++round, w0 += gridDim.x) {
+        const int w = w0 + (int)(round & 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x);
+        if (w >= n_items) break;                        // only in the last round
         const int it = n_items - 1 - w;
         const int gi = find_group(a, it, lane);
         const int info = __builtin_amdgcn_readfirstlane(*group_entry<int32_t>(a, a.o_ginfo, gi));
@@ -376,13 +418,16 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_kernel(PromptArgs a, const
 #pragma unroll
             for (int r = 1; r < 16; ++r) mx = fmaxf(mx, p[r]);
             mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float m_new = fmaxf(m, mx * scale_log2e);
+            // The scale of a column follows its maximum only once that is 2^8 past it: p, l and o are then at most 2^8 times larger
+            // and as exact (both halves of p and the sums are relative to their size).  Of 32 columns some maximum moves in most
+            // steps, and every time cost the wavefront 64 products.
+            const float mxs = mx * scale_log2e, m_new = mxs > m + 8.f ? mxs : m;
 #pragma unroll
             for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(p[r], scale_log2e, -m_new));
             float sum = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; r += 4) sum += (p[r] + p[r + 1]) + (p[r + 2] + p[r + 3]);
-            if (__builtin_amdgcn_ballot_w64(m_new != m) != 0ull) {     // rescale only when some maximum moved
+            if (__builtin_amdgcn_ballot_w64(m_new != m) != 0ull) {     // rescale only when some scale moved
                 const float alpha = __builtin_amdgcn_exp2f(m - m_new);
                 l *= alpha;
 #pragma unroll
@@ -623,7 +668,7 @@ int hx_launch_prompt_setup(const hx_engine *e, int n_rows, const int32_t *positi
     hipLaunchKernelGGL(prompt_rows_kernel, dim3(n_rows), dim3(64), 0, st, e->ws, stride, e->map.cs, e->map.blk_new, e->map.prompt_cont,
                        positions, seq_lens, table, max_blocks, e->D / 2, (double)e->cfg.rope_theta, e->cfg.max_batch);
     HX_CHECK_LAUNCH("prompt_rows");
-    hipLaunchKernelGGL(prompt_sched_kernel, dim3(1), dim3(1024), (size_t)n_rows * 4, st, a, seq_lens, e->map.prompt_cont,
+    hipLaunchKernelGGL(prompt_sched_kernel, dim3(1), dim3(1024), (size_t)n_rows * 6, st, a, seq_lens, e->map.prompt_cont,
                        HX_PROMPT_COLS / e->G, e->attn_waves / 4);
     HX_CHECK_LAUNCH("prompt_sched");
     return HX_OK;

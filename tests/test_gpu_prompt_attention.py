@@ -90,3 +90,27 @@ def test_prompt_attention_equals_row_at_a_time(hx, name, cache, waves, monkeypat
     print("%s %s waves %d: max |grouped - row-wise| %.2e (max |o| %.2f)" % (name, cache, waves, diff, scale))
     # P enters both kernels as a high + low bf16 pair: 2^-17 of each probability, plus fp32 sums in another order
     assert diff <= 2e-5 * scale
+
+
+@pytest.mark.parametrize("d,plan", [(128, [(700, 40), (1300, 1)]), (64, [(900, 70), (333, 2)])], ids=["128", "64"])
+@pytest.mark.parametrize("cache", ["bf16", "fp8"])
+@pytest.mark.parametrize("steepness", [1.0, 4.0, 16.0])
+def test_scores_that_rise_along_the_keys(hx, d, plan, cache, steepness, monkeypatch):
+    """A column's scale is moved only when its maximum is 2^8 past it: keys that grow along the sequence make maxima rise by less
+    than that, by about that and by more, over and over."""
+    fill = synth.kv_fill
+
+    def rising(*args, **kwargs):
+        k, v = fill(*args, **kwargs)
+        ramp = torch.linspace(0.05, 1.0, k.shape[0], device=k.device) * steepness
+        return (k.float() * ramp.view(-1, *[1] * (k.dim() - 1))).to(k.dtype), v
+
+    monkeypatch.setattr(synth, "kv_fill", rising)
+    s = synth.ModelShape("prompt-attn", 2, 256, 8, 2, d, 704, 1024)
+    rowwise, grouped = layer0_attention(hx, s, plan, hx.HX_KV_FP8_E4M3 if cache == "fp8" else hx.HX_KV_BF16, 0, monkeypatch)
+    assert np.isfinite(grouped).all()
+    scale = max(float(np.abs(rowwise).max()), 1.0)
+    diff = float(np.abs(grouped - rowwise).max())
+    print("%s %d x %g: max |grouped - row-wise| %.2e (max |o| %.2f)" % (cache, d, steepness, diff, scale))
+    # as above, and scores of up to about 8 steepness (in powers of two) that are sums in another order: 2^-20 of that at most
+    assert diff <= (2e-5 + 8 * steepness * 2.0 ** -20) * scale
