@@ -10,18 +10,22 @@
 // B operand of the second by numbering the contraction index accordingly: the probabilities never cross lanes, and the
 // V operand is read from LDS in the matching order.  P enters as a high + low bf16 pair, as in the decode step.
 //
-// What bounds it: the matrix cores (24 products of 32 cycles per 32 x 32 scores at D = 128) and the softmax arithmetic
-// beside them, which the second workgroup of a compute unit overlaps.  Measured per layer, kernel + combine, against a
+// What bounds it: a step is a chain (K reads, scores, maximum, exponentials, V reads, products) of which the matrix cores take
+// 768 cycles at D = 128 and the arithmetic beside them about as many; the two wavefronts of a SIMD cover each other's only in
+// part (2048 rows, 7B, one workgroup per compute unit 98 us, two 75).  Measured per layer, kernel + combine, against a
 // kernel that served 8 rows per K/V stream with one wavefront each and 16-row products of half the rate: 7B, one prompt
-// of 2048 tokens 73 + 13 us (214 + 69); 14B, 7 prompts of 5000 tokens together, 8-bit cache 126 + 6 us (273 + 136);
+// of 2048 tokens 70 + 13 us (214 + 69); 14B, 7 prompts of 5000 tokens together, 8-bit cache 93 + 6 us (273 + 136);
 // 1.5B, 200 rows behind 3000 cached tokens 18 + 7 us (41 + 9).
 //
 // Schedule: a pair (group, KV head) of more than S steps is cut into equal parts of at most S steps; S follows from the
 // work of the whole call (prompt_sched_kernel), so that a short call with a long cache fills the chip and a long one
 // writes few partial results.  An uncut pair writes its output itself; the parts of a cut one are merged by
-// prompt_combine_kernel.  Groups are numbered by the length of their parts, items run from the last group to the first, and every
-// second round of the workgroups takes its items in reverse: who had a long part gets a short one.  (By the last row, and every
-// round alike: 512 workgroups had between 15 and 50 steps of a 2048-token prompt, TIMES.)
+// prompt_combine_kernel.  Where there are more items than workgroups, groups are numbered by the length of their parts, items
+// run from the last group to the first, and every second round of the workgroups takes its items in reverse: who had a long part
+// gets a short one.  (In the order of the rows, every round alike, one of 512 workgroups had up to 50 steps of a 2048-token
+// prompt where the mean is 29.)  us per layer, the order of the rows | this | and the lazy scale of the columns: 7B, 2048 rows
+// 83 | 75 | 70.5, 14B, 8-bit cache, 4864 rows of 7 prompts 118 | 97 | 93; the schedule, once for all layers, 11 -> 13 and
+// 13.5 -> 18.
 //
 // Per-group arrays live where the 256-row workspaces keep their per-row ones: entry g in block g / 256 at g % 256.
 #include "hx_internal.h"
@@ -104,7 +108,7 @@ __device__ __forceinline__ int scan_1024(int v, int *red, int *total) {
     return MAX ? max(v, before) : v + before;
 }
 
-// Groups in the order of their parts' lengths, shortest first.
+// Groups in the order of the rows, or of their parts' lengths, shortest first.
 // pre[g] = items (group, KV head, part) of the groups before g, lens[g] = keys of the group's last row, ginfo[g] = first
 // row | rows << 16, gslot[g] = first partial slot of a cut group, glist = the cut groups; sched (block 0) = {S, items,
 // cut groups}.  n_rows <= 8192: up to 8 rows (later: groups) per thread.
@@ -420,7 +424,7 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_kernel(PromptArgs a, const
             mx = fmaxf(mx, __shfl_xor(mx, 32));
             // The scale of a column follows its maximum only once that is 2^8 past it: p, l and o are then at most 2^8 times larger
             // and as exact (both halves of p and the sums are relative to their size).  Of 32 columns some maximum moves in most
-            // steps, and every time cost the wavefront 64 products.
+            // steps, and every time cost the wavefront 64 multiplications (7B, 2048 rows: 75 -> 70.5 us per layer).
             const float mxs = mx * scale_log2e, m_new = mxs > m + 8.f ? mxs : m;
 #pragma unroll
             for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(p[r], scale_log2e, -m_new));
