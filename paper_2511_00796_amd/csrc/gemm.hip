@@ -662,10 +662,12 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
 
 // ---- the token of each row from its per-tile candidates -------------------------------------------------------
 // One workgroup per row, of 1024 threads (256 where a row has at most 1024 tiles).  A row's 4752 tiles (7B) are 5 per thread,
-// four of which are requested before the first is used: what bounds these kernels is the latency of their loads, not
-// their bytes.  37 rows of 4752 tiles: 9.2 us sampled, 4.5 greedy (256 threads with one load after the other: 20 and 8.8).
+// all requested before the first is used: what bounds these kernels is the latency of their loads and of the merges behind them,
+// not their bytes.  Of the sums every lane weighs its own once, and the wavefronts' results are merged by one of them: 37 rows of
+// 4752 tiles 5.5 us sampled, 3 rows 4.9, 128 rows 6.1, 256 rows 8.0 (four tiles per trip, every merge weighed, the wavefronts' one
+// after the other by one thread: 9.1, 8.6, 10.1, 12.0).
 #define HX_FINAL_THREADS 1024
-#define HX_FINAL_UNROLL 4
+#define HX_FINAL_UNROLL 5
 
 // Largest value wins, ties go to the smaller index; fixed order, so the result does not depend on the timing.
 __device__ __forceinline__ void keep_best(float &v, int32_t &i, float &z, float ov, int32_t oi, float oz) {
@@ -695,10 +697,13 @@ __global__ __launch_bounds__(HX_FINAL_THREADS) void argmax_final_kernel(const fl
     for (int off = 32; off > 0; off >>= 1) keep_best(best, bi, none, __shfl_xor(best, off), __shfl_xor(bi, off), 0.f);
     if ((tid & 63) == 0) { sv[tid >> 6] = best; si[tid >> 6] = bi; }
     __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < nt / 64; ++w) keep_best(best, bi, none, sv[w], si[w], 0.f);
-        out[m] = bi;
-    }
+    if (tid >= 64) return;
+    const int w = min(tid, nt / 64 - 1);
+    best = sv[w];
+    bi = si[w];
+#pragma unroll
+    for (int off = HX_FINAL_THREADS / 128; off > 0; off >>= 1) keep_best(best, bi, none, __shfl_xor(best, off), __shfl_xor(bi, off), 0.f);
+    if (tid == 0) out[m] = bi;
 }
 
 int hx_launch_argmax_final(const hx_engine *e, int batch, int32_t *tokens_out, hipStream_t st) {
@@ -709,11 +714,13 @@ int hx_launch_argmax_final(const hx_engine *e, int batch, int32_t *tokens_out, h
 }
 
 // The sampled token and its log-probability: largest perturbed score (ties: smaller column); log-sum-exp of the scaled
-// logits = M + log(S) from the tiles' (max, sum of exp(z - max)), merged pairwise in a fixed order.
-__device__ __forceinline__ void merge_lse(float &M, float &S, float oM, float oS) {
-    const float n = fmaxf(M, oM);
-    if (n > -INFINITY) S = S * expf(M - n) + oS * expf(oM - n);    // both -inf: nothing to weigh
-    M = n;
+// logits = M + log(S) from the tiles' (max, sum of exp(z - max)): the maximum over the lanes first, so that each weighs its own sum
+// once, and the sums in a fixed order.
+__device__ __forceinline__ void lse_over_lanes(float &M, float &S, int lanes) {
+    const float own = M;
+    for (int off = lanes / 2; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
+    if (M > -INFINITY) S *= expf(own - M);                         // all -inf: nothing to weigh
+    for (int off = lanes / 2; off > 0; off >>= 1) S += __shfl_xor(S, off);
 }
 
 __global__ __launch_bounds__(HX_FINAL_THREADS) void sample_final_kernel(const float *__restrict__ val, const int32_t *__restrict__ idx,
@@ -751,17 +758,21 @@ __global__ __launch_bounds__(HX_FINAL_THREADS) void sample_final_kernel(const fl
         M = mc;
     }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        keep_best(best, bi, bz, __shfl_xor(best, off), __shfl_xor(bi, off), __shfl_xor(bz, off));
-        merge_lse(M, S, __shfl_xor(M, off), __shfl_xor(S, off));
-    }
+    for (int off = 32; off > 0; off >>= 1) keep_best(best, bi, bz, __shfl_xor(best, off), __shfl_xor(bi, off), __shfl_xor(bz, off));
+    lse_over_lanes(M, S, 64);
     if ((tid & 63) == 0) { const int w = tid >> 6; sv[w] = best; si[w] = bi; sz[w] = bz; sm[w] = M; ss[w] = S; }
     __syncthreads();
+    if (tid >= 64) return;
+    const int w = min(tid, nt / 64 - 1);
+    best = sv[w];
+    bi = si[w];
+    bz = sz[w];
+    M = sm[w];
+    S = tid < nt / 64 ? ss[w] : 0.f;
+#pragma unroll
+    for (int off = NW / 2; off > 0; off >>= 1) keep_best(best, bi, bz, __shfl_xor(best, off), __shfl_xor(bi, off), __shfl_xor(bz, off));
+    lse_over_lanes(M, S, NW);
     if (tid == 0) {
-        for (int w = 1; w < nt / 64; ++w) {
-            keep_best(best, bi, bz, sv[w], si[w], sz[w]);
-            merge_lse(M, S, sm[w], ss[w]);
-        }
         tok_out[m] = bi;
         lp_out[m] = bz - (M + logf(S));
     }

@@ -80,3 +80,17 @@ def test_near_ties_are_decided_exactly(hx, vocab, batch):
         y, tok, lp, n = (t.cpu().numpy() for t in eng.stage_lm_head_top_p(x, pos, 1e-3, 0.5, seed))
         assert (n == vocab).all()
         test_gpu_top_p.check_against_oracle(tok, lp, n, y, 1e-3, 0.5, seed, np.arange(batch), pos.cpu().numpy(), "near")
+
+
+# 2, 63, 257 tiles of 256 threads; 1024 (the last of them), 1025; 5 per thread of 1024: 5120 (the last in one trip) and 5121
+@pytest.mark.parametrize("tiles", [2, 63, 257, 1024, 1025, 5120, 5121])
+def test_tokens_from_any_number_of_tiles(hx, tiles):
+    vocab = 32 * tiles - 8
+    s = synth.ModelShape("tiles", 1, 256, 4, 2, 64, 688, vocab)
+    dw = workload.build(synth.Workload("tiles", s, 4, "uniform", 1, 40, 78))
+    for seed in (3, 4):
+        tok, lp, logits = test_gpu_sampling.sample_once(dw, 1.3, seed)
+        test_gpu_sampling.check_against_oracle(tok, lp, logits, 1.3, seed, np.arange(4), dw.positions.cpu().numpy(), "tiles")
+    greedy = torch.empty(4, dtype=torch.int32, device="cuda")
+    dw.engine.decode_step(dw.kv, dw.tokens, dw.positions, dw.seq_lens_d, dw.table_d, dw.logits, greedy)
+    assert torch.equal(greedy.long(), dw.logits.argmax(1))
