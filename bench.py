@@ -23,7 +23,7 @@ HBM_PEAK_GBS = 8000.0     # MI355X published HBM3E bandwidth
 # HBM bytes per attention launch at workload 7b-b128 from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a plain
 # copy (profiles/attn_splitk_7b-b128_hbm_traffic.txt).  Valid only for the kernel source they were taken with.
 PMC_TRAFFIC = {"workload": "7b-b128",
-               "attention_hip_sha256": "65b376a2d7e347f6733e0bf45e3775782fa7d541a2820f213db81216a91edf96",
+               "attention_hip_sha256": "47dccd36c3b628d45a6cddd0cdbe57df33f929c6bd21b2df08d1af2e94237223",
                "fetch_bytes": 2150.25e6, "write_bytes": 9.45e6}
 
 
