@@ -167,7 +167,7 @@ __global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const 
     long long longest = (units + n_wgs - 1) / n_wgs;
     if (longest < HX_PROMPT_MIN_STEPS) longest = HX_PROMPT_MIN_STEPS;
     if (longest < (2 * units + cap - 1) / cap) longest = (2 * units + cap - 1) / cap;
-    const int S = (int)longest;                         // 32 bits: the quotients by it are what this kernel's end takes
+    int S = (int)longest;                               // 32 bits: the quotients by it are what this kernel's end takes
     auto parts = [&](int g) { return (((sT[g] + 31) >> 5) + S - 1) / S; };
     int want = 0;
     for (int g = g0; g < g1; ++g) want += parts(g);
@@ -179,9 +179,14 @@ __global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const 
     want = 0;
 #pragma unroll
     for (int w = 0; w < 16; ++w) want += red[w];
-    // Items in one round of the workgroups are not ordered.  Otherwise the groups by the length of their parts, in 1024 steps of
-    // it; which of two equal ones comes first decides no result.
+    // Items in one round of the workgroups are not ordered.  Otherwise parts of half as much again balance as well and are fewer: us
+    // per 4-layer call, factors of 1 | 1.25 | 1.5, 7B, 2048 rows 2392 | 2391 | 2374, 1024 rows behind 3000 tokens 1620 | 1575 | 1577, 1.5B,
+    // 2048 rows 847 | 822 | 833, 14B 2896 | 2885 | 2866 (0.75: 2403, 1612, 846, 2901).  Not where groups of few columns, which wait
+    // for memory, are more than half a pair per workgroup and the longest pair is then hardly cut: single rows of 300 to 5000 tokens,
+    // 1 | 1.5, 256 pairs 649 | 631, 288 709 | 701, 336 754 | 758, 400 833 | 855.  And the groups go by the length of their
+    // parts, in 1024 steps of it; which of two equal ones comes first decides no result.
     if (want * a.n_kv > n_wgs) {
+        if (2 * n_groups * a.n_kv <= n_wgs || 32 * n_groups < a.n_rows * a.G) S += S / 2;
         auto length = [&](int g) { const int st = (sT[g] + 31) >> 5, np = parts(g); return (st + np - 1) / np * 1023 / S; };
         for (int g = g0; g < g1; ++g) atomicAdd(&bin[length(g)], 1);
         __syncthreads();
