@@ -297,13 +297,14 @@ __global__ __launch_bounds__(WPP == 1 ? 256 : 64 * WPP) void attn_combine_kernel
     const int lane = threadIdx.x & 63, d8 = lane & 15, ph = lane >> 4;
     const bool has_d = d8 < D / 8;
     const int T = lens[b], P = pre[b];
-    const unsigned S = sched[0];
+    const unsigned S = max(sched[0], 1);
     __builtin_amdgcn_sched_barrier(0);                   // three loads in one round trip, beside the division by G
     const int kvh = (unsigned)h / (unsigned)G, g = h - kvh * G;
     const int nblk_b = (T + 15) >> 4;
     const int start = P * n_kv + kvh * nblk_b;           // tiles of this pair: [start, start + nblk_b)
     const int pair = b * n_kv + kvh;
-    const int s0 = (unsigned)start / S + pair, s1 = (unsigned)(start + nblk_b - 1) / S + pair;   // its slots, inclusive
+    // its slots, inclusive; a sequence without keys has no partials: it reads one slot, whatever that holds, and no other row does
+    const int s0 = (unsigned)start / S + pair, s1 = (unsigned)(start + max(nblk_b, 1) - 1) / S + pair;
     const int n = s1 - s0 + 1;
     const int waves = WPP > 1 && n > HX_COMBINE_FEW ? WPP : 1;      // that share the pair: the same for the whole workgroup
     if (pw >= waves) return;
