@@ -187,7 +187,7 @@ __global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const 
     // parts, in 1024 steps of it; which of two equal ones comes first decides no result.
     if (want * a.n_kv > n_wgs) {
         if (2 * n_groups * a.n_kv <= n_wgs || 32 * n_groups < a.n_rows * a.G) S += S / 2;
-        auto length = [&](int g) { const int st = (sT[g] + 31) >> 5, np = parts(g); return (st + np - 1) / np * 1023 / S; };
+        auto length = [&](int g) { const int st = (sT[g] + 31) >> 5, np = max(parts(g), 1); return (st + np - 1) / np * 1023 / S; };   // no keys: 0
         for (int g = g0; g < g1; ++g) atomicAdd(&bin[length(g)], 1);
         __syncthreads();
         int all;
