@@ -516,8 +516,7 @@ static int launch_shape(int wn, int wk, int epilogue, dim3 grid, hipStream_t st,
 // PLAN_STEPS k-steps; split products, which run in one round and read only a K-slice of the activations, keep a small charge
 // per extra tile instead (five consumers on four SIMDs); ties go to the smaller wn and fewer splits.  Fewer rows take
 // the same plan, though their rings are of 8 and their workgroups take a quarter of the LDS or less: the splits decide
-// in which order a row's products are added, and so a row comes out alike in every batch of up to 128 (of up to 64, and of 65 to 128,
-// where gate|up has a workgroup of gemm_slice.hip for every three tiles up to 64 rows).
+// in which order a row's products are added, and so a row comes out alike in every batch of up to 128.
 // Examples: the 1184 tiles of the 7B gate|up matrix make 296 workgroups of 4 (two rounds on 256 compute
 // units) but 237 workgroups of 5 (one round); the 4752 tiles of the LM head make five rounds of 4, four of 5 or
 // two of 10, measured 253 / 244 / 230 us.  Ten tiles per workgroup are twelve wavefronts (three per SIMD): only

@@ -1,7 +1,7 @@
 // Small products: those whose matrix has too few column tiles to give the streaming kernel of gemm.hip (four
 // and more tiles per workgroup, at most 9 K-splits, none of gate|up) a workgroup for every compute unit.
 //
-// Workgroup = four wavefronts on one to three 32-column tiles: k-step i of the split goes to wavefront i % 4, so the
+// Workgroup = four wavefronts on one or two 32-column tiles: k-step i of the split goes to wavefront i % 4, so the
 // workgroup reads its tile's weights as one contiguous run.  A wavefront loads its weights and activations straight into
 // registers, R steps ahead; no LDS stages, no barrier until the end, where the four sums are added in order through LDS, laid out
 // so that the outputs leave in whole 128-byte lines.
@@ -187,17 +187,19 @@ int launch_slice(int epilogue, const SliceArgs &a, int splits, hipStream_t st) {
 // 7.9 / 13.7 here.  K-splits: at least 24 k-steps each (1.5B QKV at 64 rows in 6 / 4 / 2 splits: 5.6 / 4.4 /
 // 5.2 us) and no more workgroups than compute units; two tiles per workgroup where that still leaves long ones.  Up to 128 rows are one
 // block; more are four of 64 or two of 128, whatever their number, so that a row's sums are added in one order in all such batches.
-// Gate|up, which is not split, runs here in one round of one or two tiles per workgroup, up to 64 rows also of three, where its activations
-// are few.  us, streaming -> this, 1 / 33 / 128 rows: 256 tiles of 128 k-steps 16.8 / 18.6 / 23.6 -> 8.8 / 10.5 / 14.4, 512 of 128 18.7 / 20.6 / 25.2 ->
-// 13.5 / 14.6 / 19.6, 384 of 192 24.0 / 26.6 / 33.7 -> 17.0 / 18.2 / 25.2, 560 of 96 (1.5B) 15.2 / 17.0 / 21.8 -> 13.2 / 14.8 / 26, 768 of 192 26.9 / 30.2 /
-// 38.0 -> 25.3 / 26.4 / 46; 816 tiles, in two rounds of two, 21.7 / 25.4 / 29.8 -> 21.6 / 24.9 / 34.2.
+// Gate|up, which is not split, runs here in one round of one or two tiles per workgroup.  us, streaming -> this, 1 / 33 / 128 rows: 256 tiles of
+// 128 k-steps 16.8 / 18.6 / 23.6 -> 8.8 / 10.5 / 14.4, 512 of 128 18.7 / 20.6 / 25.2 -> 13.5 / 14.6 / 19.6, 384 of 192 24.0 / 26.6 / 33.7 -> 17.0 /
+// 18.2 / 25.2; 816 tiles, in two rounds of two, 21.7 / 25.4 / 29.8 -> 21.6 / 24.9 / 34.2.  Three tiles (up to 768) gain up to 64 rows and lose beyond: 560 of
+// 96 (1.5B) 15.2 / 17.0 / 21.8 -> 13.2 / 14.8 / 26, 768 of 192 26.9 / 30.2 / 38.0 -> 25.3 / 26.4 / 46; as row blocks of 64 rows, two workgroups to a
+// compute unit, still 2 to 4 % and 11 to 13 % at 65 to 128 rows.  One plan serves all batches of up to 128 rows (a row's products are added in
+// one order in all of them), so three are left to the streaming kernel.
 hx_slice_plan hx_plan_slice(int n_tiles, int k_steps, int rows, int epilogue, int max_splits) {
     const int cus = hx_device_cus();
     const bool partial = epilogue == HX_EPI_PARTIAL;
     hx_slice_plan p{0, 1};
     if (epilogue == HX_EPI_SWIGLU && rows <= 128) {
         const int t = (n_tiles + cus - 1) / cus;
-        if (t <= (rows <= 64 ? 3 : 2)) p.tiles = t;
+        if (t <= 2) p.tiles = t;
         return p;
     }
     if ((n_tiles + 3) / 4 * HX_MAX_SPLITS * 5 > cus * 3) return p;
@@ -225,8 +227,6 @@ int hx_launch_gemm_slice(const hx_engine *e, const hx_matrix *m, int batch, hx_s
         case 21: return launch_slice<2, 2, 1, 6>(epilogue, a, plan.splits, st);
         case 41: return launch_slice<4, 4, 1, 4>(epilogue, a, plan.splits, st);
         case 81: return launch_slice<2, 8, 1, 6>(epilogue, a, plan.splits, st);
-        case 13: return launch_slice<1, 1, 3, 4>(epilogue, a, plan.splits, st);
-        case 23: return launch_slice<2, 2, 3, 4>(epilogue, a, plan.splits, st);
         case 12: return launch_slice<1, 1, 2, 6>(epilogue, a, plan.splits, st);
         case 22: return launch_slice<2, 2, 2, 6>(epilogue, a, plan.splits, st);
         case 42: return launch_slice<4, 4, 2, 3>(epilogue, a, plan.splits, st);

@@ -84,9 +84,9 @@ def test_products_of_few_columns_beyond_128_rows(hx, name, batch, max_batch):
 
 @pytest.mark.parametrize("batch", [1, 32, 33, 64, 65, 128])
 @pytest.mark.parametrize("tiles,hidden", [(69, 32), (256, 96), (257, 192), (512, 160), (513, 96), (770, 64)])
-def test_gate_up_of_one_to_three_tiles_per_workgroup(hx, tiles, hidden, batch):
-    """Both sides of the steps between one, two and three tiles per workgroup (256, 512 on 256 compute units) and to the streaming
-    kernel (768 up to 64 rows, 512 beyond), last workgroups with tiles that do not exist, fewer k-steps than wavefronts."""
+def test_gate_up_of_one_and_two_tiles_per_workgroup(hx, tiles, hidden, batch):
+    """Both sides of the steps between one and two tiles per workgroup (256 on 256 compute units) and to the streaming kernel (512),
+    last workgroups with tiles that do not exist, fewer k-steps than wavefronts."""
     s = synth.ModelShape("sp-gu", 1, hidden, 1, 1, 64, 16 * tiles, 64)
     eng = build(hx, s, 5, batch, 64)
     w = {k: v.double().cuda() for k, v in synth.layer_weights(s, 0, 5).items()}
@@ -98,3 +98,17 @@ def test_gate_up_of_one_to_three_tiles_per_workgroup(hx, tiles, hidden, batch):
     ref = gate * torch.sigmoid(gate) * (x.double() @ w["wu"])
     # one bf16 rounding of the result and the fp32 sums' own error
     assert y.shape == ref.shape and ((y.double() - ref).abs() <= ref.abs() * 2.0 ** -7 + 1e-5).all()
+
+
+@pytest.mark.parametrize("tiles,hidden", [(256, 512), (257, 512), (512, 512), (513, 512), (560, 1536), (768, 512), (769, 512)])
+def test_a_row_comes_out_alike_in_every_batch_of_up_to_128(hx, tiles, hidden):
+    """The order in which a row's products are added hangs on the matrix alone, at every number of gate|up tiles where a plan ends:
+    the rows of 1, 32, 33, 64 and 65 are those of 128, bit for bit, and so are those of the other products."""
+    s = synth.ModelShape("sp-alike", 1, hidden, 4, 2, 64, 16 * tiles, 2180)
+    eng = build(hx, s, 5, 128, 64)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    for kind, K in ((hx.HX_T_WG, hidden), (hx.HX_T_WQKV, hidden), (hx.HX_T_WO, s.q_dim), (hx.HX_T_WD, s.intermediate), (hx.HX_T_WLM, hidden)):
+        x = torch.randn(128, K, generator=g, device="cuda")
+        whole = eng.stage_linear(kind, 0, x)
+        for batch in (1, 32, 33, 64, 65):
+            assert torch.equal(eng.stage_linear(kind, 0, x[:batch].contiguous()), whole[:batch]), (kind, batch)
