@@ -10,8 +10,11 @@
 // many: 14B gate|up at 64 rows 73 us (two tiles per workgroup 56), 48 there.  us, streaming -> this, 1 / 64 / 128 rows:
 // 1.5B QKV 3.9 / 7.5 / 10.5 -> 2.7 / 4.3 / 7.0, O 4.5 / 7.1 / 9.5 -> 3.4 / 4.1 / 6.0, down 10.0 / 14.3 / 16.8 -> 8.6 / 11.2 / 13.0
 // (two tiles; one: 7.6 / 10.4 / 13.6), with weights that are partly in the memory-side cache.
-// Beyond 128 rows a workgroup takes 64 of them (two tiles: 128), and the row blocks read the weights again, from the L2.  The
-// workgroup-tiled kernel of gemm_wide.hip would give these matrices 40 to 112 of 256 compute units a workgroup.  us, there -> this, 160 / 256
+// Beyond 128 rows a workgroup takes 64 of them (two tiles: 128), and the row blocks of a tile, numbered so that one XCD takes them all, read its
+// weights again, from that XCD's L2 (so they are ordinary loads there).  Numbered block by block, tiles times splits that were no multiple of 8 put
+// them on different XCDs, and each fetched the weights from memory: down products at 129 rows with the packing of the
+// input and the sum of the splits, weights from memory: 62 tiles of 1024 k-steps 47.6 -> 39.8 us, 68 of 512 32.7 -> 28.0, 68 of 688 41.3 -> 35.4.  The workgroup-tiled kernel of gemm_wide.hip would give these matrices 40 to 112 of 256
+// compute units a workgroup.  us, there -> this, 160 / 256
 // rows, weights from memory: 1.5B QKV 14.1 / 14.6 -> 7.4 / 7.7, O 14.1 / 15.0 -> 7.2 / 7.3, down 22.2 / 22.1 -> 15.6 / 16.6 (five splits; nine 21.2 / 22.2,
 // one tile per workgroup 23.9 / 23.8); the tiny model's 9 to 13 -> 3 to 4.
 #include "hx_internal.h"
@@ -24,7 +27,7 @@ namespace {
 
 constexpr int SLICES = 4;         // wavefronts of a workgroup
 
-// TN tiles per workgroup, MG of XG m-groups (blockIdx.z), R k-steps in flight per wavefront
+// TN tiles per workgroup, MG of XG m-groups, R k-steps in flight per wavefront
 template <int MG, int XG, int TN, int R, int EPI>
 __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(const uint4 *__restrict__ a_wp, const uint4 *__restrict__ a_xp,
                                                                int a_k_steps, int a_n_tiles, int a_steps_per_split, int a_M, int a_N,
@@ -34,9 +37,17 @@ __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(const uint4 *__
     constexpr int Q = TN * MG * 4;                       // 16-byte quads of accumulators per lane
     __shared__ u32x4_t red[S * Q * 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int t0 = blockIdx.x * TN;
-    const int g0 = XG > MG ? MG * blockIdx.z : 0;
-    const int split0 = blockIdx.y * a_steps_per_split, split1 = min(a_k_steps, split0 + a_steps_per_split);
+    int tg = blockIdx.x, split = blockIdx.y, g0 = 0;     // tile group, split, first m-group
+    if (XG > MG) {
+        // consecutive workgroup ids go to different XCDs: blockIdx.x is the XCD that takes all row blocks of a (group, split)
+        const unsigned pair = 8 * blockIdx.z + blockIdx.x, groups = (unsigned)(a_n_tiles + TN - 1) / TN;
+        split = pair / groups;
+        tg = pair - split * groups;
+        g0 = MG * blockIdx.y;
+        if (split * a_steps_per_split >= a_k_steps) return;             // behind the last pair: no split is empty
+    }
+    const int t0 = tg * TN;
+    const int split0 = split * a_steps_per_split, split1 = min(a_k_steps, split0 + a_steps_per_split);
     // step i of this wavefront is k-step split0 + wave + S * i
     const int n = (split1 - split0 - wave + S - 1) / S;
     const u32x4_t *wrow[TN];
@@ -55,7 +66,7 @@ __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(const uint4 *__
         auto request = [&](int r, int i) {
             const int j = S * min(i, n - 1);
 #pragma unroll
-            for (int t = 0; t < TN; ++t) w[r][t] = __builtin_nontemporal_load(wrow[t] + (size_t)j * 64);
+            for (int t = 0; t < TN; ++t) w[r][t] = XG > MG ? wrow[t][(size_t)j * 64] : __builtin_nontemporal_load(wrow[t] + (size_t)j * 64);
 #pragma unroll
             for (int g = 0; g < MG; ++g) x[r][g] = xrow[((size_t)j * XG + g) * 64];
             __builtin_amdgcn_sched_barrier(0);
@@ -105,7 +116,7 @@ __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(const uint4 *__
     };
     if (EPI == HX_EPI_PARTIAL) {
         // lane = (row of 8, group of 4 columns): 128 contiguous bytes per row
-        float *y = a_y + (size_t)blockIdx.y * a_split_stride;
+        float *y = a_y + (size_t)split * a_split_stride;
         const int nq = lane & 7;
         for (int u = wave; u < Q; u += S) {              // 8 rows of one tile
             const int t = u / (MG * 4), g = u / 4 % MG, ml = (u & 3) * 8 + (lane >> 3);
@@ -133,7 +144,7 @@ __global__ __launch_bounds__(64 * SLICES) void gemm_slice_kernel(const uint4 *__
             }
         }
     } else {
-        for (int u = (wave + blockIdx.x) % S; u < TN * MG; u += S) {
+        for (int u = (wave + tg) % S; u < TN * MG; u += S) {
             const int t = u / MG, g = u % MG;
             if (32 * (g0 + g) >= a_M || t0 + t >= a_n_tiles) continue;
             f32x16_t v;
@@ -159,7 +170,8 @@ struct SliceArgs {
 
 template <int MG, int XG, int TN, int R>
 int launch_slice(int epilogue, const SliceArgs &a, int splits, hipStream_t st) {
-    const dim3 grid((a.n_tiles + TN - 1) / TN, splits, XG > MG ? (a.M + 32 * MG - 1) / (32 * MG) : 1), block(64 * SLICES);
+    const int groups = (a.n_tiles + TN - 1) / TN, blocks = (a.M + 32 * MG - 1) / (32 * MG);
+    const dim3 grid = XG > MG ? dim3(8, blocks, (groups * splits + 7) / 8) : dim3(groups, splits), block(64 * SLICES);
 #define HX_SLICE(EPI)                                                                                                      \
     hipLaunchKernelGGL((gemm_slice_kernel<MG, XG, TN, R, EPI>), grid, block, 0, st, a.wp, a.xp, a.k_steps, a.n_tiles, a.steps_per_split, \
                        a.M, a.N, a.split_stride, a.y, a.mp, a.lm)
@@ -216,6 +228,7 @@ int hx_launch_gemm_slice(const hx_engine *e, const hx_matrix *m, int batch, hx_s
     a.xp = (const uint4 *)xp;
     a.k_steps = m->k_steps; a.n_tiles = m->n_tiles;
     a.steps_per_split = (m->k_steps + plan.splits - 1) / plan.splits;
+    if ((plan.splits - 1) * a.steps_per_split >= m->k_steps) return hx_fail(HX_E_RANGE, "%d splits of %d k-steps: one is empty", plan.splits, m->k_steps);
     a.M = batch; a.N = m->N;
     a.y = y; a.split_stride = batch * m->N;
     a.mp = (uint16_t *)mp_out;

@@ -112,3 +112,21 @@ def test_a_row_comes_out_alike_in_every_batch_of_up_to_128(hx, tiles, hidden):
         whole = eng.stage_linear(kind, 0, x)
         for batch in (1, 32, 33, 64, 65):
             assert torch.equal(eng.stage_linear(kind, 0, x[:batch].contiguous()), whole[:batch]), (kind, batch)
+
+
+# (tile, split) pairs that are no multiple of 8 (one workgroup in 8 of the last ones has nothing to do), one and two tiles per workgroup, an odd
+# last tile group; 1 pair, 7 (one tile of 168 k-steps), 68, 25 x 5, 31 x 4, 34 x 3
+@pytest.mark.parametrize("hidden,intermediate", [(32, 16), (32, 2688), (2176, 368), (1568, 3472), (1984, 3488), (2176, 3472)])
+def test_row_blocks_of_pairs_that_do_not_fill_the_xcds(hx, hidden, intermediate):
+    """Every number of row blocks: against float64 at 256 rows, and fewer rows are, bit for bit, the first of those."""
+    s = synth.ModelShape("sp-xcd", 1, hidden, 1, 1, 64, intermediate, 64)
+    eng = build(hx, s, 5, 256, 64)
+    w = synth.layer_weights(s, 0, 5)["wd"].double().cuda()
+    x = torch.randn(256, intermediate, generator=torch.Generator(device="cuda").manual_seed(7), device="cuda").bfloat16().float()
+    eng.workspace.fill_(0xFF)
+    whole = eng.stage_linear(hx.HX_T_WD, 0, x)
+    # fp32 sums of exact products
+    assert ((whole.double() - x.double() @ w).abs() <= 1e-5 * (x.double().abs() @ w.abs())).all()
+    for batch in (129, 160, 192, 193, 255):
+        eng.workspace.fill_(0xFF)
+        assert torch.equal(eng.stage_linear(hx.HX_T_WD, 0, x[:batch].contiguous()), whole[:batch]), batch
