@@ -199,6 +199,9 @@ int launch_slice(int epilogue, const SliceArgs &a, int splits, hipStream_t st) {
 // 7.9 / 13.7 here.  K-splits: at least 24 k-steps each (1.5B QKV at 64 rows in 6 / 4 / 2 splits: 5.6 / 4.4 /
 // 5.2 us) and no more workgroups than compute units; two tiles per workgroup where that still leaves long ones.  Up to 128 rows are one
 // block; more are four of 64 or two of 128, whatever their number, so that a row's sums are added in one order in all such batches.
+// Of more than 64 tiles only three such splits fit beyond 128 rows, and long ones lose (us at 129 / 256 rows, workgroup-tiled -> this, with packing and
+// sum: 68 tiles of 512 k-steps 29.3 / 33.6 -> 28.0 / 31.3, 688 35.1 / 40.4 -> 35.4 / 39.2, 768 36.5 / 41.4 -> 37.8 / 41.6, 1280 50.1 / 56.8 -> 55.2 / 60.6; in four,
+// 64 tiles of 1792 k-steps 62.5 / 69.1 -> 61.0 / 67.6): more than 240 k-steps each go to the workgroup-tiled kernel.
 // Gate|up, which is not split, runs here in one round of one or two tiles per workgroup.  us, streaming -> this, 1 / 33 / 128 rows: 256 tiles of
 // 128 k-steps 16.8 / 18.6 / 23.6 -> 8.8 / 10.5 / 14.4, 512 of 128 18.7 / 20.6 / 25.2 -> 13.5 / 14.6 / 19.6, 384 of 192 24.0 / 26.6 / 33.7 -> 17.0 /
 // 18.2 / 25.2; 816 tiles, in two rounds of two, 21.7 / 25.4 / 29.8 -> 21.6 / 24.9 / 34.2.  Three tiles (up to 768) gain up to 64 rows and lose beyond: 560 of
@@ -217,6 +220,7 @@ hx_slice_plan hx_plan_slice(int n_tiles, int k_steps, int rows, int epilogue, in
     if ((n_tiles + 3) / 4 * HX_MAX_SPLITS * 5 > cus * 3) return p;
     p.tiles = partial && k_steps > 24 * HX_MAX_SPLITS ? 2 : 1;
     const int groups = (n_tiles + p.tiles - 1) / p.tiles * (rows <= 128 ? 1 : 4 / p.tiles);
+    if (partial && rows > 128 && cus / groups < 4 && k_steps > 240 * (cus / groups)) return hx_slice_plan{0, 1};
     if (partial) p.splits = std::max(1, std::min({max_splits, k_steps / 24, cus / groups}));
     return p;
 }

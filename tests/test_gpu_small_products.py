@@ -116,7 +116,8 @@ def test_a_row_comes_out_alike_in_every_batch_of_up_to_128(hx, tiles, hidden):
 
 # (tile, split) pairs that are no multiple of 8 (one workgroup in 8 of the last ones has nothing to do), one and two tiles per workgroup, an odd
 # last tile group; 1 pair, 7 (one tile of 168 k-steps), 68, 25 x 5, 31 x 4, 34 x 3
-@pytest.mark.parametrize("hidden,intermediate", [(32, 16), (32, 2688), (2176, 368), (1568, 3472), (1984, 3488), (2176, 3472)])
+# (the last two: 720 and 721 k-steps of 65 tiles, the step to the workgroup-tiled kernel)
+@pytest.mark.parametrize("hidden,intermediate", [(32, 16), (32, 2688), (2176, 368), (1568, 3472), (1984, 3488), (2176, 3472), (2080, 11520), (2080, 11536)])
 def test_row_blocks_of_pairs_that_do_not_fill_the_xcds(hx, hidden, intermediate):
     """Every number of row blocks: against float64 at 256 rows, and fewer rows are, bit for bit, the first of those."""
     s = synth.ModelShape("sp-xcd", 1, hidden, 1, 1, 64, intermediate, 64)
