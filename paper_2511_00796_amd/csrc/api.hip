@@ -553,7 +553,7 @@ static int launch_rows_product(const hx_engine *v0, const hx_matrix *w, int R, s
     const bool partial = epilogue == HX_EPI_PARTIAL;
     if (R == 1)
         return hx_launch_gemm(v0, w, 256, v0->ws + in_off, epilogue, partial ? (float *)(v0->ws + m.ypart) : nullptr, partial ? nullptr : v0->ws + m.mp,
-                              st, nullptr, part);
+                              st, nullptr, part, true);
     const hx_wide_plan plan = hx_plan_wide(w, R, epilogue);
     *part = hx_partials{plan.splits, (size_t)256 * w->N};
     return hx_launch_gemm_wide(v0, w, R, v0->ws, stride, in_off, epilogue, partial ? m.ypart : 0, partial ? 0 : m.mp, plan, st);

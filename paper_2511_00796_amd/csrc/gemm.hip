@@ -569,18 +569,19 @@ static gemm_launch plan_product(int n_tiles, int k_steps, int rows, int epilogue
 
 // Beyond 128 rows: the workgroup-tiled product of gemm_wide.hip, one block of 256 rows, those past the batch computed and never
 // read; its partials are 256 rows apart, so fewer splits fit the buffer of an engine for fewer rows.  Matrices of few columns
-// (slice.tiles > 0): gemm_slice.hip, unless a shape is forced.
+// (slice.tiles > 0): gemm_slice.hip, unless a shape is forced.  knobs: whether the environment has a say (a block of prompt rows plans its own).
 static bool wide_rows(int batch) { return batch > 128; }
 struct batch_plan { hx_wide_plan wide; hx_slice_plan slice; };
-static batch_plan plan_wide_batch(const hx_matrix *m, int epilogue, int max_batch) {
+static batch_plan plan_wide_batch(const hx_matrix *m, int epilogue, int max_batch, bool knobs) {
     const bool partial = epilogue == HX_EPI_PARTIAL;
-    const int max_s = partial ? splits_allowed(HX_MAX_SPLITS * max_batch / 256) : 1;
+    auto allowed = [&](int most) { return !partial ? 1 : knobs ? splits_allowed(most) : most; };
+    const int max_s = allowed(HX_MAX_SPLITS * max_batch / 256);
     batch_plan plan{hx_plan_wide(m, 1, epilogue, max_s), hx_slice_plan{0, 1}};
     int wn, wk, sp;                                      // forced: 4 to 8 tiles, no k-slices, no split without k-steps
-    if (forced_shape(&wn, &wk, &sp) && wk == 1 && wn >= 4 && wn <= 8 && sp <= max_s && (sp - 1) * hx_wide_split_steps(m, sp) < m->k_steps)
+    if (knobs && forced_shape(&wn, &wk, &sp) && wk == 1 && wn >= 4 && wn <= 8 && sp <= max_s && (sp - 1) * hx_wide_split_steps(m, sp) < m->k_steps)
         plan.wide = hx_wide_plan{wn, sp};
     else
-        plan.slice = hx_plan_slice(m->n_tiles, m->k_steps, 256, epilogue, partial ? splits_allowed(HX_MAX_SPLITS) : 1);
+        plan.slice = hx_plan_slice(m->n_tiles, m->k_steps, 256, epilogue, allowed(HX_MAX_SPLITS));
     return plan;
 }
 
@@ -592,7 +593,7 @@ extern "C" int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, 
     if (n_tiles < 1 || k_steps < 1 || batch < 1 || batch > 256) return hx_fail(HX_E_RANGE, "product %d x %d for batch %d", n_tiles, k_steps, batch);
     if (wide_rows(batch)) {
         const hx_matrix m{0, 16 * k_steps, 32 * n_tiles, k_steps, n_tiles};
-        const batch_plan plan = plan_wide_batch(&m, partial ? HX_EPI_PARTIAL : HX_EPI_SWIGLU, 256);
+        const batch_plan plan = plan_wide_batch(&m, partial ? HX_EPI_PARTIAL : HX_EPI_SWIGLU, 256, true);
         *wn_out = plan.slice.tiles ? 4 : plan.wide.wnt; *wk_out = 1; *splits_out = plan.slice.tiles ? plan.slice.splits : plan.wide.splits;
         return HX_OK;
     }
@@ -602,7 +603,7 @@ extern "C" int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, 
 }
 
 int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void *xp, int epilogue, float *y,
-                   void *mp_out, hipStream_t st, const hx_sample_params *sample, hx_partials *parts) {
+                   void *mp_out, hipStream_t st, const hx_sample_params *sample, hx_partials *parts, bool prompt_block) {
     if (epilogue == HX_EPI_SAMPLE && !sample) return hx_fail(HX_E_NULL, "sampling parameters missing");
     const int mg = hx_m_groups(batch);
     const bool partial = epilogue == HX_EPI_PARTIAL;
@@ -611,7 +612,7 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
                         sample ? sample->inv_temperature : 1.0f, sample ? sample->key0 : 0u, sample ? sample->key1 : 0u,
                         (float *)(e->ws + e->map.samp_z), (float *)(e->ws + e->map.samp_m), (float *)(e->ws + e->map.samp_s)};
     if (wide_rows(batch)) {
-        const batch_plan plan = plan_wide_batch(m, epilogue, e->cfg.max_batch);
+        const batch_plan plan = plan_wide_batch(m, epilogue, e->cfg.max_batch, !prompt_block);
         if (parts) *parts = plan.slice.tiles ? hx_partials{plan.slice.splits, (size_t)batch * m->N} : hx_partials{plan.wide.splits, (size_t)256 * m->N};
         if (plan.slice.tiles) return hx_launch_gemm_slice(e, m, batch, plan.slice, xp, epilogue, y, mp_out, lm, st);
         // The streaming kernel has one wavefront per SIMD with all rows' accumulators, and nothing beside its multiplications

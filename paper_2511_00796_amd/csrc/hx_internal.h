@@ -376,7 +376,8 @@ int hx_launch_nucleus(const hx_engine *e, int batch, const float *logits, const 
 struct hx_partials { int splits; size_t stride; };
 int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void *xp, int epilogue,
                    float *y /*partials or logits or NULL*/, void *mp_out, hipStream_t st,
-                   const hx_sample_params *sample = nullptr, hx_partials *parts = nullptr);
+                   const hx_sample_params *sample = nullptr, hx_partials *parts = nullptr,
+                   bool prompt_block = false /*256 prompt rows: the tuning knobs of a batch do not apply*/);
 // gemm_slice.hip: products of matrices with few columns
 struct hx_lm_args;
 struct hx_slice_plan { int tiles, splits; };     // 32-column tiles per workgroup (0: not this kernel), K-splits

@@ -265,3 +265,24 @@ def test_argument_errors_are_refused_on_the_host(hx):
     ws_odd = torch.empty(hx.prefill_workspace_bytes(eng_odd.cfg, 256), dtype=torch.uint8, device="cuda")
     with pytest.raises(hx.HexError):
         eng_odd.prefill_rows(kv_odd, z[:256], z[:256], z[:256], table[:256], ws_odd)
+
+
+@pytest.mark.parametrize("knob,value", [("HX_GEMM_MAX_SPLITS", "1"), ("HX_GEMM_SHAPE", "6,1,1")])
+@pytest.mark.parametrize("rows", [256, 512])
+def test_the_knobs_of_a_batch_do_not_change_prompt_rows(hx, rows, knob, value, monkeypatch):
+    """The products of one block, of few columns (K-splits) and of many, and of two blocks: the same bits under the tuning knobs of a
+    decode batch, which do change a batch of 256 rows."""
+    s = synth.ModelShape("knobs", 1, 2304, 18, 2, 128, 3072, 64)              # O and down 72 tiles, QKV 88; few columns: hidden 1536 below
+    few = synth.ModelShape("knobs-few", 1, 1536, 12, 2, 128, 3072, 64)
+    changed = False
+    for shape in (s, few):
+        eng = build(hx, shape, 5, 64)
+        ws = torch.empty(hx.prefill_workspace_bytes(eng.cfg, rows), dtype=torch.uint8, device="cuda")
+        for kind, K in ((hx.HX_T_WQKV, shape.hidden), (hx.HX_T_WO, shape.q_dim), (hx.HX_T_WG, shape.hidden), (hx.HX_T_WD, shape.intermediate)):
+            x = torch.randn(rows, K, device="cuda", generator=torch.Generator(device="cuda").manual_seed(kind))
+            plain, batch = eng.stage_linear_rows(kind, 0, x, ws), eng.stage_linear(kind, 0, x[:256].contiguous())
+            monkeypatch.setenv(knob, value)
+            assert torch.equal(eng.stage_linear_rows(kind, 0, x, ws), plain), (shape.name, kind)
+            changed |= not torch.equal(eng.stage_linear(kind, 0, x[:256].contiguous()), batch)
+            monkeypatch.delenv(knob)
+    assert changed
