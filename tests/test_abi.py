@@ -223,3 +223,19 @@ def test_packing_many_refuses_a_tensor_given_twice():
         assert lib.hx_weights_pack_many(engine, 0, None, 0, None, None, None, None) == binding.HX_E_NULL
     finally:
         lib.hx_engine_destroy(engine)
+
+
+@pytest.mark.parametrize("missing", ["_raw_stream", "_raw_device", "not set up"])
+def test_the_stream_falls_back_to_the_public_way(monkeypatch, missing):
+    """A torch without one of its unpromised functions, or whose GPU is not set up yet, is asked for the current stream."""
+    class Stream:
+        cuda_stream = 1234
+
+    monkeypatch.setattr(binding, "_raw_device", lambda: 3)
+    monkeypatch.setattr(binding, "_raw_stream", lambda device: 100 + device)
+    monkeypatch.setattr(binding.torch.cuda, "is_initialized", lambda: missing != "not set up")
+    monkeypatch.setattr(binding.torch.cuda, "current_stream", Stream)
+    if missing != "not set up":
+        assert binding._stream().value == 103
+        monkeypatch.setattr(binding, missing, None)
+    assert binding._stream().value == 1234
