@@ -280,18 +280,23 @@ int hx_attention_waves(const hx_engine *engine); /* wavefronts of the attention 
      HX_ATTN_WAVES=n        wavefronts of the attention kernel, read at hx_engine_create (default 8 per compute unit
                             of the device: 2048 on an MI355X)
      HX_GEMM_SHAPE=wn,wk,s  force tiles per workgroup, k-slices per workgroup and K-splits of the products of a batch: wn 4..6
-                            with wk = 1 or 4 with wk = 2 for up to 128 rows, wn 4..8 with wk = 1 beyond; a shape that does
+                            with wk = 1 or 4 with wk = 2 for up to 128 rows (the streaming product), wn 4..8 with wk = 1 beyond
+                            (the workgroup-tiled one), also where the product for few columns would run; a shape that does
                             not exist for a product is ignored for it.  prefill_rows plans its own
-     HX_GEMM_MAX_SPLITS=s   upper bound of the planner's K-splits for a batch (1..9)
+     HX_GEMM_MAX_SPLITS=s   upper bound of the planner's K-splits for a batch (1..9); not for prefill_rows
      HX_CHUNK_ATTENTION=0   prefill_chunk and prefill_rows attend every row on its own (the decode step's kernel)
                             instead of in groups of consecutive rows, read at hx_engine_create; for comparison */
 
 /* How the matrix product of n_tiles 32-column tiles and k_steps 16-row steps is launched for `batch` rows (host logic only,
    no GPU work): tiles per workgroup, k-slices per workgroup, and K-splits whose fp32 partial results the consumer kernel
-   adds (only if `partial` != 0; products with a fused epilogue are never split).  Up to 128 rows that is the streaming
-   product -- of a matrix of few columns (up to 68 tiles on 256 compute units) only the K-splits hold: its tiles go to single
-   workgroups, one or two each, unless HX_GEMM_SHAPE forces the streaming product --, beyond them the workgroup-tiled one of prefill_rows over one block of 256 rows, as an engine with max_batch 256
-   runs it (one for fewer rows may split less).  HX_E_RANGE for sizes < 1 or batch > 256, HX_E_NULL for NULL outputs. */
+   adds (only if `partial` != 0; products with a fused epilogue -- the answer is gate|up's -- are never split).  One of three products:
+     few columns   1 or 2 tiles, 4 k-slices (every fourth step each).  On 256 compute units matrices of up to 68 tiles at any number of
+                   rows (but for three splits of more than 240 k-steps beyond 128 rows), and gate|up of up to 512 tiles up to 128 rows;
+     streaming     4 to 6 tiles, 10 where the product is not split, 1 k-slice: the others up to 128 rows;
+     workgroup-tiled, the one of prefill_rows over one block of 256 rows   4 to 8 tiles, 1 k-slice: the others beyond, as an engine with
+                   max_batch 256 runs it (one for fewer rows may split less).
+   Up to 128 rows the plan does not depend on `batch`: a row's products are added in one order in all such batches (the LM head's and
+   gate|up's, too), and in one order in all larger ones.  HX_E_RANGE for sizes < 1 or batch > 256, HX_E_NULL for NULL outputs. */
 int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, int32_t partial, int32_t *tiles_per_workgroup_out,
                     int32_t *k_slices_out, int32_t *splits_out);
 
@@ -339,7 +344,8 @@ int hx_stage_rmsnorm(hx_engine *engine, int gain_kind, int layer, int32_t batch,
 int hx_stage_linear(hx_engine *engine, int matrix_kind, int layer, int32_t batch, const float *x_dev,
                     float *y_dev, int32_t *argmax_out_dev, void *stream);
 
-/* The same products as prefill_rows runs them (workgroup-tiled, all rows of the call at once): matrix_kind HX_T_WQKV,
+/* The same products as prefill_rows runs them (workgroup-tiled, all rows of the call at once; a call of 256 rows as a batch of that
+   many, matrices of few columns by their own product): matrix_kind HX_T_WQKV,
    HX_T_WO, HX_T_WG or HX_T_WD as above, n_rows a multiple of 256 up to HX_PREFILL_MAX_ROWS, x_dev fp32 [n_rows, in],
    y_dev fp32 [n_rows, out]; engine, workspace_dev and errors as prefill_rows. */
 int hx_stage_linear_rows(hx_engine *engine, int matrix_kind, int layer, int32_t n_rows, const float *x_dev,

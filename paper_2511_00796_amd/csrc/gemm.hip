@@ -594,11 +594,12 @@ extern "C" int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, 
     if (wide_rows(batch)) {
         const hx_matrix m{0, 16 * k_steps, 32 * n_tiles, k_steps, n_tiles};
         const batch_plan plan = plan_wide_batch(&m, partial ? HX_EPI_PARTIAL : HX_EPI_SWIGLU, 256, true);
-        *wn_out = plan.slice.tiles ? 4 : plan.wide.wnt; *wk_out = 1; *splits_out = plan.slice.tiles ? plan.slice.splits : plan.wide.splits;
+        if (plan.slice.tiles) { *wn_out = plan.slice.tiles; *wk_out = HX_FEW_COLUMN_SLICES; *splits_out = plan.slice.splits; }
+        else { *wn_out = plan.wide.wnt; *wk_out = 1; *splits_out = plan.wide.splits; }
         return HX_OK;
     }
     const gemm_launch plan = plan_product(n_tiles, k_steps, batch, partial ? HX_EPI_PARTIAL : HX_EPI_SWIGLU);
-    *wn_out = plan.wn; *wk_out = plan.wk; *splits_out = plan.splits;
+    *wn_out = plan.slice_tiles ? plan.slice_tiles : plan.wn; *wk_out = plan.slice_tiles ? HX_FEW_COLUMN_SLICES : plan.wk; *splits_out = plan.splits;
     return HX_OK;
 }
 
