@@ -17,17 +17,17 @@ def hx():
     return binding
 
 
-@pytest.mark.parametrize("waves", [1, 7, 2048])          # one run over everything; runs of a few tiles; every tile a run of its own
+@pytest.mark.parametrize("waves", [64, 500, 2048])       # runs of 13 to 37 tiles; of 2 to 5; every tile, or two, a run of its own
 @pytest.mark.parametrize("cache", ["bf16", "fp8"])
 @pytest.mark.parametrize("heads", [(8, 2, 128), (4, 1, 64)], ids=["8-2-128", "4-1-64"])
-@pytest.mark.parametrize("lens", [[0, 0, 37, 0, 250, 16], [33, 0, 900, 0, 0]], ids=["first", "last"])
+@pytest.mark.parametrize("lens", [[0, 0, 3700, 0, 2500, 16], [33, 0, 9000, 9700, 0, 0]], ids=["first", "last"])
 def test_the_other_rows_of_a_decode_batch(hx, lens, heads, cache, waves, monkeypatch):
     """The first pairs of a batch empty, some between, and the last ones: the runs of tiles are the same as without them, and so is
     every bit of the others' attention."""
     n_q, n_kv, d = heads
     s = synth.ModelShape("empty", 1, 256, n_q, n_kv, d, 704, 1024)
     monkeypatch.setenv("HX_ATTN_WAVES", str(waves))
-    eng = build(hx, s, 3, len(lens), 1024, hx.HX_KV_FP8_E4M3 if cache == "fp8" else hx.HX_KV_BF16)
+    eng = build(hx, s, 3, len(lens), 16384, hx.HX_KV_FP8_E4M3 if cache == "fp8" else hx.HX_KV_BF16)
     lens = np.array(lens, dtype=np.int32)
     table, nb = synth.block_table(np.maximum(lens, 1), s.block_size, 3)
     kv = hx.KVCache(eng, nb)
@@ -49,8 +49,8 @@ def test_a_batch_of_nothing_but_empty_rows_ends(hx):
     torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("waves", [4, 64])               # one workgroup and sixteen: more items than that, so that groups are ordered
-@pytest.mark.parametrize("heads", [(8, 2, 128), (4, 1, 64)], ids=["8-2-128", "4-1-64"])
+@pytest.mark.parametrize("waves", [64, 2048])            # 16 workgroups, fewer than items, so that the groups are ordered; 512
+@pytest.mark.parametrize("heads", [(8, 2, 128), (8, 4, 64)], ids=["8-2-128", "8-4-64"])
 def test_the_other_rows_of_a_prompt_call(hx, heads, waves, monkeypatch):
     """Rows without keys as groups of their own (first, last, several in a row) and in front of the first row of a sequence, which
     then counts as its continuation."""

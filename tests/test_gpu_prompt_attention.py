@@ -92,25 +92,71 @@ def test_prompt_attention_equals_row_at_a_time(hx, name, cache, waves, monkeypat
     assert diff <= 2e-5 * scale
 
 
-@pytest.mark.parametrize("d,plan", [(128, [(700, 40), (1300, 1)]), (64, [(900, 70), (333, 2)])], ids=["128", "64"])
+def scale_moves(s, plan, cache, steepness, parts, seed=31):
+    """Host copy of layer 0's scores over the cached keys, 32 at a time, in that many parts per pair: -> (moves of a column's scale after its first
+    step, rises of a maximum that leave it, per column; largest sum of magnitudes behind a score, in powers of two)."""
+    w, glob = synth.layer_weights(s, 0, seed), synth.global_weights(s, seed)
+    n = sum(m for _, m in plan)
+    toks = np.random.default_rng(seed).integers(0, s.vocab, size=n)
+    x = glob["embed"].float()[torch.from_numpy(toks)]
+    x = x * torch.rsqrt((x * x).mean(-1, keepdim=True) + s.rms_eps) * w["g1"].float()
+    D, half = s.head_dim, s.head_dim // 2
+    q = (x @ w["wqkv"].float() + w["bqkv"].float())[:, :s.q_dim].view(n, s.n_q_heads, D)
+    pos = torch.cat([torch.arange(c, c + m) for c, m in plan]).float()
+    ang = pos[:, None, None] * s.rope_theta ** (-torch.arange(half) / half)
+    q = torch.cat([q[..., :half] * ang.cos() - q[..., half:] * ang.sin(), q[..., half:] * ang.cos() + q[..., :half] * ang.sin()], -1)
+    total = sum(c for c, _ in plan)
+    k = rising_keys(synth.kv_fill(s, 0, total, seed, device="cuda")[0], steepness).cpu().float()
+    k = k.clamp(-448, 448).to(torch.float8_e4m3fn).float() if cache == "fp8" else k
+    moves, rises, largest, r0, t0 = [], [], 0.0, 0, 0
+    for c, m in plan:
+        kb = k[t0:t0 + c].repeat_interleave(s.group, 1)                              # the KV head of every query head
+        qb = q[r0:r0 + m] * (1.4426950408889634 / D ** 0.5)
+        sc = torch.einsum("rhd,thd->rht", qb, kb)
+        largest = max(largest, float(torch.einsum("rhd,thd->rht", qb.abs(), kb.abs()).max()))
+        mx = sc[..., :c // 32 * 32].view(m, s.n_q_heads, -1, 32).amax(-1)
+        mv, rs = torch.zeros(m, s.n_q_heads), torch.zeros(m, s.n_q_heads)
+        for i in range(mx.shape[-1]):
+            if i % -(-mx.shape[-1] // parts) == 0:
+                scale = top = mx[..., i]
+            go = mx[..., i] > scale + 8
+            mv += go
+            rs += (mx[..., i] > top) & ~go
+            scale = torch.where(go, mx[..., i], scale)
+            top = torch.maximum(top, mx[..., i])
+        moves.append(mv.flatten())
+        rises.append(rs.flatten())
+        r0, t0 = r0 + m, t0 + c
+    return torch.cat(moves), torch.cat(rises), largest
+
+
+def rising_keys(k, steepness):
+    ramp = torch.linspace(0.02, 1.0, k.shape[0], device=k.device) * steepness
+    return (k.float() * ramp.view(-1, *[1] * (k.dim() - 1))).to(k.dtype)
+
+
+@pytest.mark.parametrize("d,plan", [(128, [(4000, 40), (3000, 1)]), (64, [(4000, 70), (2500, 2)])], ids=["128", "64"])
 @pytest.mark.parametrize("cache", ["bf16", "fp8"])
-@pytest.mark.parametrize("steepness", [1.0, 4.0, 16.0])
-def test_scores_that_rise_along_the_keys(hx, d, plan, cache, steepness, monkeypatch):
+@pytest.mark.parametrize("waves,parts", [(64, 2), (2048, 16)])       # pairs in at most two parts; in parts of the shortest length, 8 steps
+@pytest.mark.parametrize("steepness", [16.0, 50.0, 200.0])
+def test_scores_that_rise_along_the_keys(hx, d, plan, cache, waves, parts, steepness, monkeypatch):
     """A column's scale is moved only when its maximum is 2^8 past it: keys that grow along the sequence make maxima rise by less
-    than that, by about that and by more, over and over."""
+    than that, by about that and by more, over and over within a part (counted on the host)."""
+    s = synth.ModelShape("prompt-attn", 2, 256, 8, 2, d, 704, 1024)
+    moves, rises, largest = scale_moves(s, plan, cache, steepness, parts)
+    print("moves per column %d..%d (median %d), rises without one: median %d" % (moves.min(), moves.max(), moves.median(), rises.median()))
+    assert moves.median() >= {16.0: 0, 50.0: 3, 200.0: 8}[steepness] and moves.max() >= 2 and rises.median() >= 4
     fill = synth.kv_fill
 
     def rising(*args, **kwargs):
         k, v = fill(*args, **kwargs)
-        ramp = torch.linspace(0.05, 1.0, k.shape[0], device=k.device) * steepness
-        return (k.float() * ramp.view(-1, *[1] * (k.dim() - 1))).to(k.dtype), v
+        return rising_keys(k, steepness), v
 
     monkeypatch.setattr(synth, "kv_fill", rising)
-    s = synth.ModelShape("prompt-attn", 2, 256, 8, 2, d, 704, 1024)
-    rowwise, grouped = layer0_attention(hx, s, plan, hx.HX_KV_FP8_E4M3 if cache == "fp8" else hx.HX_KV_BF16, 0, monkeypatch)
+    rowwise, grouped = layer0_attention(hx, s, plan, hx.HX_KV_FP8_E4M3 if cache == "fp8" else hx.HX_KV_BF16, waves, monkeypatch)
     assert np.isfinite(grouped).all()
     scale = max(float(np.abs(rowwise).max()), 1.0)
     diff = float(np.abs(grouped - rowwise).max())
-    print("%s %d x %g: max |grouped - row-wise| %.2e (max |o| %.2f)" % (cache, d, steepness, diff, scale))
-    # as above, and scores of up to about 8 steepness (in powers of two) that are sums in another order: 2^-20 of that at most
-    assert diff <= (2e-5 + 8 * steepness * 2.0 ** -20) * scale
+    print("%s %d x %g: max |grouped - row-wise| %.2e (max |o| %.2f, scores' magnitudes up to %.0f)" % (cache, d, steepness, diff, scale, largest))
+    # as above, and scores (in powers of two) that are fp32 sums in two orders: 2^-23 of the largest sum of magnitudes
+    assert diff <= (2e-5 + largest * 2.0 ** -23) * scale

@@ -162,3 +162,23 @@ def test_blocks_with_groups_that_hold_no_rows(hx, hidden, k_steps, batch, tiles,
     ref = gate * torch.sigmoid(gate) * (u.double() @ w["wu"])
     # one bf16 rounding of the result and the fp32 sums' own error
     assert m.shape == ref.shape and ((m.double() - ref).abs() <= ref.abs() * 2.0 ** -7 + 1e-5).all()
+
+
+@pytest.mark.parametrize("k_steps,splits", [(1, 1), (2, 1), (65, 1), (66, 1), (131, 1), (216, 1), (65, 2), (66, 2), (131, 2), (216, 2)])
+def test_both_matrix_instructions_give_the_same_bits(hx, k_steps, splits, monkeypatch):
+    """Six and more tiles per workgroup add a row's products with 16x16x32 instructions, fewer with 32x32x16: the same sums, bit for
+    bit, with one and two splits (the second behind an odd last k-step too), of values of very different sizes, and gate|up of them."""
+    s = synth.ModelShape("wb-bits", 1, 416, 2, 1, 64, 16 * k_steps, 64)
+    eng = build(hx, s, 5, 256, 64)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randn(256, s.intermediate, generator=g, device="cuda") * torch.exp(3 * torch.randn(256, s.intermediate, generator=g, device="cuda"))
+    u = torch.randn(256, s.hidden, generator=g, device="cuda") * torch.exp(torch.randn(256, s.hidden, generator=g, device="cuda"))
+    out = []
+    for tiles in (4, 5, 6, 7, 8):
+        monkeypatch.setenv("HX_GEMM_SHAPE", "%d,1,%d" % (tiles, splits))
+        eng.workspace.fill_(0xFF)
+        y = eng.stage_linear(hx.HX_T_WD, 0, x)
+        monkeypatch.setenv("HX_GEMM_SHAPE", "%d,1,1" % tiles)
+        out.append((y, eng.stage_linear(hx.HX_T_WG, 0, u)))
+    for y, m in out[1:]:
+        assert torch.equal(y, out[0][0]) and torch.equal(m, out[0][1])
