@@ -446,7 +446,8 @@ __global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK, gemm_ring<MG, WN, 
         const hx_lm_args lm{a_y, a_M, a_N, a_n_tiles, a_amax_val, a_amax_idx, a_positions, a_row_ids, a_inv_t, a_key0, a_key1,
                             a_samp_z, a_samp_m, a_samp_s};
         // one copy of the tile's code, the accumulators moved up behind it (unrolled it spills and leaves the instruction
-        // cache; the last is cleared, or it would stay live); m-groups that only pad the batch are left out
+        // cache; the last is cleared, or it would stay live; a drawn head's lane number is taken anew: kept, it was one register too many for two
+        // workgroups, and went to scratch memory); m-groups that only pad the batch are left out
 #pragma unroll 1
         for (int g = 0; g < MG && 32 * g < a_M; ++g) {
             const f32x16_t now = acc[0];
@@ -455,7 +456,7 @@ __global__ __launch_bounds__(64 * (WN * WK + GemmGeom<MG, WK, gemm_ring<MG, WN, 
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[MG - 1][r] = 0.f;
             if (EPI == HX_EPI_LOGITS) hx_lm_greedy_tile(lm, now, 32 * g + ml, nt, lane);
-            else                      hx_lm_sample_tile<(MG <= 2)>(lm, now, 32 * g + ml, nt, lane);
+            else                      hx_lm_sample_tile<(MG <= 2)>(lm, now, 32 * g + (int)(__lane_id() & 31), nt, lane);
         }
     }
 }

@@ -145,3 +145,10 @@ def test_kernels_that_copy_straight_into_lds_have_only_the_dynamic_array(source,
     assert len(copying) >= 4
     for kernel in copying:
         assert static[kernel] == 0, (kernel, static[kernel])
+
+
+@pytest.mark.parametrize("source", [s for s in hxbuild.SOURCES if s != "api.hip"])
+def test_no_kernel_keeps_registers_in_scratch_memory(source, tmp_path):
+    """Scratch memory is the runtime's own allocation, and a step allocates nothing."""
+    used = re.findall(r"\.private_segment_fixed_size:\s*(\d+)", assembly(source, tmp_path))
+    assert used and all(u == "0" for u in used), used
