@@ -23,8 +23,8 @@ HBM_PEAK_GBS = 8000.0     # MI355X published HBM3E bandwidth
 # HBM bytes per attention launch at workload 7b-b128 from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled by a plain
 # copy (profiles/attn_splitk_7b-b128_hbm_traffic.txt).  Valid only for the kernel source they were taken with.
 PMC_TRAFFIC = {"workload": "7b-b128",
-               "attention_hip_sha256": "47dccd36c3b628d45a6cddd0cdbe57df33f929c6bd21b2df08d1af2e94237223",
-               "fetch_bytes": 2150.25e6, "write_bytes": 9.45e6}
+               "attention_hip_sha256": "1cbd85564030c67b02ff50ebfb09cdef7d352491f7ef5d00dae00edb4da54812",
+               "fetch_bytes": 2150.36e6, "write_bytes": 9.45e6}
 
 
 def measured_traffic(workload_name):

@@ -7,7 +7,8 @@
 // and from there on the arithmetic is the bf16 kernel's, tile by tile.  The ring holds the raw bytes of two tiles, 8 KiB per
 // wavefront and 64 KiB per compute unit, as in the bf16 kernel (why: there).  What bounds it is the memory system: us per launch
 // with rings of 2 / 3 / 4 tiles, 7B, 128 sequences 182 = 5.9 TB/s / 187 / 188, 14B, 64 of them 174 / 177 / 178, 1.5B, 256 of them 84 / 88 / 90,
-// 7B, 3 long ones 13.7 / 15.4 / 17.0; the loads of the first without any arithmetic 178.  Two tiles at a time, with one maximum and one
+// 7B, 3 long ones 13.7 / 15.4 / 17.0.  The loads alone, in the same order and without any arithmetic, take as long (64 / 128 / 256 sequences of 7B 92 / 184 / 368
+// with it, 91 / 186 to 191 / 371 without): 6.4 TB/s and 9 us that do not grow; the bf16 kernel's larger tiles 6.65 and 6.  Two tiles at a time, with one maximum and one
 // rescaling for both, took 180 / 171 / 82 / 14.4, but left the result further from exact: 1.84e-6 instead of 1.79e-6 at 9 001 tokens.
 #include "hx_internal.h"
 

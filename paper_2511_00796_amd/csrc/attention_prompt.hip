@@ -24,8 +24,8 @@
 // run from the last group to the first, and every second round of the workgroups takes its items in reverse: who had a long part
 // gets a short one.  (In the order of the rows, every round alike, one of 512 workgroups had up to 50 steps of a 2048-token
 // prompt where the mean is 29.)  us per layer, the order of the rows | this | and the lazy scale of the columns: 7B, 2048 rows
-// 83 | 75 | 70.5, 14B, 8-bit cache, 4864 rows of 7 prompts 118 | 97 | 93; the schedule, once for all layers, 11 -> 13 and
-// 13.5 -> 18.
+// 83 | 75 | 70.5, 14B, 8-bit cache, 4864 rows of 7 prompts 118 | 97 | 93 (the first and the last again, in one 7B call and in turn: 82 | 67); the schedule, once
+// for all layers, 11 -> 13 and 13.5 -> 18.
 //
 // Per-group arrays live where the 256-row workspaces keep their per-row ones: entry g in block g / 256 at g % 256.
 #include "hx_internal.h"
@@ -427,8 +427,8 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_kernel(PromptArgs a, const
 #pragma unroll
             for (int r = 1; r < 16; ++r) mx = fmaxf(mx, p[r]);
             mx = fmaxf(mx, __shfl_xor(mx, 32));
-            // The scale of a column follows its maximum only once that is 2^8 past it: p, l and o are then at most 2^8 times larger
-            // and as exact (both halves of p and the sums are relative to their size).  Of 32 columns some maximum moves in most
+            // The scale of a column follows its maximum only once that is 2^8 past it (the conditional rescaling of the online softmax that
+            // FlashAttention-4 made known, T. Dao et al., 2025): p, l and o are then at most 2^8 times larger and as exact (both halves of p and the sums are relative to their size).  Of 32 columns some maximum moves in most
             // steps, and every time cost the wavefront 64 multiplications (7B, 2048 rows: 75 -> 70.5 us per layer).
             const float mxs = mx * scale_log2e, m_new = mxs > m + 8.f ? mxs : m;
 #pragma unroll

@@ -14,13 +14,16 @@
 // chunks ahead into a ring of three stages (five ahead into six: wide_stages); one barrier per chunk, passed BEFORE the chunk's last k-step is multiplied,
 // so that the first operand reads of the next chunk hide behind those products, as the reads of its second k-step (16x16x32: of the
 // second half of the longer operand) hide behind the first.  Reads, copies and products are laid out by hand in groups (sched_barrier).
-// What bounds it is the matrix cores' power, and 16x16x32 products need less of it than 32x32x16 ones: with random operands a
-// loop out of registers reaches 2 080 TFLOP/s with the former and 1 810 with the latter, on one card.  A chunk of two k-steps is one
-// 16x16x32 product's k, and its operands are read from the same stages (lane l: row l % 16 of a half group, k octet l / 16), so
+// What bounds it: the LDS path (operand reads and the copies that fill the stages) and the matrix cores, which cover each other only in
+// part, and a last round that is paid whole (7B gate|up over 2048 rows 4.6 rounds, 14B over 4864 8.02).  us as it runs | without products | with
+// copies for the first stages only | without output stores, each side with random operands: 7B, 2048 rows gate|up 449 | 307 | 428 | 409; 14B, 4864 rows gate|up
+// 1053 | 816 | 953 | 990, down 499 | 417 | 434 | 456, QKV 306 | 275 | 264 | 280.  The same instructions out of registers would take 267, 662, 331 and 168
+// (2 080 TFLOP/s; with 32x32x16 ones 1 810, on one card, which is why this kernel has the former): the reads alone take longer than that.
+// A chunk of two k-steps is one 16x16x32 product's k, and its operands are read from the same stages (lane l: row l % 16 of a half group, k octet l / 16), so
 // the layouts stay; the sums come out the same, bit for bit.  Six and more tiles per workgroup use them, us, 32x32x16 -> 16x16x32 in turn:
 // 7B, 2048 rows gate|up 453 -> 422 (1.28 PFLOP/s), down 227 -> 215, O 52.3 -> 49.4; 14B, 4864 rows gate|up 1146 -> 1096, down 551 -> 501
-// (1.38), QKV 322 -> 305.  Narrower tiles wait for memory and keep 32x32x16 (1.5B gate|up 25.5 | 26.5 at 256 rows, 63.5 | 65.5 at 1024),
-// and so does the LM head, whose epilogue is written for that accumulator.
+// (1.38), QKV 322 -> 305.  Narrower tiles keep 32x32x16: most of them wait for memory (32x32x16 | 16x16x32: 1.5B gate|up 25.5 | 26.5 at 256 rows,
+// 63.5 | 65.5 at 1024), but 7B QKV over 2048 rows, in five, does not (66.6 | 63.5).  The LM head, whose epilogue is written for that accumulator, has it, too.
 // Four wavefronts of 128 x 128, one per SIMD, move a quarter less through LDS and are slower (575 against 437 in one session).
 
 // Workgroup numbering: consecutive workgroup ids go to different XCDs, so XCD x takes the x-th eighth of the work, row
@@ -427,19 +430,19 @@ int launch_wide_epi(int epilogue, dim3 grid, hipStream_t st, const WideArgs &a) 
 }  // namespace
 
 // Tiles per workgroup and, for a product whose consumer sums partials, K-splits: the plan with the least time by a
-// model in microseconds, fitted to 7B and 14B products (224 to 1184 k-steps, 8 and 19 row blocks; it is within 8 % of
-// nearly all of 22 plans measured, and picks one within 2 % of the best of each product).  A 256 x 32 tile takes 46 ns
+// model in microseconds, fitted to 7B and 14B products (224 to 1184 k-steps, 8 and 19 row blocks) when all of them were 32x32x16.  Of the
+// present kernels, every plan of 4 to 8 tiles in 1 to 4 splits measured, it still takes the best or one within 3 % (14B O over 4864 rows 224 us, in two splits
+// of 8 tiles 207 and the sum of a second split).  A 256 x 32 tile takes 46 ns
 // per k-step on a compute unit when at most two thirds of them are busy and 52 when all are (the chip lowers its clock);
 // a workgroup's start and end 8 per round, the launch 4; partial sums are written at 4.7 TB/s and the further ones
 // read again at 10.  Narrow tiles read more operands per product.  The last round of many is only charged half.
-// Measured (us): 7B, 2048 rows: QKV 76 with 5 tiles and no split (6 tiles in 4 splits: 99, and 9 more in the consumer
-// that sums them), O + down 295 with 7 tiles in 2 splits (8 in 2: 317).  14B, 4864 rows: QKV 351 with 6 (7: 373, 8: 399,
-// 5: 397), O + down 885 with 7 (8: 951, 8 in 2 splits: 1007), gate|up 1160 with 8 (7: 1199, 6: 1193, 5: 1300).
-// One block of 256 rows (us; in brackets the streaming kernel of gemm.hip, which it replaces beyond 128 rows): 1.5B QKV 14.8
-// (17.4), O 14.8 (16.1), gate|up 27.6 (32.2), down 21.1 (25.3); 7B 20.4 (21.1), 18.4 (19.5), 78.4 (88.6), 46.7 (50.2);
-// 14B 31.2 (32.9), 25.7 (27.3), 90.9 (89.7), 46.6 (51.5).  The same two in turn on one card, with the packing of the input and the
-// sum of the partials, at 129, 192 and 256 rows: 14B gate|up 95.9, 99.5, 102.2 (98.8, 100.2, 105.5), all other products of the three
-// models 3 to 24 % faster; behind by 1 us (17.2 against 16.1) is only the 43-k-step down product of a hidden size of 256.
+// Measured, the plan taken (others), us: 7B, 2048 rows: QKV 67 with 5 tiles (6: 72, 7 in 3 splits: 73), down 213 with 7 in 2 (8 in 2: 207, 4: 237), O 50 with 7
+// in 2 (8 in 2: 49, 4: 51), gate|up 423 to 504 with 8 as the clock has it (7: 483, 4: 482, 5: 518).  14B, 4864 rows: QKV 309 with 6 (8 in 2: 315, 7: 327), down
+// 501 with 8 in 2 (7: 559), gate|up 1073 with 8 (6: 1154, 7: 1177, 5: 1244).  1.5B, 2048 rows: gate|up 108 with 6 (4: 109, 8: 119), down 53 with 6 in 4 (7 in 4: 56).
+// One block of 256 rows, products that no other kernel takes (us; in brackets the streaming kernel of gemm.hip, which it replaces beyond 128 rows): 1.5B
+// gate|up 27.6 (32.2); 7B QKV 20.4 (21.1), O 18.4 (19.5), gate|up 78.4 (88.6), down 46.7 (50.2); 14B 31.2 (32.9), 25.7 (27.3), 90.9 (89.7), 46.6 (51.5).
+// The same two in turn on one card, with the packing of the input and the sum of the partials, at 129, 192 and 256 rows: 14B gate|up 95.9, 99.5, 102.2
+// (98.8, 100.2, 105.5), the others 3 to 24 % faster.
 int hx_wide_split_steps(const hx_matrix *m, int splits) { return ((m->k_steps + splits - 1) / splits + 1) & ~1; }
 
 hx_wide_plan hx_plan_wide(const hx_matrix *m, int row_blocks, int epilogue, int max_splits) {
