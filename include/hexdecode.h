@@ -290,13 +290,14 @@ int hx_attention_waves(const hx_engine *engine); /* wavefronts of the attention 
 /* How the matrix product of n_tiles 32-column tiles and k_steps 16-row steps is launched for `batch` rows (host logic only,
    no GPU work): tiles per workgroup, k-slices per workgroup, and K-splits whose fp32 partial results the consumer kernel
    adds (only if `partial` != 0; products with a fused epilogue -- the answer is gate|up's -- are never split).  One of three products:
-     few columns   1 or 2 tiles, 4 k-slices (every fourth step each).  On 256 compute units matrices of up to 68 tiles at any number of
-                   rows (but for three splits of more than 240 k-steps beyond 128 rows), and gate|up of up to 512 tiles up to 128 rows;
-     streaming     4 to 6 tiles, 10 where the product is not split, 1 k-slice: the others up to 128 rows;
-     workgroup-tiled, the one of prefill_rows over one block of 256 rows   4 to 8 tiles, 1 k-slice: the others beyond, as an engine with
-                   max_batch 256 runs it (one for fewer rows may split less).
+     streaming     up to 128 rows: 4 to 6 tiles, 10 where the product is not split, 1 k-slice;
+     workgroup-tiled, the one of prefill_rows over one block of 256 rows   beyond: 4 to 8 tiles, 1 k-slice, as an engine with max_batch 256
+                   runs it (one for fewer rows may split less);
+     few columns   of the answer (4 tiles, 1 k-slice) only the K-splits hold: a workgroup has 1 or 2 tiles, and four wavefronts that take
+                   every fourth step.  On 256 compute units matrices of up to 68 tiles at any number of rows (but for three splits of more
+                   than 240 k-steps beyond 128 rows), and gate|up of up to 512 tiles up to 128 rows, unless HX_GEMM_SHAPE forces another.
    Up to 128 rows the plan does not depend on `batch`: a row's products are added in one order in all such batches (the LM head's and
-   gate|up's, too), and in one order in all larger ones.  HX_E_RANGE for sizes < 1 or batch > 256, HX_E_NULL for NULL outputs. */
+   gate|up's, too), and one engine adds them in one order in all larger ones.  HX_E_RANGE for sizes < 1 or batch > 256, HX_E_NULL for NULL outputs. */
 int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, int32_t partial, int32_t *tiles_per_workgroup_out,
                     int32_t *k_slices_out, int32_t *splits_out);
 

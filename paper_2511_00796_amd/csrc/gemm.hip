@@ -587,7 +587,7 @@ static batch_plan plan_wide_batch(const hx_matrix *m, int epilogue, int max_batc
 }
 
 // The plan of one product, for inspection: tiles per workgroup, k-slices per workgroup, K-splits.  Beyond 128 rows as an
-// engine for 256 rows runs it.
+// engine for 256 rows runs it; of few columns only the splits are the plan's.
 extern "C" int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, int32_t partial, int32_t *wn_out,
                                int32_t *wk_out, int32_t *splits_out) {
     if (!wn_out || !wk_out || !splits_out) return hx_fail(HX_E_NULL, "an output pointer is NULL");
@@ -595,12 +595,11 @@ extern "C" int hx_plan_product(int32_t n_tiles, int32_t k_steps, int32_t batch, 
     if (wide_rows(batch)) {
         const hx_matrix m{0, 16 * k_steps, 32 * n_tiles, k_steps, n_tiles};
         const batch_plan plan = plan_wide_batch(&m, partial ? HX_EPI_PARTIAL : HX_EPI_SWIGLU, 256, true);
-        if (plan.slice.tiles) { *wn_out = plan.slice.tiles; *wk_out = HX_FEW_COLUMN_SLICES; *splits_out = plan.slice.splits; }
-        else { *wn_out = plan.wide.wnt; *wk_out = 1; *splits_out = plan.wide.splits; }
+        *wn_out = plan.slice.tiles ? 4 : plan.wide.wnt; *wk_out = 1; *splits_out = plan.slice.tiles ? plan.slice.splits : plan.wide.splits;
         return HX_OK;
     }
     const gemm_launch plan = plan_product(n_tiles, k_steps, batch, partial ? HX_EPI_PARTIAL : HX_EPI_SWIGLU);
-    *wn_out = plan.slice_tiles ? plan.slice_tiles : plan.wn; *wk_out = plan.slice_tiles ? HX_FEW_COLUMN_SLICES : plan.wk; *splits_out = plan.splits;
+    *wn_out = plan.wn; *wk_out = plan.wk; *splits_out = plan.splits;
     return HX_OK;
 }
 

@@ -25,7 +25,7 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
 namespace {
 
-constexpr int SLICES = HX_FEW_COLUMN_SLICES;
+constexpr int SLICES = 4;         // wavefronts of a workgroup
 
 // TN tiles per workgroup, MG of XG m-groups, R k-steps in flight per wavefront
 template <int MG, int XG, int TN, int R, int EPI>

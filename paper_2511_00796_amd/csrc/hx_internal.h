@@ -379,7 +379,6 @@ int hx_launch_gemm(const hx_engine *e, const hx_matrix *m, int batch, const void
                    const hx_sample_params *sample = nullptr, hx_partials *parts = nullptr,
                    bool prompt_block = false /*256 prompt rows: the tuning knobs of a batch do not apply*/);
 // gemm_slice.hip: products of matrices with few columns
-#define HX_FEW_COLUMN_SLICES 4                   // wavefronts of a workgroup, each with every fourth k-step
 struct hx_lm_args;
 struct hx_slice_plan { int tiles, splits; };     // 32-column tiles per workgroup (0: not this kernel), K-splits
 hx_slice_plan hx_plan_slice(int n_tiles, int k_steps, int rows, int epilogue, int max_splits);

@@ -109,8 +109,8 @@ def test_engine_create_validates_buffers_on_the_host():
 
 def test_product_plans_fill_the_chip_and_respect_their_limits(monkeypatch):
     """Host-side launch planner: every plan keeps at least 16 k-steps per split, never splits a product whose epilogue
-    needs the whole sum, stays within 9 splits and 4..6 tiles per workgroup (10 only for unsplit products; 4..8 beyond 128 rows; of few
-    columns 1 or 2, in four k-slices), and for the 7B shapes picks the plans the design rests on (gate|up: 237 workgroups of 5 = one round on 256 compute
+    needs the whole sum, stays within 9 splits and 4..6 tiles per workgroup (10 only for unsplit products; 4..8 beyond 128 rows),
+    and for the 7B shapes picks the plans the design rests on (gate|up: 237 workgroups of 5 = one round on 256 compute
     units; O and QKV: 7 splits of exactly two revolutions of 16 k-steps, the planner's unit; down: 9 splits; LM head: two rounds of 10 tiles)."""
     lib = binding.load()
 
@@ -124,22 +124,19 @@ def test_product_plans_fill_the_chip_and_respect_their_limits(monkeypatch):
                               (s.intermediate, s.hidden, True), (s.hidden, s.vocab, False)):
             for batch in (1, 4, 64, 128, 256):
                 wn, wk, sp = plan((N + 31) // 32, K // 16, batch, partial)
-                if wk == 4:                             # the product for few columns
-                    assert wn in (1, 2) and 1 <= sp <= 9 and ((N + 31) // 32 <= 68 or (not partial and N <= 32 * 512 and batch <= 128))
-                elif batch <= 128:
+                if batch <= 128:
                     assert (4 <= wn <= 6 or (wn == 10 and not partial)) and wk == 1 and 1 <= sp <= 9
                 else:                                   # the workgroup-tiled product
                     assert 4 <= wn <= 8 and wk == 1 and 1 <= sp <= 9
                 assert sp == 1 or (K // 16) // sp >= 16
                 assert partial or sp == 1
-    # where the kernels meet: gate|up at 256 and 512 tiles up to 128 rows, any product at 68 tiles, three splits of more than 240 k-steps
+    # the splits tell the products for few columns from the others: up to 68 tiles, at any number of rows, and beyond 128 rows no three
+    # splits of more than 240 k-steps; up to 128 rows the number of rows decides nothing
     for batch in (1, 64, 65, 128):
-        assert [plan(n, 96, batch, False)[:2] for n in (256, 257, 512)] == [(1, 4), (2, 4), (2, 4)]
-        assert all(plan(n, 96, batch, False)[1] == 1 for n in (513, 560, 768, 769))
-        assert plan(68, 216, batch, True) == (1, 4, 3) and plan(68, 217, batch, True) == (2, 4, 7) and plan(69, 217, batch, True)[1] == 1
+        assert [plan(n, 160, batch, True)[2] for n in (64, 68, 69)] == [4, 3, 5] and plan(64, 217, batch, True)[2] == 8
     for batch in (129, 256):
-        assert plan(68, 96, batch, False) == (1, 4, 1) and plan(69, 96, batch, False)[1] == 1
-        assert plan(64, 1792, batch, True) == (2, 4, 4) and plan(65, 720, batch, True) == (2, 4, 3) and plan(65, 721, batch, True)[1] == 1
+        assert plan(64, 1792, batch, True)[2] == 4
+        assert plan(65, 720, batch, True)[2] == 3 and plan(65, 721, batch, True)[2] == 9
     s = synth.QWEN_7B
     assert plan(2 * s.intermediate // 32, s.hidden // 16, 128, False) == (5, 1, 1)
     assert plan(s.hidden // 32, s.q_dim // 16, 128, True) == (4, 1, 7)
