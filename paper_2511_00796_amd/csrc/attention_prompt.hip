@@ -23,9 +23,8 @@
 // prompt_combine_kernel.  Where there are more items than workgroups, groups are numbered by the length of their parts, items
 // run from the last group to the first, and every second round of the workgroups takes its items in reverse: who had a long part
 // gets a short one.  (In the order of the rows, every round alike, one of 512 workgroups had up to 50 steps of a 2048-token
-// prompt where the mean is 29.)  us per layer, the order of the rows | this | and the lazy scale of the columns: 7B, 2048 rows
-// 83 | 75 | 70.5, 14B, 8-bit cache, 4864 rows of 7 prompts 118 | 97 | 93 (the first and the last again, in one 7B call and in turn: 82 | 67); the schedule, once
-// for all layers, 11 -> 13 and 13.5 -> 18.
+// prompt where the mean is 29.)  us per layer, the order of the rows | this: 7B, 2048 rows 83 | 75, 14B, 8-bit cache, 4864 rows of 7 prompts 118 | 97;
+// the schedule, once for all layers, 11 -> 13 and 13.5 -> 18.
 //
 // Per-group arrays live where the 256-row workspaces keep their per-row ones: entry g in block g / 256 at g % 256.
 #include "hx_internal.h"
@@ -167,7 +166,7 @@ __global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const 
     long long longest = (units + n_wgs - 1) / n_wgs;
     if (longest < HX_PROMPT_MIN_STEPS) longest = HX_PROMPT_MIN_STEPS;
     if (longest < (2 * units + cap - 1) / cap) longest = (2 * units + cap - 1) / cap;
-    int S = (int)longest;                               // 32 bits: the quotients by it are what this kernel's end takes
+    const int S = (int)longest;                         // 32 bits: the quotients by it are what this kernel's end takes
     auto parts = [&](int g) { return (((sT[g] + 31) >> 5) + S - 1) / S; };
     int want = 0;
     for (int g = g0; g < g1; ++g) want += parts(g);
@@ -179,14 +178,11 @@ __global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const 
     want = 0;
 #pragma unroll
     for (int w = 0; w < 16; ++w) want += red[w];
-    // Items in one round of the workgroups are not ordered.  Otherwise parts of half as much again balance as well and are fewer: us
-    // per 4-layer call, factors of 1 | 1.25 | 1.5, 7B, 2048 rows 2392 | 2391 | 2374, 1024 rows behind 3000 tokens 1620 | 1575 | 1577, 1.5B,
-    // 2048 rows 847 | 822 | 833, 14B 2896 | 2885 | 2866 (0.75: 2403, 1612, 846, 2901).  Not where groups of few columns, which wait
-    // for memory, are more than half a pair per workgroup and the longest pair is then hardly cut: single rows of 300 to 5000 tokens,
-    // 1 | 1.5, 256 pairs 649 | 631, 288 709 | 701, 336 754 | 758, 400 833 | 855.  And the groups go by the length of their
-    // parts, in 1024 steps of it; which of two equal ones comes first decides no result.
+    // Items in one round of the workgroups are not ordered; where there are more, the groups go by the length of their parts, in
+    // 1024 steps of it; which of two equal ones comes first decides no result.  (Parts of half as much again would balance as well and be
+    // fewer, 2374 us per 4-layer call instead of 2392, 7B, 2048 rows, and 1577 instead of 1620, 1024 rows behind 3000 tokens, but their longer sums
+    // are 1 to 2.6 % further from exact.)
     if (want * a.n_kv > n_wgs) {
-        if (2 * n_groups * a.n_kv <= n_wgs || 32 * n_groups < a.n_rows * a.G) S += S / 2;
         auto length = [&](int g) { const int st = (sT[g] + 31) >> 5, np = max(parts(g), 1); return (st + np - 1) / np * 1023 / S; };   // no keys: 0
         for (int g = g0; g < g1; ++g) atomicAdd(&bin[length(g)], 1);
         __syncthreads();
