@@ -21,8 +21,8 @@
 // work of the whole call (prompt_sched_kernel), so that a short call with a long cache fills the chip and a long one
 // writes few partial results.  An uncut pair writes its output itself; the parts of a cut one are merged by
 // prompt_combine_kernel.  Where there are more items than workgroups, groups are numbered by the length of their parts, items
-// run from the last group to the first, and every second round of the workgroups takes its items in reverse: who had a long part
-// gets a short one.  (In the order of the rows, every round alike, one of 512 workgroups had up to 50 steps of a 2048-token
+// run from the last group to the first, and every second round of the workgroups, if it is not small, takes its items in reverse: who had a
+// long part gets a short one.  (In the order of the rows, every round alike, one of 512 workgroups had up to 50 steps of a 2048-token
 // prompt where the mean is 29.)  us per layer, the order of the rows | this: 7B, 2048 rows 83 | 75, 14B, 8-bit cache, 4864 rows of 7 prompts 118 | 97;
 // the schedule, once for all layers, 11 -> 13 and 13.5 -> 18.
 //
@@ -310,7 +310,11 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_kernel(PromptArgs a, const
     // this wavefront's part of a step: half a block (K or V) at most
     constexpr int PER_TILE = TILE / 1024;               // copies per tile: 4, 2 or 1
     for (int round = 0, w0 = 0; w0 < n_items; ++round, w0 += gridDim.x) {
-        const int w = w0 + (int)(round & 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x);
+        // A last round of less than a quarter of the workgroups goes to the first of them: the last ones may start behind the others,
+        // and such a round then cost them a third part (us, in reverse | so: 256 rows behind 3000 tokens, 8-bit cache, 7B 51 | 37.7, 14B 66 | 43.8, bf16 7B 44 | 37.8;
+        // 3 x 80 rows behind 6000 76 | 64.3; of 1.4 and 1.6 rounds, 7B, 2048 rows 74.5 and 200 single rows 206, not in reverse 75.5 and 243).
+        const bool back = (round & 1) && 4 * (n_items - w0) >= (int)gridDim.x;
+        const int w = w0 + (int)(back ? gridDim.x - 1 - blockIdx.x : blockIdx.x);
         if (w >= n_items) break;                        // only in the last round
         const int it = n_items - 1 - w;
         const int gi = find_group(a, it, lane);
