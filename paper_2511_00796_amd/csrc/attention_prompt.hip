@@ -182,7 +182,9 @@ __global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const 
     // 1024 steps of it; which of two equal ones comes first decides no result.  (Parts of half as much again would balance as well and be
     // fewer, 2374 us per 4-layer call instead of 2392, 7B, 2048 rows, and 1577 instead of 1620, 1024 rows behind 3000 tokens, but their longer sums
     // are 1 to 2.6 % further from exact.)
-    if (want * a.n_kv > n_wgs) {
+    const bool ordered = want * a.n_kv > n_wgs;
+    auto group_at = [&](int g) { return ordered ? (int)order[g] : g; };
+    if (ordered) {
         auto length = [&](int g) { const int st = (sT[g] + 31) >> 5, np = max(parts(g), 1); return (st + np - 1) / np * 1023 / S; };   // no keys: 0
         for (int g = g0; g < g1; ++g) atomicAdd(&bin[length(g)], 1);
         __syncthreads();
@@ -191,23 +193,18 @@ __global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const 
         bin[tid] = below;
         __syncthreads();
         for (int g = g0; g < g1; ++g) order[atomicAdd(&bin[length(g)], 1)] = (uint16_t)g;
-    } else {
-        for (int g = g0; g < g1; ++g) order[g] = (uint16_t)g;
+        __syncthreads();
+        int info[HX_PREFILL_MAX_ROWS / 1024];
+#pragma unroll
+        for (int k = 0; k < HX_PREFILL_MAX_ROWS / 1024; ++k) info[k] = g0 + k < g1 ? *group_entry<int32_t>(a, a.o_ginfo, order[g0 + k]) : 0;
+        __syncthreads();                                // read by everybody, before the entries move
+#pragma unroll
+        for (int k = 0; k < HX_PREFILL_MAX_ROWS / 1024; ++k) if (g0 + k < g1) *group_entry<int32_t>(a, a.o_ginfo, g0 + k) = info[k];
     }
-    __syncthreads();
-    int info[HX_PREFILL_MAX_ROWS / 1024];
-#pragma unroll
-    for (int k = 0; k < HX_PREFILL_MAX_ROWS / 1024; ++k) info[k] = g0 + k < g1 ? *group_entry<int32_t>(a, a.o_ginfo, order[g0 + k]) : 0;
-    __syncthreads();                                    // read by everybody, before the entries move
-#pragma unroll
-    for (int k = 0; k < HX_PREFILL_MAX_ROWS / 1024; ++k)
-        if (g0 + k < g1) {
-            *group_entry<int32_t>(a, a.o_ginfo, g0 + k) = info[k];
-            *group_entry<int32_t>(a, a.o_lens, g0 + k) = sT[order[g0 + k]];
-        }
+    for (int g = g0; g < g1; ++g) *group_entry<int32_t>(a, a.o_lens, g) = sT[group_at(g)];
     int items = 0, slots = 0, cut = 0;
     for (int g = g0; g < g1; ++g) {
-        const int np = parts(order[g]);
+        const int np = parts(group_at(g));
         items += np * a.n_kv;
         if (np > 1) { slots += np * a.n_kv; ++cut; }
     }
@@ -216,7 +213,7 @@ __global__ __launch_bounds__(1024) void prompt_sched_kernel(PromptArgs a, const 
     int slot = scan_1024<false>(slots, red, &n_slots) - slots;
     int ci = scan_1024<false>(cut, red, &n_cut) - cut;
     for (int g = g0; g < g1; ++g) {
-        const int np = parts(order[g]);
+        const int np = parts(group_at(g));
         *group_entry<int32_t>(a, a.o_pre, g) = at;
         at += np * a.n_kv;
         if (np > 1) {
