@@ -14,7 +14,7 @@
 // 768 cycles at D = 128 and the arithmetic beside them about as many; the two wavefronts of a SIMD cover each other's only in
 // part (2048 rows, 7B, one workgroup per compute unit 98 us, two 75).  Measured per layer, kernel + combine, against a
 // kernel that served 8 rows per K/V stream with one wavefront each and 16-row products of half the rate: 7B, one prompt
-// of 2048 tokens 70 + 13 us (214 + 69); 14B, 7 prompts of 5000 tokens together, 8-bit cache 93 + 6 us (273 + 136);
+// of 2048 tokens 75 + 13 us (214 + 69); 14B, 7 prompts of 5000 tokens together, 8-bit cache 97 + 6 us (273 + 136);
 // 1.5B, 200 rows behind 3000 cached tokens 18 + 7 us (41 + 9).
 //
 // Schedule: a pair (group, KV head) of more than S steps is cut into equal parts of at most S steps; S follows from the
